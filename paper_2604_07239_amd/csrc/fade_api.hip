@@ -102,34 +102,6 @@ uint32_t fbits(float f) { uint32_t u; std::memcpy(&u, &f, 4); return u; }
 
 }  // namespace
 
-// Coder state of fade_coder_encode_tables_noalloc: device memory that lives in the library's image instead of coming from
-// hipMalloc (eight uint32 per stream: low, high, pending, bit buffer, bit count, position, value, bit position). Every GPU
-// the library runs on holds its own copy until the process ends. The name below is a host-side stand-in, not a device
-// address: host code only ever uses the pointer hipGetSymbolAddress returns for the current device (scratch_for_device).
-static __device__ __align__(256) uint32_t scratch[8 * FADE_NOALLOC_MAX_STREAMS];
-
-namespace {
-constexpr int kMaxDevices = 64;
-uint32_t *g_scratch_ptr[kMaxDevices] = {};
-// Address of `scratch` on `device`, looked up once per device with that device current.
-hipError_t scratch_for_device(int device, uint32_t **out) {
-  if (device < 0 || device >= kMaxDevices) return hipErrorInvalidDevice;
-  if (!g_scratch_ptr[device]) {
-    int cur = -1;
-    hipError_t e = hipGetDevice(&cur);
-    if (e != hipSuccess) return e;
-    if (cur != device && (e = hipSetDevice(device)) != hipSuccess) return e;
-    void *p = nullptr;
-    e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-    if (cur != device) (void)hipSetDevice(cur);
-    if (e != hipSuccess) return e;
-    g_scratch_ptr[device] = static_cast<uint32_t *>(p);
-  }
-  *out = g_scratch_ptr[device];
-  return hipSuccess;
-}
-}  // namespace
-
 struct fade_ctx {
   fade_config cfg;
   Dims d;
@@ -210,11 +182,10 @@ struct fade_ctx {
   size_t payload_cap = 0;
   uint8_t *ones = nullptr;
   WinSrc last_ws{};
-  int *dev_err = nullptr;
+  int *dev_err = nullptr;            // error flag in host memory the kernels can write: read after a wait for the stream, without a copy
   bool rows16 = false;               // fp32 path at very small batches: 16 x 16 product tiles, row statistics per 16 columns
   size_t stats_n = 0;                // partial (sum, sum of squares) pairs per row the statistics buffers hold
   bool debug_wu_grad = false;        // FADE_DEBUG_WU_GRAD=1 at fade_create: gradients consumed where they are formed (W_U's, the sums of sliced weight gradients) are also written to the gradient array
-  uint32_t *scratch_dev = nullptr;   // this device's copy of the file-scope scratch array (see scratch_for_device)
   size_t loop_n = 0, loop_next = 0;  // job size and next step of the device-resident loop in progress
   int loop_mode = 0;
   bool enc_complete = false;
@@ -399,7 +370,7 @@ int do_reset(fade_ctx *c) {
   const Dims &d = c->d;
   hipStream_t s = c->stream;
   HIP_TRY(c, hipMemsetAsync(c->M, 0, d.B * d.Dc * c->esz, s));
-  HIP_TRY(c, hipMemsetAsync(c->dev_err, 0, sizeof(int), s));
+  HIP_TRY(c, fade_fill_u32(reinterpret_cast<uint32_t *>(c->dev_err), 0u, 1, s));
   // Frozen weights are as loaded, and so are all their compute copies. Adapted ones come back from the copy on the device:
   // 320 MB at B = 16384, 0.2 ms with the copies rebuilt (uploading them from pageable host memory took 12 ms per reset, and
   // every job and every direction of it starts with one).
@@ -1027,9 +998,8 @@ int backward(fade_ctx *c, const WinSrc &ws, const uint8_t *targets, long long ts
   return FADE_OK;
 }
 
-int check_dev_err(fade_ctx *c) {
-  int e = 0;
-  HIP_TRY(c, hipMemcpy(&e, c->dev_err, sizeof(int), hipMemcpyDeviceToHost));
+int check_dev_err(fade_ctx *c) {  // the stream is idle
+  const int e = *static_cast<volatile int *>(c->dev_err);
   if (e == 1) return fail(c, FADE_E_BUFFER_TOO_SMALL, "payload buffer exhausted");
   if (e == 2) return fail(c, FADE_E_CORRUPT_STREAM, "decoder left its interval: payload does not match the model");
   if (e == 3) return fail(c, FADE_E_NUMERIC, "non-finite probabilities");
@@ -1088,8 +1058,10 @@ int run_loop(fade_ctx *c, uint8_t *bytes_dev, size_t n, size_t first, size_t cou
   for (size_t i = first; i < last; ++i) {
     ws.i = (long long)i;
     if (i < d.T) {
+      const size_t end = std::min<size_t>(d.T, last);
       Prof p(c, "code_uniform");
-      HIP_TRY(c, fade_code_uniform(ws, bytes_dev, (int)d.B, c->cb, mode, s));
+      HIP_TRY(c, fade_code_uniform(ws, bytes_dev, (int)d.B, c->cb, (long long)end, mode, s));
+      i = end - 1;
     } else if (mode == CODE_ENCODE && c->steps_max > 1 && last - i > 1) {
       // frozen weights and the whole input at hand: the model's steps do not depend on each other, only the coder's do
       const int steps = (int)std::min<size_t>((size_t)c->steps_max, last - i);
@@ -1137,6 +1109,7 @@ void fade_destroy(fade_ctx *c) {
   for (auto &ev : c->events) { (void)hipEventDestroy(ev.a); (void)hipEventDestroy(ev.b); }
   for (void *p : c->allocs) (void)hipFree(p);
   for (void *p : c->stage) if (p) (void)hipFree(p);
+  if (c->dev_err) (void)hipHostFree(c->dev_err);
   if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
   delete c;
 }
@@ -1156,7 +1129,6 @@ int fade_create(const fade_config *cfg, fade_ctx **out) {
   if (hipSetDevice(cfg->device) != hipSuccess) return FADE_E_HIP;
   fade_ctx *c = new (std::nothrow) fade_ctx();
   if (!c) return FADE_E_OOM;
-  if (scratch_for_device(cfg->device, &c->scratch_dev) != hipSuccess) { delete c; return FADE_E_HIP; }
   c->cfg = *cfg;
   if (c->cfg.lr == 0.0f) c->cfg.lr = 1e-3f;
   if (c->cfg.beta1 == 0.0f) c->cfg.beta1 = 0.9f;
@@ -1399,10 +1371,15 @@ int fade_create(const fade_config *cfg, fade_ctx **out) {
   TRY_ALLOC(dev_alloc(c, &c->in_len, d.B));
   c->cb.in_len = c->in_len;
   TRY_ALLOC(dev_alloc(c, &c->ones, d.B));
-  TRY_ALLOC(dev_alloc(c, &c->dev_err, 1));
+  if (hipHostMalloc(reinterpret_cast<void **>(&c->dev_err), sizeof(int), hipHostMallocDefault) != hipSuccess) {
+    c->dev_err = nullptr;
+    fade_destroy(c);
+    return FADE_E_OOM;
+  }
+  *c->dev_err = 0;
   c->cb.err = c->dev_err;
 #undef TRY_ALLOC
-  if (hipMemsetAsync(c->ones, 1, d.B, c->stream) != hipSuccess || hipMemsetAsync(c->dev_err, 0, sizeof(int), c->stream) != hipSuccess ||
+  if (hipMemsetAsync(c->ones, 1, d.B, c->stream) != hipSuccess ||
       hipMemsetAsync(c->M, 0, d.B * d.Dc * c->esz, c->stream) != hipSuccess || hipStreamSynchronize(c->stream) != hipSuccess) {
     fade_destroy(c);
     return FADE_E_HIP;
@@ -1602,49 +1579,22 @@ int fade_decode(fade_ctx *c, const uint8_t *src_host, size_t src_len, uint8_t *d
 
 int fade_quantize(fade_ctx *c, const float *probs_dev, size_t rows, uint16_t *freq_dev) {
   if (!c || !probs_dev || !freq_dev) return FADE_E_INVALID_ARG;
-  HIP_TRY(c, hipMemsetAsync(c->dev_err, 0, sizeof(int), c->stream));
+  HIP_TRY(c, fade_fill_u32(reinterpret_cast<uint32_t *>(c->dev_err), 0u, 1, c->stream));
   if (rows) HIP_TRY(c, fade_quantize_rows(probs_dev, rows, freq_dev, c->dev_err, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   return check_dev_err(c);
 }
 
-// `state`: 8 * n_streams uint32 of device memory for the coder state, or NULL: allocated here and freed on return. With a
-// caller-provided state nothing in here allocates (flags are cleared by a kernel, not by a memset node).
 static int coder_tables(fade_ctx *c, const uint16_t *freq_dev, uint8_t *sym_dev, size_t n_steps, size_t n_streams, uint8_t *buf_dev,
-                        size_t cap, uint32_t *len_dev, int mode, uint32_t *state = nullptr) {
-  if (!c || (!freq_dev && n_steps) || (!sym_dev && n_steps) || !buf_dev || !len_dev || n_streams == 0) return FADE_E_INVALID_ARG;
+                        size_t cap, uint32_t *len_dev, int mode) {
+  if (!c || (!freq_dev && n_steps) || (!sym_dev && n_steps) || !buf_dev || !len_dev || n_streams == 0 || n_steps > 0x7fffffff || n_streams > 0x7fffffff)
+    return FADE_E_INVALID_ARG;
   hipStream_t s = c->stream;
-  const bool own_state = state == nullptr;
-  hipError_t e = hipSuccess;
-  if (own_state) {  // private coder state for n_streams streams
-    e = hipMalloc(reinterpret_cast<void **>(&state), 8 * n_streams * sizeof(uint32_t));
-    if (e != hipSuccess) return hip_fail(c, e, "hipMalloc(coder state)");
-  }
-  CoderBufs cb{};
-  cb.low = state; cb.high = state + n_streams; cb.pending = state + 2 * n_streams; cb.bitbuf = state + 3 * n_streams;
-  cb.nbits = state + 4 * n_streams; cb.pos = state + 5 * n_streams; cb.value = state + 6 * n_streams; cb.bitpos = state + 7 * n_streams;
-  cb.out = buf_dev; cb.in = buf_dev; cb.in_len = len_dev; cb.cap = cap; cb.err = c->dev_err;
-  int rc = FADE_OK;
-  do {
-    if (own_state) e = hipMemsetAsync(c->dev_err, 0, sizeof(int), s);
-    else e = fade_fill_u32(reinterpret_cast<uint32_t *>(c->dev_err), 0u, 1, s);
-    if (e != hipSuccess) { rc = hip_fail(c, e, "clear error flag"); break; }
-    if ((e = fade_coder_init(cb, (int)n_streams, mode == CODE_DECODE, s)) != hipSuccess) { rc = hip_fail(c, e, "coder_init"); break; }
-    for (size_t i = 0; i < n_steps && rc == FADE_OK; ++i) {
-      e = fade_code_tables(freq_dev + i * n_streams * 256, sym_dev + i * n_streams, (int)n_streams, cb, mode, s);
-      if (e != hipSuccess) rc = hip_fail(c, e, "code_tables");
-    }
-    if (rc) break;
-    if (mode == CODE_ENCODE) {
-      // every stream coded n_steps symbols: terminate all of them when there was anything to code
-      if (n_steps && (e = fade_coder_finish(cb, (int)n_streams, 1, (long long)n_streams, s)) != hipSuccess) { rc = hip_fail(c, e, "finish"); break; }
-      if ((e = hipMemcpyAsync(len_dev, cb.pos, n_streams * sizeof(uint32_t), hipMemcpyDeviceToDevice, s)) != hipSuccess) { rc = hip_fail(c, e, "copy"); break; }
-    }
-    if ((e = hipStreamSynchronize(s)) != hipSuccess) { rc = hip_fail(c, e, "sync"); break; }
-    rc = check_dev_err(c);
-  } while (0);
-  if (own_state) (void)hipFree(state);
-  return rc;
+  HIP_TRY(c, fade_fill_u32(reinterpret_cast<uint32_t *>(c->dev_err), 0u, 1, s));
+  if (n_steps) HIP_TRY(c, fade_code_tables(freq_dev, sym_dev, (int)n_steps, (int)n_streams, buf_dev, cap, len_dev, c->dev_err, mode, s));
+  else if (mode == CODE_ENCODE) HIP_TRY(c, fade_fill_u32(len_dev, 0u, n_streams, s));  // nothing to code: empty payloads
+  HIP_TRY(c, hipStreamSynchronize(s));
+  return check_dev_err(c);
 }
 
 int fade_coder_encode_tables_noalloc(fade_ctx *c, const uint16_t *freq_dev, const uint8_t *sym_dev, size_t n_steps, size_t n_streams,
@@ -1652,10 +1602,7 @@ int fade_coder_encode_tables_noalloc(fade_ctx *c, const uint16_t *freq_dev, cons
   if (!c) return FADE_E_INVALID_ARG;
   if (n_streams > FADE_NOALLOC_MAX_STREAMS)
     return fail(c, FADE_E_INVALID_ARG, "fade_coder_encode_tables_noalloc: n_streams exceeds FADE_NOALLOC_MAX_STREAMS (65536)");
-  if (!c->scratch_dev) return fail(c, FADE_E_HIP, "scratch array has no device address");
-  // coder_init rewrites all eight state words of every stream it will use, so what the previous call left behind in the
-  // shared array is never read
-  return coder_tables(c, freq_dev, const_cast<uint8_t *>(sym_dev), n_steps, n_streams, out_dev, cap, len_dev, CODE_ENCODE, c->scratch_dev);
+  return coder_tables(c, freq_dev, const_cast<uint8_t *>(sym_dev), n_steps, n_streams, out_dev, cap, len_dev, CODE_ENCODE);
 }
 
 int fade_coder_encode_tables(fade_ctx *c, const uint16_t *freq_dev, const uint8_t *sym_dev, size_t n_steps, size_t n_streams,

@@ -9,6 +9,50 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
+// ---------------------------------------------------------------------------------------------------
+// exchanges inside a wavefront on the vector ALU (DPP and gfx950's row swaps) instead of through LDS: a ds_bpermute
+// butterfly over 64 lanes is six dependent LDS round trips of 60 to 100 cycles, these are one or two instructions a level
+// ---------------------------------------------------------------------------------------------------
+template <int CTRL, int ROWS = 0xf> __device__ __forceinline__ uint32_t fade_dpp(uint32_t v) {  // lanes without a source give 0
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ uint32_t fade_bits(uint32_t v) { return v; }
+__device__ __forceinline__ uint32_t fade_bits(int v) { return (uint32_t)v; }
+__device__ __forceinline__ uint32_t fade_bits(float v) { return __builtin_bit_cast(uint32_t, v); }
+// One level of a butterfly that starts at the widest distance: op(value of this lane, value of lane ^ D), D = 32 ... 1, for a
+// commutative op. Below 16 the value already repeats with period 2 D inside a row of 16 lanes (the wider levels have been
+// done), or D is 8, so a rotation of the row by D fetches lane ^ D. Levels of 16 and 32 hold for any value.
+template <int D, typename T, typename OP> __device__ __forceinline__ T fade_level(T v, OP op) {
+  const uint32_t u = fade_bits(v);
+  if constexpr (D >= 16) {
+    const auto r = D == 32 ? __builtin_amdgcn_permlane32_swap(u, u, false, false) : __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return op(__builtin_bit_cast(T, (uint32_t)r[0]), __builtin_bit_cast(T, (uint32_t)r[1]));
+  } else {
+    return op(v, __builtin_bit_cast(T, fade_dpp<0x120 + D>(u)));
+  }
+}
+template <int W = 64, typename T, typename OP> __device__ __forceinline__ T fade_butterfly(T v, OP op) {  // over aligned groups of W lanes
+  if constexpr (W >= 64) v = fade_level<32>(v, op);
+  if constexpr (W >= 32) v = fade_level<16>(v, op);
+  if constexpr (W >= 16) v = fade_level<8>(v, op);
+  static_assert(W >= 16, "the levels below a row's 8 rely on it");
+  v = fade_level<4>(v, op);
+  v = fade_level<2>(v, op);
+  return fade_level<1>(v, op);
+}
+template <int W = 64, typename T> __device__ __forceinline__ T fade_lanes_sum(T v) { return fade_butterfly<W>(v, [](T a, T b) { return a + b; }); }
+__device__ __forceinline__ float fade_lanes_max(float v) { return fade_butterfly(v, [](float a, float b) { return fmaxf(a, b); }); }
+// inclusive prefix sum over the 64 lanes
+__device__ __forceinline__ uint32_t fade_lanes_scan(uint32_t v) {
+  v += fade_dpp<0x111>(v);  // row_shr 1, 2, 4, 8
+  v += fade_dpp<0x112>(v);
+  v += fade_dpp<0x114>(v);
+  v += fade_dpp<0x118>(v);
+  v += fade_dpp<0x142, 0xa>(v);  // last lane of rows 0 and 2 into rows 1 and 3
+  v += fade_dpp<0x143, 0xc>(v);  // lane 31 into rows 2 and 3
+  return v;
+}
+
 // Where the context windows come from: stream b's window is the T bytes ending just before symbol i,
 // i.e. base + b * stride + (i - T). n is the total byte count (streams past the end are inactive).
 struct WinSrc {

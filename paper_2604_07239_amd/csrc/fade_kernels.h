@@ -148,8 +148,10 @@ hipError_t fade_encode_ranges(const WinSrc &ws, const uint2 *ranges, int B, int 
 hipError_t fade_bmm(const float *y, const void *WU, void *z, int B, bool bf16, hipStream_t s);
 hipError_t fade_softmax_quant_code(const SqcArgs &a, int mode, hipStream_t s);
 hipError_t fade_quantize_rows(const float *probs, size_t rows, uint16_t *freq, int *err, hipStream_t s);
-hipError_t fade_code_tables(const uint16_t *freq, uint8_t *sym, int n_streams, const CoderBufs &cb, int mode, hipStream_t s);
-hipError_t fade_code_uniform(const WinSrc &ws, uint8_t *sym_base, int B, const CoderBufs &cb, int mode, hipStream_t s);
+// n_steps symbols of every stream under given tables (encode: terminated, byte counts to len; decode: byte counts from len)
+hipError_t fade_code_tables(const uint16_t *freq, uint8_t *sym, int n_steps, int n_streams, uint8_t *payload, size_t cap, uint32_t *len, int *err, int mode,
+                            hipStream_t s);
+hipError_t fade_code_uniform(const WinSrc &ws, uint8_t *sym_base, int B, const CoderBufs &cb, long long last, int mode, hipStream_t s);  // steps ws.i .. last - 1
 hipError_t fade_coder_init(const CoderBufs &cb, int B, int decode, hipStream_t s);
 hipError_t fade_fill_u32(uint32_t *dst, uint32_t value, size_t n, hipStream_t s);  // a fill as a kernel (safe to capture in a graph, unlike a memset node)
 hipError_t fade_coder_finish(const CoderBufs &cb, int B, long long stride, long long n, hipStream_t s);

@@ -10,17 +10,6 @@ namespace {
 
 __device__ __forceinline__ float gelu_f(float x) { return fade_gelu(x); }
 
-template <typename T> __device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-  return v;
-}
-
 // ---------------------------------------------------------------------------------------------------
 // weight preparation
 // ---------------------------------------------------------------------------------------------------
@@ -845,33 +834,23 @@ __device__ __forceinline__ bool quantize_wave(const float p[4], int lane, uint32
     ok = ok && (p[i] >= 0.0f) && (p[i] <= 1.0f);
     q[i] = 1u + (uint32_t)__fmul_rn(p[i], 65280.0f);
   }
-  const uint32_t total = wave_sum<uint32_t>(q[0] + q[1] + q[2] + q[3]);
+  const uint32_t total = fade_lanes_sum(q[0] + q[1] + q[2] + q[3]);
   uint32_t best = q[0], bi = 0;
 #pragma unroll
   for (int i = 1; i < 4; ++i)
     if (q[i] > best) { best = q[i]; bi = i; }
   // order by (value, then smaller index): key = value << 10 | (1023 - index)
   uint32_t key = (best << 10) | (1023u - (uint32_t)(4 * lane + bi));
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const uint32_t o = __shfl_xor(key, off, 64);
-    key = o > key ? o : key;
-  }
+  key = fade_butterfly(key, [](uint32_t x, uint32_t y) { return y > x ? y : x; });
   const int arg = 1023 - (int)(key & 1023u);
   if ((arg >> 2) == lane) q[arg & 3] += 65536u - total;  // wraps correctly when total > 65536
   return __all(ok);
 }
 
 // Exclusive prefix of the lane totals; cum[i] = sum of every frequency before symbol 4*lane + i.
-__device__ __forceinline__ void cumulate_wave(const uint32_t q[4], int lane, uint32_t cum[4]) {
+__device__ __forceinline__ void cumulate_wave(const uint32_t q[4], uint32_t cum[4]) {
   const uint32_t tot = q[0] + q[1] + q[2] + q[3];
-  uint32_t inc = tot;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t o = __shfl_up(inc, off, 64);
-    if (lane >= off) inc += o;
-  }
-  const uint32_t base = inc - tot;
+  const uint32_t base = fade_lanes_scan(tot) - tot;
   cum[0] = base; cum[1] = base + q[0]; cum[2] = cum[1] + q[1]; cum[3] = cum[2] + q[2];
 }
 
@@ -883,36 +862,48 @@ constexpr uint32_t kQuarter = 0x40000000u;
 struct EncState {
   uint32_t low, high, pending, bitbuf, nbits, pos;
 };
+__device__ __forceinline__ EncState enc_begin() { return EncState{0u, 0xFFFFFFFFu, 0u, 0u, 0u, 0u}; }
 __device__ __forceinline__ void enc_load(const CoderBufs &c, int b, EncState &e) {
   e.low = c.low[b]; e.high = c.high[b]; e.pending = c.pending[b]; e.bitbuf = c.bitbuf[b]; e.nbits = c.nbits[b]; e.pos = c.pos[b];
 }
 __device__ __forceinline__ void enc_store(const CoderBufs &c, int b, const EncState &e) {
   c.low[b] = e.low; c.high[b] = e.high; c.pending[b] = e.pending; c.bitbuf[b] = e.bitbuf; c.nbits[b] = e.nbits; c.pos[b] = e.pos;
 }
-__device__ __forceinline__ void put_bit(const CoderBufs &c, int b, EncState &e, uint32_t bit) {
-  e.bitbuf = (e.bitbuf << 1) | bit;
-  if (++e.nbits == 8) {
-    if (e.pos < c.cap) c.out[(size_t)b * c.cap + e.pos] = (uint8_t)e.bitbuf;
-    else *c.err = 1;  // payload buffer exhausted: flagged, never written out of bounds
-    ++e.pos; e.bitbuf = 0; e.nbits = 0;
-  }
-}
-__device__ __forceinline__ void emit(const CoderBufs &c, int b, EncState &e, uint32_t bit) {
-  put_bit(c, b, e, bit);
-  for (; e.pending > 0; --e.pending) put_bit(c, b, e, bit ^ 1u);
-}
-// Append the low `count` (<= 32) bits of `value`, most significant first.
-__device__ __forceinline__ void put_bits(const CoderBufs &c, int b, EncState &e, uint32_t value, uint32_t count) {
-  uint64_t acc = ((uint64_t)e.bitbuf << count) | value;
-  uint32_t total = e.nbits + count;  // < 40
-  while (total >= 8) {
-    total -= 8;
-    if (e.pos < c.cap) c.out[(size_t)b * c.cap + e.pos] = (uint8_t)(acc >> total);
-    else *c.err = 1;  // payload buffer exhausted: flagged, never written out of bounds
-    ++e.pos;
+// Where a stream's payload goes: `cap` bytes at `row`. `writer`: the one lane that stores, where a whole wavefront carries the
+// stream's state (a uniform value) through the coder.
+struct EncOut {
+  uint8_t *row;
+  size_t cap;
+  int *err;
+  bool writer;
+};
+__device__ __forceinline__ EncOut enc_out(const CoderBufs &c, int b) { return EncOut{c.out + (size_t)b * c.cap, c.cap, c.err, true}; }
+// Append the low `count` (<= 32) bits of `value`, most significant first. Up to 31 bits wait in the state; they leave four bytes
+// at a time (about every fourth symbol), so most symbols store nothing.
+__device__ __forceinline__ void put_bits(const EncOut &o, EncState &e, uint32_t value, uint32_t count) {
+  const uint64_t acc = ((uint64_t)e.bitbuf << count) | value;
+  uint32_t total = e.nbits + count;  // < 64
+  if (total >= 32) {
+    total -= 32;
+    const uint32_t word = __builtin_bswap32((uint32_t)(acc >> total));
+    if (o.writer) {
+      if (e.pos + 4 <= o.cap) __builtin_memcpy(o.row + e.pos, &word, 4);
+      else *o.err = 1;  // payload buffer exhausted: flagged, never written out of bounds
+    }
+    e.pos += 4;
   }
   e.bitbuf = (uint32_t)acc & ((1u << total) - 1u);
   e.nbits = total;
+}
+// The bit b0, then the `pending` opposite bits owed from earlier straddles.
+__device__ __forceinline__ void put_settled(const EncOut &o, EncState &e, uint32_t b0) {
+  put_bits(o, e, b0, 1);
+  for (uint32_t left = e.pending; left > 0;) {
+    const uint32_t k = left < 32u ? left : 32u;
+    put_bits(o, e, b0 ? 0u : (k == 32u ? 0xFFFFFFFFu : (1u << k) - 1u), k);
+    left -= k;
+  }
+  e.pending = 0;
 }
 // One symbol. The renormalisation loop of the classic coder (shift out a settled top bit, or drop the second bit while the
 // interval straddles the middle) always runs as n shifts of the first kind followed by m of the second: once the top bits of
@@ -922,21 +913,18 @@ __device__ __forceinline__ void put_bits(const CoderBufs &c, int b, EncState &e,
 //   m = after those shifts, the length of the run 0111.. / 1000.. below the top bit; pending becomes m (plus the old
 //       count when n = 0), and the run is cut out of both bounds.
 // The interval is wider than 2^30 before and at least 2^14 - 1 after the update, so n <= 18 and m <= 30.
-__device__ __forceinline__ void enc_symbol(const CoderBufs &c, int b, EncState &e, uint32_t cum_lo, uint32_t cum_hi) {
+__device__ __forceinline__ void enc_symbol(const EncOut &o, EncState &e, uint32_t cum_lo, uint32_t cum_hi) {
   const uint64_t range = (uint64_t)e.high - e.low + 1;
   uint32_t high = e.low + (uint32_t)((range * cum_hi) >> 16) - 1;
   uint32_t low = e.low + (uint32_t)((range * cum_lo) >> 16);
   const uint32_t n = (uint32_t)__clz((int)(low ^ high));
   if (n > 0) {
-    const uint32_t b0 = low >> 31;
-    put_bits(c, b, e, b0, 1);
-    for (uint32_t left = e.pending; left > 0;) {
-      const uint32_t k = left < 32u ? left : 32u;
-      put_bits(c, b, e, b0 ? 0u : (k == 32u ? 0xFFFFFFFFu : (1u << k) - 1u), k);
-      left -= k;
+    if (e.pending == 0) {
+      put_bits(o, e, low >> (32 - n), n);
+    } else {
+      put_settled(o, e, low >> 31);
+      if (n > 1) put_bits(o, e, (low >> (32 - n)) & ((1u << (n - 1)) - 1u), n - 1);
     }
-    e.pending = 0;
-    if (n > 1) put_bits(c, b, e, (low >> (32 - n)) & ((1u << (n - 1)) - 1u), n - 1);
     low <<= n;
     high = (high << n) | ((1u << n) - 1u);
   }
@@ -948,39 +936,57 @@ __device__ __forceinline__ void enc_symbol(const CoderBufs &c, int b, EncState &
   }
   e.low = low; e.high = high;
 }
-__device__ __forceinline__ void enc_finish(const CoderBufs &c, int b, EncState &e) {
+// Termination: one more owed bit and the quarter bit, then zeros up to a whole byte, and the bytes that still wait.
+__device__ __forceinline__ void enc_finish(const EncOut &o, EncState &e) {
   ++e.pending;
-  emit(c, b, e, e.low < kQuarter ? 0u : 1u);
-  while (e.nbits != 0) put_bit(c, b, e, 0);
+  put_settled(o, e, e.low < kQuarter ? 0u : 1u);
+  if (e.nbits & 7u) put_bits(o, e, 0u, 8u - (e.nbits & 7u));
+  for (; e.nbits > 0; ++e.pos) {
+    e.nbits -= 8;
+    if (!o.writer) continue;
+    if (e.pos < o.cap) o.row[e.pos] = (uint8_t)(e.bitbuf >> e.nbits);
+    else *o.err = 1;
+  }
+  e.bitbuf = 0;
 }
 
+// The decoder holds its next payload bits in a register: `win` has the bits from the read position on at its top; zeros past
+// the payload's end.
 struct DecState {
-  uint32_t low, high, value, bitpos;
+  uint32_t low, high, value;
+  uint32_t pos;    // payload bits taken so far
+  uint64_t win;
 };
-__device__ __forceinline__ uint32_t dec_bit(const CoderBufs &c, int b, DecState &d) {
-  const uint32_t byte = d.bitpos >> 3;
-  uint32_t bit = 0;
-  if (byte < c.in_len[b]) bit = (c.in[(size_t)b * c.cap + byte] >> (7 - (d.bitpos & 7))) & 1u;
-  ++d.bitpos;  // zeros past the end
-  return bit;
+// Eight payload bytes at or before the read position, as they lie in memory, and how many bits of them are behind it. The
+// request and the use are apart so that the load can be in flight under other work. Positions near the end read the
+// payload's last eight bytes: what is shifted in behind them are the zeros past the end.
+struct DecAhead {
+  uint64_t raw;
+  uint32_t shift;
+};
+__device__ __forceinline__ DecAhead dec_request(const uint8_t *row, uint32_t len, uint32_t pos) {
+  DecAhead w{0, pos};
+  if (len >= 8) {
+    const uint32_t base = pos >> 3 < len - 8 ? pos >> 3 : len - 8;
+    __builtin_memcpy(&w.raw, row + base, 8);
+    w.shift = pos - base * 8;
+  } else {
+    for (uint32_t k = 0; k < len; ++k) w.raw |= (uint64_t)row[k] << (8 * k);
+  }
+  return w;
 }
-__device__ __forceinline__ uint32_t dec_target(const DecState &d) {
-  const uint64_t range = (uint64_t)d.high - d.low + 1;
-  return (uint32_t)((((((uint64_t)(d.value - d.low)) + 1) << 16) - 1) / range);
+__device__ __forceinline__ void dec_fill(DecState &d, const DecAhead &w) {  // at least 57 bits; a symbol takes at most n + m <= 48
+  d.win = w.shift < 64 ? __builtin_bswap64(w.raw) << w.shift : 0ull;
 }
-// The next `count` (<= 25) payload bits of stream b, zeros past the end.
-__device__ __forceinline__ uint32_t dec_bits(const CoderBufs &c, int b, DecState &d, uint32_t count) {
-  const uint32_t byte0 = d.bitpos >> 3, off = d.bitpos & 7u, len = c.in_len[b];
-  const uint8_t *in = c.in + (size_t)b * c.cap;
-  uint32_t w = 0;
-#pragma unroll
-  for (uint32_t k = 0; k < 4; ++k) w = (w << 8) | (byte0 + k < len ? (uint32_t)in[byte0 + k] : 0u);
-  d.bitpos += count;
-  return count ? (w << off) >> (32 - count) : 0u;
+__device__ __forceinline__ uint32_t dec_take(DecState &d, uint32_t count) {  // 1 <= count <= 32
+  const uint32_t v = (uint32_t)(d.win >> 32) >> (32 - count);
+  d.win <<= count;
+  d.pos += count;
+  return v;
 }
 // The decoder's side of enc_symbol's closed form: the same n and m (the bounds do not depend on the payload), `value`
 // shifted along with them; a straddle step removes the bit below the top one.
-__device__ __forceinline__ void dec_update(const CoderBufs &c, int b, DecState &d, uint32_t cum_lo, uint32_t cum_hi) {
+__device__ __forceinline__ void dec_update(DecState &d, uint32_t cum_lo, uint32_t cum_hi) {
   const uint64_t range = (uint64_t)d.high - d.low + 1;
   uint32_t high = d.low + (uint32_t)((range * cum_hi) >> 16) - 1;
   uint32_t low = d.low + (uint32_t)((range * cum_lo) >> 16);
@@ -989,60 +995,47 @@ __device__ __forceinline__ void dec_update(const CoderBufs &c, int b, DecState &
   if (n > 0) {
     low <<= n;
     high = (high << n) | ((1u << n) - 1u);
-    value = (value << n) | dec_bits(c, b, d, n);
+    value = (value << n) | dec_take(d, n);
   }
-  uint32_t m = (uint32_t)__clz((int)~((low & ~high) << 1));
+  const uint32_t m = (uint32_t)__clz((int)~((low & ~high) << 1));
   if (m > 0) {
     low = (low << m) & 0x7FFFFFFFu;
     high = (high << m) | ((1u << m) - 1u) | 0x80000000u;
-    while (m > 0) {
-      const uint32_t k = m < 24u ? m : 24u;
-      value = (value & 0x80000000u) | ((value << k) & 0x7FFFFFFFu) | dec_bits(c, b, d, k);
-      m -= k;
-    }
+    value = (value & 0x80000000u) | ((value << m) & 0x7FFFFFFFu) | dec_take(d, m);
   }
   d.low = low; d.high = high; d.value = value;
 }
 
-// Code one symbol of stream b under the table q (lane-distributed). mode: CODE_NONE / CODE_ENCODE / CODE_DECODE.
-template <int MODE>
-__device__ __forceinline__ void code_wave(const CoderBufs &c, int b, int lane, const uint32_t q[4], uint8_t *sym_ptr) {
-  if (MODE == CODE_NONE) return;
-  uint32_t cum[4];
-  cumulate_wave(q, lane, cum);
-  if (MODE == CODE_ENCODE) {
-    const int s = *sym_ptr;
-    const uint32_t mylo = cum[s & 3], myhi = mylo + q[s & 3];
-    const uint32_t lo = __shfl(mylo, s >> 2, 64), hi = __shfl(myhi, s >> 2, 64);
-    if (lane == 0) {
-      EncState e;
-      enc_load(c, b, e);
-      enc_symbol(c, b, e, lo, hi);
-      enc_store(c, b, e);
-    }
-  } else {
-    DecState d;
-    d.low = c.low[b]; d.high = c.high[b]; d.value = c.value[b]; d.bitpos = c.bitpos[b];
-    const uint32_t target = dec_target(d);
-    int found = -1;
+// Bounds of symbol s under the table q (lane l owns symbols 4l .. 4l + 3; s is the same in every lane).
+__device__ __forceinline__ void enc_bounds(const uint32_t q[4], int lane, int s, uint32_t &lo, uint32_t &hi) {
+  uint32_t below = 0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (cum[i] <= target && target < cum[i] + q[i]) found = i;
-    const unsigned long long vote = __ballot(found >= 0);
-    if (vote == 0ull) {  // target outside [0, 2^16): the payload does not belong to this model
-      if (lane == 0) *c.err = 2;
-      return;
-    }
-    const int owner = __ffsll((long long)vote) - 1;
-    const int fi = found < 0 ? 0 : found;
-    const uint32_t lo = __shfl(cum[fi], owner, 64), hi = __shfl(cum[fi] + q[fi], owner, 64);
-    const int s = __shfl(4 * lane + fi, owner, 64);
-    if (lane == 0) {
-      dec_update(c, b, d, lo, hi);
-      c.low[b] = d.low; c.high[b] = d.high; c.value[b] = d.value; c.bitpos[b] = d.bitpos;
-      *sym_ptr = (uint8_t)s;
-    }
-  }
+  for (int i = 0; i < 4; ++i) below += 4 * lane + i < s ? q[i] : 0u;
+  lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)fade_lanes_sum(below));
+  const uint32_t qs = (s & 2) ? ((s & 1) ? q[3] : q[2]) : ((s & 1) ? q[1] : q[0]);
+  hi = lo + (uint32_t)__builtin_amdgcn_readlane((int)qs, s >> 2);
+}
+// The symbol that `value` points at, and its bounds; false when it points outside the interval (the payload does not belong to
+// this model). The classic rule is cum[s] <= ((value - low + 1) * 2^16 - 1) / range < cum[s + 1]; with integers that is
+// (cum[s] * range) >> 16 <= value - low < (cum[s + 1] * range) >> 16, so every lane tries its own four symbols with a
+// multiplication each and nobody divides (a 64-bit division is over a hundred dependent instructions).
+__device__ __forceinline__ bool dec_find(const DecState &d, const uint32_t q[4], int lane, int &s, uint32_t &lo, uint32_t &hi) {
+  uint32_t cum[4];
+  cumulate_wave(q, cum);
+  const uint64_t range = (uint64_t)d.high - d.low + 1;
+  const uint32_t off = d.value - d.low;
+  int at = -1;  // last of this lane's symbols that starts at or below the target
+#pragma unroll
+  for (int i = 0; i < 4; ++i) at = (uint32_t)((range * cum[i]) >> 16) <= off ? i : at;
+  const bool mine = at >= 0 && ((range * (cum[3] + q[3])) >> 16) > off;
+  const unsigned long long vote = __ballot(mine);
+  if (vote == 0ull) return false;
+  const int owner = __builtin_amdgcn_readfirstlane(__ffsll((long long)vote) - 1), i = __builtin_amdgcn_readlane(at, owner);
+  const uint32_t clo = i & 2 ? (i & 1 ? cum[3] : cum[2]) : (i & 1 ? cum[1] : cum[0]), qs = i & 2 ? (i & 1 ? q[3] : q[2]) : (i & 1 ? q[1] : q[0]);
+  lo = (uint32_t)__builtin_amdgcn_readlane((int)clo, owner);
+  hi = lo + (uint32_t)__builtin_amdgcn_readlane((int)qs, owner);
+  s = 4 * owner + i;
+  return true;
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -1060,6 +1053,19 @@ __global__ __launch_bounds__(256) void softmax_quant_code_kernel(SqcArgs a) {
     w.i += st;
   }
   if (!stream_active(w, sb)) return;
+  // What the coder needs is requested with the logits (it used to be read behind the quantiser, two dependent round trips at
+  // the end of the kernel): the state, the symbol to code, and, once its position is here, the payload under the decoder.
+  uint8_t *sym = MODE == CODE_NONE ? nullptr : a.sym_base + (long long)sb * w.stride + w.i;
+  EncState e;
+  DecState d;
+  uint32_t in_len = 0;
+  int sy = 0;
+  if (MODE == CODE_ENCODE || MODE == CODE_RANGES) sy = *sym;
+  if (MODE == CODE_ENCODE) enc_load(a.cb, b, e);
+  if (MODE == CODE_DECODE) {
+    d.pos = a.cb.bitpos[b]; in_len = a.cb.in_len[b];
+    d.low = a.cb.low[b]; d.high = a.cb.high[b]; d.value = a.cb.value[b];
+  }
   f32x4 z = *reinterpret_cast<const f32x4 *>(a.logits + (size_t)b * 256 + 4 * lane);
   if (a.splits > 0) {  // logits arrive as split-K partials; the head's bias is added here
     for (int s0 = 1; s0 < a.splits; s0 += 8) {  // up to 8 partials in flight, added in split order
@@ -1074,11 +1080,13 @@ __global__ __launch_bounds__(256) void softmax_quant_code_kernel(SqcArgs a) {
     z += *reinterpret_cast<const f32x4 *>(a.bias + 4 * lane);
     if (a.logits_out) *reinterpret_cast<f32x4 *>(a.logits_out + (size_t)b * 256 + 4 * lane) = z;
   }
-  const float mx = wave_max(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])));
+  DecAhead ahead{0, 0};
+  if (MODE == CODE_DECODE) ahead = dec_request(a.cb.in + (size_t)b * a.cb.cap, in_len, d.pos);
+  const float mx = fade_lanes_max(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])));
   float p[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) p[i] = expf(z[i] - mx);
-  const float sum = wave_sum<float>((p[0] + p[1]) + (p[2] + p[3]));
+  const float sum = fade_lanes_sum((p[0] + p[1]) + (p[2] + p[3]));
 #pragma unroll
   for (int i = 0; i < 4; ++i) p[i] = p[i] / sum;
   if (a.probs) {
@@ -1094,16 +1102,30 @@ __global__ __launch_bounds__(256) void softmax_quant_code_kernel(SqcArgs a) {
     ushort4 f = make_ushort4((unsigned short)q[0], (unsigned short)q[1], (unsigned short)q[2], (unsigned short)q[3]);
     *reinterpret_cast<ushort4 *>(a.freq + (size_t)b * 256 + 4 * lane) = f;
   }
-  if (MODE == CODE_RANGES) {
-    uint32_t cum[4];
-    cumulate_wave(q, lane, cum);
-    const int sy = a.sym_base[(long long)sb * w.stride + w.i];
-    const uint32_t mylo = cum[sy & 3], myhi = mylo + q[sy & 3];
-    const uint32_t lo = __shfl(mylo, sy >> 2, 64), hi = __shfl(myhi, sy >> 2, 64);
-    if (lane == 0) a.ranges[b] = make_uint2(lo, hi);
-  } else if (MODE != CODE_NONE) {
-    uint8_t *sym = a.sym_base + (long long)b * a.ws.stride + a.ws.i;
-    code_wave<MODE>(a.cb, b, lane, q, sym);
+  if (MODE == CODE_ENCODE || MODE == CODE_RANGES) {
+    uint32_t lo, hi;
+    enc_bounds(q, lane, __builtin_amdgcn_readfirstlane(sy), lo, hi);
+    if (lane == 0) {
+      if (MODE == CODE_RANGES) a.ranges[b] = make_uint2(lo, hi);
+      else {
+        enc_symbol(enc_out(a.cb, b), e, lo, hi);
+        enc_store(a.cb, b, e);
+      }
+    }
+  } else if (MODE == CODE_DECODE) {
+    uint32_t lo, hi;
+    int s;
+    const bool found = dec_find(d, q, lane, s, lo, hi);
+    if (lane == 0) {
+      if (!found) {
+        *a.cb.err = 2;
+      } else {
+        dec_fill(d, ahead);
+        dec_update(d, lo, hi);
+        a.cb.low[b] = d.low; a.cb.high[b] = d.high; a.cb.value[b] = d.value; a.cb.bitpos[b] = d.pos;
+        *sym = (uint8_t)s;
+      }
+    }
   }
 }
 
@@ -1128,7 +1150,7 @@ __global__ __launch_bounds__(64) void encode_ranges_kernel(WinSrc ws, const uint
       WinSrc w = ws;
       w.i += s0 + j;
       live = stream_active(w, b);  // a stream that has ended stays ended
-      if (live) enc_symbol(cb, b, e, slab[j][threadIdx.x].x, slab[j][threadIdx.x].y);
+      if (live) enc_symbol(enc_out(cb, b), e, slab[j][threadIdx.x].x, slab[j][threadIdx.x].y);
     }
   }
   if (mine) enc_store(cb, b, e);
@@ -1149,51 +1171,120 @@ __global__ __launch_bounds__(256) void quantize_kernel(const float *probs, size_
   *reinterpret_cast<ushort4 *>(freq + r * 256 + 4 * lane) = f;
 }
 
-// Code one symbol per stream under explicit tables freq[stream][256] (the stand-alone coder entry points).
+// Stand-alone coder: n_steps symbols of every stream under explicit tables freq[step][stream][256], one wavefront per stream
+// from its first symbol to its last. The coder's state never leaves the registers (it is the same in every lane, so most of
+// its arithmetic is scalar); a group of four tables is in flight while the one before is coded.
+// 4096 streams x 32 steps (67 MB of tables): encode 41 us, decode 36 us; a launch per step took 32 x 3.9 and 32 x 5.1 us, and
+// the two calls 400 us with the coder's state allocated, set up and read back (now 105). What bounds it is the dependent chain
+// of a step, some 300 instructions a wavefront, not the tables (14 us at the rate of a copy).
 template <int MODE>
-__global__ __launch_bounds__(256) void code_tables_kernel(const uint16_t *freq, uint8_t *sym, int n_streams, CoderBufs cb) {
-  const int b = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+__global__ __launch_bounds__(256) void code_tables_kernel(const uint16_t *freq, uint8_t *sym, int n_steps, int n_streams, uint8_t *payload, size_t cap,
+                                                          uint32_t *len, int *err) {
+  constexpr int AHEAD = 4;
+  const int b = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)), lane = threadIdx.x & 63;
   if (b >= n_streams) return;
-  const ushort4 f = *reinterpret_cast<const ushort4 *>(freq + (size_t)b * 256 + 4 * lane);
-  const uint32_t q[4] = {f.x, f.y, f.z, f.w};
-  code_wave<MODE>(cb, b, lane, q, sym + b);
+  const ushort4 *row = reinterpret_cast<const ushort4 *>(freq + (size_t)b * 256) + lane;
+  const size_t row_step = (size_t)n_streams * 64;
+  uint8_t *sp = sym + b;
+  ushort4 f[AHEAD], fn[AHEAD];
+  int x[AHEAD], xn[AHEAD];
+  auto request = [&](int i0) {
+#pragma unroll
+    for (int j = 0; j < AHEAD; ++j) {
+      const size_t i = i0 + j < n_steps ? i0 + j : n_steps - 1;
+      fn[j] = row[i * row_step];
+      if (MODE == CODE_ENCODE) xn[j] = sp[i * n_streams];
+    }
+  };
+  request(0);
+  EncState e = enc_begin();
+  const EncOut out{payload + (size_t)b * cap, cap, err, lane == 0};
+  DecState d{0u, 0xFFFFFFFFu, 0u, 0u, 0ull};
+  uint32_t in_len = 0;
+  const uint8_t *in = payload + (size_t)b * cap;
+  if (MODE == CODE_DECODE) {
+    in_len = __builtin_amdgcn_readfirstlane(len[b]);
+    dec_fill(d, dec_request(in, in_len, 0));
+    d.value = __builtin_amdgcn_readfirstlane(dec_take(d, 32));
+  }
+  for (int i0 = 0; i0 < n_steps; i0 += AHEAD) {
+    // the group requested a whole group ago is taken over, and the next one requested, in one place: the coder's stores sit in
+    // branches, behind which the compiler waits for everything in flight
+#pragma unroll
+    for (int j = 0; j < AHEAD; ++j) { f[j] = fn[j]; x[j] = xn[j]; }
+    request(i0 + AHEAD);
+#pragma unroll
+    for (int j = 0; j < AHEAD; ++j) {
+      if (i0 + j >= n_steps) break;
+      const uint32_t q[4] = {f[j].x, f[j].y, f[j].z, f[j].w};
+      const int sy = MODE == CODE_ENCODE ? __builtin_amdgcn_readfirstlane(x[j]) : 0;
+      uint32_t lo, hi;
+      if (MODE == CODE_ENCODE) {
+        enc_bounds(q, lane, sy, lo, hi);
+        enc_symbol(out, e, lo, hi);
+      } else {
+        int s;
+        DecAhead w = dec_request(in, in_len, d.pos);
+        if (!dec_find(d, q, lane, s, lo, hi)) {
+          if (lane == 0) *err = 2;
+          return;
+        }
+        w.raw = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(w.raw >> 32)) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane((int)w.raw);
+        dec_fill(d, w);
+        dec_update(d, lo, hi);
+        if (lane == 0) sp[(size_t)(i0 + j) * n_streams] = (uint8_t)s;
+      }
+    }
+  }
+  if (MODE == CODE_ENCODE) {
+    enc_finish(out, e);
+    if (lane == 0) len[b] = e.pos;
+  }
 }
 
-// Algorithm 1's first T symbols: every symbol has frequency 256 (p = 1/256). One thread per stream.
+// Algorithm 1's first T symbols: every symbol has frequency 256 (p = 1/256). One thread per stream takes it through the steps
+// ws.i .. last - 1 in one launch.
 template <int MODE>
-__global__ void code_uniform_kernel(WinSrc ws, uint8_t *sym_base, int B, CoderBufs cb) {
+__global__ void code_uniform_kernel(WinSrc ws, uint8_t *sym_base, int B, CoderBufs cb, long long last) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= B || !stream_active(ws, b)) return;
-  uint8_t *sym = sym_base + (long long)b * ws.stride + ws.i;
-  if (MODE == CODE_ENCODE) {
-    const uint32_t s = *sym;
-    EncState e;
-    enc_load(cb, b, e);
-    enc_symbol(cb, b, e, s * 256u, (s + 1u) * 256u);
-    enc_store(cb, b, e);
-  } else {
-    DecState d;
-    d.low = cb.low[b]; d.high = cb.high[b]; d.value = cb.value[b]; d.bitpos = cb.bitpos[b];
-    const uint32_t target = dec_target(d);
-    if (target >= 65536u) { *cb.err = 2; return; }
-    const uint32_t s = target >> 8;
-    dec_update(cb, b, d, s * 256u, (s + 1u) * 256u);
-    cb.low[b] = d.low; cb.high[b] = d.high; cb.value[b] = d.value; cb.bitpos[b] = d.bitpos;
-    *sym = (uint8_t)s;
+  uint8_t *sym = sym_base + (long long)b * ws.stride;
+  EncState e;
+  DecState d;
+  const EncOut out = enc_out(cb, b);
+  const uint8_t *in = cb.in + (size_t)b * cb.cap;
+  const uint32_t in_len = MODE == CODE_DECODE ? cb.in_len[b] : 0u;
+  if (MODE == CODE_ENCODE) enc_load(cb, b, e);
+  else { d.low = cb.low[b]; d.high = cb.high[b]; d.value = cb.value[b]; d.pos = cb.bitpos[b]; }
+  for (; ws.i < last && stream_active(ws, b); ++ws.i) {
+    if (MODE == CODE_ENCODE) {
+      const uint32_t s = sym[ws.i];
+      enc_symbol(out, e, s * 256u, (s + 1u) * 256u);
+    } else {
+      const uint64_t range = (uint64_t)d.high - d.low + 1;
+      const uint64_t target = ((((uint64_t)(d.value - d.low)) + 1) * 65536ull - 1) / range;
+      if (target >= 65536u) { *cb.err = 2; return; }
+      const uint32_t s = (uint32_t)target >> 8;
+      dec_fill(d, dec_request(in, in_len, d.pos));
+      dec_update(d, s * 256u, (s + 1u) * 256u);
+      sym[ws.i] = (uint8_t)s;
+    }
   }
+  if (MODE == CODE_ENCODE) enc_store(cb, b, e);
+  else { cb.low[b] = d.low; cb.high[b] = d.high; cb.value[b] = d.value; cb.bitpos[b] = d.pos; }
 }
 
 // Reset coder state; for decoding also prime `value` with the first 32 payload bits.
 __global__ void coder_init_kernel(CoderBufs cb, int B, int decode) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= B) return;
-  cb.low[b] = 0; cb.high[b] = 0xFFFFFFFFu; cb.pending[b] = 0; cb.bitbuf[b] = 0; cb.nbits[b] = 0; cb.pos[b] = 0;
-  cb.value[b] = 0; cb.bitpos[b] = 0;
+  enc_store(cb, b, enc_begin());
+  DecState d{0u, 0xFFFFFFFFu, 0u, 0u, 0ull};
   if (decode) {
-    DecState d = {0u, 0xFFFFFFFFu, 0u, 0u};
-    for (int i = 0; i < 32; ++i) d.value = (d.value << 1) | dec_bit(cb, b, d);
-    cb.value[b] = d.value; cb.bitpos[b] = d.bitpos;
+    dec_fill(d, dec_request(cb.in + (size_t)b * cb.cap, cb.in_len[b], 0));
+    d.value = dec_take(d, 32);
   }
+  cb.value[b] = d.value; cb.bitpos[b] = d.pos;
 }
 
 // Terminate every non-empty stream's payload; pos[b] becomes its byte length.
@@ -1203,7 +1294,7 @@ __global__ void coder_finish_kernel(CoderBufs cb, int B, long long stride, long 
   if ((long long)b * stride >= n) return;  // empty stream: zero-length payload
   EncState e;
   enc_load(cb, b, e);
-  enc_finish(cb, b, e);
+  enc_finish(enc_out(cb, b), e);
   enc_store(cb, b, e);
 }
 
@@ -1398,16 +1489,17 @@ hipError_t fade_quantize_rows(const float *probs, size_t rows, uint16_t *freq, i
   hipLaunchKernelGGL(quantize_kernel, dim3(blocks_for(rows, 4)), dim3(256), 0, s, probs, rows, freq, err);
   return hipGetLastError();
 }
-hipError_t fade_code_tables(const uint16_t *freq, uint8_t *sym, int n_streams, const CoderBufs &cb, int mode, hipStream_t s) {
+hipError_t fade_code_tables(const uint16_t *freq, uint8_t *sym, int n_steps, int n_streams, uint8_t *payload, size_t cap, uint32_t *len, int *err, int mode,
+                            hipStream_t s) {
   const dim3 grid((n_streams + 3) / 4), block(256);
-  if (mode == CODE_ENCODE) hipLaunchKernelGGL(code_tables_kernel<CODE_ENCODE>, grid, block, 0, s, freq, sym, n_streams, cb);
-  else hipLaunchKernelGGL(code_tables_kernel<CODE_DECODE>, grid, block, 0, s, freq, sym, n_streams, cb);
+  if (mode == CODE_ENCODE) hipLaunchKernelGGL(code_tables_kernel<CODE_ENCODE>, grid, block, 0, s, freq, sym, n_steps, n_streams, payload, cap, len, err);
+  else hipLaunchKernelGGL(code_tables_kernel<CODE_DECODE>, grid, block, 0, s, freq, sym, n_steps, n_streams, payload, cap, len, err);
   return hipGetLastError();
 }
-hipError_t fade_code_uniform(const WinSrc &ws, uint8_t *sym_base, int B, const CoderBufs &cb, int mode, hipStream_t s) {
+hipError_t fade_code_uniform(const WinSrc &ws, uint8_t *sym_base, int B, const CoderBufs &cb, long long last, int mode, hipStream_t s) {
   const dim3 grid((B + 63) / 64), block(64);
-  if (mode == CODE_ENCODE) hipLaunchKernelGGL(code_uniform_kernel<CODE_ENCODE>, grid, block, 0, s, ws, sym_base, B, cb);
-  else hipLaunchKernelGGL(code_uniform_kernel<CODE_DECODE>, grid, block, 0, s, ws, sym_base, B, cb);
+  if (mode == CODE_ENCODE) hipLaunchKernelGGL(code_uniform_kernel<CODE_ENCODE>, grid, block, 0, s, ws, sym_base, B, cb, last);
+  else hipLaunchKernelGGL(code_uniform_kernel<CODE_DECODE>, grid, block, 0, s, ws, sym_base, B, cb, last);
   return hipGetLastError();
 }
 hipError_t fade_coder_init(const CoderBufs &cb, int B, int decode, hipStream_t s) {

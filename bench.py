@@ -41,8 +41,6 @@ ROUTER_GATE_TRAFFIC_BYTES = {
     (16384, 2048, "online"): int(0.5 * (320.4 + 130.4 + 314.1 + 130.3) * MiB), # profiles/cfg5_online_kernel_trace_and_hbm.md
     (1024, 2048, "online"): int(0.5 * (48.1 + 8.2 + 45.2 + 8.2) * MiB),                    # profiles/cfg2_online_kernel_trace_and_hbm.md
 }
-# the same for the fp32 small-batch product (gemm_f32_rows_kernel) by (B, D_h, mode): profiles/cfg1_kernel_trace_and_hbm.md
-F32_ROUTER_GATE_TRAFFIC_BYTES = {(16, 512, "frozen"): int(0.5 * (2.46 + 0.05 + 2.40 + 0.05) * MiB), (16, 512, "online"): int(0.5 * (2.46 + 0.08 + 2.40 + 0.08) * MiB)}
 # adam_refresh_kernel by (parameters of the nine big matrices, mode), same counter runs
 ADAM_TRAFFIC_BYTES = {(11272192, "online"): int((174.6 + 170.0) * MiB),      # profiles/cfg2_online_kernel_trace_and_hbm.md
                       (13369344, "online"): int((349.5 + 194.5) * MiB)}        # profiles/cfg5_online_kernel_trace_and_hbm.md
@@ -220,14 +218,15 @@ def main():
                         "algorithmic_bytes_per_launch": 2 * rows * Dh + 2 * Dh * 2 * De + 4 * rows * 2 * De}
         if roofline is None and "gemm_router" in kern and spec["dtype"] == "f32":
             # fp32 at a small batch (cfg 1): every product streams its fp32 weight matrix once past a handful of rows, so the
-            # step is bound by weight bytes (and by launch latency); the widest weight stream is the D_h x D_h router / gate product
+            # step is bound by launch latency before weight bytes; the widest weight streams are the two launches with a D_h x D_h matrix
+            # (the router's with Eq. 3's product, the gate's with Up): their mean
             twins = [kern[k]["avg_us"] for k in ("gemm_router", "gemm_gate") if k in kern]
             us = sum(twins) / len(twins)
-            nbytes = 4 * (Dh * Dh + (5 if mode == "online" else 4) * B * Dh)
+            nbytes = 4 * (Dh * Dh + (Dc + dl) * Dh // 2 + (5 if mode == "online" else 4) * B * Dh)
             ach = nbytes / (us * 1e-6) / 1e9
-            roofline = {"bound": "hbm", "kernel": f"gemm_f32_rows_kernel (router / gate product, M={B}, N=K=D_h, fp32 weights)", "achieved": round(ach, 2),
+            roofline = {"bound": "hbm", "kernel": f"rows_kernel (Eq. 3 + router / Up + gate, M={B}, N=K=D_h, fp32 weights)", "achieved": round(ach, 2),
                         "peak": HBM_PEAK / 1e9, "unit": "GB/s", "frac": round(ach * 1e9 / HBM_PEAK, 5),
-                        "traffic": F32_ROUTER_GATE_TRAFFIC_BYTES.get((B, Dh, mode)), "avg_us": round(us, 2), "algorithmic_bytes_per_launch": nbytes}
+                        "traffic": None, "avg_us": round(us, 2), "algorithmic_bytes_per_launch": nbytes}
         update_roofline = None
         if "adam_matrices" in kern and spec["dtype"] == "bf16":
             # the HBM-bound pass of the update over the shared weights: Adam on the nine big matrices fused with the refresh of their bf16

@@ -6,7 +6,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfade.so")
-SOURCES = ["fade_gemm.hip", "fade_misc.hip", "fade_bwd.hip", "fade_api.hip"]
+SOURCES = ["fade_gemm.hip", "fade_misc.hip", "fade_bwd.hip", "fade_rows.hip", "fade_api.hip"]
 # packed-fp32 code generation is switched off for every device translation unit
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function"]
@@ -36,7 +36,7 @@ def build(force: bool = True) -> str:
             print(err)
         return obj
 
-    with ThreadPoolExecutor(max_workers=4) as ex:
+    with ThreadPoolExecutor(max_workers=5) as ex:
         objs = list(ex.map(cc, SOURCES))
     r = subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], capture_output=True, text=True)
     if r.returncode:

@@ -161,6 +161,7 @@ struct fade_ctx {
        *dHa = nullptr, *dac = nullptr, *dHmix1 = nullptr, *dHmix2 = nullptr, *dy_at = nullptr, *dnc = nullptr, *dar = nullptr,
        *dhm = nullptr, *dcv = nullptr, *dX1 = nullptr, *dX2 = nullptr, *dxl = nullptr;
   void *LT[8] = {};  // left operands of the weight gradients that need a copy: LN(H_coarse), LN(H_mix) row-major (bf16 path); feature-major copies [width][Bp] of all eight (fp32 path)
+  float *mom = nullptr, *xt = nullptr;  // small-batch fp32 path: row moments [3][B][2] of V, H_coarse, H_mix; x_t of the newest symbol [B][D]
   float *dz_part = nullptr, *dy = nullptr, *dgg = nullptr, *dgv = nullptr, *dxt = nullptr, *row_dlam = nullptr,
         *conv_part = nullptr, *tok_part = nullptr;
   float *ln_part = nullptr, *col_part = nullptr, *slot_part = nullptr, *emb_part = nullptr;
@@ -356,13 +357,15 @@ int prepare_compute(fade_ctx *c, bool with_wu = true) {
     if (rc) return rc;
     if (with_wu) HIP_TRY(c, fade_convert(c->P(P_WU), c->WU_c, d.B * d.dl * d.dl, true, s));
     return refresh_small(c);
-  } else {
+  } else if (!c->rows16) {  // the small-batch kernels read every weight where it lies
     HIP_TRY(c, fade_virtual_copy(c->P(P_WCONV), nullptr, (int)(d.k * d.D), (int)d.Kc, (int)d.D, 0, static_cast<float *>(c->Wconv_c), s));
     HIP_TRY(c, fade_virtual_copy(c->P(P_WFG), c->P(P_WFV), (int)d.Dh, (int)d.Dh, (int)(2 * d.De), 1, static_cast<float *>(c->Wfgv_c), s));
     if (c->online) HIP_TRY(c, fade_convt_build(c->P(P_WCONV), (int)d.k, (int)d.D, (int)d.Kc, c->convt_f32, s));
   }
-  HIP_TRY(c, fade_tables(c->E_c, c->P(P_GAMMA_E), c->P(P_BETA_E), c->P(P_GAMMA_L), c->P(P_BETA_L), (int)d.D, c->tabXe,
-                         c->tabXl, c->tabXe32, c->tabXhat, c->tabRstd, c->bf16, s));
+  TablesArgs t{c->E_c, c->P(P_GAMMA_E), c->P(P_BETA_E), c->P(P_GAMMA_L), c->P(P_BETA_L), (int)d.D, 0, c->tabXe, c->tabXl, c->tabXe32,
+               c->tabXhat, c->tabRstd, nullptr, nullptr, (int)d.c, nullptr, c->gg_tab, c->gv_tab};
+  if (c->gg_tab) { t.Wg = c->P(P_WG); t.Wv = c->P(P_WV); }
+  HIP_TRY(c, fade_tables(t, false, s));
   return FADE_OK;
 }
 
@@ -405,12 +408,11 @@ template <typename F> int for_each_run(const Layout &blob, const Layout &lay, F 
 // ---------------------------------------------------------------------------------------------------
 // one model step: windows -> logits -> (probabilities, table, coded symbol)
 // ---------------------------------------------------------------------------------------------------
-int forward_f32(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uint16_t *freq, float *probs) {
+int forward_f32(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uint16_t *freq, float *probs, float *probs2) {
   const Dims &d = c->d;
   hipStream_t s = c->stream;
   const bool bf = false;
   const int B = (int)d.B, Dh = (int)d.Dh, SN = (int)c->stats_n;
-  const int r16 = c->rows16 ? 1 : 0;
   // progressive ablation (the paper's component table): the head reads the last stage that is switched on
   const int level = c->cfg.ablation == 0 ? 5 : (int)c->cfg.ablation;
   const void *feat = c->Hg;
@@ -428,7 +430,6 @@ int forward_f32(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uint
     g.M = (int)(d.B * d.T); g.N = (int)d.D; g.K = (int)d.Kc;
     g.A = c->XL; g.T = (int)d.T; g.D = (int)d.D; g.taps = (int)d.k;
     g.W = c->Wconv_c; g.C = c->Hl; g.ldc = (int)d.D; g.C2 = c->online ? c->cv : nullptr; g.bias = c->P(P_BCONV);
-    g.rows16 = r16;
     HIP_TRY(c, fade_gemm(GEMM_CONV, bf, g, s));
   }
   {  // Eq. 3
@@ -436,7 +437,6 @@ int forward_f32(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uint
     GemmArgs g{};
     g.M = B; g.N = Dh; g.K = (int)d.Dc;
     g.A = c->M; g.lda = (int)d.Dc; g.W = c->Wm_c; g.C = c->Hg; g.ldc = Dh; g.C2 = c->online ? c->hm : nullptr; g.S1 = c->X; g.lam = c->P(P_LAMBDA_M);
-    g.rows16 = r16;
     HIP_TRY(c, fade_gemm(GEMM_GLOBAL, bf, g, s));
   }
   if (level >= 2) {  // Eq. 5-6
@@ -446,7 +446,6 @@ int forward_f32(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uint
     g.M = B; g.N = Dh; g.K = Dh;
     g.A = c->X; g.lda = Dh; g.W = c->Wr_c; g.C = c->Hmix; g.ldc = Dh; g.C2 = c->online ? c->alpha : nullptr; g.S1 = c->Hg; g.S2 = c->Hl;
     g.stats_out = c->stats_c;
-    g.rows16 = r16;
     HIP_TRY(c, fade_gemm(GEMM_ROUTER, bf, g, s));
   }
   if (level >= 3) {  // Eq. 7: Down(LN(H_mix))
@@ -455,7 +454,6 @@ int forward_f32(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uint
     g.M = B; g.N = (int)d.dl; g.K = Dh;
     g.A = c->Hmix; g.lda = Dh; g.stats = c->stats_c; g.stats_n = SN; g.gamma = c->P(P_GAMMA_C); g.beta = c->P(P_BETA_C);
     g.W = c->Wdown_c; g.C = c->y; g.ldc = (int)d.dl;
-    g.rows16 = r16;
     HIP_TRY(c, fade_gemm(GEMM_DOWN, bf, g, s));
   }
   if (level >= 3) {  // Eq. 7: the per-stream memory
@@ -468,7 +466,6 @@ int forward_f32(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uint
     GemmArgs g{};
     g.M = B; g.N = Dh; g.K = (int)d.dl;
     g.A = c->z; g.lda = (int)d.dl; g.W = c->Wup_c; g.C = c->Ha; g.ldc = Dh;
-    g.rows16 = r16;
     HIP_TRY(c, fade_gemm(GEMM_UP, bf, g, s));
   }
   if (level == 3) {  // Eq. 8 without its gate
@@ -481,7 +478,6 @@ int forward_f32(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uint
     g.M = B; g.N = Dh; g.K = Dh;
     g.A = c->Hmix; g.lda = Dh; g.W = c->Wc_c; g.C = c->Hc; g.ldc = Dh; g.C2 = c->online ? c->sg : nullptr; g.S1 = c->Ha; g.S2 = c->Hmix;
     g.lam = c->P(P_LAMBDA_C); g.stats_out = c->stats_f;
-    g.rows16 = r16;
     HIP_TRY(c, fade_gemm(GEMM_GATE, bf, g, s));
   }
   if (level >= 5) {  // Eq. 9
@@ -490,7 +486,6 @@ int forward_f32(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uint
     g.M = B; g.N = (int)(2 * d.De); g.K = Dh;
     g.A = c->Hc; g.lda = Dh; g.stats = c->stats_f; g.stats_n = SN; g.gamma = c->P(P_GAMMA_F); g.beta = c->P(P_BETA_F);
     g.W = c->Wfgv_c; g.C = c->Hexp; g.ldc = (int)d.De; if (c->online) { g.C2 = c->eg; g.C3 = c->ev; }
-    g.rows16 = r16;
     HIP_TRY(c, fade_gemm(GEMM_FNR_IN, bf, g, s));
   }
   if (level >= 5) {  // Eq. 10: H_expand W_f (+ statistics for its LayerNorm)
@@ -498,7 +493,6 @@ int forward_f32(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uint
     GemmArgs g{};
     g.M = B; g.N = Dh; g.K = (int)d.De;
     g.A = c->Hexp; g.lda = (int)d.De; g.W = c->Wf_c; g.C = c->V; g.ldc = Dh; g.stats_out = c->stats_o;
-    g.rows16 = r16;
     HIP_TRY(c, fade_gemm(GEMM_FNR_OUT, bf, g, s));
   }
   if (c->online && level >= 5) {  // the update needs H itself (for dW_o); frozen mode forms it only inside the head's operand load
@@ -513,7 +507,6 @@ int forward_f32(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uint
     GemmArgs g{};
     g.M = B; g.N = 256; g.K = Dh;
     g.A = feat; g.lda = Dh; g.W = c->Wo_c; g.C = c->logits; g.ldc = 256; g.bias = c->P(P_BO);
-    g.rows16 = r16;
     HIP_TRY(c, fade_gemm(GEMM_HEAD_PLAIN, bf, g, s));
   } else {  // Eq. 10's tail fused into the head's operand load; logits = H W_o + b_o
     Prof p(c, "gemm_head");
@@ -521,13 +514,12 @@ int forward_f32(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uint
     g.M = B; g.N = 256; g.K = Dh;
     g.A = c->V; g.A2 = c->Hc; g.lda = Dh; g.stats = c->stats_o; g.stats_n = SN; g.gamma = c->P(P_GAMMA_O); g.beta = c->P(P_BETA_O);
     g.lam = c->P(P_LAMBDA_O); g.W = c->Wo_c; g.C = c->logits; g.ldc = 256; g.bias = c->P(P_BO);
-    g.rows16 = r16;
     HIP_TRY(c, fade_gemm(GEMM_HEAD, bf, g, s));
   }
   {
     Prof p(c, "softmax_quant_code");
     SqcArgs a{};
-    a.ws = ws; a.B = B; a.logits = c->logits; a.probs = probs; a.freq = freq; a.sym_base = sym_base; a.cb = c->cb;
+    a.ws = ws; a.B = B; a.logits = c->logits; a.probs = probs; a.probs2 = probs2; a.freq = freq; a.sym_base = sym_base; a.cb = c->cb;
     HIP_TRY(c, fade_softmax_quant_code(a, mode, s));
   }
   return FADE_OK;
@@ -544,7 +536,7 @@ int pick_splits(int tiles, int k_blocks, int cap) {
 // steps > 1 (frozen weights, CODE_ENCODE only): rows s * B + b carry stream b at step ws.i + s through one pass; every row's
 // arithmetic is the one a single step performs (same split-K counts, same summation order), so the tables, and with them
 // the payload, are those of `steps` single steps.
-int forward_bf16(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uint16_t *freq, float *probs, int steps = 1) {
+int forward_bf16(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uint16_t *freq, float *probs, float *probs2 = nullptr, int steps = 1) {
   const Dims &d = c->d;
   hipStream_t s = c->stream;
   const int streams = (int)d.B, B = streams * steps;  // B: rows of this pass
@@ -691,7 +683,7 @@ int forward_bf16(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uin
     Prof p(c, "softmax_quant_code");
     SqcArgs a{};
     a.ws = ws; a.B = B; a.splits = sp_head; a.bias = c->P(P_BO); a.logits_out = steps > 1 ? nullptr : c->logits; a.logits = c->part_head;
-    a.probs = probs; a.freq = freq; a.sym_base = sym_base; a.cb = c->cb; a.streams = streams; a.ranges = c->ranges;
+    a.probs = probs; a.probs2 = probs2; a.freq = freq; a.sym_base = sym_base; a.cb = c->cb; a.streams = streams; a.ranges = c->ranges;
     HIP_TRY(c, fade_softmax_quant_code(a, steps > 1 ? CODE_RANGES : mode, s));
   }
   if (steps > 1) {
@@ -701,13 +693,98 @@ int forward_bf16(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uin
   return FADE_OK;
 }
 
-int forward(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uint16_t *freq, float *probs) {
-  float *p = c->online ? c->probs_buf : probs;  // the update needs the probabilities: keep them in the context
-  int rc = c->bf16 ? forward_bf16(c, ws, mode, sym_base, freq, p) : forward_f32(c, ws, mode, sym_base, freq, p);
-  if (rc) return rc;
-  if (c->online && probs)
-    HIP_TRY(c, hipMemcpyAsync(probs, c->probs_buf, c->d.B * 256 * sizeof(float), hipMemcpyDeviceToDevice, c->stream));
+// fp32 at small batches: eight launches (see fade_rows.hip). win_copy: where to keep the windows for a later update (step API).
+RowsOp rows_op(const void *A, int lda, const float *W, int ldw, int K) { return RowsOp{static_cast<const float *>(A), nullptr, lda, W, nullptr, ldw, K}; }
+int forward_rows(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uint16_t *freq, float *probs, float *probs2, uint8_t *win_copy) {
+  const Dims &d = c->d;
+  hipStream_t s = c->stream;
+  const int B = (int)d.B, Dh = (int)d.Dh, dl = (int)d.dl, De = (int)d.De, SN = (int)c->stats_n;
+  const int level = c->cfg.ablation == 0 ? 5 : (int)c->cfg.ablation;
+  auto F = [](void *p) { return static_cast<float *>(p); };
+  const void *feat = level == 1 ? c->Hg : level == 2 ? c->Hmix : c->Hc;
+  auto args = [&](int N, const RowsOp &op0, void *C, int ldc) {
+    RowsArgs a{};
+    a.M = B; a.N = N; a.op0 = op0; a.C = F(C); a.ldc = ldc; a.lds = ldc; a.stats_n = SN; a.width = Dh;
+    return a;
+  };
+  {
+    Prof p(c, "embed_cache");  // with Eq. 4
+    RowsWindowArgs w{ws, win_copy, B, (int)d.T, (int)d.D, Dh, (int)d.Dc, (int)d.c, F(c->tabXe), F(c->tabXl), c->gg_tab, c->gv_tab,
+                     F(c->X), c->online ? F(c->XL) : nullptr, F(c->M), c->GG, c->GV};
+    RowsArgs a = args((int)d.D, rows_op(nullptr, 0, c->P(P_WCONV), (int)d.D, (int)(d.k * d.D)), c->Hl, (int)d.D);
+    a.M = level >= 2 ? (int)(d.B * d.T) : 0;
+    a.C2 = c->online ? F(c->cv) : nullptr; a.bias = c->P(P_BCONV); a.ws = ws; a.tabXl = F(c->tabXl); a.T = (int)d.T; a.D = (int)d.D; a.taps = (int)d.k;
+    HIP_TRY(c, fade_rows_window(w, a, s));
+  }
+  {  // Eq. 3, and Eq. 5-6 on it
+    Prof p(c, level >= 2 ? "gemm_router" : "gemm_global");
+    RowsArgs a = args(Dh, rows_op(c->M, (int)d.Dc, c->P(P_WM), Dh, (int)d.Dc), level >= 2 ? c->Hmix : c->Hg, Dh);
+    a.op1 = rows_op(c->X, Dh, c->P(P_WR), Dh, Dh);
+    a.S1 = F(c->X); a.S2 = F(c->Hl); a.lam = c->P(P_LAMBDA_M); a.C4 = F(c->Hg);
+    if (c->online) { a.C2 = F(c->alpha); a.C3 = F(c->hm); }
+    if (level >= 2) a.stats_out = c->stats_c;
+    HIP_TRY(c, fade_rows(level >= 2 ? ROWS_MIX : ROWS_GLOBAL, a, s));
+  }
+  if (level >= 3) {  // Eq. 7: Down(LN(H_mix))
+    Prof p(c, "gemm_down");
+    RowsArgs a = args(dl, rows_op(c->Hmix, Dh, c->P(P_WDOWN), dl, Dh), c->y, dl);
+    a.stats = c->stats_c; a.gamma = c->P(P_GAMMA_C); a.beta = c->P(P_BETA_C); a.mom_out = c->online ? c->mom + 2 * (2 * B) : nullptr;
+    HIP_TRY(c, fade_rows(ROWS_DOWN, a, s));
+  }
+  if (level >= 3) {  // Eq. 7: the per-stream memory
+    Prof p(c, "cci_wu");
+    HIP_TRY(c, fade_rows_memory(c->y, F(c->WU_c), F(c->z), B, s));
+  }
+  if (level >= 3) {  // Eq. 7: Up, and Eq. 8 on it
+    Prof p(c, level >= 4 ? "gemm_gate" : "gemm_up");
+    RowsArgs a = args(Dh, rows_op(c->z, dl, c->P(P_WUP), Dh, dl), level >= 4 ? c->Hc : c->Ha, Dh);
+    a.op1 = rows_op(c->Hmix, Dh, c->P(P_WC), Dh, Dh);
+    a.S2 = F(c->Hmix); a.lam = c->P(P_LAMBDA_C); a.C4 = F(c->Ha); a.C2 = c->online ? F(c->sg) : nullptr;
+    if (level >= 4) a.stats_out = c->stats_f;
+    HIP_TRY(c, fade_rows(level >= 4 ? ROWS_GATE : ROWS_STORE, a, s));
+  }
+  if (level == 3) {  // Eq. 8 without its gate
+    Prof p(c, "residual_add");
+    HIP_TRY(c, fade_residual_add(c->Ha, c->Hmix, c->P(P_LAMBDA_C), c->Hc, (size_t)B * Dh, false, s));
+  }
+  if (level >= 5) {
+    {  // Eq. 9
+      Prof p(c, "gemm_fnr_in");
+      RowsArgs a = args(De, rows_op(c->Hc, Dh, c->P(P_WFG), De, Dh), c->Hexp, De);
+      a.op0.W2 = c->P(P_WFV);
+      a.stats = c->stats_f; a.gamma = c->P(P_GAMMA_F); a.beta = c->P(P_BETA_F);
+      if (c->online) { a.C2 = F(c->eg); a.C3 = F(c->ev); a.mom_out = c->mom + 2 * B; }
+      HIP_TRY(c, fade_rows(ROWS_FNR_IN, a, s));
+    }
+    {  // Eq. 10: H_expand W_f (+ statistics for its LayerNorm)
+      Prof p(c, "gemm_fnr_out");
+      RowsArgs a = args(Dh, rows_op(c->Hexp, De, c->P(P_WF), Dh, De), c->V, Dh);
+      a.stats_out = c->stats_o;
+      HIP_TRY(c, fade_rows(ROWS_STORE, a, s));
+    }
+  }
+  {  // head; at level 5 on Eq. 10's tail, formed in the operand load
+    Prof p(c, "gemm_head");
+    RowsArgs a = args(256, rows_op(level >= 5 ? c->V : feat, Dh, c->P(P_WO), 256, Dh), c->logits, 256);
+    a.op0.A2 = F(c->Hc); a.bias = c->P(P_BO);
+    a.stats = c->stats_o; a.gamma = c->P(P_GAMMA_O); a.beta = c->P(P_BETA_O); a.lam = c->P(P_LAMBDA_O);
+    if (c->online) { a.keep = F(c->Hout); a.mom_out = c->mom; }
+    HIP_TRY(c, fade_rows(level >= 5 ? ROWS_HEAD : ROWS_HEAD_PLAIN, a, s));
+  }
+  {
+    Prof p(c, "softmax_quant_code");
+    SqcArgs a{};
+    a.ws = ws; a.B = B; a.logits = c->logits; a.probs = probs; a.probs2 = probs2; a.freq = freq; a.sym_base = sym_base; a.cb = c->cb;
+    HIP_TRY(c, fade_softmax_quant_code(a, mode, s));
+  }
   return FADE_OK;
+}
+
+int forward(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uint16_t *freq, float *probs, uint8_t *win_copy = nullptr) {
+  // the update needs the probabilities: they are kept in the context, and written to the caller's buffer beside
+  float *p = c->online ? c->probs_buf : probs, *p2 = c->online ? probs : nullptr;
+  if (c->rows16) return forward_rows(c, ws, mode, sym_base, freq, p, p2, win_copy);
+  return c->bf16 ? forward_bf16(c, ws, mode, sym_base, freq, p, p2) : forward_f32(c, ws, mode, sym_base, freq, p, p2);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -718,7 +795,7 @@ GemmArgs args_x(fade_ctx *c, const void *dY, int Kred, int Nout, const void *wt_
   GemmArgs g{};
   g.M = (int)c->d.B; g.N = Nout; g.K = Kred; g.A = dY; g.lda = Kred; g.C = out; g.ldc = Nout;
   if (c->bf16) g.W = wt_frag;
-  else { g.W = w_f32; g.wt = 1; g.ldb = ld_w; g.rows16 = c->rows16 && Kred % 16 == 0 && Kred <= 2048 && Nout % 16 == 0; }
+  else { g.W = w_f32; g.wt = 1; g.ldb = ld_w; }
   return g;
 }
 // dW[Kw][N] = L^T R over the batch. bf16 path: both operands row-major as the forward / backward kernels left them
@@ -782,7 +859,9 @@ TransposeArgs tr_desc(fade_ctx *c, const void *src, int ld, void *dst, const flo
   t.stats = stats; t.stats_n = (int)c->stats_n; t.width = ld; t.gamma = gamma; t.beta = beta;
   return t;
 }
+int backward_rows(fade_ctx *c, const WinSrc &ws, const uint8_t *targets, long long tstride);
 int backward(fade_ctx *c, const WinSrc &ws, const uint8_t *targets, long long tstride) {
+  if (c->rows16) return backward_rows(c, ws, targets, tstride);
   const Dims &d = c->d;
   // The weight-gradient products (w) feed nothing but Adam and could overlap the chain of activation gradients (s) on a
   // second stream; that variant produced rare wrong results on this machine whose cause was not found, so both are one stream.
@@ -889,7 +968,7 @@ int backward(fade_ctx *c, const WinSrc &ws, const uint8_t *targets, long long ts
     GemmArgs g{};
     g.M = B; g.N = dl; g.K = Dh; g.splits = c->sp_dz; g.A = c->dHa; g.lda = Dh; g.C = c->dz_part; g.ldc = dl;
     if (bf) g.W = c->WT_up;
-    else { g.W = c->P(P_WUP); g.wt = 1; g.ldb = Dh; g.rows16 = c->rows16 && c->sp_dz <= 1 && dl % 16 == 0; }
+    else { g.W = c->P(P_WUP); g.wt = 1; g.ldb = Dh; }
     ph.add(GEMM_PARTIAL, g);
     if ((rc = run_phase(c, "gemms_gate_up", ph))) return rc;
   }
@@ -998,6 +1077,152 @@ int backward(fade_ctx *c, const WinSrc &ws, const uint8_t *targets, long long ts
   return FADE_OK;
 }
 
+// The update of the small-batch fp32 path (see fade_rows.hip): the chain of activation gradients, then every matrix's gradient
+// and Adam step in one launch, then the vectors.
+int backward_rows(fade_ctx *c, const WinSrc &ws, const uint8_t *targets, long long tstride) {
+  const Dims &d = c->d;
+  hipStream_t s = c->stream;
+  const int B = (int)d.B, Dh = (int)d.Dh, De = (int)d.De, dl = (int)d.dl, D = (int)d.D, SN = (int)c->stats_n;
+  const int RB = (B + fade_rows_per_block(B) - 1) / fade_rows_per_block(B);
+  const int level = c->cfg.ablation == 0 ? 5 : (int)c->cfg.ablation;
+  auto F = [](void *p) { return static_cast<float *>(p); };
+  auto Gp = [&](int id) { return c->grad + c->lay.off[id]; };
+  const void *feat = level >= 5 ? c->Hout : level >= 3 ? c->Hc : level == 2 ? c->Hmix : c->Hg;
+  void *dfeat = level >= 5 ? c->dHout : level >= 3 ? c->dHc : c->dHmix1;
+  ReduceBatch rq{};
+  auto dx = [&](const void *dY, int ldy, int K, int N, const float *W, int ldw, void *out) {
+    RowsArgs a{};
+    a.M = B; a.N = N; a.op0 = rows_op(dY, ldy, W, ldw, K); a.C = F(out); a.ldc = N; a.lds = N;
+    return a;
+  };
+  {  // loss gradient in the operand load of the head's activation gradient
+    Prof p(c, "gemms_head");
+    RowsArgs a = dx(c->probs_buf, 256, 256, Dh, c->P(P_WO), 256, dfeat);
+    a.ws = ws; a.targets = targets; a.tstride = tstride; a.u = c->ustate; a.beta1 = c->cfg.beta1; a.beta2 = c->cfg.beta2;
+    a.keep = F(c->dl); a.col_part = c->col_part;
+    HIP_TRY(c, fade_rows(ROWS_DHEAD, a, s));
+    rq.push((B + 15) / 16, 256, c->col_part, Gp(P_BO));
+  }
+  if (level >= 5) {
+    {  // Eq. 10
+      Prof p(c, "bwd_out");
+      BwdOutArgs a{};
+      a.B = B; a.Dh = Dh; a.stats_n = SN; a.ln_part = c->ln_part; a.dH = c->dHout; a.V = c->V; a.Hc = c->Hc; a.mom = c->mom; a.gamma = c->P(P_GAMMA_O);
+      a.beta = c->P(P_BETA_O); a.lam = c->P(P_LAMBDA_O); a.dV = c->dV; a.dHc = c->dHc; a.row_dlam = c->row_dlam;
+      HIP_TRY(c, fade_bwd_out(a, false, s));
+      rq.push(RB, 2 * Dh, c->ln_part, Gp(P_GAMMA_O));
+    }
+    {  // H_expand, and Eq. 9 element by element
+      Prof p(c, "gemms_fnr_out");
+      RowsArgs a = dx(c->dV, Dh, Dh, De, c->P(P_WF), Dh, c->dE);
+      a.ldc = 2 * De; a.S1 = F(c->eg); a.S2 = F(c->ev); a.lds = De;
+      HIP_TRY(c, fade_rows(ROWS_DGEGLU, a, s));
+    }
+    {
+      Prof p(c, "gemms_fnr_in");
+      RowsArgs a = dx(c->dE, 2 * De, 2 * De, Dh, c->P(P_WFG), De, c->du);
+      a.op0.W2 = c->P(P_WFV);
+      HIP_TRY(c, fade_rows(ROWS_DX_PAIR, a, s));
+    }
+  }
+  if (level >= 3) {
+    {  // LN of Eq. 9 + Eq. 8
+      Prof p(c, "bwd_gate");
+      BwdGateArgs a{};
+      a.B = B; a.Dh = Dh; a.stats_n = SN; a.ln_part = c->ln_part + (size_t)RB * 2 * Dh; a.du = level >= 5 ? c->du : nullptr; a.Hc = c->Hc; a.dHc = c->dHc;
+      a.sg = level >= 4 ? c->sg : nullptr; a.Ha = c->Ha; a.Hmix = c->Hmix; a.mom = c->mom + 2 * B; a.gamma = c->P(P_GAMMA_F); a.lam = c->P(P_LAMBDA_C);
+      a.dHa = c->dHa; a.dac = c->dac; a.dHmix = c->dHmix1; a.row_dlam = c->row_dlam + B;
+      HIP_TRY(c, fade_bwd_gate(a, false, s));
+      if (level >= 5) rq.push(RB, 2 * Dh, c->ln_part + (size_t)RB * 2 * Dh, Gp(P_GAMMA_F));
+    }
+    {  // Eq. 8's gate product and Eq. 7's Up
+      Prof p(c, "gemms_gate_up");
+      const RowsArgs dz = dx(c->dHa, Dh, Dh, dl, c->P(P_WUP), Dh, c->dz_part);
+      if (level >= 4) HIP_TRY(c, fade_rows_dx2(dx(c->dac, Dh, Dh, Dh, c->P(P_WC), Dh, c->dHmix2), dz, s));
+      else HIP_TRY(c, fade_rows(ROWS_DX, dz, s));
+    }
+    {  // per-stream memory: dy, and Adam on W_U in place
+      Prof p(c, "bwd_cci_adam");
+      BwdCciArgs a{};
+      a.B = B; a.splits = 1; a.dz_part = c->dz_part; a.y = c->y; a.WU_c = c->WU_c;
+      a.master = c->master + c->lay.off[P_WU]; a.m = c->adam_m + c->lay.off[P_WU]; a.v = c->adam_v + c->lay.off[P_WU];
+      a.dy = c->dy; a.dy_at = c->dy_at; a.u = c->ustate;
+      a.lr = c->cfg.lr; a.beta1 = c->cfg.beta1; a.beta2 = c->cfg.beta2; a.eps = c->cfg.eps;
+      a.g_dbg = c->debug_wu_grad ? c->grad + c->lay.off[P_WU] : nullptr;
+      HIP_TRY(c, fade_bwd_cci(a, false, s));
+    }
+    {
+      Prof p(c, "gemms_down");
+      HIP_TRY(c, fade_rows(ROWS_DX, dx(c->dy, dl, dl, Dh, c->P(P_WDOWN), dl, c->dnc), s));
+    }
+  }
+  {  // LN of Eq. 7 + Eq. 5-6 + branch activations
+    Prof p(c, "bwd_mix");
+    BwdMixArgs a{};
+    a.B = B; a.Dh = Dh; a.stats_n = SN; a.ln_part = c->ln_part + (size_t)RB * 4 * Dh; a.dnc = level >= 3 ? c->dnc : nullptr; a.Hmix = c->Hmix; a.dHmix1 = c->dHmix1;
+    a.dHmix2 = level >= 4 ? c->dHmix2 : nullptr; a.alpha = level >= 2 ? c->alpha : nullptr;
+    a.hm = c->hm; a.cv = c->cv; a.X = c->X; a.mom = c->mom + 2 * (2 * B); a.gamma = c->P(P_GAMMA_C);
+    a.lam = c->P(P_LAMBDA_M); a.dar = c->dar; a.dhm = c->dhm; a.dcv = c->dcv; a.dX = c->dX1; a.row_dlam = c->row_dlam + 2 * B;
+    HIP_TRY(c, fade_bwd_mix(a, false, s));
+    if (level >= 3) rq.push(RB, 2 * Dh, c->ln_part + (size_t)RB * 4 * Dh, Gp(P_GAMMA_C));
+    if (level >= 5) rq.push(B, 1, c->row_dlam, Gp(P_LAMBDA_O));  // the three residual scales: per-stream terms, one column each
+    if (level >= 3) rq.push(B, 1, c->row_dlam + B, Gp(P_LAMBDA_C));
+    rq.push(B, 1, c->row_dlam + 2 * B, Gp(P_LAMBDA_M));
+  }
+  {  // what starts from d(pre-activations): router, Eq. 4's two gradients, the newest slot
+    Prof p(c, "bwd_last");
+    RowsArgs rt = dx(c->dar, Dh, Dh, Dh, c->P(P_WR), Dh, c->dX2);
+    RowsArgs ct = dx(c->dcv, 0, (int)d.k * D, D, c->P(P_WCONV), 0, c->dxl);
+    ct.M = (int)(d.B * d.T); ct.T = (int)d.T; ct.D = D; ct.taps = (int)d.k;
+    if (level < 2) { rt.M = 0; ct.M = 0; }
+    const RowsSlotArgs sl{ws, B, (int)d.T, D, Dh, (int)d.c, F(c->dhm), c->P(P_WM) + (d.Dc - d.c) * d.Dh, c->GG, c->GV, c->P(P_WG), c->P(P_WV), c->tabXe32,
+                          c->dgg, c->dgv, c->dxt, c->xt};
+    const RowsConvArgs cg{F(c->XL), F(c->dcv), (int)(d.B * d.T), (int)d.T, D, (int)d.k, c->conv_part};
+    HIP_TRY(c, fade_rows_last(rt, ct, cg, sl, s));
+    if (level >= 2) rq.push(fade_rows_conv_parts(cg.tokens), ((int)d.k * D + 1) * D, c->conv_part, Gp(P_WCONV));  // W_conv then b_conv, adjacent in the blob
+  }
+  {  // the two per-token LayerNorms and the embedding
+    Prof p(c, "bwd_embed");
+    BwdTokenArgs a{};
+    a.ws = ws; a.B = B; a.T = (int)d.T; a.D = D; a.dX1 = c->dX1; a.dX2 = c->dX2; a.dxl = c->dxl; a.dxt = c->dxt;
+    a.tabXhat = c->tabXhat; a.tabRstd = c->tabRstd; a.gamma_e = c->P(P_GAMMA_E); a.gamma_l = c->P(P_GAMMA_L);
+    a.part = c->emb_part;
+    HIP_TRY(c, fade_bwd_embed(a, c->emb_blocks, c->tok_part, Gp(P_E), Gp(P_GAMMA_E), false, rq, s));
+  }
+  const AdamArrays opt{c->grad, c->master, c->adam_m, c->adam_v, c->ustate, c->cfg.lr, c->cfg.beta1, c->cfg.beta2, c->cfg.eps};
+  {
+    Prof p(c, "adam_matrices");
+    RowsDwArgs w{};
+    w.opt = opt;
+    auto add = [&](int id, const void *L, int M, const void *R_, int ldr, int N, const float *ga = nullptr, const float *be = nullptr, const float *mom = nullptr) {
+      w.d[w.count++] = RowsDw{static_cast<const float *>(L), static_cast<const float *>(R_), M, ldr, B, M, N, ga, be, mom, c->lay.off[id]};
+    };
+    add(P_WO, feat, Dh, c->dl, 256, 256);
+    if (level >= 5) {
+      add(P_WF, c->Hexp, De, c->dV, Dh, Dh);
+      add(P_WFG, c->Hc, Dh, c->dE, 2 * De, De, c->P(P_GAMMA_F), c->P(P_BETA_F), c->mom + 2 * B);
+      add(P_WFV, c->Hc, Dh, F(c->dE) + De, 2 * De, De, c->P(P_GAMMA_F), c->P(P_BETA_F), c->mom + 2 * B);
+    }
+    if (level >= 4) add(P_WC, c->Hmix, Dh, c->dac, Dh, Dh);
+    if (level >= 3) {
+      add(P_WUP, c->z, dl, c->dHa, Dh, Dh);
+      add(P_WDOWN, c->Hmix, Dh, c->dy, dl, dl, c->P(P_GAMMA_C), c->P(P_BETA_C), c->mom + 2 * (2 * B));
+    }
+    if (level >= 2) add(P_WR, c->X, Dh, c->dar, Dh, Dh);
+    add(P_WM, c->M, (int)d.Dc, c->dhm, Dh, Dh);
+    add(P_WG, c->xt, D, c->dgg, (int)d.c, (int)d.c);
+    add(P_WV, c->xt, D, c->dgv, (int)d.c, (int)d.c);
+    HIP_TRY(c, fade_rows_dw_adam(w, s));
+  }
+  {
+    Prof p(c, "refresh_small");
+    rq.opt = opt;
+    rq.push(1, (int)(256 * d.D), Gp(P_E), Gp(P_E));
+    HIP_TRY(c, fade_reduce_batch(rq, s));
+    return prepare_compute(c, false);
+  }
+}
+
 int check_dev_err(fade_ctx *c) {  // the stream is idle
   const int e = *static_cast<volatile int *>(c->dev_err);
   if (e == 1) return fail(c, FADE_E_BUFFER_TOO_SMALL, "payload buffer exhausted");
@@ -1065,7 +1290,7 @@ int run_loop(fade_ctx *c, uint8_t *bytes_dev, size_t n, size_t first, size_t cou
     } else if (mode == CODE_ENCODE && c->steps_max > 1 && last - i > 1) {
       // frozen weights and the whole input at hand: the model's steps do not depend on each other, only the coder's do
       const int steps = (int)std::min<size_t>((size_t)c->steps_max, last - i);
-      int rc = forward_bf16(c, ws, mode, bytes_dev, nullptr, nullptr, steps);
+      int rc = forward_bf16(c, ws, mode, bytes_dev, nullptr, nullptr, nullptr, steps);
       if (rc) return rc;
       i += (size_t)steps - 1;
       if (last - (i + 1) < 2)  // leave the rolling cache as the last of these steps would have: single steps may follow
@@ -1154,7 +1379,8 @@ int fade_create(const fade_config *cfg, fade_ctx **out) {
   }
   const size_t R = d.B * (size_t)c->steps_max;  // rows of the forward buffers
   const size_t np = c->lay.off[P_COUNT], BDh = R * d.Dh;
-  // fp32 contexts of up to 256 streams use the small-batch products (statistics per 16 columns); FADE_F32_ROWS16=0 keeps the general kernel
+  // fp32 contexts of up to 256 streams use the small-batch kernels of fade_rows.hip (statistics per 16 columns); FADE_F32_ROWS16=0
+  // keeps the general ones
   c->rows16 = !c->bf16 && d.B <= 256 && d.Dh <= 2048 && d.Dc <= 2048 && d.De <= 2048 && d.Dh % 16 == 0 && d.Dc % 16 == 0 && d.De % 64 == 0 &&
               d.Kc % 16 == 0 && d.D % 16 == 0;
   if (const char *e = getenv("FADE_F32_ROWS16")) c->rows16 = c->rows16 && e[0] != '0';
@@ -1214,6 +1440,10 @@ int fade_create(const fade_config *cfg, fade_ctx **out) {
     TRY_ALLOC(A(&c->Wconv_c, d.Kc * d.D));
     TRY_ALLOC(A(&c->Wfgv_c, d.Dh * 2 * d.De));
   }
+  if (c->rows16) {
+    TRY_ALLOC(dev_alloc(c, &c->gg_tab, 256 * d.c));
+    TRY_ALLOC(dev_alloc(c, &c->gv_tab, 256 * d.c));
+  }
   TRY_ALLOC(A(&c->tabXe, 256 * d.D));
   TRY_ALLOC(A(&c->tabXl, 256 * d.D));
   TRY_ALLOC(dev_alloc(c, &c->tabXe32, 256 * d.D));
@@ -1267,7 +1497,10 @@ int fade_create(const fade_config *cfg, fade_ctx **out) {
       TRY_ALLOC(A(b.p, b.n));
       if (hipMemsetAsync(*b.p, 0, b.n * c->esz, c->stream) != hipSuccess) { fade_destroy(c); return FADE_E_HIP; }
     }
-    if (!c->bf16) {  // fp32 path: feature-major copies [width][Bp] of the remaining left operands
+    if (c->rows16) {
+      TRY_ALLOC(dev_alloc(c, &c->mom, 3 * 2 * d.B));
+      TRY_ALLOC(dev_alloc(c, &c->xt, d.B * d.D));
+    } else if (!c->bf16) {  // general fp32 path: feature-major copies [width][Bp] of the remaining left operands
       struct { void **p; size_t n; } lts[] = {{&c->LT[0], d.Dh * Bp}, {&c->LT[1], d.De * Bp}, {&c->LT[3], d.Dh * Bp}, {&c->LT[4], d.dl * Bp},
                                                {&c->LT[6], d.Dc * Bp}, {&c->LT[7], d.Dh * Bp}};
       for (auto &b : lts) TRY_ALLOC(A(b.p, b.n));
@@ -1421,12 +1654,15 @@ int fade_step_probs(fade_ctx *c, const uint8_t *windows_dev, const uint8_t *acti
   if (!c->have_weights) return fail(c, FADE_E_NO_WEIGHTS, "no weights loaded");
   WinSrc ws{};
   ws.base = windows_dev; ws.stride = (long long)c->d.T; ws.n = 0; ws.active = active_dev ? active_dev : c->ones; ws.i = (long long)c->d.T;
-  if (c->online) {  // fade_step_update re-reads the windows (embedding and slot gradients): keep a copy, the caller's may be gone by then
-    HIP_TRY(c, hipMemcpyAsync(c->win_copy, windows_dev, c->d.B * c->d.T, hipMemcpyDeviceToDevice, c->stream));
-    ws.base = c->win_copy;
-  }
   c->last_ws = ws;
-  return forward(c, ws, CODE_NONE, nullptr, freq_dev, probs_dev);
+  if (c->online) {  // fade_step_update re-reads the windows (embedding and slot gradients): keep a copy, the caller's may be gone by then
+    c->last_ws.base = c->win_copy;
+    if (!c->rows16) {  // there the window kernel copies
+      HIP_TRY(c, hipMemcpyAsync(c->win_copy, windows_dev, c->d.B * c->d.T, hipMemcpyDeviceToDevice, c->stream));
+      ws.base = c->win_copy;
+    }
+  }
+  return forward(c, ws, CODE_NONE, nullptr, freq_dev, probs_dev, c->online ? c->win_copy : nullptr);
 }
 
 int fade_step_update(fade_ctx *c, const uint8_t *targets_dev, const uint8_t *active_dev) {

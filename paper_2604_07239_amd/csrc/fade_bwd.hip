@@ -336,7 +336,8 @@ __global__ __launch_bounds__(256) void bwd_out_kernel(BwdOutArgs a) {
       ld8<AT>(static_cast<const AT *>(a.dH) + base, dH);
       ld8<AT>(static_cast<const AT *>(a.V) + base, v);
       ld8<AT>(static_cast<const AT *>(a.Hc) + base, hc);
-      moments(a.stats + (size_t)b * a.stats_n * 2, a.stats_n, a.Dh, mean, rstd[r]);
+      if (a.mom) { mean = a.mom[2 * b]; rstd[r] = a.mom[2 * b + 1]; }
+      else moments(a.stats + (size_t)b * a.stats_n * 2, a.stats_n, a.Dh, mean, rstd[r]);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         xh[r][i] = (v[i] - mean) * rstd[r];
@@ -423,7 +424,8 @@ __global__ __launch_bounds__(256) void bwd_gate_kernel(BwdGateArgs a) {
       float du[8], hc[8];
       ld8<AT>(static_cast<const AT *>(a.Hc) + base, hc);  // requested before the statistics are summed
       if (!a.du_part && a.du) ld8<AT>(static_cast<const AT *>(a.du) + base, du);
-      moments(a.stats + (size_t)b * a.stats_n * 2, a.stats_n, a.Dh, mean, rstd[r]);
+      if (a.mom) { mean = a.mom[2 * b]; rstd[r] = a.mom[2 * b + 1]; }
+      else moments(a.stats + (size_t)b * a.stats_n * 2, a.stats_n, a.Dh, mean, rstd[r]);
       if (a.du_part || !a.du) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) du[i] = 0.0f;
@@ -528,7 +530,8 @@ __global__ __launch_bounds__(256) void bwd_mix_kernel(BwdMixArgs a) {
         ld8<AT>(static_cast<const AT *>(a.dnc) + base, dn);
         ld8<AT>(static_cast<const AT *>(a.Hmix) + base, hm);
       }
-      moments(a.stats + (size_t)b * a.stats_n * 2, a.stats_n, a.Dh, mean, rstd[r]);
+      if (a.mom) { mean = a.mom[2 * b]; rstd[r] = a.mom[2 * b + 1]; }
+      else moments(a.stats + (size_t)b * a.stats_n * 2, a.stats_n, a.Dh, mean, rstd[r]);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         xh[r][i] = (hm[i] - mean) * rstd[r];

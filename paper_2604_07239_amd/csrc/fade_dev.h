@@ -127,7 +127,6 @@ struct GemmArgs {
   const float *bias;
   float *stats_out;       // optional [M][N / BN][2]
   const float *fold_s, *fold_t;  // EPI_GEGLU_FOLD: the folded LayerNorm's column vectors [N] (stats / stats_n: rows of A)
-  int rows16;             // fp32 path: the small-batch kernel (16 x 16 tiles; row statistics per 16 columns instead of per 128)
   int col_groups;         // pipelined kernel: column ranges of the XCD split of the tile grid (1, 2, 4, 8; 0 = chosen by the launcher)
 };
 
@@ -154,7 +153,15 @@ struct Tn2Group {
 // Row statistics are accumulated per block tile of BN columns; consumers add the partials in index order.
 #define FADE_STATS_BN 128
 
-// (sum, sum of squares) partials of one row -> mean and 1 / sigma (biased variance, eps 1e-5). The pairs are fetched 16 at
+// Sum and sum of squares of a row of `width` -> mean and 1 / sigma (biased variance, eps 1e-5). Explicit product and fused
+// multiply-add: this is inlined into many kernels whose results must agree bit for bit, which must not depend on which of the
+// two products the compiler fuses with the subtraction.
+__device__ __forceinline__ void fade_moments_of(float s, float q, int width, float &mean, float &rstd) {
+  const float inv = 1.0f / (float)width;
+  mean = s * inv;
+  rstd = 1.0f / sqrtf(fmaxf(fmaf(q, inv, -__fmul_rn(mean, mean)), 0.0f) + 1e-5f);
+}
+// The same from a row's (sum, sum of squares) partials. The pairs are fetched 16 at
 // a time with no add between the loads (a loop of load-add-load-add would pay the memory latency once per pair); the adds
 // run in index order, slots past stats_n add an exact zero.
 __device__ __forceinline__ void fade_row_moments(const float *stats, int stats_n, int width, float &mean, float &rstd) {
@@ -174,11 +181,7 @@ __device__ __forceinline__ void fade_row_moments(const float *stats, int stats_n
       q += in ? v[j].y : 0.0f;
     }
   }
-  const float inv = 1.0f / (float)width;
-  mean = s * inv;
-  // explicit product and fused multiply-add: this function is inlined into many kernels whose results must agree bit for
-  // bit, which must not depend on which of the two products the compiler fuses with the subtraction
-  rstd = 1.0f / sqrtf(fmaxf(fmaf(q, inv, -__fmul_rn(mean, mean)), 0.0f) + 1e-5f);
+  fade_moments_of(s, q, width, mean, rstd);
 }
 
 // Row-wise element kernels: thread t = blockIdx.x * 256 + tid owns the 8-wide chunk t % chunks of the RPT rows of row

@@ -19,8 +19,8 @@
 //     atomics, so the result is reproducible bit for bit, and the same for every tile shape.
 //   * blockIdx -> tile: the chip dispatches consecutive workgroups round-robin over its 8 XCDs, each with a private L2;
 //     tile_of_block gives an XCD a range of column tiles (its share of W stays in its L2) and walks its tiles row by row.
-// fp32 path: the same prologues / epilogues around a plain FMA core (gemm_f32_kernel), and 16 x 16 tiles with the
-// contraction split over the workgroup's threads for batches of up to 256 rows (gemm_f32_rows_kernel).
+// fp32 path above 256 rows: the same prologues / epilogues around a plain FMA core (gemm_f32_kernel); smaller batches have
+// kernels of their own (fade_rows.hip).
 #include <cstdlib>
 #include <type_traits>
 
@@ -1304,162 +1304,6 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
   epilogue<EPI, AT, BM, BN>(g, Cs, m0, n0, nt, tid);
 }
 
-// ---------------------------------------------------------------------------------------------------
-// fp32 products of very small batches (the 16-stream configuration): 16 rows x 16 columns per workgroup, the whole
-// contraction inside it. With 16 rows a 128-column tile leaves four workgroups on a 256-unit chip walking K in lock step
-// (50 us for a 16 x 512 x 512 product); here N / 16 workgroups each keep the 16 operand rows in LDS (prologue applied
-// once) and split K 64 ways: thread (q, cg) owns the terms k = q, q + 64, ... of all 16 rows for 4 of the tile's columns,
-// so every weight element is loaded once per workgroup (a lane's row pieces are requested up front, before the operand
-// rows are staged: one round trip for K <= 512), the operand values come from LDS (a wavefront reads 16 consecutive k of
-// one row: conflict-free, each value broadcast to the 4 column groups). The 64 K slices are added in a fixed tree: inside
-// a wavefront a butterfly over the slice bits of the lane index that halves the rows a lane keeps at every level (lane
-// bit 5 decides rows 0-7 / 8-15, bit 4 the half of those, ...: 32 + 16 + 8 + 4 exchanges instead of 4 x 64), then the four
-// wavefronts' sums in wavefront order through LDS. A step streams the weights (4 MB for that configuration) once.
-// GeGLU tiles take 8 gate and the matching 8 value columns of a 128-column group (columns c and c + 64).
-// Row statistics are left per 16-column tile: consumers must be told stats_n = N / 16.
-// ---------------------------------------------------------------------------------------------------
-template <int PRO, int EPI>
-__global__ __launch_bounds__(256) void gemm_f32_rows_kernel(GemmArgs g) {
-  typedef float AT;
-  constexpr int BM = 16, BN = 16, LDC = BN + 4;
-  constexpr bool kGeglu = EPI == EPI_GEGLU;
-  extern __shared__ __align__(16) unsigned char smem[];
-  const int LDA = g.K + 16;  // rows 16 banks apart
-  float *As = reinterpret_cast<float *>(smem);   // [16][LDA]
-  float *Cs = As + BM * LDA;                     // [16][LDC]
-  float *mom = Cs + BM * LDC;                    // [16][2]
-  float *red = mom + 2 * BM;                     // [4 wavefronts][16][16]
-  const int tid = threadIdx.x, nt = blockIdx.x, m0 = blockIdx.y * BM;
-  const int n0 = kGeglu ? (nt / 8) * 128 + (nt % 8) * 8 : nt * BN;   // first (gate) column of the tile in W
-  const int q = tid >> 2, cg = tid & 3, lane = tid & 63, wave = tid >> 6;
-  // this thread's 4 columns of W: gate columns 0-7 then value columns 64-71 for a GeGLU tile
-  const float *W = static_cast<const float *>(g.W) + n0 + (kGeglu ? (cg >> 1) * 64 + (cg & 1) * 4 : cg * 4);
-  constexpr int U = 8;  // k values of a lane per batch (K <= 512: all of them)
-  f32x4 w[U];
-  // W given transposed ([N][ldb], K contiguous: the activation gradients of the update): the 16 slices of a wavefront
-  // read 64 contiguous bytes of each of the tile's columns
-  const float *Wt = static_cast<const float *>(g.W) + (size_t)(n0 + cg * 4) * g.ldb;
-  auto load_w = [&](int k0) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int k = k0 + 64 * u, kk = k < g.K ? k : 0;  // past K: any row, its term is dropped
-      if (g.wt) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) w[u][j] = Wt[(size_t)j * g.ldb + kk];
-      } else {
-        w[u] = *reinterpret_cast<const f32x4 *>(W + (size_t)kk * g.N);
-      }
-    }
-  };
-  load_w(q);
-  float lam = 0.0f;
-  if (PRO == PRO_FINAL) lam = g.lam[0];
-  if (PRO == PRO_LN || PRO == PRO_FINAL) {
-    if (tid < BM) {
-      float mean, rstd;
-      row_moments(g, m0 + tid, mean, rstd);
-      mom[tid * 2] = mean; mom[tid * 2 + 1] = rstd;
-    }
-    __syncthreads();
-  }
-  const int kch = g.K / 8;
-  for (int c = tid; c < BM * kch; c += 256) {
-    const int row = c / kch, kc = (c - row * kch) * 8;
-    Raw8<AT> a, a2;
-    stage_load<PRO, AT>(g, m0 + row, kc, a, a2);
-    float v[8];
-    stage_transform<PRO, AT>(g, kc, a, a2, (PRO == PRO_LN || PRO == PRO_FINAL) ? mom[row * 2] : 0.0f,
-                             (PRO == PRO_LN || PRO == PRO_FINAL) ? mom[row * 2 + 1] : 1.0f, lam, v);
-    store8(As + row * LDA + kc, v);
-  }
-  __syncthreads();
-  float acc[16][4];
-#pragma unroll
-  for (int r = 0; r < 16; ++r)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[r][j] = 0.0f;
-  for (int k0 = q; k0 < g.K; k0 += 64 * U) {
-    if (k0 != q) load_w(k0);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {  // in k order
-      const int k = k0 + 64 * u;
-      if (k < g.K) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float a = As[r * LDA + k];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[r][j] = fmaf(a, w[u][j], acc[r][j]);
-        }
-      }
-    }
-  }
-  // butterfly over the 16 K slices of a wavefront (lane bits 2-5), keeping half of the rows at every level
-  float h8[8][4], h4[4][4], h2[2][4], h1[4];
-  {
-    const bool up = lane & 32;
-#pragma unroll
-    for (int r = 0; r < 8; ++r)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float keep = up ? acc[8 + r][j] : acc[r][j], send = up ? acc[r][j] : acc[8 + r][j];
-        h8[r][j] = keep + __shfl_xor(send, 32, 64);
-      }
-  }
-  {
-    const bool up = lane & 16;
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float keep = up ? h8[4 + r][j] : h8[r][j], send = up ? h8[r][j] : h8[4 + r][j];
-        h4[r][j] = keep + __shfl_xor(send, 16, 64);
-      }
-  }
-  {
-    const bool up = lane & 8;
-#pragma unroll
-    for (int r = 0; r < 2; ++r)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float keep = up ? h4[2 + r][j] : h4[r][j], send = up ? h4[r][j] : h4[2 + r][j];
-        h2[r][j] = keep + __shfl_xor(send, 8, 64);
-      }
-  }
-  {
-    const bool up = lane & 4;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float keep = up ? h2[1][j] : h2[0][j], send = up ? h2[0][j] : h2[1][j];
-      h1[j] = keep + __shfl_xor(send, 4, 64);
-    }
-  }
-  {  // the lane now holds row (bits 5, 4, 3, 2 of the lane index), its 4 columns, summed over the wavefront's 16 slices
-    const int row = ((lane >> 5) & 1) * 8 + ((lane >> 4) & 1) * 4 + ((lane >> 3) & 1) * 2 + ((lane >> 2) & 1);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) red[(wave * 16 + row) * 16 + cg * 4 + j] = h1[j];
-  }
-  __syncthreads();
-  Cs[(tid >> 4) * LDC + (tid & 15)] = (red[tid] + red[256 + tid]) + (red[512 + tid] + red[768 + tid]);
-  __syncthreads();
-  epilogue<EPI, AT, BM, BN>(g, Cs, m0, kGeglu ? 0 : n0, nt, tid);
-}
-
-template <int PRO, int EPI>
-hipError_t launch_f32_rows(const GemmArgs &g, hipStream_t s) {
-  constexpr bool kGeglu = EPI == EPI_GEGLU;
-  if (g.M <= 0 || g.K % 16 || g.K > 2048 || g.N % (kGeglu ? 128 : 16) || (g.wt && (kGeglu || g.ldb < g.K))) return hipErrorInvalidValue;
-  const size_t lds = ((size_t)16 * (g.K + 16) + 16 * 20 + 32 + 4 * 256) * sizeof(float);
-  static size_t attr = 0;
-  auto kern = gemm_f32_rows_kernel<PRO, EPI>;
-  if (lds > attr) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    attr = lds;
-  }
-  hipLaunchKernelGGL(kern, dim3(g.N / 16, (g.M + 15) / 16), dim3(256), lds, s, g);
-  return hipGetLastError();
-}
-
 template <int WM, int WN, int TM, int TN, int PRO, int EPI, bool KEEP = false>
 hipError_t launch_bf16(const GemmArgs &g, hipStream_t s) {
   constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
@@ -1818,25 +1662,6 @@ hipError_t fade_gemm(int op, bool bf16, const GemmArgs &g, hipStream_t s) {
         if (!g.stats || !g.A2 || !g.gamma || !g.beta || !g.lam || g.N != 256) return hipErrorInvalidValue;
         if (g.C2) return launch_bf16<1, 4, 1, 2, PRO_FINAL, EPI_PARTIAL, true>(g, s);  // H itself kept for the update
         return launch_bf16<1, 4, 1, 2, PRO_FINAL, EPI_PARTIAL>(g, s);
-      default: return hipErrorInvalidValue;
-    }
-  }
-  if (g.rows16) {  // very small batches: 16 x 16 tiles, statistics per 16 columns (see gemm_f32_rows_kernel)
-    switch (op) {
-      case GEMM_CONV:     return launch_f32_rows<PRO_CONV, EPI_CONV>(g, s);
-      case GEMM_GLOBAL:   return launch_f32_rows<PRO_PLAIN, EPI_GLOBAL>(g, s);
-      case GEMM_ROUTER:   return launch_f32_rows<PRO_PLAIN, EPI_MIX>(g, s);
-      case GEMM_DOWN:     return launch_f32_rows<PRO_LN, EPI_STORE_F32>(g, s);
-      case GEMM_UP:       return launch_f32_rows<PRO_PLAIN, EPI_STORE>(g, s);
-      case GEMM_GATE:     return launch_f32_rows<PRO_PLAIN, EPI_GATE>(g, s);
-      case GEMM_FNR_IN:   return launch_f32_rows<PRO_LN, EPI_GEGLU>(g, s);
-      case GEMM_FNR_OUT:  return launch_f32_rows<PRO_PLAIN, EPI_STORE>(g, s);
-      case GEMM_HEAD:     return launch_f32_rows<PRO_FINAL, EPI_STORE_F32>(g, s);
-      case GEMM_HEAD_PLAIN: return launch_f32_rows<PRO_PLAIN, EPI_STORE_F32>(g, s);
-      case GEMM_X_STORE:  return launch_f32_rows<PRO_PLAIN, EPI_STORE>(g, s);  // W passed transposed (wt = 1)
-      case GEMM_PARTIAL:  // one range only: a plain fp32 store
-        if (g.splits > 1 || g.sum_splits) return hipErrorInvalidValue;
-        return launch_f32_rows<PRO_PLAIN, EPI_PARTIAL>(g, s);
       default: return hipErrorInvalidValue;
     }
   }

@@ -90,6 +90,7 @@ struct SqcArgs {
   float *logits_out;    // optional [B][256]: the reduced logits
   const float *logits;  // [B][256] or [splits][B][256]
   float *probs;         // optional [B][256]
+  float *probs2;        // optional second copy
   uint16_t *freq;       // optional [B][256]
   uint8_t *sym_base;    // symbol of stream b at step i lives at sym_base + b * ws.stride + i
   CoderBufs cb;
@@ -116,9 +117,9 @@ struct PrepDesc {
 struct TablesArgs {
   const float *E, *ge, *be, *gl, *bl;
   int D, round_bf16;       // round_bf16: E counts as its bf16 rounding (what the bf16 path's embedding copy holds)
-  void *tabXe, *tabXl;     // bf16
+  void *tabXe, *tabXl;     // activation type
   float *tabXe32, *tabXhat, *tabRstd;
-  // optional, same launch: Eq. 1 per symbol from the masters W_g, W_v [D][c] (rounded to bf16 as their compute copies are):
+  // optional, same launch: Eq. 1 per symbol from the masters W_g, W_v [D][c] (round_bf16: rounded as their compute copies are):
   // slot_tab [256][c] bf16 entries (frozen weights) and / or gg_tab, gv_tab [256][c] fp32 pre-activations (adapting weights)
   const float *Wg, *Wv;
   int c;
@@ -140,8 +141,7 @@ hipError_t fade_hout(const HoutArgs &a, bool bf16, hipStream_t s);
 hipError_t fade_virtual_copy(const float *W0, const float *W1, int k_real, int K, int N, int interleave, float *out, hipStream_t s);
 hipError_t fade_convert(const float *src, void *dst, size_t n, bool bf16, hipStream_t s);
 hipError_t fade_round_bf16(const float *src, float *dst, size_t n, hipStream_t s);
-hipError_t fade_tables(const float *E, const float *ge, const float *be, const float *gl, const float *bl, int D, void *tabXe,
-                       void *tabXl, float *tabXe32, float *tabXhat, float *tabRstd, bool bf16, hipStream_t s);
+hipError_t fade_tables(const TablesArgs &t, bool bf16, hipStream_t s);
 hipError_t fade_embed_cache(const EmbedArgs &a, int B, bool bf16, hipStream_t s);
 hipError_t fade_embed_steps(const EmbedArgs &a, hipStream_t s);  // bf16, a.B * a.S rows, cache rebuilt from the window
 hipError_t fade_encode_ranges(const WinSrc &ws, const uint2 *ranges, int B, int S, const CoderBufs &cb, hipStream_t s);
@@ -200,6 +200,7 @@ struct BwdOutArgs {
   int groups;  // row groups per workgroup (set by the launcher)
   float *ln_part;  // [blocks][2][Dh] partial sums of d gamma, d beta over this workgroup's rows
   const void *dH, *V, *Hc;
+  const float *mom;    // optional [B][2]: the rows' mean and 1 / sigma (else from stats)
   const float *stats, *gamma, *beta, *lam;
   void *dV, *dHc;
   float *row_dlam;
@@ -209,6 +210,7 @@ struct BwdGateArgs {
   int groups;  // row groups per workgroup (set by the launcher)
   float *ln_part;
   const void *du, *Hc, *dHc, *sg, *Ha, *Hmix;
+  const float *mom;    // as in BwdOutArgs
   const float *stats, *gamma, *lam;
   void *dHa, *dac, *dHmix;
   float *row_dlam;
@@ -220,6 +222,7 @@ struct BwdMixArgs {
   int groups;  // row groups per workgroup (set by the launcher)
   float *ln_part;
   const void *dnc, *Hmix, *dHmix1, *dHmix2, *alpha, *hm, *cv, *X;  // hm, cv: pre-activations of the global / local stream
+  const float *mom;    // as in BwdOutArgs
   const float *stats, *gamma, *lam;
   void *dar, *dhm, *dcv, *dX;
   float *row_dlam;
@@ -338,3 +341,86 @@ hipError_t fade_bwd_slot_conv(const BwdSlotArgs &sa, float *dWgv, const ConvGrad
 hipError_t fade_conv_grad(const ConvGradArgs &a, float *dWb, bool bf16, ReduceBatch &rb, hipStream_t s);
 hipError_t fade_bwd_embed(const BwdTokenArgs &a, int nblocks, float *contrib, float *dE, float *dparams, bool bf16, ReduceBatch &rb,
                           hipStream_t s);
+
+// ---------------------------------------------------------------------------------------------------
+// fp32 path at small batches (fade_rows.hip): 16 x 16 tiles, row statistics per 16 columns
+// ---------------------------------------------------------------------------------------------------
+enum {
+  ROWS_GLOBAL = 0,  // Eq. 3 alone (ablation level 1)
+  ROWS_MIX,         // Eq. 3 (op0) and Eq. 5-6 (op1)
+  ROWS_STORE,       // C = A W (+ row statistics)
+  ROWS_DOWN,        // Eq. 7's Down: C = LN(A) W
+  ROWS_GATE,        // Eq. 7's Up (op0) and Eq. 8 (op1)
+  ROWS_FNR_IN,      // Eq. 9 on LN(A), W = gate, W2 = value matrix, N = D_e
+  ROWS_HEAD,        // logits = (psi(LN(A)) + lam A2) W + bias; H itself to keep when set
+  ROWS_HEAD_PLAIN,  // logits = A W + bias
+  ROWS_DHEAD,       // loss gradient (to keep) and its product with W_o^T
+  ROWS_DX,          // dX = dY W^T
+  ROWS_DGEGLU,      // dH_expand = dY W_f^T, then Eq. 9's element-wise backward: C = [d gate | d value], ldc = 2 D_e
+  ROWS_DX_PAIR,     // dX = dY [W | W2]^T
+};
+struct RowsOp {
+  const float *A, *A2;  // [M][lda]
+  int lda;
+  const float *W, *W2;  // [K][ldw], or [N][ldw] where W is applied transposed
+  int ldw, K;
+};
+struct RowsArgs {
+  int M, N;
+  RowsOp op0, op1;
+  const float *stats; int stats_n, width;  // LayerNorm of op0's rows
+  const float *gamma, *beta, *lam;
+  float *mom_out;                          // optional [M][2]: mean and 1 / sigma of op0's rows, for the update
+  float *C, *C2, *C3, *C4; int ldc;        // C2: alpha / sigma-gate / gate, C3: pre-activation of Eq. 3 / value, C4: H_global / H_a
+  const float *S1, *S2; int lds;
+  const float *bias;
+  float *stats_out;
+  float *keep;                             // ROWS_HEAD: H; ROWS_DHEAD: dlogits
+  // window geometry of Eq. 4
+  WinSrc ws;
+  const float *tabXl;
+  int T, D, taps;
+  // loss gradient (op0.A = probabilities)
+  const uint8_t *targets; long long tstride;
+  UpdateState *u;
+  float beta1, beta2;
+  float *col_part;                         // [M / 16][256] first stage of db_o
+};
+struct RowsWindowArgs {
+  WinSrc ws;
+  uint8_t *win_copy;  // optional [B][T]
+  int B, T, D, Dh, Dc, c;
+  const float *tabXe, *tabXl, *gg_tab, *gv_tab;
+  float *X, *XL, *M, *GG, *GV;
+};
+struct RowsSlotArgs {
+  WinSrc ws;
+  int B, T, D, Dh, c;
+  const float *dhm, *Wslot;  // [B][Dh]; rows [Dc - c, Dc) of W_m
+  const float *GG, *GV, *Wg, *Wv, *tabXe32;
+  float *dgg, *dgv, *dxt, *xt;
+};
+struct RowsConvArgs {  // Eq. 4's weight gradient: partial sums [fade_rows_conv_parts(tokens)][taps * D + 1][D]
+  const float *XL, *dcv;
+  int tokens, T, D, taps;
+  float *part;
+};
+struct RowsDw {  // dW[M][N] = sum over k < K of L[k][m] R[k][n], then Adam at offset off of the state arrays
+  const float *L, *R;
+  int ldl, ldr, K, M, N;
+  const float *gamma, *beta, *mom;  // optional: L is normalised on the way
+  unsigned long long off;
+};
+struct RowsDwArgs {
+  int count;
+  RowsDw d[12];
+  int first[13];
+  AdamArrays opt;
+};
+hipError_t fade_rows(int op, const RowsArgs &a, hipStream_t s);
+hipError_t fade_rows_window(const RowsWindowArgs &a, const RowsArgs &conv, hipStream_t s);  // conv.M = 0: no Eq. 4
+hipError_t fade_rows_memory(const float *y, const float *WU, float *z, int B, hipStream_t s);
+hipError_t fade_rows_dx2(const RowsArgs &a, const RowsArgs &b, hipStream_t s);
+hipError_t fade_rows_last(const RowsArgs &router, const RowsArgs &convt, const RowsConvArgs &conv, const RowsSlotArgs &slot, hipStream_t s);  // convt.M = 0: neither conv part
+int fade_rows_conv_parts(int tokens);
+hipError_t fade_rows_dw_adam(RowsDwArgs &a, hipStream_t s);

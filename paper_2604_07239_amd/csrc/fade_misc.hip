@@ -103,8 +103,8 @@ __device__ __forceinline__ void tables_body(int s, const float *E, bool round_bf
   }
   if (i == 0 && tabRstd) tabRstd[s] = rstd;
 }
-// Eq. 1 for symbol s in the same workgroup: x = the row just formed (fp32, as tabXe32 holds it), W_g / W_v rounded to bf16 as
-// their compute copies are; slot_pair's order of operations, so the values are those that function gives from the copies.
+// Eq. 1 for symbol s in the same workgroup: x = the row just formed (fp32, as tabXe32 holds it), W_g / W_v as their compute copies
+// are (rounded to bf16 in the bf16 path); slot_pair's order of operations, so the values are those that function gives from the copies.
 __device__ __forceinline__ void tables_slot_body(int s, const TablesArgs &t) {
   __shared__ float xrow[256];
   const int i = threadIdx.x;
@@ -114,17 +114,18 @@ __device__ __forceinline__ void tables_slot_body(int s, const TablesArgs &t) {
   for (int q = i; q < t.c; q += 256) {
     float gg = 0.0f, gv = 0.0f;
     for (int k = 0; k < t.D; ++k) {
-      gg = fmaf(xrow[k], (float)(bf16_t)t.Wg[k * t.c + q], gg);
-      gv = fmaf(xrow[k], (float)(bf16_t)t.Wv[k * t.c + q], gv);
+      const float wg = t.Wg[k * t.c + q], wv = t.Wv[k * t.c + q];
+      gg = fmaf(xrow[k], t.round_bf16 ? (float)(bf16_t)wg : wg, gg);
+      gv = fmaf(xrow[k], t.round_bf16 ? (float)(bf16_t)wv : wv, gv);
     }
     if (t.slot_tab) static_cast<bf16_t *>(t.slot_tab)[(size_t)s * t.c + q] = (bf16_t)(gelu_f(gg) * gv);
     if (t.gg_tab) { t.gg_tab[(size_t)s * t.c + q] = gg; t.gv_tab[(size_t)s * t.c + q] = gv; }
   }
 }
-template <typename AT>
-__global__ __launch_bounds__(256) void tables_kernel(const float *E, const float *ge, const float *be, const float *gl, const float *bl, int D,
-                                                     AT *tabXe, AT *tabXl, float *tabXe32, float *tabXhat, float *tabRstd) {
-  tables_body<AT>(blockIdx.x, E, false, ge, be, gl, bl, D, tabXe, tabXl, tabXe32, tabXhat, tabRstd);
+template <typename AT> __global__ __launch_bounds__(256) void tables_kernel(TablesArgs t) {
+  tables_body<AT>(blockIdx.x, t.E, t.round_bf16 != 0, t.ge, t.be, t.gl, t.bl, t.D, static_cast<AT *>(t.tabXe), static_cast<AT *>(t.tabXl), t.tabXe32,
+                  t.tabXhat, t.tabRstd);
+  if (t.Wg) tables_slot_body(blockIdx.x, t);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -1092,6 +1093,7 @@ __global__ __launch_bounds__(256) void softmax_quant_code_kernel(SqcArgs a) {
   if (a.probs) {
     f32x4 o = {p[0], p[1], p[2], p[3]};
     *reinterpret_cast<f32x4 *>(a.probs + (size_t)b * 256 + 4 * lane) = o;
+    if (a.probs2) *reinterpret_cast<f32x4 *>(a.probs2 + (size_t)b * 256 + 4 * lane) = o;
   }
   uint32_t q[4];
   if (!quantize_wave(p, lane, q)) {
@@ -1339,15 +1341,10 @@ hipError_t fade_round_bf16(const float *src, float *dst, size_t n, hipStream_t s
   hipLaunchKernelGGL(round_bf16_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, src, dst, n);
   return hipGetLastError();
 }
-hipError_t fade_tables(const float *E, const float *ge, const float *be, const float *gl, const float *bl, int D, void *tabXe,
-                       void *tabXl, float *tabXe32, float *tabXhat, float *tabRstd, bool bf16, hipStream_t s) {
-  if (D > 256) return hipErrorInvalidValue;
-  if (bf16)
-    hipLaunchKernelGGL(tables_kernel<bf16_t>, dim3(256), dim3(256), 0, s, E, ge, be, gl, bl, D, static_cast<bf16_t *>(tabXe),
-                       static_cast<bf16_t *>(tabXl), tabXe32, tabXhat, tabRstd);
-  else
-    hipLaunchKernelGGL(tables_kernel<float>, dim3(256), dim3(256), 0, s, E, ge, be, gl, bl, D, static_cast<float *>(tabXe),
-                       static_cast<float *>(tabXl), tabXe32, tabXhat, tabRstd);
+hipError_t fade_tables(const TablesArgs &t, bool bf16, hipStream_t s) {
+  if (t.D > 256) return hipErrorInvalidValue;
+  if (bf16) hipLaunchKernelGGL(tables_kernel<bf16_t>, dim3(256), dim3(256), 0, s, t);
+  else hipLaunchKernelGGL(tables_kernel<float>, dim3(256), dim3(256), 0, s, t);
   return hipGetLastError();
 }
 hipError_t fade_embed_cache(const EmbedArgs &a, int B, bool bf16, hipStream_t s) {

@@ -1,0 +1,34 @@
+"""The fp32 kernels of small batches (16 x 16 tiles, products sharing a launch, weight gradients with their Adam step) at the
+sizes where a tile, a strip or a batch of loads ends: against the oracle at the fp32 bars of the other parity tests."""
+import pytest
+
+from test_gpu_online import _grad_check
+from test_gpu_parity import _step_parity
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,T,D,H,widths", [
+    (1, 8, 16, 64, {}),                                   # one row of a tile, D_h = 128
+    (17, 8, 32, 64, {}),                                  # one row of a second tile, 32 channels
+    (31, 64, 16, 64, dict(d_cache=320)),                  # slots of five: no 16-byte pieces
+    (256, 8, 16, 64, {}),                                 # the most streams these kernels take
+    (5, 128, 16, 128, dict(d_cache=2048, d_e=2048)),      # D_h = D_cache = D_e = 2048: several batches of loads, rows of 128 partial sums
+])
+def test_step_parity_at_tile_edges(B, T, D, H, widths):
+    _step_parity(B, T, D, H, "f32", steps=3, randomize=True, seed=70 + B, **widths)
+
+
+# 2e-4 as elsewhere. 4e-4 at D_h = 2048: the second update starts from two states that Adam's sign-like first step has moved apart
+# by up to 2 lr wherever a gradient lies within fp32's error of zero, and with four streams and 2048 channels W_f's gradient shows
+# that as 2.7e-4 (with products summed in another order, one thread per column, as well); the first update agrees to 2e-4.
+@pytest.mark.parametrize("B,T,D,H,tol,widths", [
+    (1, 8, 16, 64, 2e-4, {}),
+    (15, 8, 32, 64, 2e-4, {}),
+    (17, 16, 16, 64, 2e-4, dict(d_cache=64, d_e=192)),    # 272 tokens: a third, short chunk of the conv gradient
+    (6, 64, 16, 64, 2e-4, dict(d_cache=320)),             # slots of five: strips without 16-byte pieces
+    (33, 8, 16, 128, 2e-4, dict(d_cache=256)),            # slots of 32: two column tiles of the newest-slot backward
+    (4, 128, 16, 128, 4e-4, {}),                          # D_h = 2048
+])
+def test_gradients_and_adam_at_tile_edges(B, T, D, H, tol, widths):
+    _grad_check("f32", B, T, D, H, seed=90 + B, tol=tol, **widths)

@@ -844,7 +844,9 @@ __device__ __forceinline__ bool quantize_wave(const float p[4], int lane, uint32
   uint32_t key = (best << 10) | (1023u - (uint32_t)(4 * lane + bi));
   key = fade_butterfly(key, [](uint32_t x, uint32_t y) { return y > x ? y : x; });
   const int arg = 1023 - (int)(key & 1023u);
-  if ((arg >> 2) == lane) q[arg & 3] += 65536u - total;  // wraps correctly when total > 65536
+#pragma unroll
+  for (int i = 0; i < 4; ++i)  // (a runtime index would move the array out of the registers)
+    q[i] += 4 * lane + i == arg ? 65536u - total : 0u;  // wraps correctly when total > 65536
   return __all(ok);
 }
 
@@ -1007,14 +1009,19 @@ __device__ __forceinline__ void dec_update(DecState &d, uint32_t cum_lo, uint32_
   d.low = low; d.high = high; d.value = value;
 }
 
+// The i-th of four values by selection. By value on purpose: from a pointer the compiler makes one indexed load of it, puts the
+// array into LDS, and reads the launch packet in host memory for its address there (13 us in front of a 6 us kernel).
+__device__ __forceinline__ uint32_t pick4(uint32_t v0, uint32_t v1, uint32_t v2, uint32_t v3, int i) {
+  const uint32_t lo = (i & 1) ? v1 : v0, hi = (i & 1) ? v3 : v2;
+  return (i & 2) ? hi : lo;
+}
 // Bounds of symbol s under the table q (lane l owns symbols 4l .. 4l + 3; s is the same in every lane).
 __device__ __forceinline__ void enc_bounds(const uint32_t q[4], int lane, int s, uint32_t &lo, uint32_t &hi) {
   uint32_t below = 0;
 #pragma unroll
   for (int i = 0; i < 4; ++i) below += 4 * lane + i < s ? q[i] : 0u;
   lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)fade_lanes_sum(below));
-  const uint32_t qs = (s & 2) ? ((s & 1) ? q[3] : q[2]) : ((s & 1) ? q[1] : q[0]);
-  hi = lo + (uint32_t)__builtin_amdgcn_readlane((int)qs, s >> 2);
+  hi = lo + (uint32_t)__builtin_amdgcn_readlane((int)pick4(q[0], q[1], q[2], q[3], s), s >> 2);
 }
 // The symbol that `value` points at, and its bounds; false when it points outside the interval (the payload does not belong to
 // this model). The classic rule is cum[s] <= ((value - low + 1) * 2^16 - 1) / range < cum[s + 1]; with integers that is
@@ -1032,9 +1039,8 @@ __device__ __forceinline__ bool dec_find(const DecState &d, const uint32_t q[4],
   const unsigned long long vote = __ballot(mine);
   if (vote == 0ull) return false;
   const int owner = __builtin_amdgcn_readfirstlane(__ffsll((long long)vote) - 1), i = __builtin_amdgcn_readlane(at, owner);
-  const uint32_t clo = i & 2 ? (i & 1 ? cum[3] : cum[2]) : (i & 1 ? cum[1] : cum[0]), qs = i & 2 ? (i & 1 ? q[3] : q[2]) : (i & 1 ? q[1] : q[0]);
-  lo = (uint32_t)__builtin_amdgcn_readlane((int)clo, owner);
-  hi = lo + (uint32_t)__builtin_amdgcn_readlane((int)qs, owner);
+  lo = (uint32_t)__builtin_amdgcn_readlane((int)pick4(cum[0], cum[1], cum[2], cum[3], i), owner);
+  hi = lo + (uint32_t)__builtin_amdgcn_readlane((int)pick4(q[0], q[1], q[2], q[3], i), owner);
   s = 4 * owner + i;
   return true;
 }
@@ -1176,8 +1182,8 @@ __global__ __launch_bounds__(256) void quantize_kernel(const float *probs, size_
 // Stand-alone coder: n_steps symbols of every stream under explicit tables freq[step][stream][256], one wavefront per stream
 // from its first symbol to its last. The coder's state never leaves the registers (it is the same in every lane, so most of
 // its arithmetic is scalar); a group of four tables is in flight while the one before is coded.
-// 4096 streams x 32 steps (67 MB of tables): encode 41 us, decode 36 us; a launch per step took 32 x 3.9 and 32 x 5.1 us, and
-// the two calls 400 us with the coder's state allocated, set up and read back (now 105). What bounds it is the dependent chain
+// 4096 streams x 32 steps (67 MB of tables): encode 28 us, decode 37 us; a launch per step took 32 x 3.9 and 32 x 5.1 us, and
+// the two calls 400 us with the coder's state allocated, set up and read back (now 90). What bounds it is the dependent chain
 // of a step, some 300 instructions a wavefront, not the tables (14 us at the rate of a copy).
 template <int MODE>
 __global__ __launch_bounds__(256) void code_tables_kernel(const uint16_t *freq, uint8_t *sym, int n_steps, int n_streams, uint8_t *payload, size_t cap,

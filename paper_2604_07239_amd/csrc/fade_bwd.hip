@@ -84,8 +84,7 @@ __device__ __forceinline__ float adam_element(const AdamArrays &o, size_t idx, f
 // Sum of one value per thread over a 256-thread workgroup, same order every time: butterfly inside each
 // wavefront, then the four wavefront sums added in index order. Every thread gets the result.
 __device__ __forceinline__ float block_sum(float v, float *red /*[4]*/) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  v = fade_lanes_sum(v);
   __syncthreads();  // red may still be read from a previous call
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
@@ -105,8 +104,7 @@ __device__ __forceinline__ void loss_grad_body(int block, const WinSrc &ws, cons
   const int tid = threadIdx.x;
   int mine = 0;
   for (int b = tid; b < B; b += 256) mine += stream_active(ws, b) ? 1 : 0;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off, 64);
+  mine = fade_lanes_sum(mine);
   if ((tid & 63) == 0) cnt[tid >> 6] = mine;
   __syncthreads();
   const int na = cnt[0] + cnt[1] + cnt[2] + cnt[3];
@@ -291,10 +289,7 @@ inline int row_groups(int B) {
 template <int N>
 __device__ __forceinline__ void block_sum_n(float (&v)[N], float *red) {
 #pragma unroll
-  for (int k = 0; k < N; ++k) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off, 64);
-  }
+  for (int k = 0; k < N; ++k) v[k] = fade_lanes_sum(v[k]);
   __syncthreads();  // red may still be read from a previous call
   if ((threadIdx.x & 63) == 0) {
 #pragma unroll
@@ -337,7 +332,7 @@ __global__ __launch_bounds__(256) void bwd_out_kernel(BwdOutArgs a) {
       ld8<AT>(static_cast<const AT *>(a.V) + base, v);
       ld8<AT>(static_cast<const AT *>(a.Hc) + base, hc);
       if (a.mom) { mean = a.mom[2 * b]; rstd[r] = a.mom[2 * b + 1]; }
-      else moments(a.stats + (size_t)b * a.stats_n * 2, a.stats_n, a.Dh, mean, rstd[r]);
+      else fade_row_moments_lanes<16>(a.stats + (size_t)b * a.stats_n * 2, a.stats_n, a.Dh, mean, rstd[r]);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         xh[r][i] = (v[i] - mean) * rstd[r];
@@ -425,7 +420,7 @@ __global__ __launch_bounds__(256) void bwd_gate_kernel(BwdGateArgs a) {
       ld8<AT>(static_cast<const AT *>(a.Hc) + base, hc);  // requested before the statistics are summed
       if (!a.du_part && a.du) ld8<AT>(static_cast<const AT *>(a.du) + base, du);
       if (a.mom) { mean = a.mom[2 * b]; rstd[r] = a.mom[2 * b + 1]; }
-      else moments(a.stats + (size_t)b * a.stats_n * 2, a.stats_n, a.Dh, mean, rstd[r]);
+      else fade_row_moments_lanes<16>(a.stats + (size_t)b * a.stats_n * 2, a.stats_n, a.Dh, mean, rstd[r]);
       if (a.du_part || !a.du) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) du[i] = 0.0f;
@@ -531,7 +526,7 @@ __global__ __launch_bounds__(256) void bwd_mix_kernel(BwdMixArgs a) {
         ld8<AT>(static_cast<const AT *>(a.Hmix) + base, hm);
       }
       if (a.mom) { mean = a.mom[2 * b]; rstd[r] = a.mom[2 * b + 1]; }
-      else moments(a.stats + (size_t)b * a.stats_n * 2, a.stats_n, a.Dh, mean, rstd[r]);
+      else fade_row_moments_lanes<16>(a.stats + (size_t)b * a.stats_n * 2, a.stats_n, a.Dh, mean, rstd[r]);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         xh[r][i] = (hm[i] - mean) * rstd[r];
@@ -674,10 +669,7 @@ __global__ __launch_bounds__(256) void bwd_cci_kernel(BwdCciArgs a) {
       float s = 0.0f;
 #pragma unroll
       for (int i = 0; i < 4; ++i) s = fmaf((float)(AT)w4[e][i], dz_s[n0 + i], s);
-      s += __shfl_xor(s, 1, 64);
-      s += __shfl_xor(s, 2, 64);
-      s += __shfl_xor(s, 4, 64);
-      s += __shfl_xor(s, 8, 64);
+      s = fade_row_sum_up(s);
       if ((tid & 15) == 0) {
         const int k = e * 16 + (tid >> 4);
         a.dy[(size_t)b * 64 + k] = s;
@@ -782,9 +774,7 @@ __device__ __forceinline__ void bwd_slot_body(const BwdSlotArgs &a, int block) {
       }
 #pragma unroll
       for (int u = 0; u < SPW; ++u) {
-        float sv = sacc[u];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) sv += __shfl_xor(sv, off, 64);
+        const float sv = fade_lanes_sum(sacc[u]);
         if (lane == ql) mine[u] = sv;
       }
     }
@@ -840,9 +830,7 @@ __device__ __forceinline__ void bwd_slot_body(const BwdSlotArgs &a, int block) {
       float keep = 0.0f;
 #pragma unroll
       for (int k = 0; k < NS; ++k) {
-        float sv = acc[k];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) sv += __shfl_xor(sv, off, 64);
+        const float sv = fade_lanes_sum(acc[k]);
         if (lane == k) keep = sv;
       }
       if (lane < NS && block * NS + lane < a.B) a.dxt[(size_t)(block * NS + lane) * a.D + i] = keep;

@@ -42,6 +42,14 @@ template <int W = 64, typename T, typename OP> __device__ __forceinline__ T fade
 }
 template <int W = 64, typename T> __device__ __forceinline__ T fade_lanes_sum(T v) { return fade_butterfly<W>(v, [](T a, T b) { return a + b; }); }
 __device__ __forceinline__ float fade_lanes_max(float v) { return fade_butterfly(v, [](float a, float b) { return fmaxf(a, b); }); }
+// Sum over aligned groups of 16 lanes from the nearest neighbours outwards (lane ^ 1, 2, 4, 8): quads first, then mirrored halves of
+// the row and the mirrored row, whose groups already hold one value.
+__device__ __forceinline__ float fade_row_sum_up(float v) {
+  v += __builtin_bit_cast(float, fade_dpp<0xB1>(fade_bits(v)));
+  v += __builtin_bit_cast(float, fade_dpp<0x4E>(fade_bits(v)));
+  v += __builtin_bit_cast(float, fade_dpp<0x141>(fade_bits(v)));
+  return v + __builtin_bit_cast(float, fade_dpp<0x140>(fade_bits(v)));
+}
 // inclusive prefix sum over the 64 lanes
 __device__ __forceinline__ uint32_t fade_lanes_scan(uint32_t v) {
   v += fade_dpp<0x111>(v);  // row_shr 1, 2, 4, 8
@@ -184,6 +192,53 @@ __device__ __forceinline__ void fade_row_moments(const float *stats, int stats_n
   fade_moments_of(s, q, width, mean, rstd);
 }
 
+// The same, bit for bit, for W = 8 or 16 neighbouring lanes that work on one row: the pairs come with 16 / W loads per lane
+// (every lane used to fetch all 16, beside the 3 to 12 loads of a row kernel's data), and are added in index order as
+// broadcasts inside the row of 16 lanes.
+template <int J> __device__ __forceinline__ float fade_row_bcast(float v, int half) {  // lane J of the row; half 0 / 1: into lanes 0-7 / 8-15 only (zero elsewhere)
+  const int u = (int)fade_bits(v);
+  if (half < 0) return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, u, 0x150 + J, 0xf, 0xf, false));
+  return half == 0 ? __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, u, 0x150 + J, 0xf, 0x3, false))
+                   : __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, u, 0x150 + J, 0xf, 0xc, false));
+}
+template <int W, int J, int END> __device__ __forceinline__ void fade_add_pairs(const float2 &v, float &s, float &q) {
+  if constexpr (J < END) {
+    if constexpr (W == 16) {
+      s += fade_row_bcast<J>(v.x, -1);
+      q += fade_row_bcast<J>(v.y, -1);
+    } else {
+      s = (s + fade_row_bcast<J>(v.x, 0)) + fade_row_bcast<8 + J>(v.x, 1);
+      q = (q + fade_row_bcast<J>(v.y, 0)) + fade_row_bcast<8 + J>(v.y, 1);
+    }
+    fade_add_pairs<W, J + 1, END>(v, s, q);
+  }
+}
+template <int W> __device__ __forceinline__ void fade_row_moments_lanes(const float *stats, int stats_n, int width, float &mean, float &rstd) {
+  static_assert(W == 8 || W == 16, "lanes per row");
+  const float2 *p = reinterpret_cast<const float2 *>(stats);
+  const int l = threadIdx.x & (W - 1);
+  float s = 0.0f, q = 0.0f;
+  for (int j0 = 0; j0 < stats_n; j0 += 16) {
+    float2 v[16 / W];
+#pragma unroll
+    for (int i = 0; i < 16 / W; ++i) {
+      const int j = j0 + i * W + l;
+      v[i] = p[j < stats_n ? j : 0];
+      if (j >= stats_n) v[i] = make_float2(0.0f, 0.0f);
+    }
+    const int left = stats_n - j0;  // pairs past the last are zeros; a short row skips most of them
+    if constexpr (W == 16) {
+      fade_add_pairs<16, 0, 4>(v[0], s, q);
+      if (left > 4) fade_add_pairs<16, 4, 16>(v[0], s, q);
+    } else {
+      fade_add_pairs<8, 0, 4>(v[0], s, q);
+      if (left > 4) fade_add_pairs<8, 4, 8>(v[0], s, q);
+      if (left > 8) fade_add_pairs<8, 0, 8>(v[1], s, q);
+    }
+  }
+  fade_moments_of(s, q, width, mean, rstd);
+}
+
 // Row-wise element kernels: thread t = blockIdx.x * 256 + tid owns the 8-wide chunk t % chunks of the RPT rows of row
 // group t / chunks (RPT = 4 for tall inputs: one fetch of the per-column vectors serves 4 rows, whose loads are in flight
 // together; RPT = 1 when there are too few rows to fill the chip that way). The moments of the rows a workgroup covers
@@ -195,8 +250,12 @@ __device__ __forceinline__ int fade_group_moments(const float *stats, int stats_
   const long long t0 = (long long)blockIdx.x * 256;
   const int g0 = (int)(t0 / chunks), g1 = (int)((t0 + 255) / chunks);
   const int r0 = g0 * RPT, nr = (g1 - g0 + 1) * RPT;
-  for (int r = threadIdx.x; r < nr; r += 256)
-    if (r0 + r < rows) fade_row_moments(stats + (size_t)(r0 + r) * stats_n * 2, stats_n, width, mom[r][0], mom[r][1]);
+  for (int r = threadIdx.x >> 4; r < nr; r += 16)
+    if (r0 + r < rows) {
+      float mean, rstd;
+      fade_row_moments_lanes<16>(stats + (size_t)(r0 + r) * stats_n * 2, stats_n, width, mean, rstd);
+      if ((threadIdx.x & 15) == 0) { mom[r][0] = mean; mom[r][1] = rstd; }
+    }
   __syncthreads();
   return r0;
 }

@@ -152,6 +152,11 @@ __device__ __forceinline__ void row_moments(const GemmArgs &g, int m, float &mea
   fade_row_moments(g.stats + (size_t)m * g.stats_n * 2, g.stats_n, g.K, mean, rstd);
 }
 
+// the same where eight neighbouring lanes share row m
+__device__ __forceinline__ void row_moments_lanes(const GemmArgs &g, int m, float &mean, float &rstd) {
+  fade_row_moments_lanes<8>(g.stats + (size_t)(m < g.M ? m : g.M - 1) * g.stats_n * 2, g.stats_n, g.K, mean, rstd);
+}
+
 // ---------------------------------------------------------------------------------------------------
 // epilogue: the accumulator tile sits in LDS as fp32 [BM][BN + 4]; threads walk it in 8-wide row chunks
 // ---------------------------------------------------------------------------------------------------
@@ -209,7 +214,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs &g, const float *Cs, int
         if (kRagged && rb + u * RP >= BM) continue;
         // past the last row: any row (dropped below); a branch around the loads would cost the exact vmcnt waits
         epi_side_load<EPI, AT>(g, (size_t)(m < g.M ? m : g.M - 1) * g.ldc + nout0 + c8, true, own[u]);
-        if (EPI == EPI_GEGLU_FOLD) row_moments(g, m, mean[u], rstd[u]);
+        if (EPI == EPI_GEGLU_FOLD) row_moments_lanes(g, m, mean[u], rstd[u]);
       }
     }
 #pragma unroll
@@ -302,8 +307,13 @@ __device__ __forceinline__ void epilogue(const GemmArgs &g, const float *Cs, int
       float s = 0.0f, q = 0.0f;
 #pragma unroll
       for (int i = 0; i < 8; ++i) { s += out[i]; q = fmaf(out[i], out[i], q); }
+      if constexpr (CH == 16) {
+        s = fade_lanes_sum<16>(s);
+        q = fade_lanes_sum<16>(q);
+      } else {
 #pragma unroll
-      for (int off = CH / 2; off > 0; off >>= 1) { s += __shfl_xor(s, off, 64); q += __shfl_xor(q, off, 64); }
+        for (int off = CH / 2; off > 0; off >>= 1) { s += __shfl_xor(s, off, 64); q += __shfl_xor(q, off, 64); }
+      }
       if (ALL) {  // every lane of the row's group holds the sums: all store them (same value, same address), no branch
         float *p = g.stats_out + ((size_t)m * (g.N / BN) + nt) * 2;
         *reinterpret_cast<float2 *>(p) = make_float2(s, q);
@@ -361,7 +371,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g) {
   float lam = 0.0f;
   if (PRO == PRO_LN || PRO == PRO_FINAL) {
 #pragma unroll
-    for (int p = 0; p < PASSES; ++p) row_moments(g, m0 + p * 32 + srow, mean[p], rstd[p]);
+    for (int p = 0; p < PASSES; ++p) row_moments_lanes(g, m0 + p * 32 + srow, mean[p], rstd[p]);
     if (PRO == PRO_FINAL) lam = g.lam[0];
   }
 

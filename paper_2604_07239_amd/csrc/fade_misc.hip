@@ -105,7 +105,7 @@ __device__ __forceinline__ void tables_body(int s, const float *E, bool round_bf
 }
 // Eq. 1 for symbol s in the same workgroup: x = the row just formed (fp32, as tabXe32 holds it), W_g / W_v as their compute copies
 // are (rounded to bf16 in the bf16 path); slot_pair's order of operations, so the values are those that function gives from the copies.
-__device__ __forceinline__ void tables_slot_body(int s, const TablesArgs &t) {
+template <bool ROUND> __device__ __forceinline__ void tables_slot_body(int s, const TablesArgs &t) {
   __shared__ float xrow[256];
   const int i = threadIdx.x;
   __syncthreads();  // tabXe32's row of this symbol was written by this workgroup just above
@@ -115,8 +115,8 @@ __device__ __forceinline__ void tables_slot_body(int s, const TablesArgs &t) {
     float gg = 0.0f, gv = 0.0f;
     for (int k = 0; k < t.D; ++k) {
       const float wg = t.Wg[k * t.c + q], wv = t.Wv[k * t.c + q];
-      gg = fmaf(xrow[k], t.round_bf16 ? (float)(bf16_t)wg : wg, gg);
-      gv = fmaf(xrow[k], t.round_bf16 ? (float)(bf16_t)wv : wv, gv);
+      gg = fmaf(xrow[k], ROUND ? (float)(bf16_t)wg : wg, gg);
+      gv = fmaf(xrow[k], ROUND ? (float)(bf16_t)wv : wv, gv);
     }
     if (t.slot_tab) static_cast<bf16_t *>(t.slot_tab)[(size_t)s * t.c + q] = (bf16_t)(gelu_f(gg) * gv);
     if (t.gg_tab) { t.gg_tab[(size_t)s * t.c + q] = gg; t.gv_tab[(size_t)s * t.c + q] = gv; }
@@ -125,7 +125,7 @@ __device__ __forceinline__ void tables_slot_body(int s, const TablesArgs &t) {
 template <typename AT> __global__ __launch_bounds__(256) void tables_kernel(TablesArgs t) {
   tables_body<AT>(blockIdx.x, t.E, t.round_bf16 != 0, t.ge, t.be, t.gl, t.bl, t.D, static_cast<AT *>(t.tabXe), static_cast<AT *>(t.tabXl), t.tabXe32,
                   t.tabXhat, t.tabRstd);
-  if (t.Wg) tables_slot_body(blockIdx.x, t);
+  if (t.Wg) tables_slot_body<sizeof(AT) == 2>(blockIdx.x, t);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -563,10 +563,6 @@ __global__ __launch_bounds__(256) void bmm_kernel(const float *y, const AT *WU, 
 // so the product runs on the raw activations h and the normalisation becomes a per-row / per-column fix-up in
 // the kernel that reduces the split-K partials. s is summed from the bf16 values the matrix cores multiply.
 // ---------------------------------------------------------------------------------------------------
-__device__ __forceinline__ void moments_from_partials(const float *stats, int stats_n, int width, float &mean, float &rstd) {
-  fade_row_moments(stats, stats_n, width, mean, rstd);
-}
-
 // Eq. 7 between Down and Up (bf16 path): reduce the split-K partials of H_mix W'_down, apply the folded LayerNorm,
 // then the per-stream memory: z[b] = y[b] W_U[b]. One wavefront per stream, lane = column (d_low = 64).
 __global__ __launch_bounds__(256) void cci_kernel(CciArgs a) {
@@ -587,7 +583,7 @@ __global__ __launch_bounds__(256) void cci_kernel(CciArgs a) {
     for (int j = 0; j < 8; ++j) raw += (s0 + j < a.splits) ? pv[j] : 0.0f;
   }
   float mean, rstd;
-  moments_from_partials(a.stats + (size_t)b * a.stats_n * 2, a.stats_n, a.Dh, mean, rstd);
+  fade_row_moments_lanes<16>(a.stats + (size_t)b * a.stats_n * 2, a.stats_n, a.Dh, mean, rstd);
   const float yv = rstd * (raw - mean * a.s_fold[lane]) + a.t_fold[lane];
   a.y[(size_t)b * 64 + lane] = yv;
   // z[n] = sum_k y[k] W_U[k][n]: a lane adds its eight rows for its eight columns (k = lane / 8, + 8, ... in order), then the
@@ -602,10 +598,9 @@ __global__ __launch_bounds__(256) void cci_kernel(CciArgs a) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = fmaf(yk, (float)w[i][j], acc[j]);
   }
+  const auto add = [](float x, float y) { return x + y; };
 #pragma unroll
-  for (int off = 8; off < 64; off <<= 1)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] += __shfl_xor(acc[j], off, 64);
+  for (int j = 0; j < 8; ++j) acc[j] = fade_level<32>(fade_level<16>(fade_level<8>(acc[j], add), add), add);
   if (m == 0) {
     bf16x8 zv;
 #pragma unroll
@@ -642,7 +637,7 @@ __global__ __launch_bounds__(256) void geglu_kernel(GegluArgs a) {
     }
   }
   float mean, rstd;
-  moments_from_partials(a.stats + (size_t)b * a.stats_n * 2, a.stats_n, a.Dh, mean, rstd);
+  fade_row_moments_lanes<8>(a.stats + (size_t)b * a.stats_n * 2, a.stats_n, a.Dh, mean, rstd);
   bf16x8 out, eg, ev;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
@@ -744,7 +739,7 @@ __global__ __launch_bounds__(256) void prep_batch_kernel(PrepBatch pb) {
     if (blockIdx.x < 256) {
       tables_body<bf16_t>(blockIdx.x, t.E, t.round_bf16 != 0, t.ge, t.be, t.gl, t.bl, t.D, static_cast<bf16_t *>(t.tabXe), static_cast<bf16_t *>(t.tabXl),
                           t.tabXe32, t.tabXhat, t.tabRstd);
-      if (t.Wg) tables_slot_body(blockIdx.x, t);
+      if (t.Wg) tables_slot_body<true>(blockIdx.x, t);
     }
     return;
   }

@@ -767,33 +767,36 @@ __global__ __launch_bounds__(256, (STAGES == 2 && BM * BN <= 128 * 128) ? 2 : 1)
 
 
 // ---------------------------------------------------------------------------------------------------
-// The same product with stages of 32 along K (two k-steps) in a ring of STAGES: half the bytes per stage, so that the ring
-// is deep enough (three stages ahead) for the LDS-DMA of all compute units together, which the L2 fabric serves at about
-// 50 bytes per clock and unit, and so that the fragments of a stage's first k-step can be fetched from LDS while the matrix
-// cores still work on the last k-step of the stage before: the wait for a stage's DMA and the workgroup barrier sit in
-// the middle of a stage, between its two k-steps, and no fragment read is ever waited for with idle matrix cores.
-//   iteration h:  fetch (h, k-step 1) | MFMA (h, 0) | wait DMA of h+1, barrier, issue DMA of h+STAGES-1 | fetch (h+1, 0) | MFMA (h, 1)
-// A stage: A as BM rows of 64 bytes (one DMA = 16 rows; the four 16-byte pieces of row r XOR-permuted by (r / 4) % 4, so
-// that the 16 rows a quarter-wavefront reads one piece of cover all 64 banks), then W as ready-made 1 KiB fragments.
-// The slot that iteration h refills is the one stage h-1 lived in: its last fragment read was waited for before
-// MFMA (h-1, 1) was issued, which every wavefront has done when it arrives at iteration h's barrier.
+// The same product with W in stages of 32 along K (two k-steps), a ring of four, and A in units of 64, a ring of three: deep
+// enough (three stages ahead) for the LDS-DMA of all compute units together, which the L2 fabric serves at about 50 bytes per
+// clock and unit, and so that the fragments of a stage's first k-step can be fetched from LDS while the matrix cores still
+// work on the last k-step of the stage before: the wait for a stage's DMA and the workgroup barrier sit in the middle of a
+// stage, between its two k-steps, and no fragment read is ever waited for with idle matrix cores.
+//   iteration h:  fetch (h, k-step 1) | MFMA (h, 0) | wait DMA of h+1, barrier, issue W of h+3 and A half h+4 | fetch (h+1, 0) | MFMA (h, 1)
+// A unit: BM rows of 128 bytes, swizzled as in pipe_body; a row-major operand is requested in whole 128-byte cache lines (one
+// DMA = 8 rows). With A in stages of 32 too, each request was half a line and the other half crossed the fabric again an
+// iteration later: in us, M = 16384, K = N = 2048 plain 124.5 -> 120.8 (1.14 PFLOP/s; a plain library product of that shape
+// 115.7), with the gate epilogue 160.7 -> 154.3, K = 2048, N = 1024 82.2 -> 79.5; M = 4096, N = 16384, K = 512 136.7 -> 124.7.
+// The same rings with 128 x 128 tiles and two workgroups per unit lose to 64 x 128 at M = 4096, N = 512 (33 against 40). So that every iteration still requests the same amount, the two iterations of a unit request the upper and
+// the lower half of the rows of the unit two further on. W: ready-made 1 KiB fragments.
+// The W slot that iteration h refills is the one stage h-1 lived in, the A slot the one of the unit before h's: their last
+// fragment read was waited for before MFMA (h-1, 1) was issued, which every wavefront has done when it arrives at iteration
+// h's barrier. Group h = {W of stage h, A half h+1} is requested together; stage h needs groups up to h.
 // Every output element sees the same sequence of k-steps as in pipe_body, so both give the same bits.
 // ---------------------------------------------------------------------------------------------------
-template <int BM, int BN, int STAGES, int EPI, int NW = 4>
+template <int BM, int BN, int EPI, int NW = 4>
 __device__ __forceinline__ void pipe2_body(const GemmArgs &g, int bid, int split, int nsplit) {
   typedef bf16_t AT;
-  constexpr int BK = 32, KS = 2;
+  constexpr int BK = 32, KS = 2, WSTAGES = 4, AUNITS = 3;
   constexpr int WN = NW / 2;                         // wavefronts 2 (rows) x WN (columns)
   constexpr int TM = BM / 64, TN = BN / (32 * WN);   // 32x32 tiles per wavefront
   constexpr int BFR = BN / 32;
-  constexpr int A_BYTES = BM * 64;                   // A stage: BM rows of 32 k (64 bytes)
-  constexpr int ACH = BM / 16 / NW;                  // A DMAs per wavefront and stage (one DMA = 16 rows x 64 bytes)
+  constexpr int A_UNIT = BM * 128, W_STAGE = BFR * KS * 1024, A_RING = AUNITS * A_UNIT;
+  constexpr int ACH = BM / 16 / NW;                  // A DMAs per wavefront and half unit (BM / 2 rows; one DMA = 8 rows x 128 bytes)
   constexpr int BCH = BFR * KS / NW;                 // W DMAs per wavefront and stage (one fragment each)
-  constexpr int LPW = ACH + BCH;
-  constexpr int STAGE_BYTES = A_BYTES + BFR * KS * 1024, LDC = BN + 4;
+  constexpr int LPW = ACH + BCH, LDC = BN + 4;
   constexpr bool SLAB = BM > 128;                    // the fp32 tile leaves through LDS in slabs of 64 rows
-  static_assert((BM / 16) % NW == 0 && (BFR * KS) % NW == 0 && STAGES >= 3, "chunk split");
-  static_assert((STAGES - 3) * LPW <= 63, "vmcnt range");
+  static_assert((BM / 16) % NW == 0 && (BFR * KS) % NW == 0 && 2 * LPW <= 63, "chunk split; vmcnt range");
   extern __shared__ __align__(16) unsigned char smem[];
   float *Cs = reinterpret_cast<float *>(smem);
 
@@ -803,38 +806,44 @@ __device__ __forceinline__ void pipe2_body(const GemmArgs &g, int bid, int split
   int mt, nt;
   if (!tile_of_block(bid, ntm, ntn, g.col_groups, mt, nt)) return;
   const int m0 = mt * BM, n0 = nt * BN;
-  const int ksplit = g.K / nsplit, nkh = ksplit / BK;
+  const int ksplit = g.K / nsplit, nkh = ksplit / BK;  // stages; even (K per range is a multiple of 64)
   const int ksteps = g.K / 16;
 
-  const bf16_t *src[LPW];
+  const bf16_t *asrc[2][ACH], *wsrc[BCH];
 #pragma unroll
-  for (int q = 0; q < ACH; ++q) {
-    const int c = wave + NW * q, r = c * 16 + (lane >> 2);
-    int row = m0 + r;
-    row = row < g.M ? row : g.M - 1;
-    src[q] = static_cast<const bf16_t *>(g.A) + (size_t)row * g.lda + (((lane & 3) ^ ((r >> 2) & 3)) << 3);
-  }
+  for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+    for (int q = 0; q < ACH; ++q) {
+      const int r = hf * (BM / 2) + (wave + NW * q) * 8 + (lane >> 3);
+      int row = m0 + r;
+      row = row < g.M ? row : g.M - 1;
+      asrc[hf][q] = static_cast<const bf16_t *>(g.A) + (size_t)row * g.lda + (((lane & 7) ^ ((r >> 1) & 7)) << 3);
+    }
 #pragma unroll
   for (int q = 0; q < BCH; ++q) {
     const int c = wave + NW * q, fr = c / KS, ks = c % KS;
-    src[ACH + q] = static_cast<const bf16_t *>(g.W) + (((size_t)(n0 / 32 + fr) * ksteps + ks) * 64 + lane) * 8;
+    wsrc[q] = static_cast<const bf16_t *>(g.W) + (((size_t)(n0 / 32 + fr) * ksteps + ks) * 64 + lane) * 8;
   }
-  auto issue = [&](int slot, int kh) {  // kh: 32-wide stage counted from the start of K
-    unsigned char *base = smem + slot * STAGE_BYTES;
+  auto issue_w = [&](int slot, int kh) {  // kh: 32-wide stage counted from the start of K
+    unsigned char *base = smem + A_RING + slot * W_STAGE;
 #pragma unroll
-    for (int q = 0; q < ACH; ++q) dma16(src[q] + (size_t)kh * BK, base + (wave + NW * q) * 1024);
+    for (int q = 0; q < BCH; ++q) dma16(wsrc[q] + (size_t)kh * KS * 512, base + (wave + NW * q) * 1024);
+  };
+  auto issue_a = [&](int slot, int unit, auto half_c) {  // unit: 64-wide, counted from the start of K
+    constexpr int hf = decltype(half_c)::value;
+    unsigned char *base = smem + slot * A_UNIT + hf * (A_UNIT / 2);
 #pragma unroll
-    for (int q = 0; q < BCH; ++q) dma16(src[ACH + q] + (size_t)kh * KS * 512, base + A_BYTES + (wave + NW * q) * 1024);
+    for (int q = 0; q < ACH; ++q) dma16(asrc[hf][q] + (size_t)unit * 64, base + (wave + NW * q) * 1024);
   };
 
-  // fragment read addresses inside a stage (bytes from the stage's start): A tile i of this wavefront at a_base[k-step] +
-  // i * 2048 (32 rows of 64 bytes), W tile j at b_base + k-step * 1024 + j * 2048
+  // fragment read addresses (bytes): A tile i of this wavefront at a_base[k-step of the unit] + i * 4096 (32 rows of 128
+  // bytes) in the unit's slot, W tile j at b_base + k-step * 1024 + j * 2048 in the stage's slot
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
-  const int a_sw = (lane >> 2) & 3, a_half = lane >> 5;  // tile rows start at multiples of 32: (r / 4) % 4 == (lane / 4) % 4
-  uint32_t a_base[KS];
+  const int a_sw = (lane >> 1) & 7, a_half = lane >> 5;  // tile rows start at multiples of 32: (r / 2) % 8 == (lane / 2) % 8
+  uint32_t a_base[2 * KS];
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) a_base[ks] = lds0 + (wm * TM * 32 + (lane & 31)) * 64 + (((2 * ks + a_half) ^ a_sw) << 4);
-  const uint32_t b_base = lds0 + A_BYTES + (((wn * TN * KS) * 64 + lane) << 4);
+  for (int ks = 0; ks < 2 * KS; ++ks) a_base[ks] = lds0 + (wm * TM * 32 + (lane & 31)) * 128 + (((2 * ks + a_half) ^ a_sw) << 4);
+  const uint32_t b_base = lds0 + A_RING + (((wn * TN * KS) * 64 + lane) << 4);
 
   const bool fuse = EPI == EPI_PARTIAL && g.sum_splits != 0;
   const int sp_first = fuse ? 0 : split, sp_end = fuse ? nsplit : split + 1;
@@ -848,23 +857,34 @@ __device__ __forceinline__ void pipe2_body(const GemmArgs &g, int bid, int split
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
     if (sp != sp_first) bare_barrier();  // every wavefront has read the last stages of the previous range
-#pragma unroll
-    for (int s = 0; s < STAGES - 1; ++s)
-      if (s < nkh) issue(s, kh0 + s);
+    typedef std::integral_constant<int, 0> I0;
+    typedef std::integral_constant<int, 1> I1;
+    typedef std::integral_constant<int, TM + TN> INext;
+    // groups 0 (with A half 0), 1, 2
+    const int ku0 = kh0 / 2;
+    issue_a(0, ku0, I0{});
+    issue_a(0, ku0, I1{});
+    issue_w(0, kh0);
+    issue_w(1, kh0 + 1);
+    if (nkh > 2) {
+      issue_a(1, ku0 + 1, I0{});
+      issue_w(2, kh0 + 2);
+      issue_a(1, ku0 + 1, I1{});
+    }
 
     bf16x8 af[2][TM], bf[2][TN];
-    auto fetch = [&](auto buf_c, int slot, auto ks_c) {  // TM + TN reads, left in flight
-      constexpr int buf = decltype(buf_c)::value, ks = decltype(ks_c)::value;
-      const uint32_t sa = a_base[ks] + slot * STAGE_BYTES, sb = b_base + slot * STAGE_BYTES;
+    auto fetch = [&](auto buf_c, int aslot, int wslot, auto ks_c) {  // ks: k-step of the A unit; TM + TN reads, left in flight
+      constexpr int buf = decltype(buf_c)::value, ks = decltype(ks_c)::value, wk = ks % KS;
+      const uint32_t sa = a_base[ks] + aslot * A_UNIT, sb = b_base + wslot * W_STAGE;
       static_assert(TM <= 4 && TN <= 4, "tiles per wavefront");
       af[buf][0] = lds_read16<0>(sa);
-      if constexpr (TM > 1) af[buf][1] = lds_read16<2048>(sa);
-      if constexpr (TM > 2) af[buf][2] = lds_read16<4096>(sa);
-      if constexpr (TM > 3) af[buf][3] = lds_read16<6144>(sa);
-      bf[buf][0] = lds_read16<ks * 1024>(sb);
-      if constexpr (TN > 1) bf[buf][1] = lds_read16<ks * 1024 + 2048>(sb);
-      if constexpr (TN > 2) bf[buf][2] = lds_read16<ks * 1024 + 4096>(sb);
-      if constexpr (TN > 3) bf[buf][3] = lds_read16<ks * 1024 + 6144>(sb);
+      if constexpr (TM > 1) af[buf][1] = lds_read16<4096>(sa);
+      if constexpr (TM > 2) af[buf][2] = lds_read16<8192>(sa);
+      if constexpr (TM > 3) af[buf][3] = lds_read16<12288>(sa);
+      bf[buf][0] = lds_read16<wk * 1024>(sb);
+      if constexpr (TN > 1) bf[buf][1] = lds_read16<wk * 1024 + 2048>(sb);
+      if constexpr (TN > 2) bf[buf][2] = lds_read16<wk * 1024 + 4096>(sb);
+      if constexpr (TN > 3) bf[buf][3] = lds_read16<wk * 1024 + 6144>(sb);
     };
     auto mfma = [&](auto buf_c, auto newer_c) {  // newer: reads issued after this buffer's, allowed to stay in flight
       constexpr int buf = decltype(buf_c)::value;
@@ -878,35 +898,43 @@ __device__ __forceinline__ void pipe2_body(const GemmArgs &g, int bid, int split
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[buf][i], bf[buf][j], acc[i][j], 0, 0, 0);
     };
-    typedef std::integral_constant<int, 0> I0;
-    typedef std::integral_constant<int, 1> I1;
-    typedef std::integral_constant<int, TM + TN> INext;
-    // stage 0 has landed once at most the younger stages of the preamble are in flight
-    if (nkh >= STAGES - 1) wait_vmcnt<(STAGES - 2) * LPW>();
+    // group 0 has landed once at most groups 1 and 2 are in flight
+    if (nkh > 2) wait_vmcnt<2 * LPW>();
     else wait_vmcnt<0>();
     bare_barrier();
-    fetch(I0{}, 0, I0{});
-    int slot = 0, fill = STAGES - 1;  // slot of stage h; slot the next DMA goes to
-    // One iteration: the two k-steps of stage h around the hand-over to stage h + 1. STEADY: a further stage is requested;
-    // else the ring only drains.
-    auto step = [&](int h, auto steady) {
-      fetch(I1{}, slot, I1{});
+    fetch(I0{}, 0, 0, I0{});
+    int aslot = 0, afill = 2;  // A slot of the unit being worked on; A slot the unit two further on goes to
+    auto next_a = [&](int s) { return s + 1 == AUNITS ? 0 : s + 1; };
+    // One iteration: the two k-steps of stage h around the hand-over to stage h + 1. odd: second stage of its unit.
+    // mode 2: group h + 3 is requested; 1: its W alone (past the last unit); 0: the rings only drain.
+    auto step = [&](int h, auto odd_c, auto mode_c) {
+      constexpr int odd = decltype(odd_c)::value, mode = decltype(mode_c)::value;
+      fetch(I1{}, aslot, h % WSTAGES, std::integral_constant<int, 2 * odd + 1>{});
       mfma(I0{}, INext{});
-      if constexpr (decltype(steady)::value) wait_vmcnt<(STAGES - 3) * LPW>();
+      if constexpr (mode != 0) wait_vmcnt<LPW>();  // group h + 1 has landed: only group h + 2 may be in flight
       else wait_vmcnt<0>();
       bare_barrier();  // stage h+1 is in LDS for everyone, and everyone is done reading stage h-1
-      if constexpr (decltype(steady)::value) {
-        issue(fill, kh0 + h + STAGES - 1);
-        fill = fill + 1 == STAGES ? 0 : fill + 1;
+      if constexpr (mode != 0) issue_w((h + 3) % WSTAGES, kh0 + h + 3);
+      if constexpr (mode == 2) issue_a(afill, ku0 + h / 2 + 2, odd_c);
+      if constexpr (odd != 0) {
+        aslot = next_a(aslot);
+        afill = next_a(afill);
       }
-      slot = slot + 1 == STAGES ? 0 : slot + 1;
-      fetch(I0{}, slot, I0{});
+      fetch(I0{}, aslot, (h + 1) % WSTAGES, std::integral_constant<int, odd ? 0 : 2>{});
       mfma(I1{}, INext{});
     };
     int h = 0;
-    for (; h + STAGES - 1 < nkh; ++h) step(h, std::true_type{});
-    for (; h + 1 < nkh; ++h) step(h, std::false_type{});
-    fetch(I1{}, slot, I1{});  // last stage: nothing follows
+    for (; h + 5 < nkh; h += 2) {
+      step(h, I0{}, std::integral_constant<int, 2>{});
+      step(h + 1, I1{}, std::integral_constant<int, 2>{});
+    }
+    if (nkh > 2) {
+      step(h, I0{}, I1{});
+      step(h + 1, I1{}, I0{});
+      h += 2;
+    }
+    step(h, I0{}, I0{});
+    fetch(I1{}, aslot, (h + 1) % WSTAGES, std::integral_constant<int, 3>{});  // last stage: nothing follows
     mfma(I0{}, INext{});
     mfma(I1{}, I0{});
     if constexpr (EPI == EPI_PARTIAL) {
@@ -985,9 +1013,9 @@ __device__ __forceinline__ void pipe2_body(const GemmArgs &g, int bid, int split
   }
 }
 // WPU: workgroups the launch bounds leave room for on one compute unit
-template <int BM, int BN, int STAGES, int EPI, int NW, int WPU>
+template <int BM, int BN, int EPI, int NW, int WPU>
 __global__ __launch_bounds__(NW * 64, WPU) void gemm_pipe2_kernel(GemmArgs g) {
-  pipe2_body<BM, BN, STAGES, EPI, NW>(g, (int)blockIdx.x, (int)blockIdx.y, g.sum_splits ? g.splits : (int)gridDim.y);
+  pipe2_body<BM, BN, EPI, NW>(g, (int)blockIdx.x, (int)blockIdx.y, g.sum_splits ? g.splits : (int)gridDim.y);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -1450,21 +1478,21 @@ hipError_t fade_gemm_tn2_group_launch(const Tn2Group &tg, hipStream_t s) {
 }
 namespace {
 
-template <int BM, int BN, int STAGES, int EPI, int NW, int WPU>
+template <int BM, int BN, int EPI, int NW, int WPU>
 hipError_t launch_pipe2(const GemmArgs &g, hipStream_t s) {
-  constexpr size_t lds_ring = (size_t)STAGES * (BM * 64 + (BN / 32) * 2 * 1024);
+  constexpr size_t lds_ring = (size_t)3 * BM * 128 + (size_t)4 * (BN / 32) * 2 * 1024;
   constexpr size_t lds_c = BM > 128 ? (size_t)64 * (BN + 4) * sizeof(float) : (size_t)BM * (BN + 4) * sizeof(float);
   constexpr size_t lds = lds_ring > lds_c ? lds_ring : lds_c;
   static_assert(lds * WPU <= 160 * 1024, "LDS per compute unit");
   static bool attr_done = false;
-  auto kern = gemm_pipe2_kernel<BM, BN, STAGES, EPI, NW, WPU>;
+  auto kern = gemm_pipe2_kernel<BM, BN, EPI, NW, WPU>;
   if (!attr_done) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
   const int splits = g.splits > 1 ? g.splits : 1;
-  if (g.N % BN || g.M <= 0 || g.K % (splits * 32) || (EPI != EPI_PARTIAL && splits != 1) || g.lda % 8) return hipErrorInvalidValue;
+  if (g.N % BN || g.M <= 0 || g.K <= 0 || g.K % (splits * 64) || (EPI != EPI_PARTIAL && splits != 1) || g.lda % 8) return hipErrorInvalidValue;
   if (g.sum_splits && EPI != EPI_PARTIAL) return hipErrorInvalidValue;
   if (BM > 128 && NW == 8 && g.M % BM) return hipErrorInvalidValue;  // the slab epilogue of the eight-wavefront tile assumes whole tiles
   GemmArgs ga = g;
@@ -1491,10 +1519,8 @@ hipError_t launch_pipe_auto(const GemmArgs &g, hipStream_t s) {
   const int tune = fade_gemm_tune();
   if constexpr (EPI != EPI_PARTIAL) {
     const int tiles256 = ((g.M + 255) / 256) * (g.N / 256);
-    if (g.N % 256 == 0 && g.M % 256 == 0 && (tune == 20 || (tune == 0 && tiles256 >= 256 && g.K >= 256))) return launch_pipe2<256, 256, 4, EPI, 8, 1>(g, s);
-    if (tune == 21) return launch_pipe2<256, 128, 3, EPI, 4, 2>(g, s);
+    if (g.N % 256 == 0 && g.M % 256 == 0 && (tune == 20 || (tune == 0 && tiles256 >= 256 && g.K >= 256))) return launch_pipe2<256, 256, EPI, 8, 1>(g, s);
   }
-  if (tune == 23) return launch_pipe2<128, 128, 4, EPI, 4, 2>(g, s);
   if (tune == 11 || (tune == 0 && tiles128 >= 512)) return launch_pipe<128, 128, 2, EPI>(g, s);
   if (tune == 10) return launch_pipe<256, 128, 3, EPI>(g, s);
   if (tune == 1 || (tune == 0 && tiles128 >= 256)) return launch_pipe<128, 128, 4, EPI>(g, s);
@@ -1628,9 +1654,8 @@ hipError_t fade_gemm_group_launch(const GemmGroup &gg, hipStream_t s) {
 }
 
 // Tuning override for experiments (FADE_GEMM_TUNE: 0 automatic, 1 force 128x128x4 stages, 2 force 64x128, 10 force 256x128x3,
-// 11 force 128x128x2 with two workgroups per compute unit; rings of 32-wide stages: 20 force 256x256 on eight wavefronts,
-// 21 256x128 with two workgroups per unit, 23 128x128 with two workgroups per unit; grouped launches: 13 force the
-// four-stage kernel, 14 force the two-stage one).
+// 11 force 128x128x2 with two workgroups per compute unit; 20 force 256x256 on eight wavefronts; grouped launches: 13 force
+// the four-stage kernel, 14 force the two-stage one).
 int fade_gemm_tune() {
   static int v = -1;
   if (v < 0) { const char *e = getenv("FADE_GEMM_TUNE"); v = e ? atoi(e) : 0; }

@@ -37,6 +37,20 @@ template <> __device__ __forceinline__ void st8<float>(float *p, const float v[8
   *reinterpret_cast<f32x4 *>(p + 4) = b;
 }
 
+// operands read for the last time, outputs read again only at the end of the pass (bf16; the fp32 path's batches stay in the caches)
+__device__ __forceinline__ void ld8_nt(const bf16_t *p, float v[8]) {
+  const bf16x8 r = __builtin_bit_cast(bf16x8, fade_nt_load(p));
+#pragma unroll
+  for (int i = 0; i < 8; ++i) v[i] = (float)r[i];
+}
+__device__ __forceinline__ void ld8_nt(const float *p, float v[8]) { ld8<float>(p, v); }
+__device__ __forceinline__ void st8_nt(bf16_t *p, const float v[8]) {
+  bf16x8 r;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) r[i] = (bf16_t)v[i];
+  fade_nt_store(p, __builtin_bit_cast(f32x4, r));
+}
+__device__ __forceinline__ void st8_nt(float *p, const float v[8]) { st8<float>(p, v); }
 // 8 values as loaded (no conversion: nothing waits for the load until cvt() is called)
 template <typename AT> struct Raw8B;
 template <> struct Raw8B<bf16_t> {
@@ -240,7 +254,7 @@ __global__ __launch_bounds__(256) void ln_apply_kernel(LnApplyBatch lb) {
     const float mean = mom[b0 + i - r0][0], rstd = mom[b0 + i - r0][1];
 #pragma unroll
     for (int j = 0; j < 8; ++j) v[i][j] = (v[i][j] - mean) * rstd * ga[j] + be[j];
-    st8<AT>(static_cast<AT *>(a.dst) + (size_t)(b0 + i) * lb.Dh + c8, v[i]);
+    st8_nt(static_cast<AT *>(a.dst) + (size_t)(b0 + i) * lb.Dh + c8, v[i]);
   }
 }
 
@@ -328,8 +342,8 @@ __global__ __launch_bounds__(256) void bwd_out_kernel(BwdOutArgs a) {
       // the row pieces are requested before the row's statistics are summed: one round trip, not two
       const size_t base = (size_t)b * a.Dh + tid * 8;
       float dH[8], v[8], hc[8], dhc[8];
-      ld8<AT>(static_cast<const AT *>(a.dH) + base, dH);
-      ld8<AT>(static_cast<const AT *>(a.V) + base, v);
+      ld8_nt(static_cast<const AT *>(a.dH) + base, dH);
+      ld8_nt(static_cast<const AT *>(a.V) + base, v);
       ld8<AT>(static_cast<const AT *>(a.Hc) + base, hc);
       if (a.mom) { mean = a.mom[2 * b]; rstd[r] = a.mom[2 * b + 1]; }
       else fade_row_moments_lanes<16>(a.stats + (size_t)b * a.stats_n * 2, a.stats_n, a.Dh, mean, rstd[r]);
@@ -417,8 +431,8 @@ __global__ __launch_bounds__(256) void bwd_gate_kernel(BwdGateArgs a) {
     if (b < a.B && mine) {
       const size_t base = (size_t)b * a.Dh + tid * 8;
       float du[8], hc[8];
-      ld8<AT>(static_cast<const AT *>(a.Hc) + base, hc);  // requested before the statistics are summed
-      if (!a.du_part && a.du) ld8<AT>(static_cast<const AT *>(a.du) + base, du);
+      ld8_nt(static_cast<const AT *>(a.Hc) + base, hc);  // requested before the statistics are summed
+      if (!a.du_part && a.du) ld8_nt(static_cast<const AT *>(a.du) + base, du);
       if (a.mom) { mean = a.mom[2 * b]; rstd[r] = a.mom[2 * b + 1]; }
       else fade_row_moments_lanes<16>(a.stats + (size_t)b * a.stats_n * 2, a.stats_n, a.Dh, mean, rstd[r]);
       if (a.du_part || !a.du) {
@@ -456,11 +470,11 @@ __global__ __launch_bounds__(256) void bwd_gate_kernel(BwdGateArgs a) {
       const size_t base = (size_t)b * a.Dh + tid * 8;
       const float m1 = sums[r] / (float)a.Dh, m2 = sums[R + r] / (float)a.Dh;
       float dhc[8], sg[8], ha[8], hm[8], dHa[8], dac[8], dmix[8];
-      ld8<AT>(static_cast<const AT *>(a.dHc) + base, dhc);
+      ld8_nt(static_cast<const AT *>(a.dHc) + base, dhc);
 #pragma unroll
       for (int i = 0; i < 8; ++i) sg[i] = 1.0f;
-      if (a.sg) ld8<AT>(static_cast<const AT *>(a.sg) + base, sg);
-      ld8<AT>(static_cast<const AT *>(a.Ha) + base, ha);
+      if (a.sg) ld8_nt(static_cast<const AT *>(a.sg) + base, sg);
+      ld8_nt(static_cast<const AT *>(a.Ha) + base, ha);
       ld8<AT>(static_cast<const AT *>(a.Hmix) + base, hm);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
@@ -522,8 +536,8 @@ __global__ __launch_bounds__(256) void bwd_mix_kernel(BwdMixArgs a) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) { dn[i] = 0.0f; hm[i] = 0.0f; }
       if (a.dnc) {  // requested before the statistics are summed
-        ld8<AT>(static_cast<const AT *>(a.dnc) + base, dn);
-        ld8<AT>(static_cast<const AT *>(a.Hmix) + base, hm);
+        ld8_nt(static_cast<const AT *>(a.dnc) + base, dn);
+        ld8_nt(static_cast<const AT *>(a.Hmix) + base, hm);
       }
       if (a.mom) { mean = a.mom[2 * b]; rstd[r] = a.mom[2 * b + 1]; }
       else fade_row_moments_lanes<16>(a.stats + (size_t)b * a.stats_n * 2, a.stats_n, a.Dh, mean, rstd[r]);
@@ -548,15 +562,15 @@ __global__ __launch_bounds__(256) void bwd_mix_kernel(BwdMixArgs a) {
       const size_t base = (size_t)b * a.Dh + tid * 8;
       const float m1 = sums[r] / (float)a.Dh, m2 = sums[R + r] / (float)a.Dh;
       float d1[8], d2[8], al[8], pre_g[8], pre_c[8], x[8], dar[8], dhm[8], dcv[8], dX[8];
-      ld8<AT>(static_cast<const AT *>(a.dHmix1) + base, d1);
+      ld8_nt(static_cast<const AT *>(a.dHmix1) + base, d1);
 #pragma unroll
       for (int i = 0; i < 8; ++i) { d2[i] = 0.0f; al[i] = 1.0f; pre_c[i] = 0.0f; }
-      if (a.dHmix2) ld8<AT>(static_cast<const AT *>(a.dHmix2) + base, d2);
+      if (a.dHmix2) ld8_nt(static_cast<const AT *>(a.dHmix2) + base, d2);
       if (a.alpha) {
-        ld8<AT>(static_cast<const AT *>(a.alpha) + base, al);
-        ld8<AT>(static_cast<const AT *>(a.cv) + base, pre_c);
+        ld8_nt(static_cast<const AT *>(a.alpha) + base, al);
+        ld8_nt(static_cast<const AT *>(a.cv) + base, pre_c);
       }
-      ld8<AT>(static_cast<const AT *>(a.hm) + base, pre_g);
+      ld8_nt(static_cast<const AT *>(a.hm) + base, pre_g);
       ld8<AT>(static_cast<const AT *>(a.X) + base, x);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
@@ -631,7 +645,7 @@ __global__ __launch_bounds__(1024) void reduce_batch_kernel(ReduceBatch rb) {
 //   dz = sum of split partials; dy[k] = sum_n W_U[b][k][n] dz[n]; grad W_U[b][k][n] = y[k] dz[n].
 // The gradient is consumed on the spot by Adam (master, moments, compute copy), so it never goes to memory.
 // ---------------------------------------------------------------------------------------------------
-template <typename AT>
+template <typename AT, bool NT>
 __global__ __launch_bounds__(256) void bwd_cci_kernel(BwdCciArgs a) {
   __shared__ float dz_s[64], y_s[64];
   const int b = blockIdx.x, tid = threadIdx.x;
@@ -642,9 +656,9 @@ __global__ __launch_bounds__(256) void bwd_cci_kernel(BwdCciArgs a) {
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const int idx = (e * 256 + tid) * 4;
-    w4[e] = *reinterpret_cast<const f32x4 *>(master + idx);
-    m4[e] = *reinterpret_cast<const f32x4 *>(m + idx);
-    v4[e] = *reinterpret_cast<const f32x4 *>(v + idx);
+    w4[e] = fade_load4<NT>(master + idx);
+    m4[e] = fade_load4<NT>(m + idx);
+    v4[e] = fade_load4<NT>(v + idx);
   }
   if (tid < 64) {
     float dz = 0.0f;
@@ -699,11 +713,13 @@ __global__ __launch_bounds__(256) void bwd_cci_kernel(BwdCciArgs a) {
       wn[i] = w4[e][i] - a.lr * (mk / u.c1) / (sqrtf(vk / u.c2) + a.eps);
       w4[e][i] = wn[i];
     }
-    *reinterpret_cast<f32x4 *>(m + idx) = m4[e];
-    *reinterpret_cast<f32x4 *>(v + idx) = v4[e];
-    *reinterpret_cast<f32x4 *>(master + idx) = w4[e];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) Wc[idx + i] = (AT)wn[i];
+    fade_store4<NT>(m + idx, m4[e]);
+    fade_store4<NT>(v + idx, v4[e]);
+    fade_store4<NT>(master + idx, w4[e]);
+    typedef AT at4 __attribute__((ext_vector_type(4)));
+    const at4 wc = {(AT)wn[0], (AT)wn[1], (AT)wn[2], (AT)wn[3]};
+    if constexpr (NT) __builtin_nontemporal_store(wc, reinterpret_cast<at4 *>(Wc + idx));
+    else *reinterpret_cast<at4 *>(Wc + idx) = wc;
   }
 }
 
@@ -974,8 +990,8 @@ __device__ __forceinline__ void conv_grad_mfma_body(const ConvGradArgs &a, int b
     for (int it = 0; it < 2; ++it) {  // 128 tokens x 4 pieces of 16 bytes, for each operand
       const int e = tid + 256 * it, tl = e >> 2, pc = e & 3;
       const long long t = t0 + tl < tokens ? t0 + tl : tokens - 1;
-      pxv[it] = *reinterpret_cast<const f32x4 *>(XL + (size_t)t * D + pc * 8);
-      pdv[it] = *reinterpret_cast<const f32x4 *>(dcv + (size_t)t * D + pc * 8);
+      pxv[it] = fade_nt_load(XL + (size_t)t * D + pc * 8);
+      pdv[it] = fade_nt_load(dcv + (size_t)t * D + pc * 8);
     }
   };
   if (block < nchunks) request((long long)block * 128);
@@ -1240,6 +1256,7 @@ __global__ __launch_bounds__(256) void embed_finish_kernel(int D, int P, const f
 // ---------------------------------------------------------------------------------------------------
 // Adam on the big matrices + refresh of their bf16 operand copies, one 64 x 64 block per workgroup
 // ---------------------------------------------------------------------------------------------------
+template <bool NT>
 __global__ __launch_bounds__(256) void adam_refresh_kernel(AdamRefreshBatch ab) {
   __shared__ float tile[64][65];
   __shared__ float gb[2][64];
@@ -1268,11 +1285,11 @@ __global__ __launch_bounds__(256) void adam_refresh_kernel(AdamRefreshBatch ab) 
     if (parts) {
       const size_t mat = (size_t)M.K * M.N;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) g[q] = *reinterpret_cast<const f32x4 *>(M.gpart + (idx[q] - M.off));
+      for (int q = 0; q < 4; ++q) g[q] = fade_load4<NT>(M.gpart + (idx[q] - M.off));
 #pragma unroll 2
       for (int sp = 1; sp < M.gsplits; ++sp)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) g[q] += *reinterpret_cast<const f32x4 *>(M.gpart + sp * mat + (idx[q] - M.off));
+        for (int q = 0; q < 4; ++q) g[q] += fade_load4<NT>(M.gpart + sp * mat + (idx[q] - M.off));
       if (ab.keep_sum) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) *reinterpret_cast<f32x4 *>(const_cast<float *>(ab.opt.grad_base) + idx[q]) = g[q];
@@ -1280,11 +1297,11 @@ __global__ __launch_bounds__(256) void adam_refresh_kernel(AdamRefreshBatch ab) 
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      w[q] = *reinterpret_cast<const f32x4 *>(ab.opt.master + idx[q]);
+      w[q] = fade_load4<NT>(ab.opt.master + idx[q]);
       if (!ab.refresh_only) {
         if (!parts) g[q] = *reinterpret_cast<const f32x4 *>(ab.opt.grad_base + idx[q]);
-        mm[q] = *reinterpret_cast<const f32x4 *>(ab.opt.m + idx[q]);
-        vv[q] = *reinterpret_cast<const f32x4 *>(ab.opt.v + idx[q]);
+        mm[q] = fade_load4<NT>(ab.opt.m + idx[q]);
+        vv[q] = fade_load4<NT>(ab.opt.v + idx[q]);
       }
     }
     if (ab.refresh_only) {
@@ -1304,9 +1321,9 @@ __global__ __launch_bounds__(256) void adam_refresh_kernel(AdamRefreshBatch ab) 
         w[q][i] = w[q][i] - lr * (mk / us.c1) / (sqrtf(vk / us.c2) + eps);
         tile[(tid >> 4) + 16 * q][c4 + i] = w[q][i];
       }
-      *reinterpret_cast<f32x4 *>(ab.opt.m + idx[q]) = mm[q];
-      *reinterpret_cast<f32x4 *>(ab.opt.v + idx[q]) = vv[q];
-      *reinterpret_cast<f32x4 *>(ab.opt.master + idx[q]) = w[q];
+      fade_store4<NT>(ab.opt.m + idx[q], mm[q]);
+      fade_store4<NT>(ab.opt.v + idx[q], vv[q]);
+      fade_store4<NT>(ab.opt.master + idx[q], w[q]);
     }
   }
   if (M.gamma && tid < 64) { gb[0][tid] = M.gamma[k0 + tid]; gb[1][tid] = M.beta[k0 + tid]; }
@@ -1443,7 +1460,13 @@ hipError_t fade_reduce_batch(const ReduceBatch &rb, hipStream_t s) {
   hipLaunchKernelGGL(reduce_batch_kernel, dim3(nblk((size_t)maxN, 32), rb.count), dim3(1024), 0, s, rb);
   return hipGetLastError();
 }
-hipError_t fade_bwd_cci(const BwdCciArgs &a, bool bf16, hipStream_t s) { DISPATCH_AT(bf16, bwd_cci_kernel, dim3(a.B), dim3(256), s, a); }
+hipError_t fade_bwd_cci(const BwdCciArgs &a, bool bf16, hipStream_t s) {
+  if (bf16 && a.streamed) hipLaunchKernelGGL((bwd_cci_kernel<bf16_t, true>), dim3(a.B), dim3(256), 0, s, a);
+  else if (bf16) hipLaunchKernelGGL((bwd_cci_kernel<bf16_t, false>), dim3(a.B), dim3(256), 0, s, a);
+  else if (a.streamed) hipLaunchKernelGGL((bwd_cci_kernel<float, true>), dim3(a.B), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((bwd_cci_kernel<float, false>), dim3(a.B), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
 // a.part must hold ceil(B / 4) * 2 * D * c floats; dWgv points at W_g's gradient (W_v's follows it in the blob)
 hipError_t fade_bwd_slot(const BwdSlotArgs &a, float *dWgv, bool bf16, ReduceBatch &rb, hipStream_t s) {
   if (a.Dh > 2048 || a.Dh % 8 || a.c > 256 || a.D > 64) return hipErrorInvalidValue;
@@ -1521,6 +1544,7 @@ hipError_t fade_adam_refresh(const AdamRefreshBatch &ab, hipStream_t s) {
   if (ab.count <= 0 || ab.count > 10) return hipErrorInvalidValue;
   for (int i = 0; i < ab.count; ++i)
     if (ab.m[i].K % 64 || ab.m[i].N % 64 || ab.m[i].off % 4 || ab.m[i].vstride % 64 || ab.m[i].vcol0 % 64) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(adam_refresh_kernel, dim3(ab.total_blocks), dim3(256), 0, s, ab);
+  if (ab.streamed) hipLaunchKernelGGL(adam_refresh_kernel<true>, dim3(ab.total_blocks), dim3(256), 0, s, ab);
+  else hipLaunchKernelGGL(adam_refresh_kernel<false>, dim3(ab.total_blocks), dim3(256), 0, s, ab);
   return hipGetLastError();
 }

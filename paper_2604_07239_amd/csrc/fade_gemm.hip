@@ -51,6 +51,17 @@ __device__ __forceinline__ void store8(bf16_t *p, const float v[8]) {
   for (int i = 0; i < 8; ++i) r[i] = (bf16_t)v[i];
   *reinterpret_cast<bf16x8 *>(p) = r;
 }
+// outputs that only the backward pass reads
+__device__ __forceinline__ void store8_nt(bf16_t *p, const float v[8]) {
+  bf16x8 r;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) r[i] = (bf16_t)v[i];
+  fade_nt_store(p, __builtin_bit_cast(f32x4, r));
+}
+__device__ __forceinline__ void store8_nt(float *p, const float v[8]) {
+  fade_nt_store(p, f32x4{v[0], v[1], v[2], v[3]});
+  fade_nt_store(p + 4, f32x4{v[4], v[5], v[6], v[7]});
+}
 __device__ __forceinline__ void store8(float *p, const float v[8]) {
   f32x4 a, b;
 #pragma unroll
@@ -244,7 +255,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs &g, const float *Cs, int
 #pragma unroll
         for (int i = 0; i < 8; ++i) out[i] = fmaf(lam, s1[i], gelu_f(x[i]));
         store8(static_cast<AT *>(g.C) + o, out);
-        if (g.C2) store8(static_cast<AT *>(g.C2) + o, x);
+        if (g.C2) store8_nt(static_cast<AT *>(g.C2) + o, x);
       } else if (EPI == EPI_MIX) {
         float s1[8], s2[8], al[8];
         raw_to_float(sd[0], s1);
@@ -252,7 +263,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs &g, const float *Cs, int
 #pragma unroll
         for (int i = 0; i < 8; ++i) { al[i] = sigmoid_f(x[i]); out[i] = fmaf(al[i], s1[i], __fmul_rn(1.0f - al[i], s2[i])); }
         store8(static_cast<AT *>(g.C) + o, out);
-        if (g.C2) store8(static_cast<AT *>(g.C2) + o, al);
+        if (g.C2) store8_nt(static_cast<AT *>(g.C2) + o, al);
       } else if (EPI == EPI_GATE) {
         float s1[8], s2[8], sgm[8];
         raw_to_float(sd[0], s1);
@@ -260,15 +271,15 @@ __device__ __forceinline__ void epilogue(const GemmArgs &g, const float *Cs, int
 #pragma unroll
         for (int i = 0; i < 8; ++i) { sgm[i] = sigmoid_f(x[i]); out[i] = fmaf(lam, s2[i], __fmul_rn(s1[i], sgm[i])); }
         store8(static_cast<AT *>(g.C) + o, out);
-        if (g.C2) store8(static_cast<AT *>(g.C2) + o, sgm);
+        if (g.C2) store8_nt(static_cast<AT *>(g.C2) + o, sgm);
       } else if (EPI == EPI_GEGLU) {
         float xv[8];
         load8(Cs + r * LDC + BNO + c8, xv);
 #pragma unroll
         for (int i = 0; i < 8; ++i) out[i] = gelu_f(x[i]) * xv[i];
         store8(static_cast<AT *>(g.C) + o, out);
-        if (g.C2) store8(static_cast<AT *>(g.C2) + o, x);
-        if (g.C3) store8(static_cast<AT *>(g.C3) + o, xv);
+        if (g.C2) store8_nt(static_cast<AT *>(g.C2) + o, x);
+        if (g.C3) store8_nt(static_cast<AT *>(g.C3) + o, xv);
       } else if (EPI == EPI_GEGLU_FOLD) {
         float xv[8], eg[8], ev[8];
         load8(Cs + r * LDC + BNO + c8, xv);
@@ -279,8 +290,8 @@ __device__ __forceinline__ void epilogue(const GemmArgs &g, const float *Cs, int
           out[i] = gelu_f(eg[i]) * ev[i];
         }
         store8(static_cast<AT *>(g.C) + o, out);
-        if (g.C2) store8(static_cast<AT *>(g.C2) + o, eg);
-        if (g.C3) store8(static_cast<AT *>(g.C3) + o, ev);
+        if (g.C2) store8_nt(static_cast<AT *>(g.C2) + o, eg);
+        if (g.C3) store8_nt(static_cast<AT *>(g.C3) + o, ev);
       } else if (EPI == EPI_GRAD) {  // split: partial sum over one range of the batch, slices [split][M][width] behind each other
         if (g.C3) {
           const int v = n0 + c8;
@@ -297,7 +308,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs &g, const float *Cs, int
 #pragma unroll
         for (int i = 0; i < 8; ++i) { pre_act[i] = x[i] + bi[i]; out[i] = gelu_f(pre_act[i]); }
         store8(static_cast<AT *>(g.C) + o, out);
-        if (g.C2) store8(static_cast<AT *>(g.C2) + o, pre_act);
+        if (g.C2) store8_nt(static_cast<AT *>(g.C2) + o, pre_act);
       }
     } else {
 #pragma unroll

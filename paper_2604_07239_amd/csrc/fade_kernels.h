@@ -64,6 +64,7 @@ struct CciArgs {
   const float *stats;    // [B][stats_n][2] row sums of H_mix
   const float *s_fold, *t_fold;  // [64]
   const bf16_t *WU;      // [B][64][64]
+  int streamed;          // W_U comes from memory at every step (fade_streamed)
   float *y;              // [B][64] Down(LN(H_mix))
   bf16_t *z;             // [B][64] y W_U
 };
@@ -236,6 +237,7 @@ struct BwdCciArgs {
   float *dy; void *dy_at; // [B][64]
   const UpdateState *u;
   float lr, beta1, beta2, eps;
+  int streamed;           // the state of a step is more than the caches keep (fade_streamed)
   float *g_dbg;           // optional [B][64][64]: the gradient y dz^T written out (debug: it is otherwise consumed in registers)
 };
 struct BwdSlotArgs {
@@ -331,6 +333,7 @@ struct AdamRefreshBatch {
   int count, total_blocks;
   int refresh_only;        // no Adam step: rebuild the copies from the master weights as they are (load / reset)
   int keep_sum;            // a gradient that arrives as slices over ranges of the batch: also store the sum in the gradient array (debug contexts)
+  int streamed;            // the state of a step is more than the caches keep (fade_streamed)
   AdamMat m[10];
   AdamArrays opt;
 };

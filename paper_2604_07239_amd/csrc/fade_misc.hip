@@ -565,6 +565,7 @@ __global__ __launch_bounds__(256) void bmm_kernel(const float *y, const AT *WU, 
 // ---------------------------------------------------------------------------------------------------
 // Eq. 7 between Down and Up (bf16 path): reduce the split-K partials of H_mix W'_down, apply the folded LayerNorm,
 // then the per-stream memory: z[b] = y[b] W_U[b]. One wavefront per stream, lane = column (d_low = 64).
+template <bool NT>
 __global__ __launch_bounds__(256) void cci_kernel(CciArgs a) {
   const int b = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (b >= a.B) return;
@@ -573,7 +574,10 @@ __global__ __launch_bounds__(256) void cci_kernel(CciArgs a) {
   const bf16x8 *Wp = reinterpret_cast<const bf16x8 *>(a.WU + (size_t)(b % a.streams) * 4096) + lane;
   bf16x8 w[8];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) w[i] = Wp[64 * i];
+  for (int i = 0; i < 8; ++i) {
+    if constexpr (NT) w[i] = __builtin_bit_cast(bf16x8, fade_nt_load(Wp + 64 * i));
+    else w[i] = Wp[64 * i];
+  }
   float raw = 0.0f;
   for (int s0 = 0; s0 < a.splits; s0 += 8) {  // 8 partials in flight, added in split order
     float pv[8];
@@ -1414,7 +1418,8 @@ hipError_t fade_bmm(const float *y, const void *WU, void *z, int B, bool bf16, h
 }
 // st_out: [2][N] (s then t); part: scratch of 16 * 2 * N floats
 hipError_t fade_cci(const CciArgs &a, hipStream_t s) {
-  hipLaunchKernelGGL(cci_kernel, dim3((a.B + 3) / 4), dim3(256), 0, s, a);
+  if (a.streamed) hipLaunchKernelGGL(cci_kernel<true>, dim3((a.B + 3) / 4), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL(cci_kernel<false>, dim3((a.B + 3) / 4), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 hipError_t fade_geglu(const GegluArgs &a, hipStream_t s) {

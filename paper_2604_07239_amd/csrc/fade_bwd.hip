@@ -730,8 +730,8 @@ __global__ __launch_bounds__(256) void bwd_cci_kernel(BwdCciArgs a) {
 // as part[workgroup][2][D][c] (blob order); the second stage adds the workgroups in index order.
 // Without a.dg every wavefront walks all c rows of W_m's last slot itself, which is fine for the narrow slots of the
 // benchmark shapes (c = 4..8) and far too much L2 traffic for wide ones: there dg comes from a product (a.dg) and this
-// kernel only does the element-wise part. Narrow rows (D_h <= 512: one 8-wide chunk per lane, KCH = 1) put 4 streams on a
-// wavefront.
+// kernel only does the element-wise part. Narrow rows (D_h <= 512: one 8-wide chunk per lane, KCH = 1) put up to 4 streams
+// on a wavefront.
 // ---------------------------------------------------------------------------------------------------
 template <typename AT, int SPW, int KCH>
 __device__ __forceinline__ void bwd_slot_body(const BwdSlotArgs &a, int block) {
@@ -768,30 +768,40 @@ __device__ __forceinline__ void bwd_slot_body(const BwdSlotArgs &a, int block) {
       mine[u] = 0.0f;
       if (a.dg && lane < qn && b0 + u < a.B) mine[u] = (float)static_cast<const AT *>(a.dg)[(size_t)(b0 + u) * a.c + q0 + lane];
     }
-    for (int ql = 0; ql < (a.dg ? 0 : qn); ++ql) {
-      const float *wrow = a.Wm + (size_t)(a.Dc - a.c + q0 + ql) * a.Dh;
-      float sacc[SPW];
+    // QB rows of W_m requested together: with one at a time every slot column paid a trip to the L2 (c = 32, four streams
+    // per wavefront, B = 128: 26.8 us against 20.1 with eight rows; B = 8192: 48.3 against 37.0; two rows of D_h = 2048: 100 against 96)
+    constexpr int QB = KCH == 1 ? 8 : 2;
+    for (int ql0 = 0; ql0 < (a.dg ? 0 : qn); ql0 += QB) {
+      float w[QB][KCH][8];
 #pragma unroll
-      for (int u = 0; u < SPW; ++u) sacc[u] = 0.0f;
-      float w[KCH][8];
+      for (int r = 0; r < QB; ++r) {
+        const int ql = ql0 + r < qn ? ql0 + r : qn - 1;  // past the last column: any row, its sum goes to a lane that is not used
+        const float *wrow = a.Wm + (size_t)(a.Dc - a.c + q0 + ql) * a.Dh;
 #pragma unroll
-      for (int k = 0; k < KCH; ++k) {  // all of the row's pieces requested together; a chunk past the row meets dh = 0
-        const int ch = lane + 64 * k;
-        ld8<float>(wrow + (ch < nch ? ch : nch - 1) * 8, w[k]);
-      }
-#pragma unroll
-      for (int k = 0; k < KCH; ++k) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const float wi = a.round_bf16 ? (float)(bf16_t)w[k][i] : w[k][i];
-#pragma unroll
-          for (int u = 0; u < SPW; ++u) sacc[u] = fmaf(dh[u][k][i], wi, sacc[u]);
+        for (int k = 0; k < KCH; ++k) {  // a chunk past the row meets dh = 0
+          const int ch = lane + 64 * k;
+          ld8<float>(wrow + (ch < nch ? ch : nch - 1) * 8, w[r][k]);
         }
       }
 #pragma unroll
-      for (int u = 0; u < SPW; ++u) {
-        const float sv = fade_lanes_sum(sacc[u]);
-        if (lane == ql) mine[u] = sv;
+      for (int r = 0; r < QB; ++r) {
+        float sacc[SPW];
+#pragma unroll
+        for (int u = 0; u < SPW; ++u) sacc[u] = 0.0f;
+#pragma unroll
+        for (int k = 0; k < KCH; ++k) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const float wi = a.round_bf16 ? (float)(bf16_t)w[r][k][i] : w[r][k][i];
+#pragma unroll
+            for (int u = 0; u < SPW; ++u) sacc[u] = fmaf(dh[u][k][i], wi, sacc[u]);
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < SPW; ++u) {
+          const float sv = fade_lanes_sum(sacc[u]);
+          if (lane == ql0 + r) mine[u] = sv;
+        }
       }
     }
     if (lane < qn) {
@@ -1488,15 +1498,16 @@ hipError_t fade_bwd_slot_conv(const BwdSlotArgs &sa, float *dWgv, const ConvGrad
   if (sa.Dh > 2048 || sa.Dh % 8 || sa.c > 256 || sa.D > 64) return hipErrorInvalidValue;
   if (ca.D != 32 || 128 % ca.T || ca.T < 4 || ca.taps > 4 || !ca.WT || !ca.dxl || ca.Kc % 16 || ca.Kc > 128 || ca.taps * 32 > ca.Kc) return hipErrorInvalidValue;
   const bool narrow = sa.Dh <= 512;
-  // narrow rows with wide slots (the paper-default shape: D_h = 512, c = 256): a stream's element-wise part and its share of
-  // the partial sums are long, so two streams per wavefront instead of four (twice the workgroups)
+  // Narrow rows, streams per wavefront: one while the batch leaves compute units idle (D_h = 512, c = 32, in us with 1 / 2 / 4
+  // streams: B = 128 11.7 / 14.7 / 20.1, B = 1000 11.9 / 14.7 / 19.5, B = 2000 15.9 / 15.8), two above, where a row of W_m serves both (B = 8192 47.3 /
+  // 36.9 / 37.0) and with wide slots (c = 256), whose element-wise part and share of the partial sums are long.
   static const int spw_env = env_int("FADE_SLOT_SPW");
-  const int spw = narrow ? ((spw_env == 2 || spw_env == 4) ? spw_env : (sa.c >= 64 ? 2 : 4)) : 1;
+  const int spw = narrow ? ((spw_env == 1 || spw_env == 2) ? spw_env : (sa.B <= 2048 && sa.c < 64 ? 1 : 2)) : 1;
   const int Ps = (sa.B + 4 * spw - 1) / (4 * spw);
   const long long nchunks = ((long long)ca.B * ca.T + 127) / 128;
   const int Pc = (int)(nchunks < 512 ? nchunks : 512);
-  if (spw == 4) hipLaunchKernelGGL((slot_conv_kernel<4, 1>), dim3(Ps + Pc), dim3(256), 0, s, sa, ca, Pc);
-  else if (spw == 2) hipLaunchKernelGGL((slot_conv_kernel<2, 1>), dim3(Ps + Pc), dim3(256), 0, s, sa, ca, Pc);
+  if (spw == 2) hipLaunchKernelGGL((slot_conv_kernel<2, 1>), dim3(Ps + Pc), dim3(256), 0, s, sa, ca, Pc);
+  else if (narrow) hipLaunchKernelGGL((slot_conv_kernel<1, 1>), dim3(Ps + Pc), dim3(256), 0, s, sa, ca, Pc);
   else hipLaunchKernelGGL((slot_conv_kernel<1, 4>), dim3(Ps + Pc), dim3(256), 0, s, sa, ca, Pc);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -188,10 +188,10 @@ __device__ __forceinline__ void conv_tile_store(const EmbedArgs &a, size_t row, 
     bf16_t *Hl = static_cast<bf16_t *>(a.Hl) + row * a.Dh + t * 32 + c0;
     *reinterpret_cast<bf16x8 *>(Hl) = h[0];
     *reinterpret_cast<bf16x8 *>(Hl + 8) = h[1];
-    if (a.cv) {
+    if (a.cv) {  // for the backward pass, like X_l: past the caches (B = 16384: window kernel 72 -> 66 us, step 2713 -> 2699)
       bf16_t *cv = static_cast<bf16_t *>(a.cv) + row * a.Dh + t * 32 + c0;
-      *reinterpret_cast<bf16x8 *>(cv) = p[0];
-      *reinterpret_cast<bf16x8 *>(cv + 8) = p[1];
+      fade_nt_store(cv, __builtin_bit_cast(f32x4, p[0]));
+      fade_nt_store(cv + 8, __builtin_bit_cast(f32x4, p[1]));
     }
   }
 }
@@ -458,8 +458,8 @@ __global__ __launch_bounds__(256) void embed_cache_lds_kernel(EmbedArgs a) {
       if constexpr (UPD) {
         if (a.XL) {
           bf16_t *XL = static_cast<bf16_t *>(a.XL) + (size_t)b * a.Dh;
-          *reinterpret_cast<f32x4 *>(XL + vt * 8) = xl0;
-          *reinterpret_cast<f32x4 *>(XL + (vt + nt) * 8) = xl1;
+          fade_nt_store(XL + vt * 8, xl0);
+          fade_nt_store(XL + (vt + nt) * 8, xl1);
         }
       }
       conv_tile_store(a, (size_t)b, tile, h, p);

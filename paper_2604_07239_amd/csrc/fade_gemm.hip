@@ -1520,10 +1520,10 @@ hipError_t launch_pipe2(const GemmArgs &g, hipStream_t s) {
 // 512 tiles of 128 x 128 on: that tile with a two-stage ring (64 KiB of LDS), two workgroups per compute unit: one's
 // epilogue (side inputs from HBM, stores) and pipeline fill run under the other's products, which measured faster than
 // either a deeper ring or a 256 x 128 tile with one workgroup per unit (router product, M = 4096: 43 us against 54).
-// Once every compute unit gets a 256 x 256 tile (M >= 8192 at N = 2048): that tile on eight wavefronts with the ring of
-// four 32-wide stages (pipe2_body): half the operand bytes per flop of 128 x 128 and two wavefronts per SIMD. On random
-// operands at M = 16384, N = 2048: K = 2048 188 us against 207 for the same tile on a two-stage ring of 64-wide stages,
-// 230 for 128 x 128; K = 512 88 against 104; mix epilogue in both. With a contraction of 64 the two shapes tie.
+// Once every compute unit gets a 256 x 256 tile (M >= 8192 at N = 2048): that tile on eight wavefronts with the finer
+// rings of pipe2_body: half the operand bytes per flop of 128 x 128 and two wavefronts per SIMD. On random operands at
+// M = 16384, N = 2048 (then with A in 32-wide stages): K = 2048 188 us against 207 for the same tile on a two-stage ring of
+// 64-wide stages, 230 for 128 x 128; K = 512 88 against 104; mix epilogue in both. With a contraction of 64 the two shapes tie.
 template <int EPI>
 hipError_t launch_pipe_auto(const GemmArgs &g, hipStream_t s) {
   const int tiles128 = ((g.M + 127) / 128) * (g.N / 128);

@@ -229,14 +229,16 @@ __global__ __launch_bounds__(256) void transpose_batch_kernel(TransposeBatch tb)
 
 template <typename AT, int RPT>
 __global__ __launch_bounds__(256) void ln_apply_kernel(LnApplyBatch lb) {
-  if ((int)blockIdx.y == lb.count) {  // the loss gradient's workgroups (with_loss)
+  // The loss gradient's workgroups (with_loss) come first: each counts the active streams of the whole batch, a serial chain that
+  // runs under the copies when they follow and alone at the launch's end otherwise (B = 1024: 8.9 -> 6.8 us, 16384: 68.7 -> 64.3).
+  if (lb.with_loss && blockIdx.y == 0) {
     const LossGradArgs &l = lb.loss;
     if ((int)blockIdx.x < (lb.B + 7) / 8)
       loss_grad_body<AT>(blockIdx.x, l.ws, l.targets, l.tstride, lb.B, l.probs, l.u, l.beta1, l.beta2, static_cast<AT *>(l.dl), l.col_part);
     return;
   }
   __shared__ float mom[FADE_GROUP_ROWS_MAX][2];
-  const LnApplyArgs &a = lb.a[blockIdx.y];
+  const LnApplyArgs &a = lb.a[blockIdx.y - (lb.with_loss ? 1 : 0)];
   const int chunks = lb.Dh / 8;
   const int r0 = fade_group_moments<RPT>(a.stats, lb.stats_n, lb.Dh, chunks, lb.B, mom);
   const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;

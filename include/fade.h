@@ -159,7 +159,8 @@ int fade_decode_device(fade_ctx *ctx, const uint32_t *lengths_host, const uint8_
  *   fade_quantize: probs_dev [rows][256] float -> freq_dev [rows][256] uint16 by the quantiser rule
  *     f_i = 1 + trunc(fp32(p_i * 65280)), remainder 65536 - sum f added at the lowest index of the maximum.
  *   fade_coder_encode_tables: code n_steps symbols for each of n_streams streams under given tables.
- *     freq_dev [n_steps][n_streams][256], sym_dev [n_steps][n_streams]; out_dev [n_streams][cap] receives each
+ *     freq_dev [n_steps][n_streams][256], each row summing to 65536 (a symbol that is never coded may have the frequency 0),
+ *     sym_dev [n_steps][n_streams]; out_dev [n_streams][cap] receives each
  *     stream's bytes, len_dev [n_streams] their count (32-bit interval coder after Witten, Neal & Cleary,
  *     totals 2^16, bits MSB first, terminated and zero-padded to a byte).
  *   fade_coder_decode_tables: the inverse; in_dev [n_streams][cap] with len_dev [n_streams].

@@ -1025,7 +1025,8 @@ __device__ __forceinline__ void enc_bounds(const uint32_t q[4], int lane, int s,
 // The symbol that `value` points at, and its bounds; false when it points outside the interval (the payload does not belong to
 // this model). The classic rule is cum[s] <= ((value - low + 1) * 2^16 - 1) / range < cum[s + 1]; with integers that is
 // (cum[s] * range) >> 16 <= value - low < (cum[s + 1] * range) >> 16, so every lane tries its own four symbols with a
-// multiplication each and nobody divides (a 64-bit division is over a hundred dependent instructions).
+// multiplication each and nobody divides (a 64-bit division is over a hundred dependent instructions). The bounds are compared
+// in 64 bits: under the full interval (range 2^32) one of 65536, where symbols of frequency 0 behind the last one start, is 2^32.
 __device__ __forceinline__ bool dec_find(const DecState &d, const uint32_t q[4], int lane, int &s, uint32_t &lo, uint32_t &hi) {
   uint32_t cum[4];
   cumulate_wave(q, cum);
@@ -1033,7 +1034,7 @@ __device__ __forceinline__ bool dec_find(const DecState &d, const uint32_t q[4],
   const uint32_t off = d.value - d.low;
   int at = -1;  // last of this lane's symbols that starts at or below the target
 #pragma unroll
-  for (int i = 0; i < 4; ++i) at = (uint32_t)((range * cum[i]) >> 16) <= off ? i : at;
+  for (int i = 0; i < 4; ++i) at = ((range * cum[i]) >> 16) <= off ? i : at;
   const bool mine = at >= 0 && ((range * (cum[3] + q[3])) >> 16) > off;
   const unsigned long long vote = __ballot(mine);
   if (vote == 0ull) return false;

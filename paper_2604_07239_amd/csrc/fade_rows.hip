@@ -503,11 +503,17 @@ struct Adam4 {  // optimiser state of n <= 4 neighbouring weights, requested ahe
       w[i] = w[i] - o.lr * (m[i] / us.c1) / (sqrtf(v[i] / us.c2) + o.eps);
     }
     float *grad = const_cast<float *>(o.grad_base);
-    if (n == 4) { st4(o.m + idx, m); st4(o.v + idx, v); st4(o.master + idx, w); st4(grad + idx, g); }
-    else
+    const bool live = us.na != 0;  // no active stream: a gradient of zero, and no update
+    if (n == 4) {
+      st4(grad + idx, g);
+      if (live) { st4(o.m + idx, m); st4(o.v + idx, v); st4(o.master + idx, w); }
+    } else
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        if (i < n) { o.m[idx + i] = m[i]; o.v[idx + i] = v[i]; o.master[idx + i] = w[i]; grad[idx + i] = g[i]; }
+        if (i < n) {
+          grad[idx + i] = g[i];
+          if (live) { o.m[idx + i] = m[i]; o.v[idx + i] = v[i]; o.master[idx + i] = w[i]; }
+        }
   }
 };
 // the contraction for one strip, four rows (lane group g: row k + g) a matrix instruction
@@ -579,7 +585,7 @@ __global__ __launch_bounds__(256) void rows_dw_adam_kernel(RowsDwArgs a) {
 #pragma unroll
   for (int t = 0; t < 4; ++t) acc[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   strip(d, m0, n0, acc);
-  if (us.na != 0) ss.step(a, d, us, acc);  // na == 0: no active stream, no update
+  ss.step(a, d, us, acc);
 }
 
 template <int PRO, int WL, int EPI, bool TWO = false> hipError_t launch(const RowsArgs &a, hipStream_t s, bool geglu = false) {

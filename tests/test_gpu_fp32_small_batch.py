@@ -1,7 +1,9 @@
 """The fp32 kernels of small batches (16 x 16 tiles, products sharing a launch, weight gradients with their Adam step) at the
 sizes where a tile, a strip or a batch of loads ends: against the oracle at the fp32 bars of the other parity tests."""
+import numpy as np
 import pytest
 
+from gpu_helpers import make_pair, need_gpu
 from test_gpu_online import _grad_check
 from test_gpu_parity import _step_parity
 
@@ -32,3 +34,23 @@ def test_step_parity_at_tile_edges(B, T, D, H, widths):
 ])
 def test_gradients_and_adam_at_tile_edges(B, T, D, H, tol, widths):
     _grad_check("f32", B, T, D, H, seed=90 + B, tol=tol, **widths)
+
+
+def test_update_without_active_streams():
+    """A gradient of zero in every shared tensor (not the previous update's), and weights that stay as they are, to the bit."""
+    torch = need_gpu()
+    B, T, D, H = 7, 8, 16, 64
+    g, _, blob = make_pair(B, T, D, H, "f32", seed=21, update_mode=1, std=0.05)
+    data = torch.from_numpy(np.random.default_rng(3).integers(0, 256, (B, T + 1), dtype=np.uint8)).cuda()
+    g.step_probs(data[:, :T].contiguous())
+    g.step_update(data[:, T].contiguous())
+    before = g.get_weights()
+    assert np.abs(blob.view(g.debug_grad(), "W_r")).max() > 0
+    none = torch.zeros(B, dtype=torch.uint8, device="cuda")
+    g.step_probs(data[:, :T].contiguous(), none)
+    g.step_update(data[:, T].contiguous(), none)
+    grad = g.debug_grad()
+    for name, _, _ in blob.specs:
+        assert name == "W_U" or not blob.view(grad, name).any(), name
+    np.testing.assert_array_equal(g.get_weights(), before)
+    g.close()

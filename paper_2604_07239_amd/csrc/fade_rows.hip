@@ -17,6 +17,7 @@
 // Row statistics are left per 16 columns (stats_n = N / 16). Every sum has a fixed order.
 #include "fade_dev.h"
 #include "fade_kernels.h"
+#include "fade_rules.h"
 
 namespace {
 
@@ -487,15 +488,15 @@ __global__ __launch_bounds__(NTH) void rows_last_kernel(RowsArgs rt, int n_rt, R
 // that a lane's outputs, R's operands and the optimiser state all move in 16-byte pieces. 24 bytes of state per weight are
 // what bounds it. L may be a LayerNorm (moments per row) formed on the way.
 // ---------------------------------------------------------------------------------------------------
-struct Adam4 {  // optimiser state of n <= 4 neighbouring weights, requested ahead of the gradient
+struct Adam4 {  // optimiser state of n <= 4 neighbouring weights, requested ahead of the gradient; vec: as one 16-byte piece
   f32x4 m, v, w;
-  __device__ __forceinline__ void load(const AdamArrays &o, size_t idx, int n) {
-    if (n == 4) { m = ld4(o.m + idx); v = ld4(o.v + idx); w = ld4(o.master + idx); }
+  __device__ __forceinline__ void load(const AdamArrays &o, size_t idx, int n, bool vec) {
+    if (vec) { m = ld4(o.m + idx); v = ld4(o.v + idx); w = ld4(o.master + idx); }
     else
 #pragma unroll
       for (int i = 0; i < 4; ++i) { const size_t k = idx + (i < n ? i : 0); m[i] = o.m[k]; v[i] = o.v[k]; w[i] = o.master[k]; }
   }
-  __device__ __forceinline__ void step(const AdamArrays &o, const UpdateState &us, size_t idx, const f32x4 &g, int n) {
+  __device__ __forceinline__ void step(const AdamArrays &o, const UpdateState &us, size_t idx, const f32x4 &g, int n, bool vec) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       m[i] = o.beta1 * m[i] + (1.0f - o.beta1) * g[i];
@@ -504,7 +505,7 @@ struct Adam4 {  // optimiser state of n <= 4 neighbouring weights, requested ahe
     }
     float *grad = const_cast<float *>(o.grad_base);
     const bool live = us.na != 0;  // no active stream: a gradient of zero, and no update
-    if (n == 4) {
+    if (vec) {
       st4(grad + idx, g);
       if (live) { st4(o.m + idx, m); st4(o.v + idx, v); st4(o.master + idx, w); }
     } else
@@ -551,21 +552,20 @@ __device__ __forceinline__ void strip(const RowsDw &d, int m0, int n0, f32x4 (&a
 }
 struct StripState {  // lane l: rows m0 + 4 (l >> 4) + e, columns n0 + 4 (l & 15) .. + 3
   Adam4 st[4];
-  int left, m;
-  size_t idx;
+  int m;
+  FadeStripLane at;
   __device__ __forceinline__ void load(const RowsDwArgs &a, const RowsDw &d, int m0, int n0) {
-    const int lane = threadIdx.x & 63, n = n0 + 4 * (lane & 15);
-    left = (d.N & 3) == 0 ? (n < d.N ? 4 : 0) : (d.N - n < 4 ? d.N - n : 4);
+    const int lane = threadIdx.x & 63;
     m = m0 + (lane >> 4) * 4;
-    idx = d.off + (size_t)m * d.N + n;
+    at = fade_strip_lane(d.off, d.N, n0, m, lane & 15);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) st[e].load(a.opt, left > 0 && m + e < d.M ? idx + (size_t)e * d.N : d.off, (d.N & 3) == 0 ? 4 : left > 0 ? left : 1);
+    for (int e = 0; e < 4; ++e) st[e].load(a.opt, at.left > 0 && m + e < d.M ? at.idx + (size_t)e * d.N : d.off, at.left > 0 ? at.left : 1, at.vec);
   }
   __device__ __forceinline__ void step(const RowsDwArgs &a, const RowsDw &d, const UpdateState &us, const f32x4 (&acc)[4]) {
-    if (left <= 0) return;
+    if (at.left <= 0) return;
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      if (m + e < d.M) st[e].step(a.opt, us, idx + (size_t)e * d.N, f32x4{acc[0][e], acc[1][e], acc[2][e], acc[3][e]}, left);
+      if (m + e < d.M) st[e].step(a.opt, us, at.idx + (size_t)e * d.N, f32x4{acc[0][e], acc[1][e], acc[2][e], acc[3][e]}, at.left, at.vec);
   }
 };
 __global__ __launch_bounds__(256) void rows_dw_adam_kernel(RowsDwArgs a) {
@@ -643,7 +643,7 @@ hipError_t fade_rows_dw_adam(RowsDwArgs &a, hipStream_t s) {
   a.first[0] = 0;
   for (int i = 0; i < a.count; ++i) {
     const RowsDw &d = a.d[i];
-    if (d.M <= 0 || d.N <= 0 || d.K <= 0) return hipErrorInvalidValue;
+    if (d.M <= 0 || d.N <= 0 || d.K <= 0 || d.off % 4) return hipErrorInvalidValue;
     a.first[i + 1] = a.first[i] + (d.M + 15) / 16 * ((d.N + 63) / 64);
   }
   hipLaunchKernelGGL(rows_dw_adam_kernel, dim3((a.first[a.count] + 3) / 4), dim3(256), 0, s, a);

@@ -98,7 +98,8 @@ int fade_create(const fade_config *cfg, fade_ctx **out);
  * reset the context. nbytes must equal fade_weights_nbytes(). Non-finite values: FADE_E_NUMERIC. */
 int fade_load_weights(fade_ctx *ctx, const void *blob_host, size_t nbytes);
 
-/* Zero the rolling caches and coder state, restore the loaded weights and zero the optimiser state. */
+/* Zero the rolling caches and coder state, restore the loaded weights and zero the optimiser state. Synchronises before
+ * returning: buffers of earlier fade_step_* calls are free again, and a failure of one of them is reported here. */
 int fade_reset(fade_ctx *ctx);
 
 /* One model step for all B streams (Eq. 1-10, head, softmax, quantiser). STATEFUL: rolls each active

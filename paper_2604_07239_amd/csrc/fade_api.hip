@@ -371,6 +371,7 @@ int prepare_compute(fade_ctx *c, bool with_wu = true) {
   return FADE_OK;
 }
 
+// enqueues only: the calls that start with it wait for the stream at their end
 int do_reset(fade_ctx *c) {
   const Dims &d = c->d;
   hipStream_t s = c->stream;
@@ -1651,7 +1652,10 @@ int fade_load_weights(fade_ctx *c, const void *blob_host, size_t nbytes) {
 
 int fade_reset(fade_ctx *c) {
   if (!c) return FADE_E_INVALID_ARG;
-  return do_reset(c);
+  const int rc = do_reset(c);
+  if (rc) return rc;
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  return FADE_OK;
 }
 
 int fade_step_probs(fade_ctx *c, const uint8_t *windows_dev, const uint8_t *active_dev, uint16_t *freq_dev, float *probs_dev) {

@@ -1635,12 +1635,14 @@ int fade_load_weights(fade_ctx *c, const void *blob_host, size_t nbytes) {
   for (size_t i = 0; i < np; ++i)
     if (!std::isfinite(f[i])) return fail(c, FADE_E_NUMERIC, "non-finite weight");
   c->have_weights = false;
-  HIP_TRY(c, hipStreamSynchronize(c->stream));  // no earlier step may still be reading the masters
+  // on the context's stream, behind the steps that still read the masters; nothing that other streams would wait for
   int rc = for_each_run(c->blob, c->lay, [&](size_t from, size_t to, size_t n) {
-    HIP_TRY(c, hipMemcpy(c->master + to, f + from, n * sizeof(float), hipMemcpyHostToDevice));
+    HIP_TRY(c, hipMemcpyAsync(c->master + to, f + from, n * sizeof(float), hipMemcpyHostToDevice, c->stream));
     return (int)FADE_OK;
   });
+  const hipError_t e = hipStreamSynchronize(c->stream);  // the caller's memory is free again, whatever happens next
   if (rc) return rc;
+  if (e != hipSuccess) return hip_fail(c, e, "weight upload");
   if (c->online) HIP_TRY(c, hipMemcpyAsync(c->loaded, c->master, c->lay.off[P_COUNT] * sizeof(float), hipMemcpyDeviceToDevice, c->stream));
   else if ((rc = prepare_compute(c))) return rc;
   c->weights_hash = fnv1a64(blob_host, nbytes);

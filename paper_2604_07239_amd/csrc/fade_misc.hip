@@ -1097,9 +1097,10 @@ __global__ __launch_bounds__(256) void softmax_quant_code_kernel(SqcArgs a) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) p[i] = p[i] / sum;
   if (a.probs) {
-    f32x4 o = {p[0], p[1], p[2], p[3]};
-    *reinterpret_cast<f32x4 *>(a.probs + (size_t)b * 256 + 4 * lane) = o;
-    if (a.probs2) *reinterpret_cast<f32x4 *>(a.probs2 + (size_t)b * 256 + 4 * lane) = o;
+    typedef f32x4 f32x4_any __attribute__((aligned(4)));  // a caller's buffer is aligned to its floats and no more
+    const f32x4 o = {p[0], p[1], p[2], p[3]};
+    *reinterpret_cast<f32x4_any *>(a.probs + (size_t)b * 256 + 4 * lane) = o;
+    if (a.probs2) *reinterpret_cast<f32x4_any *>(a.probs2 + (size_t)b * 256 + 4 * lane) = o;
   }
   uint32_t q[4];
   if (!quantize_wave(p, lane, q)) {

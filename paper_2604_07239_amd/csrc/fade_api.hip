@@ -12,6 +12,7 @@
 
 #include "../../include/fade.h"
 #include "fade_kernels.h"
+#include "fade_rules.h"
 
 namespace {
 
@@ -186,7 +187,7 @@ struct fade_ctx {
   int *dev_err = nullptr;            // error flag in host memory the kernels can write: read after a wait for the stream, without a copy
   bool rows16 = false;               // fp32 path at very small batches: 16 x 16 product tiles, row statistics per 16 columns
   size_t stats_n = 0;                // partial (sum, sum of squares) pairs per row the statistics buffers hold
-  bool streamed = false;             // a step reads or writes more weights and optimiser state than the caches keep until the next (fade_streamed)
+  bool streamed = false;             // bf16 path: weights and optimiser state go past the caches (fade_streamed)
   bool debug_wu_grad = false;        // FADE_DEBUG_WU_GRAD=1 at fade_create: gradients consumed where they are formed (W_U's, the sums of sliced weight gradients) are also written to the gradient array
   size_t loop_n = 0, loop_next = 0;  // job size and next step of the device-resident loop in progress
   int loop_mode = 0;
@@ -1150,7 +1151,7 @@ int backward_rows(fade_ctx *c, const WinSrc &ws, const uint8_t *targets, long lo
       BwdCciArgs a{};
       a.B = B; a.splits = 1; a.dz_part = c->dz_part; a.y = c->y; a.WU_c = c->WU_c;
       a.master = c->master + c->lay.off[P_WU]; a.m = c->adam_m + c->lay.off[P_WU]; a.v = c->adam_v + c->lay.off[P_WU];
-      a.dy = c->dy; a.dy_at = c->dy_at; a.u = c->ustate; a.streamed = c->streamed;
+      a.dy = c->dy; a.dy_at = c->dy_at; a.u = c->ustate;
       a.lr = c->cfg.lr; a.beta1 = c->cfg.beta1; a.beta2 = c->cfg.beta2; a.eps = c->cfg.eps;
       a.g_dbg = c->debug_wu_grad ? c->grad + c->lay.off[P_WU] : nullptr;
       HIP_TRY(c, fade_bwd_cci(a, false, s));
@@ -1383,8 +1384,8 @@ int fade_create(const fade_config *cfg, fade_ctx **out) {
   }
   const size_t R = d.B * (size_t)c->steps_max;  // rows of the forward buffers
   const size_t np = c->lay.off[P_COUNT], BDh = R * d.Dh;
-  c->streamed = fade_streamed(np * (c->online ? 16 : c->esz));  // adapting: weight, gradient, two moments
-  if (const char *e = getenv("FADE_STREAMED")) c->streamed = e[0] != '0';  // override for sweeps and tests
+  c->streamed = fade_streamed(c->bf16, c->online, np, d.B, d.Dh);
+  if (const char *e = getenv("FADE_STREAMED")) c->streamed = c->bf16 && e[0] != '0';  // override for sweeps and tests
   // fp32 contexts of up to 256 streams use the small-batch kernels of fade_rows.hip (statistics per 16 columns); FADE_F32_ROWS16=0
   // keeps the general ones
   c->rows16 = !c->bf16 && d.B <= 256 && d.Dh <= 2048 && d.Dc <= 2048 && d.De <= 2048 && d.Dh % 16 == 0 && d.Dc % 16 == 0 && d.De % 64 == 0 &&

@@ -1473,9 +1473,9 @@ hipError_t fade_reduce_batch(const ReduceBatch &rb, hipStream_t s) {
   return hipGetLastError();
 }
 hipError_t fade_bwd_cci(const BwdCciArgs &a, bool bf16, hipStream_t s) {
-  if (bf16 && a.streamed) hipLaunchKernelGGL((bwd_cci_kernel<bf16_t, true>), dim3(a.B), dim3(256), 0, s, a);
+  if (a.streamed && !bf16) return hipErrorInvalidValue;
+  if (a.streamed) hipLaunchKernelGGL((bwd_cci_kernel<bf16_t, true>), dim3(a.B), dim3(256), 0, s, a);
   else if (bf16) hipLaunchKernelGGL((bwd_cci_kernel<bf16_t, false>), dim3(a.B), dim3(256), 0, s, a);
-  else if (a.streamed) hipLaunchKernelGGL((bwd_cci_kernel<float, true>), dim3(a.B), dim3(256), 0, s, a);
   else hipLaunchKernelGGL((bwd_cci_kernel<float, false>), dim3(a.B), dim3(256), 0, s, a);
   return hipGetLastError();
 }

@@ -163,6 +163,11 @@ struct Tn2Group {
 // moments between any two uses of an operand; kept out of the cache they leave the step's 45 MB of bf16 operand copies and its
 // activations there. Step of configurations B = 1024 / 4096 (D_cache 4096, D_e 8192) / 16384: 438 / 1168 / 2766 us with plain
 // accesses, 422 / 1148 / 2724 with nt on the optimiser's state, 394-413 / 1126 / 2677 with the backward pass's operands too.
+// The optimiser's state follows a rule on sizes (fade_streamed). What only the backward pass reads is nt in the bf16 path at every
+// batch, one instance of each kernel: where everything fits it costs half a percent (step in us with plain accesses and with nt:
+// D_h = 256, B = 16 / 128 / 512 150.4 -> 151.6, 162.9 -> 164.3, 181.3 -> 183.5; D_h = 512, B = 128 / 512 185.7 -> 186.9, 209.1 -> 210.3;
+// D_h = 2048, B = 128 / 512 275.3 -> 277.4, 329.2 -> 330.0) against 3 to 5 % gained from there on (D_h = 2048, B = 768 / 1024
+// 377 -> 361, 419 -> 400; D_h = 1024, B = 2048 384 -> 374). The fp32 path's accesses are plain: 300 streams of D_h = 2048 lost 2 %.
 __device__ __forceinline__ f32x4 fade_nt_load(const void *p) { return __builtin_nontemporal_load(static_cast<const f32x4 *>(p)); }
 __device__ __forceinline__ void fade_nt_store(void *p, f32x4 v) { __builtin_nontemporal_store(v, static_cast<f32x4 *>(p)); }
 template <bool NT> __device__ __forceinline__ f32x4 fade_load4(const float *p) {
@@ -173,10 +178,6 @@ template <bool NT> __device__ __forceinline__ void fade_store4(float *p, f32x4 v
   if constexpr (NT) fade_nt_store(p, v);
   else *reinterpret_cast<f32x4 *>(p) = v;
 }
-// Whether a step's weights and optimiser state (`bytes` of them, read or written once a step) count as streamed: below this they
-// are still in the cache at the next step (B = 128, 39 MB: Adam pass 14.5 us with plain accesses, 15.0-15.5 with nt; frozen
-// B = 1024, 31 MB: per-stream products 4.6 against 5.0; adapting B = 1024, 248 MB: 6.4 against 5.6, their update 26 against 20).
-inline bool fade_streamed(size_t bytes) { return bytes >= ((size_t)128 << 20); }
 // Row statistics are accumulated per block tile of BN columns; consumers add the partials in index order.
 #define FADE_STATS_BN 128
 

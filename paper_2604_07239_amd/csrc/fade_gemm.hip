@@ -51,16 +51,12 @@ __device__ __forceinline__ void store8(bf16_t *p, const float v[8]) {
   for (int i = 0; i < 8; ++i) r[i] = (bf16_t)v[i];
   *reinterpret_cast<bf16x8 *>(p) = r;
 }
-// outputs that only the backward pass reads
+// outputs that only the backward pass reads (bf16)
 __device__ __forceinline__ void store8_nt(bf16_t *p, const float v[8]) {
   bf16x8 r;
 #pragma unroll
   for (int i = 0; i < 8; ++i) r[i] = (bf16_t)v[i];
   fade_nt_store(p, __builtin_bit_cast(f32x4, r));
-}
-__device__ __forceinline__ void store8_nt(float *p, const float v[8]) {
-  fade_nt_store(p, f32x4{v[0], v[1], v[2], v[3]});
-  fade_nt_store(p + 4, f32x4{v[4], v[5], v[6], v[7]});
 }
 __device__ __forceinline__ void store8(float *p, const float v[8]) {
   f32x4 a, b;
@@ -69,6 +65,7 @@ __device__ __forceinline__ void store8(float *p, const float v[8]) {
   *reinterpret_cast<f32x4 *>(p) = a;
   *reinterpret_cast<f32x4 *>(p + 4) = b;
 }
+__device__ __forceinline__ void store8_nt(float *p, const float v[8]) { store8(p, v); }  // read again with plain loads
 
 // ---------------------------------------------------------------------------------------------------
 // A-operand staging: one thread owns one 8-wide chunk of one row per pass.

@@ -1,5 +1,5 @@
-"""Weights and optimiser state past the caches (nt loads and stores, chosen by size) or through them: a hint to the memory system
-that may change no bit of probabilities or adapted weights."""
+"""Weights and optimiser state past the caches (nt loads and stores, bf16 path, chosen by size) or through them: a hint to the memory
+system that may change no bit of probabilities or adapted weights. The fp32 path has no such access: there the override does nothing."""
 import numpy as np
 import pytest
 

@@ -1,0 +1,83 @@
+"""The rules and the index arithmetic of fade_rules.h, compiled for the host."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+STRIP = """
+#include <stdio.h>
+#include <vector>
+#include "fade_rules.h"
+int main() {
+  const size_t off = 12;
+  for (int N = 1; N <= 200; ++N) {
+    const int M = 21;
+    std::vector<int> seen(M * N, 0);
+    for (int n0 = 0; n0 < N; n0 += 64)
+      for (int m = 0; m < M; ++m)
+        for (int q = 0; q < 16; ++q) {
+          const FadeStripLane at = fade_strip_lane(off, N, n0, m, q);
+          if (at.left <= 0) continue;
+          if (at.vec && (at.left != 4 || at.idx % 4 != 0)) { printf("N=%d row %d lane %d: piece at %zu, %d left\\n", N, m, q, at.idx, at.left); return 1; }
+          if (N % 4 == 0 && !at.vec) { printf("N=%d: no pieces\\n", N); return 1; }
+          for (int i = 0; i < at.left; ++i) ++seen[at.idx - off + i];
+        }
+    for (int i = 0; i < M * N; ++i)
+      if (seen[i] != 1) { printf("N=%d: element %d covered %d times\\n", N, i, seen[i]); return 1; }
+  }
+  return 0;
+}
+"""
+
+
+def _run(text, tmp_path):
+    src, exe = tmp_path / "rule.cpp", tmp_path / "rule"
+    src.write_text(text)
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2604_07239_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+
+
+def test_strip_pieces_are_aligned_and_cover_the_matrix(tmp_path):
+    """The fused weight-gradient + Adam kernel: a lane that takes its four columns as one 16-byte piece does so on 16-byte
+    boundaries, and the lanes of a matrix cover every element exactly once."""
+    _run(STRIP, tmp_path)
+
+
+STREAMED = """
+#include <stdio.h>
+#include "fade_rules.h"
+static size_t params(size_t B, size_t T, size_t D, size_t H) {  // the matrices
+  const size_t Dh = T * D;
+  return B * 4096 + 4 * H * Dh + 2 * Dh * Dh + 2 * 64 * Dh + 256 * Dh + 256 * D;
+}
+static int wrong = 0;
+static void want(bool streamed, bool bf16, bool online, size_t B, size_t T, size_t D, size_t H) {
+  if (fade_streamed(bf16, online, params(B, T, D, H), B, T * D) == streamed) return;
+  printf("%s %s B=%zu T=%zu D=%zu H=%zu\\n", bf16 ? "bf16" : "fp32", online ? "adapting" : "frozen", B, T, D, H);
+  ++wrong;
+}
+int main() {
+  // either side of the line as measured, and far from it
+  want(false, true, true, 16, 64, 32, 128);
+  want(false, true, true, 128, 64, 32, 128);
+  want(false, true, true, 16, 64, 32, 256);
+  want(true, true, true, 256, 64, 32, 128);
+  want(true, true, true, 16, 64, 32, 512);
+  want(false, true, true, 128, 16, 32, 512);
+  want(false, true, true, 1024, 16, 32, 512);
+  want(true, true, true, 2048, 16, 32, 512);
+  want(true, true, true, 1024, 64, 32, 256);
+  want(true, true, true, 16384, 64, 32, 512);
+  want(false, true, false, 8192, 16, 32, 256);
+  want(true, true, false, 16384, 16, 32, 256);
+  // fp32 never, however large
+  want(false, false, true, 300, 64, 32, 512);
+  want(false, false, true, 16384, 32, 16, 128);
+  want(false, false, false, 16384, 64, 32, 512);
+  return wrong != 0;
+}
+"""
+
+
+def test_which_sizes_go_past_the_caches(tmp_path):
+    _run(STREAMED, tmp_path)

@@ -87,7 +87,9 @@ enum {
 size_t fade_weights_nbytes(const fade_config *cfg);
 
 /* Create a context: validates the configuration and allocates all device state (compute weights, rolling
- * caches M [B][D_cache], per-stream memories W_U, activations, coder state; optimiser state in online mode).
+ * caches M [B][D_cache], per-stream memories W_U, activations, coder state; in online mode the optimiser state, and a copy of
+ * the weights as loaded, which a reset restores from: five fp32 arrays of the blob's size in all, 16 KiB of each per stream for
+ * W_U. On a card that has no room for that copy it lies in host memory, and a reset takes the upload).
  * Supported shapes: D % 32 == 0 (FADE_BF16) or D % 16 == 0 (FADE_F32), (T*D) % 128 == 0, D_cache % 64 == 0 and
  * D_cache <= 4096, D_e % 64 == 0 and D_e <= 8192, d_low == 64, conv_k <= 4, D_cache % cache_chunk == 0,
  * cache_chunk <= 256; with FADE_ONLINE_ADAM also T*D <= 2048, D <= 32, T a divisor of 128 and D a divisor of 256;

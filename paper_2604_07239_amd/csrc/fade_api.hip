@@ -6,6 +6,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <string>
 #include <vector>
@@ -119,7 +120,10 @@ struct fade_ctx {
   size_t stage_cap[3] = {0, 0, 0};
 
   bool have_weights = false;
-  float *loaded = nullptr;    // adapting weights: the masters as loaded, on the device (frozen contexts never change theirs)
+  // adapting weights: the masters as loaded (frozen contexts never change theirs), on the device, or, once the card was too full
+  // for that (restore_from_host), in host memory
+  float *loaded = nullptr;
+  std::unique_ptr<float[]> loaded_host;
   uint64_t weights_hash = 0;
 
   // parameters
@@ -188,6 +192,7 @@ struct fade_ctx {
   bool rows16 = false;               // fp32 path at very small batches: 16 x 16 product tiles, row statistics per 16 columns
   size_t stats_n = 0;                // partial (sum, sum of squares) pairs per row the statistics buffers hold
   bool streamed = false;             // bf16 path: weights and optimiser state go past the caches (fade_streamed)
+  bool host_restore = false;         // FADE_RESTORE_FROM_HOST=1 at fade_create: as on a card too full for the device copy of the masters
   bool debug_wu_grad = false;        // FADE_DEBUG_WU_GRAD=1 at fade_create: gradients consumed where they are formed (W_U's, the sums of sliced weight gradients) are also written to the gradient array
   size_t loop_n = 0, loop_next = 0;  // job size and next step of the device-resident loop in progress
   int loop_mode = 0;
@@ -220,9 +225,34 @@ int hip_fail(fade_ctx *c, hipError_t e, const char *what) {
     if (e_ != hipSuccess) return hip_fail(ctx, e_, #call); \
   } while (0)
 
+// Moves the masters as loaded from the device to host memory: a reset then uploads them, which takes longer (12 ms instead of
+// 0.2 for 320 MB). False: they were not on the device.
+bool restore_from_host(fade_ctx *c) {
+  if (!c->loaded) return false;
+  const size_t np = c->lay.off[P_COUNT];
+  if (c->have_weights) {
+    c->loaded_host.reset(new (std::nothrow) float[np]);
+    if (!c->loaded_host || hipMemcpyAsync(c->loaded_host.get(), c->loaded, np * sizeof(float), hipMemcpyDeviceToHost, c->stream) != hipSuccess) return false;
+  }
+  if (hipStreamSynchronize(c->stream) != hipSuccess) return false;
+  (void)hipFree(c->loaded);
+  c->loaded = nullptr;
+  return true;
+}
+// Device memory for the context. The copy of the masters is the one allocation it can do without: given up for one that does not fit.
+hipError_t ctx_malloc(fade_ctx *c, void **p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e != hipErrorOutOfMemory) return e;
+  (void)hipGetLastError();  // not the next launch's error
+  if (!restore_from_host(c)) return e;
+  e = hipMalloc(p, bytes);
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e;
+}
+
 template <typename T> int dev_alloc(fade_ctx *c, T **p, size_t count) {
   void *q = nullptr;
-  hipError_t e = hipMalloc(&q, (count ? count : 1) * sizeof(T));
+  hipError_t e = ctx_malloc(c, &q, (count ? count : 1) * sizeof(T));
   if (e != hipSuccess) return hip_fail(c, e, "hipMalloc");
   c->allocs.push_back(q);
   *p = static_cast<T *>(q);
@@ -252,7 +282,7 @@ int stage_buf(fade_ctx *c, int slot, size_t bytes, void **p) {
       (void)hipFree(c->stage[slot]);
       c->stage[slot] = nullptr; c->stage_cap[slot] = 0;
     }
-    hipError_t e = hipMalloc(&c->stage[slot], bytes);
+    hipError_t e = ctx_malloc(c, &c->stage[slot], bytes);
     if (e != hipSuccess) { c->stage[slot] = nullptr; return hip_fail(c, e, "hipMalloc(staging)"); }
     c->stage_cap[slot] = bytes;
   }
@@ -382,7 +412,9 @@ int do_reset(fade_ctx *c) {
   // 320 MB at B = 16384, 0.2 ms with the copies rebuilt (uploading them from pageable host memory took 12 ms per reset, and
   // every job and every direction of it starts with one).
   if (c->have_weights && c->online) {
-    HIP_TRY(c, hipMemcpyAsync(c->master, c->loaded, c->lay.off[P_COUNT] * sizeof(float), hipMemcpyDeviceToDevice, s));
+    const size_t bytes = c->lay.off[P_COUNT] * sizeof(float);
+    if (c->loaded) HIP_TRY(c, hipMemcpyAsync(c->master, c->loaded, bytes, hipMemcpyDeviceToDevice, s));
+    else HIP_TRY(c, hipMemcpyAsync(c->master, c->loaded_host.get(), bytes, hipMemcpyHostToDevice, s));
     int rc = prepare_compute(c);
     if (rc) return rc;
   }
@@ -1339,6 +1371,7 @@ void fade_destroy(fade_ctx *c) {
   for (auto &ev : c->events) { (void)hipEventDestroy(ev.a); (void)hipEventDestroy(ev.b); }
   for (void *p : c->allocs) (void)hipFree(p);
   for (void *p : c->stage) if (p) (void)hipFree(p);
+  if (c->loaded) (void)hipFree(c->loaded);
   if (c->dev_err) (void)hipHostFree(c->dev_err);
   if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
   delete c;
@@ -1370,6 +1403,7 @@ int fade_create(const fade_config *cfg, fade_ctx **out) {
   c->bf16 = cfg->dtype == FADE_BF16;
   c->online = cfg->update_mode == FADE_ONLINE_ADAM;
   c->esz = c->bf16 ? 2 : 4;
+  if (const char *e = getenv("FADE_RESTORE_FROM_HOST")) c->host_restore = e[0] == '1';
   if (const char *e = getenv("FADE_DEBUG_WU_GRAD")) c->debug_wu_grad = e[0] == '1';
   if (cfg->hip_stream) c->stream = static_cast<hipStream_t>(cfg->hip_stream);
   else {
@@ -1473,7 +1507,6 @@ int fade_create(const fade_config *cfg, fade_ctx **out) {
     TRY_ALLOC(dev_alloc(c, &c->GV, d.B * d.c));
     TRY_ALLOC(dev_alloc(c, &c->probs_buf, d.B * 256));
     if (!c->bf16) TRY_ALLOC(A(&c->Hout, BDh));
-    TRY_ALLOC(dev_alloc(c, &c->loaded, np));
     TRY_ALLOC(dev_alloc(c, &c->grad, np));
     TRY_ALLOC(dev_alloc(c, &c->adam_m, np));
     TRY_ALLOC(dev_alloc(c, &c->adam_v, np));
@@ -1619,6 +1652,10 @@ int fade_create(const fade_config *cfg, fade_ctx **out) {
   *c->dev_err = 0;
   c->cb.err = c->dev_err;
 #undef TRY_ALLOC
+  if (c->online && hipMalloc(reinterpret_cast<void **>(&c->loaded), np * sizeof(float)) != hipSuccess) {  // last: nothing gives way to it
+    (void)hipGetLastError();
+    c->loaded = nullptr;
+  }
   if (hipMemsetAsync(c->ones, 1, d.B, c->stream) != hipSuccess ||
       hipMemsetAsync(c->M, 0, d.B * d.Dc * c->esz, c->stream) != hipSuccess || hipStreamSynchronize(c->stream) != hipSuccess) {
     fade_destroy(c);
@@ -1644,10 +1681,18 @@ int fade_load_weights(fade_ctx *c, const void *blob_host, size_t nbytes) {
   const hipError_t e = hipStreamSynchronize(c->stream);  // the caller's memory is free again, whatever happens next
   if (rc) return rc;
   if (e != hipSuccess) return hip_fail(c, e, "weight upload");
-  if (c->online) HIP_TRY(c, hipMemcpyAsync(c->loaded, c->master, c->lay.off[P_COUNT] * sizeof(float), hipMemcpyDeviceToDevice, c->stream));
-  else if ((rc = prepare_compute(c))) return rc;
+  if (c->loaded) {
+    HIP_TRY(c, hipMemcpyAsync(c->loaded, c->master, c->lay.off[P_COUNT] * sizeof(float), hipMemcpyDeviceToDevice, c->stream));
+  } else if (c->online) {
+    c->loaded_host.reset(new (std::nothrow) float[c->lay.off[P_COUNT]]());
+    if (!c->loaded_host) return fail(c, FADE_E_OOM, "host copy of the weights");
+    for (int t = 0; t < P_COUNT; ++t) std::memcpy(c->loaded_host.get() + c->lay.off[t], f + c->blob.off[t], c->blob.len[t] * sizeof(float));
+  } else if ((rc = prepare_compute(c))) {
+    return rc;
+  }
   c->weights_hash = fnv1a64(blob_host, nbytes);
   c->have_weights = true;
+  if (c->host_restore) (void)restore_from_host(c);
   if ((rc = do_reset(c))) return rc;
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   return FADE_OK;

@@ -785,17 +785,21 @@ __global__ __launch_bounds__(256, (STAGES == 2 && BM * BN <= 128 * 128) ? 2 : 1)
 // DMA = 8 rows). With A in stages of 32 too, each request was half a line and the other half crossed the fabric again an
 // iteration later: in us, M = 16384, K = N = 2048 plain 124.5 -> 120.8 (1.14 PFLOP/s; a plain library product of that shape
 // 115.7), with the gate epilogue 160.7 -> 154.3, K = 2048, N = 1024 82.2 -> 79.5; M = 4096, N = 16384, K = 512 136.7 -> 124.7.
-// The same rings with 128 x 128 tiles and two workgroups per unit lose to 64 x 128 at M = 4096, N = 512 (33 against 40). So that every iteration still requests the same amount, the two iterations of a unit request the upper and
-// the lower half of the rows of the unit two further on. W: ready-made 1 KiB fragments.
+// So that every iteration still requests the same amount, the two iterations of a unit request the upper and the lower half of
+// the rows of the unit two further on. W: ready-made 1 KiB fragments.
+// One shape: 256 x 256 on eight wavefronts, whole tiles, the contraction in one range, 160 KiB of LDS. (The same rings with 128 x 128
+// tiles and two workgroups per unit lost to 64 x 128 at M = 4096, N = 512: 40 us against 33.)
 // The W slot that iteration h refills is the one stage h-1 lived in, the A slot the one of the unit before h's: their last
 // fragment read was waited for before MFMA (h-1, 1) was issued, which every wavefront has done when it arrives at iteration
 // h's barrier. Group h = {W of stage h, A half h+1} is requested together; stage h needs groups up to h.
 // Every output element sees the same sequence of k-steps as in pipe_body, so both give the same bits.
 // ---------------------------------------------------------------------------------------------------
-template <int BM, int BN, int EPI, int NW = 4>
-__device__ __forceinline__ void pipe2_body(const GemmArgs &g, int bid, int split, int nsplit) {
+constexpr int PIPE2_LDS = 160 * 1024;
+template <int EPI>
+__device__ __forceinline__ void pipe2_body(const GemmArgs &g, int bid) {
   typedef bf16_t AT;
-  constexpr int BK = 32, KS = 2, WSTAGES = 4, AUNITS = 3;
+  static_assert(EPI != EPI_PARTIAL, "one range of K");
+  constexpr int BM = 256, BN = 256, NW = 8, BK = 32, KS = 2, WSTAGES = 4, AUNITS = 3;
   constexpr int WN = NW / 2;                         // wavefronts 2 (rows) x WN (columns)
   constexpr int TM = BM / 64, TN = BN / (32 * WN);   // 32x32 tiles per wavefront
   constexpr int BFR = BN / 32;
@@ -803,18 +807,17 @@ __device__ __forceinline__ void pipe2_body(const GemmArgs &g, int bid, int split
   constexpr int ACH = BM / 16 / NW;                  // A DMAs per wavefront and half unit (BM / 2 rows; one DMA = 8 rows x 128 bytes)
   constexpr int BCH = BFR * KS / NW;                 // W DMAs per wavefront and stage (one fragment each)
   constexpr int LPW = ACH + BCH, LDC = BN + 4;
-  constexpr bool SLAB = BM > 128;                    // the fp32 tile leaves through LDS in slabs of 64 rows
-  static_assert((BM / 16) % NW == 0 && (BFR * KS) % NW == 0 && 2 * LPW <= 63, "chunk split; vmcnt range");
+  static_assert(A_RING + WSTAGES * W_STAGE == PIPE2_LDS && 64 * LDC * 4 <= PIPE2_LDS, "LDS");
   extern __shared__ __align__(16) unsigned char smem[];
   float *Cs = reinterpret_cast<float *>(smem);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
-  const int ntn = g.N / BN, ntm = (g.M + BM - 1) / BM;
+  const int ntn = g.N / BN, ntm = g.M / BM;
   int mt, nt;
   if (!tile_of_block(bid, ntm, ntn, g.col_groups, mt, nt)) return;
   const int m0 = mt * BM, n0 = nt * BN;
-  const int ksplit = g.K / nsplit, nkh = ksplit / BK;  // stages; even (K per range is a multiple of 64)
+  const int nkh = g.K / BK;  // stages; even (K is a multiple of 64)
   const int ksteps = g.K / 16;
 
   const bf16_t *asrc[2][ACH], *wsrc[BCH];
@@ -823,9 +826,7 @@ __device__ __forceinline__ void pipe2_body(const GemmArgs &g, int bid, int split
 #pragma unroll
     for (int q = 0; q < ACH; ++q) {
       const int r = hf * (BM / 2) + (wave + NW * q) * 8 + (lane >> 3);
-      int row = m0 + r;
-      row = row < g.M ? row : g.M - 1;
-      asrc[hf][q] = static_cast<const bf16_t *>(g.A) + (size_t)row * g.lda + (((lane & 7) ^ ((r >> 1) & 7)) << 3);
+      asrc[hf][q] = static_cast<const bf16_t *>(g.A) + (size_t)(m0 + r) * g.lda + (((lane & 7) ^ ((r >> 1) & 7)) << 3);
     }
 #pragma unroll
   for (int q = 0; q < BCH; ++q) {
@@ -853,178 +854,137 @@ __device__ __forceinline__ void pipe2_body(const GemmArgs &g, int bid, int split
   for (int ks = 0; ks < 2 * KS; ++ks) a_base[ks] = lds0 + (wm * TM * 32 + (lane & 31)) * 128 + (((2 * ks + a_half) ^ a_sw) << 4);
   const uint32_t b_base = lds0 + A_RING + (((wn * TN * KS) * 64 + lane) << 4);
 
-  const bool fuse = EPI == EPI_PARTIAL && g.sum_splits != 0;
-  const int sp_first = fuse ? 0 : split, sp_end = fuse ? nsplit : split + 1;
-  f32x16 acc[TM][TN], tot[EPI == EPI_PARTIAL ? TM : 1][EPI == EPI_PARTIAL ? TN : 1];
-  for (int sp = sp_first; sp < sp_end; ++sp) {
-    const int kh0 = sp * nkh;
+  f32x16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+  typedef std::integral_constant<int, 0> I0;
+  typedef std::integral_constant<int, 1> I1;
+  typedef std::integral_constant<int, TM + TN> INext;
+  // groups 0 (with A half 0), 1, 2
+  issue_a(0, 0, I0{});
+  issue_a(0, 0, I1{});
+  issue_w(0, 0);
+  issue_w(1, 1);
+  if (nkh > 2) {
+    issue_a(1, 1, I0{});
+    issue_w(2, 2);
+    issue_a(1, 1, I1{});
+  }
+
+  bf16x8 af[2][TM], bf[2][TN];
+  auto fetch = [&](auto buf_c, int aslot, int wslot, auto ks_c) {  // ks: k-step of the A unit; TM + TN reads, left in flight
+    constexpr int buf = decltype(buf_c)::value, ks = decltype(ks_c)::value, wk = ks % KS;
+    const uint32_t sa = a_base[ks] + aslot * A_UNIT, sb = b_base + wslot * W_STAGE;
+    static_assert(TM <= 4 && TN <= 4, "tiles per wavefront");
+    af[buf][0] = lds_read16<0>(sa);
+    if constexpr (TM > 1) af[buf][1] = lds_read16<4096>(sa);
+    if constexpr (TM > 2) af[buf][2] = lds_read16<8192>(sa);
+    if constexpr (TM > 3) af[buf][3] = lds_read16<12288>(sa);
+    bf[buf][0] = lds_read16<wk * 1024>(sb);
+    if constexpr (TN > 1) bf[buf][1] = lds_read16<wk * 1024 + 2048>(sb);
+    if constexpr (TN > 2) bf[buf][2] = lds_read16<wk * 1024 + 4096>(sb);
+    if constexpr (TN > 3) bf[buf][3] = lds_read16<wk * 1024 + 6144>(sb);
+  };
+  auto mfma = [&](auto buf_c, auto newer_c) {  // newer: reads issued after this buffer's, allowed to stay in flight
+    constexpr int buf = decltype(buf_c)::value;
+    lds_wait<decltype(newer_c)::value>();
+#pragma unroll
+    for (int i = 0; i < TM; ++i) lds_landed(af[buf][i]);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) lds_landed(bf[buf][j]);
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-    if (sp != sp_first) bare_barrier();  // every wavefront has read the last stages of the previous range
-    typedef std::integral_constant<int, 0> I0;
-    typedef std::integral_constant<int, 1> I1;
-    typedef std::integral_constant<int, TM + TN> INext;
-    // groups 0 (with A half 0), 1, 2
-    const int ku0 = kh0 / 2;
-    issue_a(0, ku0, I0{});
-    issue_a(0, ku0, I1{});
-    issue_w(0, kh0);
-    issue_w(1, kh0 + 1);
-    if (nkh > 2) {
-      issue_a(1, ku0 + 1, I0{});
-      issue_w(2, kh0 + 2);
-      issue_a(1, ku0 + 1, I1{});
-    }
-
-    bf16x8 af[2][TM], bf[2][TN];
-    auto fetch = [&](auto buf_c, int aslot, int wslot, auto ks_c) {  // ks: k-step of the A unit; TM + TN reads, left in flight
-      constexpr int buf = decltype(buf_c)::value, ks = decltype(ks_c)::value, wk = ks % KS;
-      const uint32_t sa = a_base[ks] + aslot * A_UNIT, sb = b_base + wslot * W_STAGE;
-      static_assert(TM <= 4 && TN <= 4, "tiles per wavefront");
-      af[buf][0] = lds_read16<0>(sa);
-      if constexpr (TM > 1) af[buf][1] = lds_read16<4096>(sa);
-      if constexpr (TM > 2) af[buf][2] = lds_read16<8192>(sa);
-      if constexpr (TM > 3) af[buf][3] = lds_read16<12288>(sa);
-      bf[buf][0] = lds_read16<wk * 1024>(sb);
-      if constexpr (TN > 1) bf[buf][1] = lds_read16<wk * 1024 + 2048>(sb);
-      if constexpr (TN > 2) bf[buf][2] = lds_read16<wk * 1024 + 4096>(sb);
-      if constexpr (TN > 3) bf[buf][3] = lds_read16<wk * 1024 + 6144>(sb);
-    };
-    auto mfma = [&](auto buf_c, auto newer_c) {  // newer: reads issued after this buffer's, allowed to stay in flight
-      constexpr int buf = decltype(buf_c)::value;
-      lds_wait<decltype(newer_c)::value>();
-#pragma unroll
-      for (int i = 0; i < TM; ++i) lds_landed(af[buf][i]);
-#pragma unroll
-      for (int j = 0; j < TN; ++j) lds_landed(bf[buf][j]);
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[buf][i], bf[buf][j], acc[i][j], 0, 0, 0);
-    };
-    // group 0 has landed once at most groups 1 and 2 are in flight
-    if (nkh > 2) wait_vmcnt<2 * LPW>();
-    else wait_vmcnt<0>();
-    bare_barrier();
-    fetch(I0{}, 0, 0, I0{});
-    int aslot = 0, afill = 2;  // A slot of the unit being worked on; A slot the unit two further on goes to
-    auto next_a = [&](int s) { return s + 1 == AUNITS ? 0 : s + 1; };
-    // One iteration: the two k-steps of stage h around the hand-over to stage h + 1. odd: second stage of its unit.
-    // mode 2: group h + 3 is requested; 1: its W alone (past the last unit); 0: the rings only drain.
-    auto step = [&](int h, auto odd_c, auto mode_c) {
-      constexpr int odd = decltype(odd_c)::value, mode = decltype(mode_c)::value;
-      fetch(I1{}, aslot, h % WSTAGES, std::integral_constant<int, 2 * odd + 1>{});
-      mfma(I0{}, INext{});
-      if constexpr (mode != 0) wait_vmcnt<LPW>();  // group h + 1 has landed: only group h + 2 may be in flight
-      else wait_vmcnt<0>();
-      bare_barrier();  // stage h+1 is in LDS for everyone, and everyone is done reading stage h-1
-      if constexpr (mode != 0) issue_w((h + 3) % WSTAGES, kh0 + h + 3);
-      if constexpr (mode == 2) issue_a(afill, ku0 + h / 2 + 2, odd_c);
-      if constexpr (odd != 0) {
-        aslot = next_a(aslot);
-        afill = next_a(afill);
-      }
-      fetch(I0{}, aslot, (h + 1) % WSTAGES, std::integral_constant<int, odd ? 0 : 2>{});
-      mfma(I1{}, INext{});
-    };
-    int h = 0;
-    for (; h + 5 < nkh; h += 2) {
-      step(h, I0{}, std::integral_constant<int, 2>{});
-      step(h + 1, I1{}, std::integral_constant<int, 2>{});
-    }
-    if (nkh > 2) {
-      step(h, I0{}, I1{});
-      step(h + 1, I1{}, I0{});
-      h += 2;
-    }
-    step(h, I0{}, I0{});
-    fetch(I1{}, aslot, (h + 1) % WSTAGES, std::integral_constant<int, 3>{});  // last stage: nothing follows
+      for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[buf][i], bf[buf][j], acc[i][j], 0, 0, 0);
+  };
+  // group 0 has landed once at most groups 1 and 2 are in flight
+  if (nkh > 2) wait_vmcnt<2 * LPW>();
+  else wait_vmcnt<0>();
+  bare_barrier();
+  fetch(I0{}, 0, 0, I0{});
+  int aslot = 0, afill = 2;  // A slot of the unit being worked on; A slot the unit two further on goes to
+  auto next_a = [&](int s) { return s + 1 == AUNITS ? 0 : s + 1; };
+  // One iteration: the two k-steps of stage h around the hand-over to stage h + 1. odd: second stage of its unit.
+  // mode 2: group h + 3 is requested; 1: its W alone (past the last unit); 0: the rings only drain.
+  auto step = [&](int h, auto odd_c, auto mode_c) {
+    constexpr int odd = decltype(odd_c)::value, mode = decltype(mode_c)::value;
+    fetch(I1{}, aslot, h % WSTAGES, std::integral_constant<int, 2 * odd + 1>{});
     mfma(I0{}, INext{});
-    mfma(I1{}, I0{});
-    if constexpr (EPI == EPI_PARTIAL) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          if (sp == sp_first) tot[i][j] = acc[i][j];
-          else tot[i][j] += acc[i][j];
-        }
+    if constexpr (mode != 0) wait_vmcnt<LPW>();  // group h + 1 has landed: only group h + 2 may be in flight
+    else wait_vmcnt<0>();
+    bare_barrier();  // stage h+1 is in LDS for everyone, and everyone is done reading stage h-1
+    if constexpr (mode != 0) issue_w((h + 3) % WSTAGES, h + 3);
+    if constexpr (mode == 2) issue_a(afill, h / 2 + 2, odd_c);
+    if constexpr (odd != 0) {
+      aslot = next_a(aslot);
+      afill = next_a(afill);
     }
+    fetch(I0{}, aslot, (h + 1) % WSTAGES, std::integral_constant<int, odd ? 0 : 2>{});
+    mfma(I1{}, INext{});
+  };
+  int h = 0;
+  for (; h + 5 < nkh; h += 2) {
+    step(h, I0{}, std::integral_constant<int, 2>{});
+    step(h + 1, I1{}, std::integral_constant<int, 2>{});
   }
-
+  if (nkh > 2) {
+    step(h, I0{}, I1{});
+    step(h + 1, I1{}, I0{});
+    h += 2;
+  }
+  step(h, I0{}, I0{});
+  fetch(I1{}, aslot, (h + 1) % WSTAGES, std::integral_constant<int, 3>{});  // last stage: nothing follows
+  mfma(I0{}, INext{});
+  mfma(I1{}, I0{});
   wait_vmcnt<0>();
-  if constexpr (SLAB) {
-    // The fp32 tile does not fit LDS at once: it leaves in slabs of 64 rows, each handed to the epilogue as 128-column
-    // pieces (the width the row statistics are kept at), so every output is formed exactly as by the smaller tiles.
-    // (a GeGLU tile is gate | value per 128 columns, so each 128-column piece is a complete pair)
-    static_assert(EPI != EPI_PARTIAL && TM % 2 == 0 && BN % 128 == 0, "slab epilogue");
-    constexpr int NT = NW * 64, SP = 64 / (NT / 16);     // passes of a thread over a 64-row, 128-column slab piece
-    // With one workgroup on the unit (eight wavefronts) the side inputs of slab p + 1 are requested before slab p is worked
-    // on; with two workgroups per unit the other one's matrix work covers that latency and the registers are not spent.
-    constexpr bool PRE = NW == 8 && EpiSides<EPI>::n != 0;
-    Raw8<AT> sd[PRE ? 2 : 1][BN / 128][SP][2];
-    auto side = [&](int buf, int p) {
-      if constexpr (PRE) {
-#pragma unroll
-        for (int h = 0; h < BN / 128; ++h)
-#pragma unroll
-          for (int u = 0; u < SP; ++u) {
-            int m = m0 + p * 64 + u * (NT / 16) + tid / 16;
-            m = m < g.M ? m : g.M - 1;  // past the last row: any row (the epilogue drops it); no branch around the loads
-            epi_side_load<EPI, AT>(g, (size_t)m * g.ldc + n0 + h * 128 + (tid % 16) * 8, true, sd[buf][h][u]);
-          }
-      }
-    };
-    side(0, 0);
-#pragma unroll
-    for (int p = 0; p < BM / 64; ++p) {
-      constexpr int ROWS_PER_WAVE = 32 * TM;
-      const int owner = (p * 64) / ROWS_PER_WAVE, i0 = ((p * 64) % ROWS_PER_WAVE) / 32;
-      if (p + 1 < BM / 64) side((p + 1) & 1, p + 1);
-      __syncthreads();  // the ring, or the previous slab, is no longer being read
-      if (wm == owner) {
-#pragma unroll
-        for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-              const int row = ii * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
-              const int col = (wn * TN + j) * 32 + (lane & 31);
-              Cs[row * LDC + col] = acc[i0 + ii][j][e];
-            }
-      }
-      __syncthreads();
+  // The fp32 tile does not fit LDS at once: it leaves in slabs of 64 rows, each handed to the epilogue as 128-column
+  // pieces (the width the row statistics are kept at), so every output is formed exactly as by the smaller tiles.
+  // (a GeGLU tile is gate | value per 128 columns, so each 128-column piece is a complete pair)
+  constexpr int NT = NW * 64, SP = 64 / (NT / 16);     // passes of a thread over a 64-row, 128-column slab piece
+  // the side inputs of slab p + 1 are requested before slab p is worked on: no other workgroup is on the unit to cover them
+  constexpr bool PRE = EpiSides<EPI>::n != 0;
+  Raw8<AT> sd[PRE ? 2 : 1][BN / 128][SP][2];
+  auto side = [&](int buf, int p) {
+    if constexpr (PRE) {
 #pragma unroll
       for (int h = 0; h < BN / 128; ++h)
-        epilogue<EPI, AT, 64, 128, LDC, NT, PRE, NW == 8>(g, Cs + h * 128, m0 + p * 64, n0 + h * 128, nt * (BN / 128) + h, tid, 0, sd[PRE ? (p & 1) : 0][h]);
-    }
-  } else {
-    __syncthreads();
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int row = (wm * TM + i) * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
-          const int col = (wn * TN + j) * 32 + (lane & 31);
-          if constexpr (EPI == EPI_PARTIAL) Cs[row * LDC + col] = tot[i][j][e];
-          else Cs[row * LDC + col] = acc[i][j][e];
+        for (int u = 0; u < SP; ++u) {
+          const int m = m0 + p * 64 + u * (NT / 16) + tid / 16;
+          epi_side_load<EPI, AT>(g, (size_t)m * g.ldc + n0 + h * 128 + (tid % 16) * 8, true, sd[buf][h][u]);
         }
+    }
+  };
+  side(0, 0);
+#pragma unroll
+  for (int p = 0; p < BM / 64; ++p) {
+    constexpr int ROWS_PER_WAVE = 32 * TM;
+    const int owner = (p * 64) / ROWS_PER_WAVE, i0 = ((p * 64) % ROWS_PER_WAVE) / 32;
+    if (p + 1 < BM / 64) side((p + 1) & 1, p + 1);
+    __syncthreads();  // the ring, or the previous slab, is no longer being read
+    if (wm == owner) {
+#pragma unroll
+      for (int ii = 0; ii < 2; ++ii)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            const int row = ii * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
+            const int col = (wn * TN + j) * 32 + (lane & 31);
+            Cs[row * LDC + col] = acc[i0 + ii][j][e];
+          }
+    }
     __syncthreads();
-    epilogue<EPI, AT, BM, BN>(g, Cs, m0, n0, nt, tid, fuse ? 0 : split);
+#pragma unroll
+    for (int h = 0; h < BN / 128; ++h)
+      epilogue<EPI, AT, 64, 128, LDC, NT, PRE, true>(g, Cs + h * 128, m0 + p * 64, n0 + h * 128, nt * (BN / 128) + h, tid, 0, sd[PRE ? (p & 1) : 0][h]);
   }
 }
-// WPU: workgroups the launch bounds leave room for on one compute unit
-template <int BM, int BN, int EPI, int NW, int WPU>
-__global__ __launch_bounds__(NW * 64, WPU) void gemm_pipe2_kernel(GemmArgs g) {
-  pipe2_body<BM, BN, EPI, NW>(g, (int)blockIdx.x, (int)blockIdx.y, g.sum_splits ? g.splits : (int)gridDim.y);
-}
+template <int EPI> __global__ __launch_bounds__(512, 1) void gemm_pipe2_kernel(GemmArgs g) { pipe2_body<EPI>(g, (int)blockIdx.x); }
 
 // ---------------------------------------------------------------------------------------------------
 // Weight gradients from ROW-MAJOR operands: C[M][N] = sum over rows b < K of A[b][m] * W[b][n]  (dW = L^T R over the batch;
@@ -1486,30 +1446,22 @@ hipError_t fade_gemm_tn2_group_launch(const Tn2Group &tg, hipStream_t s) {
 }
 namespace {
 
-template <int BM, int BN, int EPI, int NW, int WPU>
+template <int EPI>
 hipError_t launch_pipe2(const GemmArgs &g, hipStream_t s) {
-  constexpr size_t lds_ring = (size_t)3 * BM * 128 + (size_t)4 * (BN / 32) * 2 * 1024;
-  constexpr size_t lds_c = BM > 128 ? (size_t)64 * (BN + 4) * sizeof(float) : (size_t)BM * (BN + 4) * sizeof(float);
-  constexpr size_t lds = lds_ring > lds_c ? lds_ring : lds_c;
-  static_assert(lds * WPU <= 160 * 1024, "LDS per compute unit");
   static bool attr_done = false;
-  auto kern = gemm_pipe2_kernel<BM, BN, EPI, NW, WPU>;
+  auto kern = gemm_pipe2_kernel<EPI>;
   if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, PIPE2_LDS);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
-  const int splits = g.splits > 1 ? g.splits : 1;
-  if (g.N % BN || g.M <= 0 || g.K <= 0 || g.K % (splits * 64) || (EPI != EPI_PARTIAL && splits != 1) || g.lda % 8) return hipErrorInvalidValue;
-  if (g.sum_splits && EPI != EPI_PARTIAL) return hipErrorInvalidValue;
-  if (BM > 128 && NW == 8 && g.M % BM) return hipErrorInvalidValue;  // the slab epilogue of the eight-wavefront tile assumes whole tiles
+  if (g.M <= 0 || g.N <= 0 || g.K <= 0 || g.M % 256 || g.N % 256 || g.K % 64 || g.splits > 1 || g.sum_splits || g.lda % 8) return hipErrorInvalidValue;
   GemmArgs ga = g;
-  const int ntm = (g.M + BM - 1) / BM, ntn = g.N / BN;
-  if (ga.col_groups == 0) ga.col_groups = fade_gemm_col_groups(g.M, g.K, g.N, BN >= 256 ? (size_t)4 << 20 : (size_t)2 << 20);
+  const int ntm = g.M / 256, ntn = g.N / 256;
+  if (ga.col_groups == 0) ga.col_groups = fade_gemm_col_groups(g.M, g.K, g.N, (size_t)4 << 20);
   if ((ga.col_groups != 1 && ga.col_groups != 2 && ga.col_groups != 4) || ntn % ga.col_groups) ga.col_groups = 8;
   const int rg = 8 / ga.col_groups;
-  const dim3 grid((ntn % ga.col_groups == 0 ? (ntm + rg - 1) / rg * rg : ntm) * ntn, ga.sum_splits ? 1 : splits);
-  hipLaunchKernelGGL(kern, grid, dim3(NW * 64), lds, s, ga);
+  hipLaunchKernelGGL(kern, dim3((ntn % ga.col_groups == 0 ? (ntm + rg - 1) / rg * rg : ntm) * ntn), dim3(512), PIPE2_LDS, s, ga);
   return hipGetLastError();
 }
 
@@ -1527,7 +1479,7 @@ hipError_t launch_pipe_auto(const GemmArgs &g, hipStream_t s) {
   const int tune = fade_gemm_tune();
   if constexpr (EPI != EPI_PARTIAL) {
     const int tiles256 = ((g.M + 255) / 256) * (g.N / 256);
-    if (g.N % 256 == 0 && g.M % 256 == 0 && (tune == 20 || (tune == 0 && tiles256 >= 256 && g.K >= 256))) return launch_pipe2<256, 256, EPI, 8, 1>(g, s);
+    if (g.N % 256 == 0 && g.M % 256 == 0 && (tune == 20 || (tune == 0 && tiles256 >= 256 && g.K >= 256))) return launch_pipe2<EPI>(g, s);
   }
   if (tune == 11 || (tune == 0 && tiles128 >= 512)) return launch_pipe<128, 128, 2, EPI>(g, s);
   if (tune == 10) return launch_pipe<256, 128, 3, EPI>(g, s);

@@ -1478,12 +1478,13 @@ int fade_create(const fade_config *cfg, fade_ctx **out) {
     c->Wc_c = c->master + c->lay.off[P_WC];
     c->Wf_c = c->master + c->lay.off[P_WF];
     c->Wo_c = c->master + c->lay.off[P_WO];
-    TRY_ALLOC(A(&c->Wconv_c, d.Kc * d.D));
-    TRY_ALLOC(A(&c->Wfgv_c, d.Dh * 2 * d.De));
-  }
-  if (c->rows16) {
-    TRY_ALLOC(dev_alloc(c, &c->gg_tab, 256 * d.c));
-    TRY_ALLOC(dev_alloc(c, &c->gv_tab, 256 * d.c));
+    if (c->rows16) {
+      TRY_ALLOC(dev_alloc(c, &c->gg_tab, 256 * d.c));
+      TRY_ALLOC(dev_alloc(c, &c->gv_tab, 256 * d.c));
+    } else {
+      TRY_ALLOC(A(&c->Wconv_c, d.Kc * d.D));
+      TRY_ALLOC(A(&c->Wfgv_c, d.Dh * 2 * d.De));
+    }
   }
   TRY_ALLOC(A(&c->tabXe, 256 * d.D));
   TRY_ALLOC(A(&c->tabXl, 256 * d.D));
@@ -1513,7 +1514,6 @@ int fade_create(const fade_config *cfg, fade_ctx **out) {
     TRY_ALLOC(dev_alloc(c, &c->ustate, 1));
     TRY_ALLOC(dev_alloc(c, &c->tabXhat, 256 * d.D));
     TRY_ALLOC(dev_alloc(c, &c->tabRstd, 256));
-    TRY_ALLOC(dev_alloc(c, &c->convt_f32, d.Kc * d.D));
     if (c->bf16) {
       TRY_ALLOC(A(&c->WT_o, d.Dh * 256));
       TRY_ALLOC(A(&c->WT_f, d.De * d.Dh));
@@ -1525,22 +1525,24 @@ int fade_create(const fade_config *cfg, fade_ctx **out) {
       TRY_ALLOC(A(&c->WT_conv, d.Kc * d.D));
       if (d.c % 64 == 0) TRY_ALLOC(A(&c->WT_mslot, d.Dh * d.c));
     }
-    if (d.c % 64 == 0) TRY_ALLOC(A(&c->dg_slot, Bp * d.c));
+    if (!c->rows16 && d.c % 64 == 0) TRY_ALLOC(A(&c->dg_slot, Bp * d.c));
     // gradients that serve as the right operand of a weight-gradient product have Bp rows (padding rows stay zero)
     struct { void **p; size_t n; } bufs[] = {
-        {&c->dl, Bp * 256}, {&c->dHout, BDh}, {&c->dV, BpDh}, {&c->dHc, BDh}, {&c->dHexp, d.B * d.De},
-        {&c->dE, Bp * 2 * d.De}, {&c->du, BDh}, {&c->dHa, BpDh}, {&c->dac, BpDh}, {&c->dHmix1, BDh}, {&c->dHmix2, BDh},
+        {&c->dl, Bp * 256}, {&c->dHout, BDh}, {&c->dV, BpDh}, {&c->dHc, BDh}, {&c->dE, Bp * 2 * d.De}, {&c->du, BDh}, {&c->dHa, BpDh}, {&c->dac, BpDh}, {&c->dHmix1, BDh}, {&c->dHmix2, BDh},
         {&c->dy_at, Bp * d.dl}, {&c->dnc, BDh}, {&c->dar, BpDh}, {&c->dhm, BpDh}, {&c->dcv, BDh}, {&c->dX1, BDh}, {&c->dX2, BDh},
         {&c->dxl, BDh},
-        {&c->LT[2], d.Dh * Bp}, {&c->LT[5], d.Dh * Bp}};
+        // the small-batch fp32 kernels need none of the rest
+        {&c->dHexp, c->rows16 ? 0 : d.B * d.De}, {&c->LT[2], c->rows16 ? 0 : d.Dh * Bp}, {&c->LT[5], c->rows16 ? 0 : d.Dh * Bp}};
     for (auto &b : bufs) {
+      if (b.n == 0) continue;
       TRY_ALLOC(A(b.p, b.n));
       if (hipMemsetAsync(*b.p, 0, b.n * c->esz, c->stream) != hipSuccess) { fade_destroy(c); return FADE_E_HIP; }
     }
     if (c->rows16) {
       TRY_ALLOC(dev_alloc(c, &c->mom, 3 * 2 * d.B));
       TRY_ALLOC(dev_alloc(c, &c->xt, d.B * d.D));
-    } else if (!c->bf16) {  // general fp32 path: feature-major copies [width][Bp] of the remaining left operands
+    } else if (!c->bf16) {  // general fp32 path: W_conv transposed, feature-major copies [width][Bp] of the remaining left operands
+      TRY_ALLOC(dev_alloc(c, &c->convt_f32, d.Kc * d.D));
       struct { void **p; size_t n; } lts[] = {{&c->LT[0], d.Dh * Bp}, {&c->LT[1], d.De * Bp}, {&c->LT[3], d.Dh * Bp}, {&c->LT[4], d.dl * Bp},
                                                {&c->LT[6], d.Dc * Bp}, {&c->LT[7], d.Dh * Bp}};
       for (auto &b : lts) TRY_ALLOC(A(b.p, b.n));
@@ -1635,7 +1637,7 @@ int fade_create(const fade_config *cfg, fade_ctx **out) {
     TRY_ALLOC(dev_alloc(c, &c->tok_part, 256 * 4 * d.D));
     TRY_ALLOC(dev_alloc(c, &c->ln_part, 3 * rb * 2 * d.Dh));
     TRY_ALLOC(dev_alloc(c, &c->col_part, (d.B + 7) / 8 * 256));
-    TRY_ALLOC(dev_alloc(c, &c->slot_part, (d.B + 3) / 4 * 2 * d.D * d.c));
+    if (!c->rows16) TRY_ALLOC(dev_alloc(c, &c->slot_part, (d.B + 3) / 4 * 2 * d.D * d.c));
     TRY_ALLOC(dev_alloc(c, &c->emb_part, (size_t)c->emb_blocks * 2 * 256 * d.D));
     if (hipMemsetAsync(c->grad, 0, np * sizeof(float), c->stream) != hipSuccess) { fade_destroy(c); return FADE_E_HIP; }
   }

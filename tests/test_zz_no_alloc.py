@@ -1,6 +1,6 @@
-"""The entry point that allocates nothing (fade_coder_encode_tables_noalloc: coder state in the library's own device array)
-against the allocating one it mirrors, through the C ABI: same tables and symbols in, byte-identical payloads and lengths
-out, on two calls in a row, the second smaller than the first (the shared array keeps the first call's contents)."""
+"""The entry point for callers that cannot allocate (fade_coder_encode_tables_noalloc): every stream's payload against the
+oracle's coder, on two calls in a row, the second smaller than the first, the same bytes from fade_coder_encode_tables (both keep
+the coder's state in registers and differ in the limit on the streams of a call), and that limit."""
 import numpy as np
 import pytest
 
@@ -43,14 +43,14 @@ def test_no_alloc_coder_matches_the_allocating_entry_point():
         assert len_a.min() > 0
         for k in range(n_streams):
             assert out_n[k, :len_n[k]].tobytes() == out_a[k, :len_a[k]].tobytes(), k
-        # and the oracle's coder writes the same bytes (the allocating entry point's own parity bar)
-        ref = orc.coder_encode(f[:, 0], sym[:, 0])
-        assert out_n[0, :len_n[0]].tobytes() == ref.tobytes()
+            ref = orc.coder_encode(f[:, k], sym[:, k])
+            assert len_n[k] == ref.size and out_n[k, :len_n[k]].tobytes() == ref.tobytes(), k
+            assert (out_n[k, len_n[k]:] == 0xA5).all(), k
         # decode what the no-alloc call wrote
         dec = torch.zeros((n_steps, n_streams), dtype=torch.uint8, device="cuda")
         g.coder_decode_tables(fd, n_steps, n_streams, torch.from_numpy(out_n).cuda(), cap, torch.from_numpy(len_n.astype(np.int32)).cuda(), dec)
         np.testing.assert_array_equal(dec.cpu().numpy(), sym)
-    with pytest.raises(fa.FadeError) as e:   # beyond the array's size: refused on the host, nothing launched
+    with pytest.raises(fa.FadeError) as e:   # beyond its limit: refused on the host, nothing launched
         g.coder_encode_tables_noalloc(fd, sd, 1, 65537, out, cap, ln)
     assert e.value.code == -1
     g.close()

@@ -189,7 +189,7 @@ struct fade_ctx {
   uint8_t *ones = nullptr;
   WinSrc last_ws{};
   int *dev_err = nullptr;            // error flag in host memory the kernels can write: read after a wait for the stream, without a copy
-  bool rows16 = false;               // fp32 path at very small batches: 16 x 16 product tiles, row statistics per 16 columns
+  bool rows16 = false;               // fp32 path at small batches: 16 x 16 product tiles, row statistics per 16 columns
   size_t stats_n = 0;                // partial (sum, sum of squares) pairs per row the statistics buffers hold
   bool streamed = false;             // bf16 path: weights and optimiser state go past the caches (fade_streamed)
   bool host_restore = false;         // FADE_RESTORE_FROM_HOST=1 at fade_create: as on a card too full for the device copy of the masters
@@ -730,7 +730,7 @@ int forward_bf16(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uin
   return FADE_OK;
 }
 
-// fp32 at small batches: eight launches (see fade_rows.hip). win_copy: where to keep the windows for a later update (step API).
+// fp32 at small batches: nine launches (see fade_rows.hip). win_copy: where to keep the windows for a later update (step API).
 RowsOp rows_op(const void *A, int lda, const float *W, int ldw, int K) { return RowsOp{static_cast<const float *>(A), nullptr, lda, W, nullptr, ldw, K}; }
 int forward_rows(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uint16_t *freq, float *probs, float *probs2, uint8_t *win_copy) {
   const Dims &d = c->d;
@@ -1421,7 +1421,9 @@ int fade_create(const fade_config *cfg, fade_ctx **out) {
   c->streamed = fade_streamed(c->bf16, c->online, np, d.B, d.Dh);
   if (const char *e = getenv("FADE_STREAMED")) c->streamed = c->bf16 && e[0] != '0';  // override for sweeps and tests
   // fp32 contexts of up to 256 streams use the small-batch kernels of fade_rows.hip (statistics per 16 columns); FADE_F32_ROWS16=0
-  // keeps the general ones
+  // keeps the general ones. Adapting step in us, small-batch against general: T = 32, D = 16, H = 128 with 16 / 64 / 128 / 256 streams
+  // 112 / 122 / 134 / 167 against 887 / 889 / 943 / 1046; T = 64, D = 32, H = 512 with 64 / 256 streams 310 / 692 against 3225 / 3497.
+  // The two do not cross below the line; above it the 16-row tiles have not been measured (the loss gradient's count ends at 512).
   c->rows16 = !c->bf16 && d.B <= 256 && d.Dh <= 2048 && d.Dc <= 2048 && d.De <= 2048 && d.Dh % 16 == 0 && d.Dc % 16 == 0 && d.De % 64 == 0 &&
               d.Kc % 16 == 0 && d.D % 16 == 0;
   if (const char *e = getenv("FADE_F32_ROWS16")) c->rows16 = c->rows16 && e[0] != '0';

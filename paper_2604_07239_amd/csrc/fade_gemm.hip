@@ -19,8 +19,8 @@
 //     atomics, so the result is reproducible bit for bit, and the same for every tile shape.
 //   * blockIdx -> tile: the chip dispatches consecutive workgroups round-robin over its 8 XCDs, each with a private L2;
 //     tile_of_block gives an XCD a range of column tiles (its share of W stays in its L2) and walks its tiles row by row.
-// fp32 path above 256 rows: the same prologues / epilogues around a plain FMA core (gemm_f32_kernel); smaller batches have
-// kernels of their own (fade_rows.hip).
+// fp32 path above 256 rows, and at any batch with D_h, D_cache or D_e above 2048: the same prologues / epilogues around a plain
+// FMA core (gemm_f32_kernel); the other batches have kernels of their own (fade_rows.hip).
 #include <cstdlib>
 #include <type_traits>
 

@@ -13,7 +13,7 @@
 //   * weight gradients and Adam are one launch for all matrices: a wavefront contracts the batch for a 16 x 64 strip from the
 //     row-major activations (no transposed copies) and steps the weights it just formed the gradient of.
 // A step at 16 streams (T = 32, D = 16, H = 128), kernel time: forward 12 launches, 79 us -> 9 launches, 41 us; with the update
-// 46 launches, 300 us -> 25 launches, 117 us.
+// 46 launches, 300 us -> 24 launches, 117 us.
 // Row statistics are left per 16 columns (stats_n = N / 16). Every sum has a fixed order.
 #include "fade_dev.h"
 #include "fade_kernels.h"

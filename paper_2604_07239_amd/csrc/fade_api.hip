@@ -1530,7 +1530,8 @@ int fade_create(const fade_config *cfg, fade_ctx **out) {
     if (!c->rows16 && d.c % 64 == 0) TRY_ALLOC(A(&c->dg_slot, Bp * d.c));
     // gradients that serve as the right operand of a weight-gradient product have Bp rows (padding rows stay zero)
     struct { void **p; size_t n; } bufs[] = {
-        {&c->dl, Bp * 256}, {&c->dHout, BDh}, {&c->dV, BpDh}, {&c->dHc, BDh}, {&c->dE, Bp * 2 * d.De}, {&c->du, BDh}, {&c->dHa, BpDh}, {&c->dac, BpDh}, {&c->dHmix1, BDh}, {&c->dHmix2, BDh},
+        {&c->dl, Bp * 256}, {&c->dHout, BDh}, {&c->dV, BpDh}, {&c->dHc, BDh},
+        {&c->dE, Bp * 2 * d.De}, {&c->du, BDh}, {&c->dHa, BpDh}, {&c->dac, BpDh}, {&c->dHmix1, BDh}, {&c->dHmix2, BDh},
         {&c->dy_at, Bp * d.dl}, {&c->dnc, BDh}, {&c->dar, BpDh}, {&c->dhm, BpDh}, {&c->dcv, BDh}, {&c->dX1, BDh}, {&c->dX2, BDh},
         {&c->dxl, BDh},
         // the small-batch fp32 kernels need none of the rest

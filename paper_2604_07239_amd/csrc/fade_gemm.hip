@@ -179,19 +179,65 @@ __device__ __forceinline__ void epi_side_load(const GemmArgs &g, size_t o, bool 
   if (EpiSides<EPI>::n >= 2) raw_load(sd[1], static_cast<const AT *>(g.S2) + o);
 }
 
-// The arithmetic below is written with explicit fused multiply-adds and unfusable products (fmaf, __fmul_rn): instances of
-// this function for different tile shapes must give the same bits (a pass over many steps and a single step use different
-// ones), which must not depend on where the compiler chooses to contract a * b + c.
+// What happens to one 8-wide chunk of finished sums x at element offset o, for the epilogues that more than one kernel body has.
+// The arithmetic is written with explicit fused multiply-adds and unfusable products (fmaf, __fmul_rn): instances for
+// different tile shapes must give the same bits (a pass over many steps and a single step use different ones), which must not
+// depend on where the compiler chooses to contract a * b + c.
+// KEEP: whether the copies for the backward pass (C2, C3) are written; KEEP_ASK looks at the pointer here.
+enum { KEEP_NO = 0, KEEP_YES = 1, KEEP_ASK = 2 };
+template <int KEEP> __device__ __forceinline__ bool keeps(const void *p) { return KEEP == KEEP_ASK ? p != nullptr : KEEP == KEEP_YES; }
+template <int EPI, typename AT, int KEEP = KEEP_ASK>
+__device__ __forceinline__ void epi_finish(const GemmArgs &g, size_t o, float lam, const Raw8<AT> *sd, const float x[8], float out[8]) {
+  static_assert(EPI == EPI_STORE || EPI == EPI_GLOBAL || EPI == EPI_MIX || EPI == EPI_GATE, "epilogue");
+  if constexpr (EPI == EPI_STORE) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) out[i] = x[i];
+    store8(static_cast<AT *>(g.C) + o, out);
+  } else if constexpr (EPI == EPI_GLOBAL) {
+    float s1[8];
+    raw_to_float(sd[0], s1);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) out[i] = fmaf(lam, s1[i], gelu_f(x[i]));
+    store8(static_cast<AT *>(g.C) + o, out);
+    if (keeps<KEEP>(g.C2)) store8_nt(static_cast<AT *>(g.C2) + o, x);
+  } else if constexpr (EPI == EPI_MIX) {
+    float s1[8], s2[8], al[8];
+    raw_to_float(sd[0], s1);
+    raw_to_float(sd[1], s2);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) { al[i] = sigmoid_f(x[i]); out[i] = fmaf(al[i], s1[i], __fmul_rn(1.0f - al[i], s2[i])); }
+    store8(static_cast<AT *>(g.C) + o, out);
+    if (keeps<KEEP>(g.C2)) store8_nt(static_cast<AT *>(g.C2) + o, al);
+  } else {
+    float s1[8], s2[8], sgm[8];
+    raw_to_float(sd[0], s1);
+    raw_to_float(sd[1], s2);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) { sgm[i] = sigmoid_f(x[i]); out[i] = fmaf(lam, s2[i], __fmul_rn(s1[i], sgm[i])); }
+    store8(static_cast<AT *>(g.C) + o, out);
+    if (keeps<KEEP>(g.C2)) store8_nt(static_cast<AT *>(g.C2) + o, sgm);
+  }
+}
+struct FoldCols { float sg[8], tg[8], sv[8], tv[8]; };  // the folded LayerNorm's column vectors of a gate chunk and its value chunk
+template <typename AT, int KEEP = KEEP_ASK>
+__device__ __forceinline__ void epi_finish_geglu_fold(const GemmArgs &g, size_t o, float mean, float rstd, const FoldCols &f, const float x[8], const float xv[8]) {
+  float eg[8], ev[8], out[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    eg[i] = fade_fold_ln(x[i], mean, rstd, f.sg[i], f.tg[i]);
+    ev[i] = fade_fold_ln(xv[i], mean, rstd, f.sv[i], f.tv[i]);
+    out[i] = gelu_f(eg[i]) * ev[i];
+  }
+  store8(static_cast<AT *>(g.C) + o, out);
+  if (keeps<KEEP>(g.C2)) store8_nt(static_cast<AT *>(g.C2) + o, eg);
+  if (keeps<KEEP>(g.C3)) store8_nt(static_cast<AT *>(g.C3) + o, ev);
+}
+
 // A thread walks rows r0, r0 + RP, ... of its 8-wide column chunk. The side inputs (and the row moments of the folded
 // form) of U consecutive passes are requested together before the first of them is used, so that one memory latency
-// covers U rows; with PRE the caller has requested them even earlier (`pre`: [pass][input], all BM / RP passes).
-// ALL: every row of the tile exists (M is a multiple of the tile height): the stores then sit behind no branch. The counter
-// of outstanding memory operations is in order and covers stores; for a load older than stores that sit in branches the
-// compiler's wait count assumes the branches not taken, so the wait for the next slab's side inputs would also wait for
-// this slab's stores to be acknowledged.
-template <int EPI, typename AT, int BM, int BN, int LDC = BN + 4, int NT = 256, bool PRE = false, bool ALL = false>
-__device__ __forceinline__ void epilogue(const GemmArgs &g, const float *Cs, int m0, int n0, int nt, int tid, int split = 0,
-                                         const Raw8<AT> (*pre)[2] = nullptr) {
+// covers U rows.
+template <int EPI, typename AT, int BM, int BN, int LDC = BN + 4, int NT = 256>
+__device__ __forceinline__ void epilogue(const GemmArgs &g, const float *Cs, int m0, int n0, int nt, int tid, int split = 0) {
   constexpr bool kGeglu = EPI == EPI_GEGLU || EPI == EPI_GEGLU_FOLD;
   constexpr int BNO = kGeglu ? BN / 2 : BN;  // output columns of this tile
   constexpr int CH = BNO / 8;                            // chunks (threads) per row
@@ -199,76 +245,49 @@ __device__ __forceinline__ void epilogue(const GemmArgs &g, const float *Cs, int
   constexpr int PASSES = (BM + RP - 1) / RP;
   constexpr int NS = EpiSides<EPI>::n;
   constexpr bool kAhead = NS > 0 || EPI == EPI_GEGLU_FOLD;
-  constexpr int U = PRE ? PASSES : (kAhead ? (PASSES < 4 ? PASSES : 4) : 1);
+  constexpr int U = kAhead ? (PASSES < 4 ? PASSES : 4) : 1;
   constexpr bool kRagged = BM % (RP * U) != 0;  // a tile shorter than one round of passes: some threads own no row
-  static_assert(PASSES % U == 0 && !(PRE && kRagged), "row passes");
+  static_assert(PASSES % U == 0, "row passes");
   const int c8 = (tid % CH) * 8, r0 = tid / CH;
   const int nout0 = kGeglu ? nt * BNO : n0;  // first output column of the tile
   float lam = 0.0f;
   if (EPI == EPI_GLOBAL || EPI == EPI_GATE) lam = g.lam[0];
-  float sg[8], tg[8], sv[8], tv[8];
+  FoldCols fc;
   if (EPI == EPI_GEGLU_FOLD) {
-    load8(g.fold_s + n0 + c8, sg); load8(g.fold_t + n0 + c8, tg);
-    load8(g.fold_s + n0 + BNO + c8, sv); load8(g.fold_t + n0 + BNO + c8, tv);
+    load8(g.fold_s + n0 + c8, fc.sg); load8(g.fold_t + n0 + c8, fc.tg);
+    load8(g.fold_s + n0 + BNO + c8, fc.sv); load8(g.fold_t + n0 + BNO + c8, fc.tv);
   }
 #pragma unroll 1
   for (int rb = r0; rb < BM; rb += RP * U) {
-    Raw8<AT> own[PRE ? 1 : U][2];
+    Raw8<AT> own[U][2];
     float mean[U], rstd[U];
-    if (!PRE) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int m = m0 + rb + u * RP;
-        if (kRagged && rb + u * RP >= BM) continue;
-        // past the last row: any row (dropped below); a branch around the loads would cost the exact vmcnt waits
-        epi_side_load<EPI, AT>(g, (size_t)(m < g.M ? m : g.M - 1) * g.ldc + nout0 + c8, true, own[u]);
-        if (EPI == EPI_GEGLU_FOLD) row_moments_lanes(g, m, mean[u], rstd[u]);
-      }
+    for (int u = 0; u < U; ++u) {
+      const int m = m0 + rb + u * RP;
+      if (kRagged && rb + u * RP >= BM) continue;
+      // past the last row: any row (dropped below); a branch around the loads would cost the exact vmcnt waits
+      epi_side_load<EPI, AT>(g, (size_t)(m < g.M ? m : g.M - 1) * g.ldc + nout0 + c8, true, own[u]);
+      if (EPI == EPI_GEGLU_FOLD) row_moments_lanes(g, m, mean[u], rstd[u]);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-    const Raw8<AT> *sd = PRE ? pre[u] : own[u];
+    const Raw8<AT> *sd = own[u];
     const int r = rb + u * RP;
     if (kRagged && r >= BM) continue;
     const int m = m0 + r;
-    const bool live = ALL || m < g.M;
+    const bool live = m < g.M;
     float x[8], out[8];
     load8(Cs + r * LDC + c8, x);
     const size_t o = (size_t)m * g.ldc + nout0 + c8;
     if (live) {
-      if (EPI == EPI_STORE) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) out[i] = x[i];
-        store8(static_cast<AT *>(g.C) + o, out);
+      if constexpr (EPI == EPI_STORE || EPI == EPI_GLOBAL || EPI == EPI_MIX || EPI == EPI_GATE) {
+        epi_finish<EPI, AT>(g, o, lam, sd, x, out);
       } else if (EPI == EPI_STORE_F32) {
         float bi[8];
         if (g.bias) load8(g.bias + n0 + c8, bi);
 #pragma unroll
         for (int i = 0; i < 8; ++i) out[i] = g.bias ? x[i] + bi[i] : x[i];
         store8(static_cast<float *>(g.C) + o, out);
-      } else if (EPI == EPI_GLOBAL) {
-        float s1[8];
-        raw_to_float(sd[0], s1);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) out[i] = fmaf(lam, s1[i], gelu_f(x[i]));
-        store8(static_cast<AT *>(g.C) + o, out);
-        if (g.C2) store8_nt(static_cast<AT *>(g.C2) + o, x);
-      } else if (EPI == EPI_MIX) {
-        float s1[8], s2[8], al[8];
-        raw_to_float(sd[0], s1);
-        raw_to_float(sd[1], s2);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) { al[i] = sigmoid_f(x[i]); out[i] = fmaf(al[i], s1[i], __fmul_rn(1.0f - al[i], s2[i])); }
-        store8(static_cast<AT *>(g.C) + o, out);
-        if (g.C2) store8_nt(static_cast<AT *>(g.C2) + o, al);
-      } else if (EPI == EPI_GATE) {
-        float s1[8], s2[8], sgm[8];
-        raw_to_float(sd[0], s1);
-        raw_to_float(sd[1], s2);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) { sgm[i] = sigmoid_f(x[i]); out[i] = fmaf(lam, s2[i], __fmul_rn(s1[i], sgm[i])); }
-        store8(static_cast<AT *>(g.C) + o, out);
-        if (g.C2) store8_nt(static_cast<AT *>(g.C2) + o, sgm);
       } else if (EPI == EPI_GEGLU) {
         float xv[8];
         load8(Cs + r * LDC + BNO + c8, xv);
@@ -278,17 +297,9 @@ __device__ __forceinline__ void epilogue(const GemmArgs &g, const float *Cs, int
         if (g.C2) store8_nt(static_cast<AT *>(g.C2) + o, x);
         if (g.C3) store8_nt(static_cast<AT *>(g.C3) + o, xv);
       } else if (EPI == EPI_GEGLU_FOLD) {
-        float xv[8], eg[8], ev[8];
+        float xv[8];
         load8(Cs + r * LDC + BNO + c8, xv);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          eg[i] = fade_fold_ln(x[i], mean[u], rstd[u], sg[i], tg[i]);
-          ev[i] = fade_fold_ln(xv[i], mean[u], rstd[u], sv[i], tv[i]);
-          out[i] = gelu_f(eg[i]) * ev[i];
-        }
-        store8(static_cast<AT *>(g.C) + o, out);
-        if (g.C2) store8_nt(static_cast<AT *>(g.C2) + o, eg);
-        if (g.C3) store8_nt(static_cast<AT *>(g.C3) + o, ev);
+        epi_finish_geglu_fold<AT>(g, o, mean[u], rstd[u], fc, x, xv);
       } else if (EPI == EPI_GRAD) {  // split: partial sum over one range of the batch, slices [split][M][width] behind each other
         if (g.C3) {
           const int v = n0 + c8;
@@ -322,10 +333,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs &g, const float *Cs, int
 #pragma unroll
         for (int off = CH / 2; off > 0; off >>= 1) { s += __shfl_xor(s, off, 64); q += __shfl_xor(q, off, 64); }
       }
-      if (ALL) {  // every lane of the row's group holds the sums: all store them (same value, same address), no branch
-        float *p = g.stats_out + ((size_t)m * (g.N / BN) + nt) * 2;
-        *reinterpret_cast<float2 *>(p) = make_float2(s, q);
-      } else if (live && (tid % CH) == 0) {
+      if (live && (tid % CH) == 0) {
         float *p = g.stats_out + ((size_t)m * (g.N / BN) + nt) * 2;
         p[0] = s; p[1] = q;
       }
@@ -775,84 +783,78 @@ __global__ __launch_bounds__(256, (STAGES == 2 && BM * BN <= 128 * 128) ? 2 : 1)
 
 
 // ---------------------------------------------------------------------------------------------------
-// The same product with W in stages of 32 along K (two k-steps), a ring of four, and A in units of 64, a ring of three: deep
-// enough (three stages ahead) for the LDS-DMA of all compute units together, which the L2 fabric serves at about 50 bytes per
-// clock and unit, and so that the fragments of a stage's first k-step can be fetched from LDS while the matrix cores still
-// work on the last k-step of the stage before: the wait for a stage's DMA and the workgroup barrier sit in the middle of a
-// stage, between its two k-steps, and no fragment read is ever waited for with idle matrix cores.
-//   iteration h:  fetch (h, k-step 1) | MFMA (h, 0) | wait DMA of h+1, barrier, issue W of h+3 and A half h+4 | fetch (h+1, 0) | MFMA (h, 1)
-// A unit: BM rows of 128 bytes, swizzled as in pipe_body; a row-major operand is requested in whole 128-byte cache lines (one
-// DMA = 8 rows). With A in stages of 32 too, each request was half a line and the other half crossed the fabric again an
-// iteration later: in us, M = 16384, K = N = 2048 plain 124.5 -> 120.8 (1.14 PFLOP/s; a plain library product of that shape
-// 115.7), with the gate epilogue 160.7 -> 154.3, K = 2048, N = 1024 82.2 -> 79.5; M = 4096, N = 16384, K = 512 136.7 -> 124.7.
-// So that every iteration still requests the same amount, the two iterations of a unit request the upper and the lower half of
-// the rows of the unit two further on. W: ready-made 1 KiB fragments.
-// One shape: 256 x 256 on eight wavefronts, whole tiles, the contraction in one range, 160 KiB of LDS. (The same rings with 128 x 128
-// tiles and two workgroups per unit lost to 64 x 128 at M = 4096, N = 512: 40 us against 33.)
-// The W slot that iteration h refills is the one stage h-1 lived in, the A slot the one of the unit before h's: their last
-// fragment read was waited for before MFMA (h-1, 1) was issued, which every wavefront has done when it arrives at iteration
-// h's barrier. Group h = {W of stage h, A half h+1} is requested together; stage h needs groups up to h.
+// The same product on 256 x 256 tiles, eight wavefronts (2 x 4, 128 x 64 each), one workgroup per compute unit, for batches that
+// give every unit a tile. Both operands come in units of 64 along K (32 KiB each: A as rows of 128 bytes, whole cache lines,
+// swizzled as in pipe_body; W as ready-made fragments), A through a ring of three, W through a ring of two: 160 KiB of LDS.
+// One hand-over (DMA wait, barrier) per unit, between its third and fourth k-step: the fragments of the fourth are in
+// registers by then, so behind the barrier the unit's slots are free, and the reads of the next unit's first k-step run under
+// the fourth's matrix instructions. unit u requests A of unit u + 2 during its first two k-steps and W of unit u + 2 behind
+// its barrier; unit u + 1's barrier waits for both (all but the youngest CH requests).
+// What bounds it is the power the matrix cores draw on real data: M = 16384, K = N = 2048 plain 107-109 us (1.27 PFLOP/s) on
+// random operands, 79.5 (1.73) on zeros; the ring of 32-wide W stages with a barrier each that this replaces took 117-120 and
+// 95, a plain library product 115.7. M = N = K = 8192: 757 us (1.45 PFLOP/s) against 827. What made the difference, each
+// on its own (16384 x 2048 x 2048): requests spread between the matrix instructions instead of in front of them 118 -> 115;
+// their addresses as a buffer resource with scalar offsets, so that a request needs no vector instruction, 115 -> 112; one
+// barrier per 64 of K instead of two 112 -> 109. Four wavefronts of 128 x 128 (a third fewer LDS reads, one wavefront per SIMD):
+// 113; two groups of four that alternate between reading and multiplying: 146.
 // Every output element sees the same sequence of k-steps as in pipe_body, so both give the same bits.
+//
+// The epilogue keeps to the wavefront: the operands enter the matrix instructions exchanged (columns of W as rows), so a lane
+// holds four consecutive columns of one row, which it parks in its wavefront's own 32 x 64 LDS slab in 16-byte pieces and reads
+// back row-wise; no barrier until the row statistics, whose chunk sums meet in LDS at the end. The side inputs of a
+// pass are requested a whole slab ahead, those of the first slab before the last unit. A GeGLU tile is gate | value per 128 columns: the
+// wavefront then takes 32 gate columns and their 32 value columns.
 // ---------------------------------------------------------------------------------------------------
 constexpr int PIPE2_LDS = 160 * 1024;
 template <int EPI>
 __device__ __forceinline__ void pipe2_body(const GemmArgs &g, int bid) {
   typedef bf16_t AT;
-  static_assert(EPI != EPI_PARTIAL, "one range of K");
-  constexpr int BM = 256, BN = 256, NW = 8, BK = 32, KS = 2, WSTAGES = 4, AUNITS = 3;
+  static_assert(EPI == EPI_STORE || EPI == EPI_GLOBAL || EPI == EPI_MIX || EPI == EPI_GATE || EPI == EPI_GEGLU_FOLD, "epilogue");
+  constexpr bool kPair = EPI == EPI_GEGLU_FOLD;
+  constexpr int BM = 256, BN = 256, NW = 8, KS = 4, AUNITS = 3, WUNITS = 2;
   constexpr int WN = NW / 2;                         // wavefronts 2 (rows) x WN (columns)
-  constexpr int TM = BM / 64, TN = BN / (32 * WN);   // 32x32 tiles per wavefront
-  constexpr int BFR = BN / 32;
-  constexpr int A_UNIT = BM * 128, W_STAGE = BFR * KS * 1024, A_RING = AUNITS * A_UNIT;
-  constexpr int ACH = BM / 16 / NW;                  // A DMAs per wavefront and half unit (BM / 2 rows; one DMA = 8 rows x 128 bytes)
-  constexpr int BCH = BFR * KS / NW;                 // W DMAs per wavefront and stage (one fragment each)
-  constexpr int LPW = ACH + BCH, LDC = BN + 4;
-  static_assert(A_RING + WSTAGES * W_STAGE == PIPE2_LDS && 64 * LDC * 4 <= PIPE2_LDS, "LDS");
+  constexpr int TM = BM / 64, TN = BN / (32 * WN), NRD = TM + TN;  // 32x32 tiles per wavefront; fragment reads per k-step
+  constexpr int UNIT = BM * 128, A_RING = AUNITS * UNIT;
+  constexpr int CH = UNIT / 1024 / NW;               // DMAs per wavefront, operand and unit
+  constexpr int FS = kPair ? 2 : 1;                  // distance of the wavefront's two W fragments
+  static_assert((AUNITS + WUNITS) * UNIT == PIPE2_LDS && BM == BN && TM == 4 && TN == 2, "LDS, tile");
   extern __shared__ __align__(16) unsigned char smem[];
-  float *Cs = reinterpret_cast<float *>(smem);
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
   const int ntn = g.N / BN, ntm = g.M / BM;
   int mt, nt;
   if (!tile_of_block(bid, ntm, ntn, g.col_groups, mt, nt)) return;
   const int m0 = mt * BM, n0 = nt * BN;
-  const int nkh = g.K / BK;  // stages; even (K is a multiple of 64)
-  const int ksteps = g.K / 16;
+  const int nku = g.K / 64;
 
-  const bf16_t *asrc[2][ACH], *wsrc[BCH];
+  // DMA sources: a resource at the tile's first row / fragment, one lane offset each, and scalar offsets per request
+  const auto rsrc_a = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(static_cast<const bf16_t *>(g.A) + (size_t)m0 * g.lda), 0, 0x7fffffff, 0x00020000);
+  const auto rsrc_w = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(static_cast<const bf16_t *>(g.W) + (size_t)n0 * g.K), 0, 0x7fffffff, 0x00020000);
+  // A: DMA c = wave + NW q covers rows 8c .. 8c + 7, lane i piece (i % 8) ^ ((r / 2) % 8) of row r = 8c + i / 8; as NW is even,
+  // (r / 2) % 8 is 4 (wave % 2) + i / 16 for every q
+  const uint32_t a_vo = (uint32_t)((lane >> 3) * g.lda * 2 + (((lane & 7) ^ (((wave & 1) << 2) + (lane >> 4))) << 4)), w_vo = (uint32_t)lane * 16;
+  const uint32_t a_so = (uint32_t)(wave * 8 * g.lda * 2), a_q = (uint32_t)(NW * 8 * g.lda * 2);
+  uint32_t w_so[CH];
 #pragma unroll
-  for (int hf = 0; hf < 2; ++hf)
-#pragma unroll
-    for (int q = 0; q < ACH; ++q) {
-      const int r = hf * (BM / 2) + (wave + NW * q) * 8 + (lane >> 3);
-      asrc[hf][q] = static_cast<const bf16_t *>(g.A) + (size_t)(m0 + r) * g.lda + (((lane & 7) ^ ((r >> 1) & 7)) << 3);
-    }
-#pragma unroll
-  for (int q = 0; q < BCH; ++q) {
-    const int c = wave + NW * q, fr = c / KS, ks = c % KS;
-    wsrc[q] = static_cast<const bf16_t *>(g.W) + (((size_t)(n0 / 32 + fr) * ksteps + ks) * 64 + lane) * 8;
+  for (int q = 0; q < CH; ++q) {
+    const int c = wave + NW * q;  // fragment c / 4 (32 columns), k-step c % 4
+    w_so[q] = (uint32_t)(((c / KS) * (g.K / 16) + c % KS) * 1024);
   }
-  auto issue_w = [&](int slot, int kh) {  // kh: 32-wide stage counted from the start of K
-    unsigned char *base = smem + A_RING + slot * W_STAGE;
-#pragma unroll
-    for (int q = 0; q < BCH; ++q) dma16(wsrc[q] + (size_t)kh * KS * 512, base + (wave + NW * q) * 1024);
+  auto dma_a = [&](int q, int u, int slot) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_a, (__attribute__((address_space(3))) void *)(smem + slot * UNIT + (wave + NW * q) * 1024), 16, a_vo,
+                                             a_so + q * a_q + u * 128, 0, 0);
   };
-  auto issue_a = [&](int slot, int unit, auto half_c) {  // unit: 64-wide, counted from the start of K
-    constexpr int hf = decltype(half_c)::value;
-    unsigned char *base = smem + slot * A_UNIT + hf * (A_UNIT / 2);
-#pragma unroll
-    for (int q = 0; q < ACH; ++q) dma16(asrc[hf][q] + (size_t)unit * 64, base + (wave + NW * q) * 1024);
+  auto dma_w = [&](int q, int u, int slot) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_w, (__attribute__((address_space(3))) void *)(smem + A_RING + slot * UNIT + (wave + NW * q) * 1024), 16, w_vo,
+                                             w_so[q] + u * (KS * 1024), 0, 0);
   };
-
-  // fragment read addresses (bytes): A tile i of this wavefront at a_base[k-step of the unit] + i * 4096 (32 rows of 128
-  // bytes) in the unit's slot, W tile j at b_base + k-step * 1024 + j * 2048 in the stage's slot
+  // fragment reads: row r, piece p of a unit at r * 128 + ((p ^ ((r / 2) % 8)) * 16); k-step ks, half h reads piece 2 ks + h, i.e.
+  // the address of k-step 0 with 32 ks XORed in (slots start at multiples of 128)
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
-  const int a_sw = (lane >> 1) & 7, a_half = lane >> 5;  // tile rows start at multiples of 32: (r / 2) % 8 == (lane / 2) % 8
-  uint32_t a_base[2 * KS];
-#pragma unroll
-  for (int ks = 0; ks < 2 * KS; ++ks) a_base[ks] = lds0 + (wm * TM * 32 + (lane & 31)) * 128 + (((2 * ks + a_half) ^ a_sw) << 4);
-  const uint32_t b_base = lds0 + A_RING + (((wn * TN * KS) * 64 + lane) << 4);
+  const uint32_t a_first = lds0 + (wm * TM * 32 + (lane & 31)) * 128 + (((lane >> 5) ^ ((lane >> 1) & 7)) << 4);
+  const uint32_t w_first = lds0 + A_RING + (kPair ? (wn >> 1) * 4 + (wn & 1) : wn * TN) * (KS * 1024) + lane * 16;
+  uint32_t a_cur = a_first, w_cur = w_first;
 
   f32x16 acc[TM][TN];
 #pragma unroll
@@ -863,125 +865,195 @@ __device__ __forceinline__ void pipe2_body(const GemmArgs &g, int bid) {
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
   typedef std::integral_constant<int, 0> I0;
   typedef std::integral_constant<int, 1> I1;
-  typedef std::integral_constant<int, TM + TN> INext;
-  // groups 0 (with A half 0), 1, 2
-  issue_a(0, 0, I0{});
-  issue_a(0, 0, I1{});
-  issue_w(0, 0);
-  issue_w(1, 1);
-  if (nkh > 2) {
-    issue_a(1, 1, I0{});
-    issue_w(2, 2);
-    issue_a(1, 1, I1{});
+  typedef std::integral_constant<int, 2> I2;
+  typedef std::integral_constant<int, 3> I3;
+  typedef std::integral_constant<int, 4> I4;
+  typedef std::integral_constant<int, 5> I5;
+#pragma unroll
+  for (int q = 0; q < CH; ++q) dma_a(q, 0, 0);
+#pragma unroll
+  for (int q = 0; q < CH; ++q) dma_w(q, 0, 0);
+  if (nku > 1) {
+#pragma unroll
+    for (int q = 0; q < CH; ++q) dma_a(q, 1, 1);
+#pragma unroll
+    for (int q = 0; q < CH; ++q) dma_w(q, 1, 1);
+    wait_vmcnt<2 * CH>();
+  } else {
+    wait_vmcnt<0>();
   }
+  bare_barrier();  // unit 0 is in LDS for everyone
 
   bf16x8 af[2][TM], bf[2][TN];
-  auto fetch = [&](auto buf_c, int aslot, int wslot, auto ks_c) {  // ks: k-step of the A unit; TM + TN reads, left in flight
-    constexpr int buf = decltype(buf_c)::value, ks = decltype(ks_c)::value, wk = ks % KS;
-    const uint32_t sa = a_base[ks] + aslot * A_UNIT, sb = b_base + wslot * W_STAGE;
-    static_assert(TM <= 4 && TN <= 4, "tiles per wavefront");
-    af[buf][0] = lds_read16<0>(sa);
-    if constexpr (TM > 1) af[buf][1] = lds_read16<4096>(sa);
-    if constexpr (TM > 2) af[buf][2] = lds_read16<8192>(sa);
-    if constexpr (TM > 3) af[buf][3] = lds_read16<12288>(sa);
-    bf[buf][0] = lds_read16<wk * 1024>(sb);
-    if constexpr (TN > 1) bf[buf][1] = lds_read16<wk * 1024 + 2048>(sb);
-    if constexpr (TN > 2) bf[buf][2] = lds_read16<wk * 1024 + 4096>(sb);
-    if constexpr (TN > 3) bf[buf][3] = lds_read16<wk * 1024 + 6144>(sb);
+  auto read = [&](auto buf_c, auto ks_c, auto x_c, uint32_t sa, uint32_t sb) {  // read x of the k-step's NRD
+    constexpr int buf = decltype(buf_c)::value, ks = decltype(ks_c)::value, x = decltype(x_c)::value;
+    if constexpr (x < TN) bf[buf][x] = lds_read16<ks * 1024 + x * FS * KS * 1024>(sb);
+    else af[buf][x - TN] = lds_read16<(x - TN) * 4096>(sa);
   };
-  auto mfma = [&](auto buf_c, auto newer_c) {  // newer: reads issued after this buffer's, allowed to stay in flight
+  auto landed = [&](auto buf_c) {
     constexpr int buf = decltype(buf_c)::value;
-    lds_wait<decltype(newer_c)::value>();
+    lds_wait<0>();
 #pragma unroll
     for (int i = 0; i < TM; ++i) lds_landed(af[buf][i]);
 #pragma unroll
     for (int j = 0; j < TN; ++j) lds_landed(bf[buf][j]);
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[buf][i], bf[buf][j], acc[i][j], 0, 0, 0);
   };
-  // group 0 has landed once at most groups 1 and 2 are in flight
-  if (nkh > 2) wait_vmcnt<2 * LPW>();
-  else wait_vmcnt<0>();
-  bare_barrier();
-  fetch(I0{}, 0, 0, I0{});
-  int aslot = 0, afill = 2;  // A slot of the unit being worked on; A slot the unit two further on goes to
-  auto next_a = [&](int s) { return s + 1 == AUNITS ? 0 : s + 1; };
-  // One iteration: the two k-steps of stage h around the hand-over to stage h + 1. odd: second stage of its unit.
-  // mode 2: group h + 3 is requested; 1: its W alone (past the last unit); 0: the rings only drain.
-  auto step = [&](int h, auto odd_c, auto mode_c) {
-    constexpr int odd = decltype(odd_c)::value, mode = decltype(mode_c)::value;
-    fetch(I1{}, aslot, h % WSTAGES, std::integral_constant<int, 2 * odd + 1>{});
-    mfma(I0{}, INext{});
-    if constexpr (mode != 0) wait_vmcnt<LPW>();  // group h + 1 has landed: only group h + 2 may be in flight
-    else wait_vmcnt<0>();
-    bare_barrier();  // stage h+1 is in LDS for everyone, and everyone is done reading stage h-1
-    if constexpr (mode != 0) issue_w((h + 3) % WSTAGES, h + 3);
-    if constexpr (mode == 2) issue_a(afill, h / 2 + 2, odd_c);
-    if constexpr (odd != 0) {
-      aslot = next_a(aslot);
-      afill = next_a(afill);
-    }
-    fetch(I0{}, aslot, (h + 1) % WSTAGES, std::integral_constant<int, odd ? 0 : 2>{});
-    mfma(I1{}, INext{});
+  // One k-step: the matrix instructions of register buffer `buf` in four pairs, in front of each pair two reads of the next k-step
+  // into the other buffer and its share of the k-step's ND requests. The order is fixed (sched_barrier): left alone the
+  // compiler gathers the requests behind the barrier, where eight wavefronts' worth of them hold up the matrix instructions.
+  auto kstep = [&](auto buf_c, auto nks_c, uint32_t sa, uint32_t sb, auto reads_c, auto nd_c, auto dma) {
+    constexpr int buf = decltype(buf_c)::value, ND = decltype(nd_c)::value;
+    static_assert(ND <= 4, "one request per pair");
+    auto pair = [&](auto i_c, auto x0_c, auto x1_c) {
+      constexpr int i = decltype(i_c)::value;
+      typedef std::integral_constant<int, 1 - buf> NB;
+      if constexpr (decltype(reads_c)::value) {
+        if constexpr (decltype(x0_c)::value < NRD) read(NB{}, nks_c, x0_c, sa, sb);
+        if constexpr (decltype(x1_c)::value < NRD) read(NB{}, nks_c, x1_c, sa, sb);
+      }
+      if constexpr (i < ND) dma(i);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[buf][j], af[buf][i], acc[i][j], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    typedef std::integral_constant<int, NRD> None;
+    pair(I0{}, I0{}, I1{});
+    pair(I1{}, I2{}, I3{});
+    pair(I2{}, I4{}, I5{});
+    pair(I3{}, None{}, None{});
   };
-  int h = 0;
-  for (; h + 5 < nkh; h += 2) {
-    step(h, I0{}, std::integral_constant<int, 2>{});
-    step(h + 1, I1{}, std::integral_constant<int, 2>{});
+  {
+    auto first = [&](auto x_c) { read(I0{}, I0{}, x_c, a_cur, w_cur); };
+    first(I0{}); first(I1{}); first(I2{}); first(I3{}); first(I4{}); first(I5{});
   }
-  if (nkh > 2) {
-    step(h, I0{}, I1{});
-    step(h + 1, I1{}, I0{});
-    h += 2;
-  }
-  step(h, I0{}, I0{});
-  fetch(I1{}, aslot, (h + 1) % WSTAGES, std::integral_constant<int, 3>{});  // last stage: nothing follows
-  mfma(I0{}, INext{});
-  mfma(I1{}, I0{});
-  wait_vmcnt<0>();
-  // The fp32 tile does not fit LDS at once: it leaves in slabs of 64 rows, each handed to the epilogue as 128-column
-  // pieces (the width the row statistics are kept at), so every output is formed exactly as by the smaller tiles.
-  // (a GeGLU tile is gate | value per 128 columns, so each 128-column piece is a complete pair)
-  constexpr int NT = NW * 64, SP = 64 / (NT / 16);     // passes of a thread over a 64-row, 128-column slab piece
-  // the side inputs of slab p + 1 are requested before slab p is worked on: no other workgroup is on the unit to cover them
-  constexpr bool PRE = EpiSides<EPI>::n != 0;
-  Raw8<AT> sd[PRE ? 2 : 1][BN / 128][SP][2];
-  auto side = [&](int buf, int p) {
-    if constexpr (PRE) {
-#pragma unroll
-      for (int h = 0; h < BN / 128; ++h)
-#pragma unroll
-        for (int u = 0; u < SP; ++u) {
-          const int m = m0 + p * 64 + u * (NT / 16) + tid / 16;
-          epi_side_load<EPI, AT>(g, (size_t)m * g.ldc + n0 + h * 128 + (tid % 16) * 8, true, sd[buf][h][u]);
-        }
+  int aslot = 0, afill = 2;  // A slot of this unit and of the unit two further on
+  auto none = [](int) {};
+  // mode 2: unit u + 2 is requested; 1: nothing is left to request; 0: the last unit
+  auto unit = [&](int u, auto mode_c) {
+    constexpr int mode = decltype(mode_c)::value;
+    typedef std::integral_constant<int, mode == 2 ? CH / 2 : 0> NDA;
+    typedef std::integral_constant<int, mode == 2 ? CH : 0> NDW;
+    landed(I0{});
+    kstep(I0{}, I1{}, a_cur ^ 32, w_cur, std::true_type{}, NDA{}, [&](int q) { dma_a(q, u + 2, afill); });
+    landed(I1{});
+    kstep(I1{}, I2{}, a_cur ^ 64, w_cur, std::true_type{}, NDA{}, [&](int q) { dma_a(CH / 2 + q, u + 2, afill); });
+    landed(I0{});
+    kstep(I0{}, I3{}, a_cur ^ 96, w_cur, std::true_type{}, I0{}, none);
+    landed(I1{});  // every read of this unit
+    if constexpr (mode != 0) {
+      if constexpr (mode == 2) wait_vmcnt<CH>();  // unit u + 1 has landed, A of unit u + 2 may be in flight
+      else wait_vmcnt<0>();
+      __builtin_amdgcn_sched_barrier(0);
+      bare_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      aslot = aslot == AUNITS - 1 ? 0 : aslot + 1;
+      afill = afill == AUNITS - 1 ? 0 : afill + 1;
+      a_cur = a_first + aslot * UNIT;
+      w_cur = w_first + ((u + 1) & 1) * UNIT;
+      kstep(I1{}, I0{}, a_cur, w_cur, std::true_type{}, NDW{}, [&](int q) { dma_w(q, u + 2, u & 1); });
+    } else {
+      kstep(I1{}, I0{}, a_cur, w_cur, std::false_type{}, I0{}, none);
     }
   };
-  side(0, 0);
+  int u = 0;
+  for (; u + 2 < nku; ++u) unit(u, I2{});
+  if (u + 1 < nku) {
+    unit(u, I1{});
+    ++u;
+  }
+
+  constexpr int LDC = 68;                                    // slab row: 64 columns; 68 keeps writes and reads free of bank conflicts
+  constexpr int OCH = kPair ? 4 : 8, RP = 64 / OCH, PASSES = 32 / RP;  // 8-wide output chunks per row, rows per pass, passes per slab
+  constexpr int CSP = 17;                                    // pitch of the chunk sums of a row's 128-column piece
+  constexpr int SLABS = NW * 32 * LDC * 4, NS = EpiSides<EPI>::n;
+  static_assert(SLABS + 2 * BM * CSP * 8 <= PIPE2_LDS, "LDS");
+  const int c8 = (lane % OCH) * 8, r0 = lane / OCH;
+  const size_t nout = kPair ? (size_t)nt * (BN / 2) + wn * 32 + c8 : (size_t)n0 + wn * 64 + c8;  // first output column of this lane's chunk
+  Raw8<AT> sd[NS ? PASSES : 1][2];  // side inputs of the next PASSES passes
+  auto side = [&](int i, int p) {
+    if constexpr (NS != 0) epi_side_load<EPI, AT>(g, (size_t)(m0 + wm * 128 + i * 32 + p * RP + r0) * g.ldc + nout, true, sd[p]);
+  };
+  float lam = 0.0f, mean0 = 0.0f, rstd0 = 1.0f;
+  if constexpr (EPI == EPI_GLOBAL || EPI == EPI_GATE) lam = g.lam[0];
+  FoldCols fc;
+  if constexpr (kPair) {
+    const int v = n0 + (wn >> 1) * 128 + (wn & 1) * 32 + c8;
+    load8(g.fold_s + v, fc.sg); load8(g.fold_t + v, fc.tg);
+    load8(g.fold_s + v + 64, fc.sv); load8(g.fold_t + v + 64, fc.tv);
+    row_moments(g, m0 + (tid & (BM - 1)), mean0, rstd0);
+  }
 #pragma unroll
-  for (int p = 0; p < BM / 64; ++p) {
-    constexpr int ROWS_PER_WAVE = 32 * TM;
-    const int owner = (p * 64) / ROWS_PER_WAVE, i0 = ((p * 64) % ROWS_PER_WAVE) / 32;
-    if (p + 1 < BM / 64) side((p + 1) & 1, p + 1);
-    __syncthreads();  // the ring, or the previous slab, is no longer being read
-    if (wm == owner) {
-#pragma unroll
-      for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int row = ii * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
-            const int col = (wn * TN + j) * 32 + (lane & 31);
-            Cs[row * LDC + col] = acc[i0 + ii][j][e];
-          }
-    }
+  for (int p = 0; p < PASSES; ++p) side(0, p);
+  unit(u, I0{});
+
+  __syncthreads();  // the rings are no longer being read
+  float *slab = reinterpret_cast<float *>(smem) + wave * 32 * LDC;
+  float2 *sums = reinterpret_cast<float2 *>(smem + SLABS);  // [2 pieces][256 rows][16 chunks]; of a pair: the rows' moments
+  if constexpr (kPair) {
+    if (tid < BM) sums[tid] = make_float2(mean0, rstd0);
     __syncthreads();
+  }
+  // keep_c: whether C2 / C3 are written, decided once. The counter of outstanding memory operations is in order and covers stores;
+  // for a load older than stores that sit in branches the compiler's wait count assumes the branches not taken, so the wait
+  // for the next slab's side inputs would also wait for this slab's stores to be acknowledged.
+  auto slabs = [&](auto keep_c) {
+  constexpr int KEEP = decltype(keep_c)::value;
 #pragma unroll
-    for (int h = 0; h < BN / 128; ++h)
-      epilogue<EPI, AT, 64, 128, LDC, NT, PRE, true>(g, Cs + h * 128, m0 + p * 64, n0 + h * 128, nt * (BN / 128) + h, tid, 0, sd[PRE ? (p & 1) : 0][h]);
+  for (int i = 0; i < TM; ++i) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<f32x4 *>(slab + (lane & 31) * LDC + j * 32 + q * 8 + (lane >> 5) * 4) = f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+    // the wavefront's lanes exchange through its own slab: LDS serves one wavefront's accesses in order
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+      const int r = p * RP + r0, row = wm * 128 + i * 32 + r;
+      const size_t o = (size_t)(m0 + row) * g.ldc + nout;
+      float x[8];
+      load8(slab + r * LDC + c8, x);
+      if constexpr (kPair) {
+        float xv[8];
+        load8(slab + r * LDC + 32 + c8, xv);
+        const float2 mr = sums[row];
+        epi_finish_geglu_fold<AT, KEEP>(g, o, mr.x, mr.y, fc, x, xv);
+      } else {
+        float out[8];
+        epi_finish<EPI, AT, KEEP>(g, o, lam, sd[NS ? p : 0], x, out);
+        if (i + 1 < TM) side(i + 1, p);
+        if constexpr (EPI != EPI_GLOBAL) {
+          if (g.stats_out) {
+            float s = 0.0f, q = 0.0f;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) { s += out[k]; q = fmaf(out[k], out[k], q); }
+            sums[((wn >> 1) * BM + row) * CSP + (wn & 1) * 8 + lane % OCH] = make_float2(s, q);
+          }
+        }
+      }
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+  }
+  };
+  if (EPI != EPI_STORE && g.C2) slabs(std::integral_constant<int, KEEP_YES>{});
+  else slabs(std::integral_constant<int, KEEP_NO>{});
+  if constexpr (EPI == EPI_STORE || EPI == EPI_MIX || EPI == EPI_GATE) {
+    if (g.stats_out) {  // a row's 16 chunk sums per 128 columns, added as the 16-lane butterfly of the smaller tiles adds them
+      __syncthreads();
+      const int row = tid >> 1, piece = tid & 1;
+      const float2 *p = sums + (piece * BM + row) * CSP;
+      float2 v[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) v[k] = p[k];
+#pragma unroll
+      for (int w = 8; w > 0; w >>= 1)
+#pragma unroll
+        for (int k = 0; k < w; ++k) { v[k].x += v[k + w].x; v[k].y += v[k + w].y; }
+      *reinterpret_cast<float2 *>(g.stats_out + ((size_t)(m0 + row) * (g.N / 128) + nt * 2 + piece) * 2) = v[0];
+    }
   }
 }
 template <int EPI> __global__ __launch_bounds__(512, 1) void gemm_pipe2_kernel(GemmArgs g) { pipe2_body<EPI>(g, (int)blockIdx.x); }
@@ -1456,6 +1528,7 @@ hipError_t launch_pipe2(const GemmArgs &g, hipStream_t s) {
     attr_done = true;
   }
   if (g.M <= 0 || g.N <= 0 || g.K <= 0 || g.M % 256 || g.N % 256 || g.K % 64 || g.splits > 1 || g.sum_splits || g.lda % 8) return hipErrorInvalidValue;
+  if ((size_t)256 * g.lda * 2 + (size_t)g.K * 2 > 0x7fffffff || (EPI == EPI_GEGLU_FOLD && (g.C2 == nullptr) != (g.C3 == nullptr))) return hipErrorInvalidValue;
   GemmArgs ga = g;
   const int ntm = g.M / 256, ntn = g.N / 256;
   if (ga.col_groups == 0) ga.col_groups = fade_gemm_col_groups(g.M, g.K, g.N, (size_t)4 << 20);

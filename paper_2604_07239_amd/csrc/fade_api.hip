@@ -119,6 +119,8 @@ struct fade_ctx {
   void *stage[3] = {nullptr, nullptr, nullptr};
   size_t stage_cap[3] = {0, 0, 0};
 
+  // progressive ablation: the last stage that is switched on feeds the head (5: the full model)
+  int level() const { return cfg.ablation == 0 ? 5 : (int)cfg.ablation; }
   bool have_weights = false;
   // adapting weights: the masters as loaded (frozen contexts never change theirs), on the device, or, once the card was too full
   // for that (restore_from_host), in host memory
@@ -174,9 +176,10 @@ struct fade_ctx {
   // weight gradients with few output tiles are left as partial sums over ranges of the batch (bf16 path): per parameter
   // tensor the number of ranges (1: none) and the slices [ranges][K][N]; the Adam pass adds them up
   int gsp[P_COUNT] = {};
-  // weight gradients on 256 x 256 tiles wait here until the end of the backward pass and run as one launch (defer_tn2)
+  // weight gradients on 256 x 256 tiles wait here until the end of the backward pass and run as one launch: tn2q.g[tn2_slot[id]]
   Tn2Group tn2q{};
-  bool defer_tn2 = false;
+  int tn2_slot[P_COUNT] = {};  // -1: not there
+  uint8_t *gparts[P_COUNT] = {};  // partial sums per 256 x 256 tile
   float *gpart[P_COUNT] = {};
   int sp_du = 1;            // ranges of K = 2 D_e in du = dE [W_fg W_fv]^T (bf16 path, wide refiners)
   float *du_part = nullptr;
@@ -334,7 +337,7 @@ int refresh_matrices(fade_ctx *c, bool adam) {
     m.off = c->lay.off[id]; m.K = (int)K; m.N = (int)N; m.vcol0 = vcol0; m.vstride = vstride; m.VN = (int)VN;
     m.frag = bf ? frag : nullptr; m.fragT = (bf && c->online) ? fragT : nullptr; m.gamma = bf ? ga : nullptr; m.beta = bf ? be : nullptr; m.fold_part = fp;
     m.first_block = ab.total_blocks;
-    m.gpart = (adam && c->gsp[id] > 1) ? c->gpart[id] : nullptr; m.gsplits = c->gsp[id];
+    m.gpart = (adam && c->gsp[id] > 1) ? c->gpart[id] : nullptr; m.gsplits = c->gsp[id]; m.gparts = c->gparts[id];
     ab.total_blocks += (int)((K / 64) * (N / 64));
   };
   // matrices whose gradient may arrive as partial sums go first: their blocks have the longer chain of loads
@@ -450,7 +453,7 @@ int forward_f32(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uint
   const bool bf = false;
   const int B = (int)d.B, Dh = (int)d.Dh, SN = (int)c->stats_n;
   // progressive ablation (the paper's component table): the head reads the last stage that is switched on
-  const int level = c->cfg.ablation == 0 ? 5 : (int)c->cfg.ablation;
+  const int level = c->level();
   const void *feat = c->Hg;
   {
     Prof p(c, "embed_cache");
@@ -583,7 +586,7 @@ int forward_bf16(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uin
   const int sp_down = fuse ? 1 : c->sp_down, sp_fnr = fuse ? 1 : c->sp_fnr, sp_head = fuse ? 1 : c->sp_head;
   if (steps > 1 && (steps > c->steps_max || mode != CODE_ENCODE || c->online)) return fail(c, FADE_E_INVALID_ARG, "multi-step pass not available");
   // progressive ablation (the paper's component table): the head reads the last stage that is switched on
-  const int level = c->cfg.ablation == 0 ? 5 : (int)c->cfg.ablation;
+  const int level = c->level();
   const void *feat = c->Hg;
   const bool conv_fused = level >= 2 && d.D == 32 && d.T <= 128 && d.k * 32 <= d.Kc && d.Kc <= 128;
   {
@@ -736,7 +739,7 @@ int forward_rows(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uin
   const Dims &d = c->d;
   hipStream_t s = c->stream;
   const int B = (int)d.B, Dh = (int)d.Dh, dl = (int)d.dl, De = (int)d.De, SN = (int)c->stats_n;
-  const int level = c->cfg.ablation == 0 ? 5 : (int)c->cfg.ablation;
+  const int level = c->level();
   auto F = [](void *p) { return static_cast<float *>(p); };
   const void *feat = level == 1 ? c->Hg : level == 2 ? c->Hmix : c->Hc;
   auto args = [&](int N, const RowsOp &op0, void *C, int ldc) {
@@ -841,7 +844,7 @@ GemmArgs args_x(fade_ctx *c, const void *dY, int Kred, int Nout, const void *wt_
 GemmArgs args_w(fade_ctx *c, const void *L, int ldL, const void *LT, int Kw, const void *R, int N, int id, int id_pair = -1) {
   GemmArgs g{};
   float *G = c->grad;
-  g.M = Kw; g.N = N; g.K = (int)c->Bp; g.ldc = N; g.W = R;
+  g.M = Kw; g.N = N; g.K = (int)c->Bp; g.ldc = N; g.W = R; g.weight = id + 1;
   g.C = G + c->lay.off[id];
   if (id_pair >= 0) g.C3 = G + c->lay.off[id_pair];
   if (c->bf16) {
@@ -878,9 +881,8 @@ int run_phase(fade_ctx *c, const char *name, const PhaseGemms &ph) {
     GemmGroup gg{};
     for (int i = 0; i < ph.n; ++i) {
       const GemmArgs &g = ph.g[i];
-      const bool alone = (ph.op[i] == GEMM_X_STORE && g.N % 256 == 0 && g.K >= 1024 && ((g.M + 255) / 256) * (g.N / 256) >= 256) ||
-                         (ph.op[i] == GEMM_W_TN && fade_gemm_tn2_ok(g.M, g.N, g.K));
-      if (alone && ph.op[i] == GEMM_W_TN && c->defer_tn2) HIP_TRY(c, fade_gemm_tn2_group_add(c->tn2q, g));  // launched at the end of the pass
+      const bool alone = ph.op[i] == GEMM_X_STORE && g.N % 256 == 0 && g.K >= 1024 && ((g.M + 255) / 256) * (g.N / 256) >= 256;
+      if (ph.op[i] == GEMM_W_TN && c->tn2_slot[g.weight - 1] >= 0) c->tn2q.g[c->tn2_slot[g.weight - 1]] = g;  // launched at the end of the pass
       else if (alone) HIP_TRY(c, fade_gemm(ph.op[i], true, g, c->stream));
       else HIP_TRY(c, fade_gemm_group_add(gg, ph.op[i], g));
     }
@@ -889,6 +891,63 @@ int run_phase(fade_ctx *c, const char *name, const PhaseGemms &ph) {
     for (int i = 0; i < ph.n; ++i) HIP_TRY(c, fade_gemm(ph.op[i] == GEMM_W_TN ? GEMM_W : ph.op[i], false, ph.g[i], c->stream));
   }
   return FADE_OK;
+}
+// A weight gradient as a product over the batch: dW[M][N] of parameter id (and pair: columns interleaved per 64); level: the
+// ablation level from which the matrix takes part.
+struct WeightGrad { int id, pair, M, N, level; };
+
+// Weight gradients on 256 x 256 tiles feed nothing but the optimiser: they wait for the end of the backward pass and run as ONE
+// launch, whose workgroups share the tiles' contractions out in equal pieces (fade_tile_plan). The order of the tiles:
+// neighbours behind one another, in blocks of 2 x 4.
+int plan_weight_gradients(fade_ctx *c, const WeightGrad *gw, int n_gw) try {
+  for (int &v : c->tn2_slot) v = -1;
+  std::vector<uint32_t> order;
+  std::vector<std::pair<int, std::vector<size_t>>> at;  // per matrix: its row of gw, its tiles' places in the order
+  for (int i = 0; i < n_gw; ++i) {
+    if (!fade_gemm_tn2_ok(gw[i].M, gw[i].N, (int)c->Bp) || c->level() < gw[i].level || at.size() == 8) continue;
+    const uint32_t p = (uint32_t)at.size();
+    const int tm = gw[i].M / 256, tn = gw[i].N / 256;
+    at.emplace_back(i, std::vector<size_t>((size_t)tm * tn));
+    for (int m = 0; m < tm; m += 2)
+      for (int n = 0; n < tn; n += 4)
+        for (int mm = m; mm < m + 2 && mm < tm; ++mm)
+          for (int nn = n; nn < n + 4 && nn < tn; ++nn) {
+            at.back().second[(size_t)mm * tn + nn] = order.size();
+            order.push_back(p << 24 | (uint32_t)mm << 12 | (uint32_t)nn);
+          }
+  }
+  if (order.empty()) return FADE_OK;
+  Tn2Group &tg = c->tn2q;
+  tg.count = (int)at.size();
+  tg.tiles = (int)order.size();
+  tg.plan = fade_tile_plan(tg.tiles, (int)(c->Bp / 64));
+  uint32_t *dev = nullptr;
+  int rc = dev_alloc(c, &dev, order.size());
+  if (rc) return rc;
+  tg.order = dev;
+  HIP_TRY(c, hipMemcpyAsync(dev, order.data(), order.size() * sizeof(uint32_t), hipMemcpyHostToDevice, c->stream));
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  for (size_t p = 0; p < at.size(); ++p) {
+    const WeightGrad &w = gw[at[p].first];
+    std::vector<uint8_t> parts;
+    for (size_t seq : at[p].second) parts.push_back((uint8_t)fade_tile_parts(tg.plan, fade_tile_of_seq(tg.plan, (int)seq)));
+    const int most = *std::max_element(parts.begin(), parts.end());
+    c->tn2_slot[w.id] = (int)p;
+    if (most == 1) continue;  // every tile whole: straight to the gradient array
+    uint8_t *dp = nullptr;
+    if ((rc = dev_alloc(c, &dp, parts.size()))) return rc;
+    HIP_TRY(c, hipMemcpyAsync(dp, parts.data(), parts.size(), hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    for (int id : {w.id, w.pair}) {
+      if (id < 0) continue;
+      c->gsp[id] = most;
+      c->gparts[id] = dp;
+      if ((rc = dev_alloc(c, &c->gpart[id], (size_t)most * c->lay.len[id]))) return rc;
+    }
+  }
+  return FADE_OK;
+} catch (const std::bad_alloc &) {
+  return FADE_E_OOM;
 }
 TransposeArgs tr_desc(fade_ctx *c, const void *src, int ld, void *dst, const float *stats, const float *gamma, const float *beta) {
   TransposeArgs t{};
@@ -909,11 +968,10 @@ int backward(fade_ctx *c, const WinSrc &ws, const uint8_t *targets, long long ts
   auto Gp = [&](int id) { return G + c->lay.off[id]; };
   const int RB = (B + fade_rows_per_block(B) - 1) / fade_rows_per_block(B);
   ReduceBatch rq{};  // second-stage reductions nothing in here waits for: one launch before Adam
-  c->tn2q.count = 0;
   int rc;
   // ablation level: the head's gradient enters the chain at the level's feature vector; the stages behind it do not run
   // and their parameters keep a zero gradient (their Adam step is then exactly zero)
-  const int level = c->cfg.ablation == 0 ? 5 : (int)c->cfg.ablation;
+  const int level = c->level();
   const void *feat = level >= 5 ? c->Hout : level >= 3 ? c->Hc : level == 2 ? c->Hmix : c->Hg;
   void *dfeat = level >= 5 ? c->dHout : level >= 3 ? c->dHc : c->dHmix1;
   if (bf) {  // the loss gradient, and in the same launch the two left operands the forward pass never stores: LN(H_coarse), LN(H_mix), row-major
@@ -1091,8 +1149,7 @@ int backward(fade_ctx *c, const WinSrc &ws, const uint8_t *targets, long long ts
   // operand copies and the per-symbol tables
   if (c->tn2q.count > 0) {  // the weight gradients that waited: their operands are activations and gradients of this pass, all still in place
     Prof p(c, "gemms_weights");
-    HIP_TRY(c, fade_gemm_tn2_group_launch(c->tn2q, s));
-    c->tn2q.count = 0;
+    HIP_TRY(c, fade_gemm_tn2_launch(c->tn2q, s));
   }
   {
     Prof p(c, "adam_matrices");
@@ -1121,7 +1178,7 @@ int backward_rows(fade_ctx *c, const WinSrc &ws, const uint8_t *targets, long lo
   hipStream_t s = c->stream;
   const int B = (int)d.B, Dh = (int)d.Dh, De = (int)d.De, dl = (int)d.dl, D = (int)d.D, SN = (int)c->stats_n;
   const int RB = (B + fade_rows_per_block(B) - 1) / fade_rows_per_block(B);
-  const int level = c->cfg.ablation == 0 ? 5 : (int)c->cfg.ablation;
+  const int level = c->level();
   auto F = [](void *p) { return static_cast<float *>(p); };
   auto Gp = [&](int id) { return c->grad + c->lay.off[id]; };
   const void *feat = level >= 5 ? c->Hout : level >= 3 ? c->Hc : level == 2 ? c->Hmix : c->Hg;
@@ -1562,43 +1619,14 @@ int fade_create(const fade_config *cfg, fade_ctx **out) {
       // workgroup slots they run on half the chip, and two ranges make that second round a full one. The Adam pass pays
       // 15 us for the two extra 16 MiB slices, which B = 4096 only just gets back (phases 114 / 123 -> 106 / 115 us) and
       // B = 16384 does (445 / 460 -> 375 / 470, step 3.74 -> 3.64 ms): from 8192 rows on, with W_up and W_m of the same phases.
-      const struct { int id, pair, M, N; } gw[] = {{P_WO, -1, (int)d.Dh, 256}, {P_WF, -1, (int)d.De, (int)d.Dh}, {P_WFG, P_WFV, (int)d.Dh, (int)(2 * d.De)},
-                                                    {P_WDOWN, -1, (int)d.Dh, (int)d.dl}, {P_WUP, -1, (int)d.dl, (int)d.Dh}, {P_WM, -1, (int)d.Dc, (int)d.Dh},
-                                                    {P_WC, -1, (int)d.Dh, (int)d.Dh}, {P_WR, -1, (int)d.Dh, (int)d.Dh}};
-      // Weight gradients on 256 x 256 tiles feed nothing but the optimiser: with two or more of them they wait for the end
-      // of the backward pass and run as ONE launch with the same number of ranges of the batch for every matrix, so that
-      // all workgroups are equally long; the count is the smallest that gives at least two workgroups per compute unit
-      // and wastes least of the last round (D_h = 2048, D_e = D_cache = 512, B = 16384: 192 tiles x 4 ranges = 3 rounds of
-      // 256, 192 MiB of slices for the Adam pass to add up; launched one by one, with 4 / 8 / 16 ranges until each launch
-      // had 256 workgroups: 320 MiB). FADE_TN2_DEFER=0 keeps the launches apart.
-      int tn2_total = 0, tn2_count = 0, tn2_sp = 0;
-      for (const auto &w : gw)
-        if (fade_gemm_tn2_ok(w.M, w.N, (int)Bp)) { tn2_total += (w.M / 256) * (w.N / 256); ++tn2_count; }
-      const char *defer_env = getenv("FADE_TN2_DEFER");
-      if (tn2_count >= 2 && tn2_count <= 8 && !(defer_env && defer_env[0] == '0')) {
-        const int nkb = (int)(Bp / 64);
-        double best = 0.0;
-        for (int sp = 1; sp <= 16; sp *= 2) {
-          if (nkb % sp || nkb / sp < 8 || tn2_total * sp < 512) continue;
-          const int blocks = tn2_total * sp;
-          const double fill = (double)blocks / (((blocks + 255) / 256) * 256);
-          if (fill > best + 1e-9) { best = fill; tn2_sp = sp; }
-        }
-        c->defer_tn2 = tn2_sp > 0;
-      }
+      // level: the ablation level from which the matrix takes part
+      const WeightGrad gw[] = {{P_WC, -1, (int)d.Dh, (int)d.Dh, 4}, {P_WR, -1, (int)d.Dh, (int)d.Dh, 2},
+                                                           {P_WFG, P_WFV, (int)d.Dh, (int)(2 * d.De), 5}, {P_WF, -1, (int)d.De, (int)d.Dh, 5},
+                                                           {P_WM, -1, (int)d.Dc, (int)d.Dh, 1}, {P_WO, -1, (int)d.Dh, 256, 1},
+                                                           {P_WDOWN, -1, (int)d.Dh, (int)d.dl, 3}, {P_WUP, -1, (int)d.dl, (int)d.Dh, 3}};
+      TRY_ALLOC(plan_weight_gradients(c, gw, (int)(sizeof gw / sizeof gw[0])));
       for (const auto &w : gw) {
-        if (fade_gemm_tn2_ok(w.M, w.N, (int)Bp)) {  // 256 x 256 tiles, one workgroup per compute unit: ranges until every unit has one
-          const int tiles256 = (w.M / 256) * (w.N / 256), nkb = (int)(Bp / 64);
-          int sp = 1;
-          if (c->defer_tn2) sp = tn2_sp;
-          else while (sp < 16 && tiles256 * sp * 2 <= 256 && nkb % (sp * 2) == 0 && nkb / (sp * 2) >= 8) sp *= 2;
-          if (sp > 1) {
-            c->gsp[w.id] = sp;
-            TRY_ALLOC(dev_alloc(c, &c->gpart[w.id], (size_t)sp * c->lay.len[w.id]));
-            if (w.pair >= 0) { c->gsp[w.pair] = sp; TRY_ALLOC(dev_alloc(c, &c->gpart[w.pair], (size_t)sp * c->lay.len[w.pair])); }
-          }
-          continue;
-        }
+        if (c->tn2_slot[w.id] >= 0) continue;
         const int tiles = fade_gemm_tn_tiles(w.M, w.N);
         if (tiles <= 0) continue;
         const bool small = c->lay.len[w.id] <= (256u << 10);

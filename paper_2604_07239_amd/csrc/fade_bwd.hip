@@ -1296,10 +1296,11 @@ __global__ __launch_bounds__(256) void adam_refresh_kernel(AdamRefreshBatch ab) 
     const bool parts = !ab.refresh_only && M.gpart != nullptr;
     if (parts) {
       const size_t mat = (size_t)M.K * M.N;
+      const int slices = M.gparts ? M.gparts[(k0 >> 8) * (M.VN >> 8) + (((n0 >> 6) * M.vstride + M.vcol0) >> 8)] : M.gsplits;
 #pragma unroll
       for (int q = 0; q < 4; ++q) g[q] = fade_load4<NT>(M.gpart + (idx[q] - M.off));
 #pragma unroll 2
-      for (int sp = 1; sp < M.gsplits; ++sp)
+      for (int sp = 1; sp < slices; ++sp)
 #pragma unroll
         for (int q = 0; q < 4; ++q) g[q] += fade_load4<NT>(M.gpart + sp * mat + (idx[q] - M.off));
       if (ab.keep_sum) {

@@ -4,6 +4,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "fade_rules.h"
+
 typedef __bf16 bf16_t;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
@@ -135,6 +137,7 @@ struct GemmArgs {
   const float *bias;
   float *stats_out;       // optional [M][N / BN][2]
   const float *fold_s, *fold_t;  // EPI_GEGLU_FOLD: the folded LayerNorm's column vectors [N] (stats / stats_n: rows of A)
+  int weight;             // weight gradient: index of the parameter + 1 (0: not one)
   int col_groups;         // pipelined kernel: column ranges of the XCD split of the tile grid (1, 2, 4, 8; 0 = chosen by the launcher)
 };
 
@@ -147,14 +150,13 @@ struct GemmGroup {
   GemmArgs g[4];
 };
 
-// Weight gradients on 256 x 256 tiles (gemm_tn2_kernel's body) of several matrices in ONE launch: blocks [first_block[p],
-// first_block[p + 1]) are the tiles[p] x splits[p] workgroups of product p. A weight gradient feeds nothing but the
-// optimiser, so the products of a whole backward pass can wait for its end; with one range count for all of them the
-// workgroups are equally long and fill whole rounds of the chip.
+// Weight gradients on 256 x 256 tiles of several matrices in ONE launch (gemm_tn2_kernel). A weight gradient feeds nothing but the
+// optimiser, so the products of a whole backward pass can wait for its end. order[i]: the i-th tile as product << 24 |
+// row tile << 12 | column tile; the plan says which workgroup works on which rows of the batch of which tiles.
 struct Tn2Group {
-  int count;
-  int near;  // an XCD's units are consecutive ones (see tn2_block)
-  int splits[8], first_block[9];
+  int count, tiles;
+  FadeTilePlan plan;
+  const uint32_t *order;
   GemmArgs g[8];
 };
 

@@ -601,7 +601,6 @@ template <int OFF> __device__ __forceinline__ i32x2 tr_read8(uint32_t addr) {
 }
 __device__ __forceinline__ void tr_landed(i32x2 &v) { asm volatile("" : "+v"(v)); }
 __device__ __forceinline__ bf16x8 tr_pair(i32x2 lo, i32x2 hi) {
-  typedef __attribute__((ext_vector_type(4))) int i32x4;
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3));
 }
 
@@ -1081,12 +1080,10 @@ template <int PITCH> __device__ __forceinline__ int tn_swizzle(int r) {
   return PITCH >= 256 ? ((r & 3) << 2) : (((r >> 1) & 1) << 2);  // 512: the permutation stays inside a row's 256-byte half
 }
 
-// NW wavefronts as 2 (rows) x NW / 2 (columns); a 256 x 256 tile on eight of them hands its fp32 result to the epilogue in
-// slabs of 64 rows (as pipe2_body does), half the operand bytes and three quarters of the LDS reads per flop of 128 x 128.
-template <int BM, int BN, int STAGES, int NW = 4>
-__device__ __forceinline__ void tn_body(const GemmArgs &g, int bid, int split = 0, int nsplit = 1, int mt_in = -1, int nt_in = -1) {
+template <int BM, int BN, int STAGES>
+__device__ __forceinline__ void tn_body(const GemmArgs &g, int bid, int split = 0, int nsplit = 1) {
   typedef bf16_t AT;
-  constexpr int BK = 64, KS = 4;
+  constexpr int BK = 64, KS = 4, NW = 4;
   constexpr int WN = NW / 2;
   constexpr int TM = BM / 64, TN = BN / (32 * WN);
   constexpr int PA = BM / 8, PB = BN / 8;          // 16-byte pieces per row
@@ -1102,8 +1099,8 @@ __device__ __forceinline__ void tn_body(const GemmArgs &g, int bid, int split = 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
   const int ntn = g.N / BN, ntm = g.M / BM;
-  int mt = mt_in, nt = nt_in;
-  if (mt_in < 0 && !tile_of_block(bid, ntm, ntn, 8, mt, nt)) return;
+  int mt, nt;
+  if (!tile_of_block(bid, ntm, ntn, 8, mt, nt)) return;
   const int m0 = mt * BM, n0 = nt * BN;
   const int nkb = g.K / BK / nsplit, kb0 = split * nkb;  // this workgroup's range of the contraction (the batch)
 
@@ -1214,31 +1211,6 @@ __device__ __forceinline__ void tn_body(const GemmArgs &g, int bid, int split = 
   }
 
   wait_vmcnt<0>();
-  if constexpr (BM > 128) {
-    static_assert(TM % 2 == 0 && BN % 128 == 0, "slab epilogue");
-#pragma unroll
-    for (int p = 0; p < BM / 64; ++p) {
-      constexpr int ROWS_PER_WAVE = 32 * TM;
-      const int owner = (p * 64) / ROWS_PER_WAVE, i0 = ((p * 64) % ROWS_PER_WAVE) / 32;
-      __syncthreads();  // the ring, or the previous slab, is no longer being read
-      if (wm == owner) {
-#pragma unroll
-        for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-              const int row = ii * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
-              const int col = (wn * TN + j) * 32 + (lane & 31);
-              Cs[row * LDC + col] = acc[i0 + ii][j][e];
-            }
-      }
-      __syncthreads();
-#pragma unroll
-      for (int h = 0; h < BN / 128; ++h)
-        epilogue<EPI_GRAD, AT, 64, 128, LDC, NW * 64>(g, Cs + h * 128, m0 + p * 64, n0 + h * 128, nt * (BN / 128) + h, tid, split);
-    }
-  } else {
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -1252,37 +1224,218 @@ __device__ __forceinline__ void tn_body(const GemmArgs &g, int bid, int split = 
       }
   __syncthreads();
   epilogue<EPI_GRAD, AT, BM, BN>(g, Cs, m0, n0, nt, tid, split);
-  }
 }
 template <int BM, int BN, int STAGES>
 __global__ __launch_bounds__(256) void gemm_tn_kernel(GemmArgs g) {
   tn_body<BM, BN, STAGES>(g, (int)blockIdx.x);
 }
-// 256 x 256 tiles on eight wavefronts, one workgroup per compute unit; blockIdx.y is the range of the batch.
-// Workgroups go to the eight XCDs round-robin and each XCD has its own L2: an XCD takes whole units of eight workgroups,
-// a unit being a block of 2 x 4 tiles of one range of the batch (2 + 4 operand panels for 8 tiles; one row or column of
-// tiles would need 1 + 8).
-// near: an XCD's units are consecutive ones (unit = tile block within a range, ranges outermost), so the units it runs
-// side by side are neighbouring tile blocks of one range and share operand panels in its L2 (D_h x D_h over four ranges:
-// an XCD's four units are 4 x 8 tiles of one range, 4 + 8 panels for 32 tiles instead of 4 x (2 + 4)).
-__device__ __forceinline__ void tn2_block(const GemmArgs &g, int bid, int nsplit, bool near) {
-  const int ntm = g.M / 256, ntn = g.N / 256, tiles = ntm * ntn;
-  if (ntm % 2 == 0 && ntn % 4 == 0 && (tiles / 8 * nsplit) % 8 == 0) {
-    const int x = bid & 7, r = bid >> 3, w = r & 7, U = tiles / 8;
-    const int u = near ? x * (U * nsplit / 8) + (r >> 3) : x + 8 * (r >> 3), b = u % U, split = u / U;
-    tn_body<256, 256, 2, 8>(g, 0, split, nsplit, (b / (ntn / 4)) * 2 + (w >> 2), (b % (ntn / 4)) * 4 + (w & 3));
+// ---------------------------------------------------------------------------------------------------
+// The same on 256 x 256 tiles, eight wavefronts (2 x 4, 128 x 64 each), for large batches: all such matrices of a backward pass in
+// one launch, one workgroup per compute unit (Tn2Group). The tiles' contractions are laid end to end and cut into 256 pieces of
+// equal length (fade_tile_plan: D_h = 2048, D_cache = D_e = 512: 192 tiles, three quarters of one per workgroup), so no round of
+// the chip is left half full whatever the number of tiles, and a tile arrives as two slices of the batch instead of the four that
+// equal ranges took; the Adam pass adds a tile's slices in order (tile_parts). Members of a group start at different rows of
+// the batch, but the same members of an XCD's groups work on neighbouring tiles (2 x 4) and the same rows, so six operand
+// panels in its L2 serve eight workgroups.
+// The K loop is pipe2_body's: units of 64 rows of the batch (32 KiB per operand, rows of 512 bytes as they lie in memory), L through a
+// ring of three, R through a ring of two, one hand-over per unit, requests with scalar offsets spread between the matrix
+// instructions. It does not stop at the end of a tile: the requests run two units ahead into the next tile while the sums
+// leave as they lie in the registers (a lane holds a column: 128-byte runs).
+// B = 16384 (411 Gflop): the launch 412 -> TN2_US us, the Adam pass behind it ADAM_OLD -> ADAM_NEW (half the slices to add).
+// ---------------------------------------------------------------------------------------------------
+constexpr int TN2_LDS = 160 * 1024;
+__global__ __launch_bounds__(512, 1) void gemm_tn2_kernel(Tn2Group tg) {
+  constexpr int NW = 8, TM = 4, TN = 2, AUNITS = 3, UNIT = 64 * 512, R_RING = AUNITS * UNIT, CH = UNIT / 1024 / NW;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 2, wn = wave & 3;
+  const FadeTilePlan pl = tg.plan;
+  const int xcd = (int)blockIdx.x & 7, slot = (int)blockIdx.x >> 3, grp = slot / pl.wgs, member = slot - grp * pl.wgs;
+  if (grp >= pl.groups) return;
+  const int begin = member * pl.per_wg, end = fade_tile_end(pl, tg.tiles, xcd, grp, member);
+  if (begin >= end) return;
+
+  // requests: one cursor two units ahead of the arithmetic. f_*: tile (position in the group), rows left of it, operand addresses
+  struct Cursor { int j, k; } f{begin / pl.units, begin % pl.units}, c = f;
+  const bf16_t *pa = nullptr, *pb = nullptr;  // first row of the unit the cursor stands at, first column of the tile
+  int lda = 0, ldb = 0, rows = 0;             // rows of L that exist from that row on
+  auto open = [&](const Cursor &t) {
+    const uint32_t e = (uint32_t)__builtin_amdgcn_readfirstlane((int)tg.order[fade_tile_seq(pl, xcd, grp, t.j)]);
+    const GemmArgs &g = tg.g[e >> 24];
+    lda = g.lda; ldb = g.ldb;
+    pa = static_cast<const bf16_t *>(g.A) + (size_t)t.k * 64 * lda + (size_t)((e >> 12) & 0xfff) * 256;
+    pb = static_cast<const bf16_t *>(g.W) + (size_t)t.k * 64 * ldb + (size_t)(e & 0xfff) * 256;
+    rows = g.a_rows - t.k * 64;
+  };
+  open(f);
+  auto advance = [&](int u) {  // to the unit behind u (counted like begin); nothing past the end
+    if (u + 1 >= end) return;
+    if (++f.k == pl.units) { f.k = 0; ++f.j; open(f); }
+    else { pa += (size_t)64 * lda; pb += (size_t)64 * ldb; rows -= 64; }
+  };
+  // DMA c = wave + NW q covers rows 2c, 2c + 1 of the unit; lane i lands at byte 16 i of that KiB, i.e. at row 2c + i / 32, piece i % 32,
+  // and fetches the piece whose index is XORed with 4 (row % 4); as NW is even, row % 4 is 2 (wave % 2) + i / 32 for every q
+  const int lrow = lane >> 5, lpiece = ((lane & 31) ^ ((((wave & 1) << 1) + lrow) << 2)) << 4;
+  auto request_l = [&](int q, int s) {
+    const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(pa), 0, 0x7fffffff, 0x00020000);
+    const int r = 2 * (wave + NW * q);
+    auto *dst = (__attribute__((address_space(3))) void *)(smem + s * UNIT + (wave + NW * q) * 1024);
+    if (rows >= 64) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst, 16, lrow * lda * 2 + lpiece, r * lda * 2, 0, 0);
+    } else {  // past the batch: any finite row, its partner row of R is zero
+      const int rr = r + lrow < rows ? r + lrow : rows - 1;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst, 16, rr * lda * 2 + lpiece, 0, 0, 0);
+    }
+  };
+  auto request_r = [&](int q, int s) {
+    const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(pb), 0, 0x7fffffff, 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)(smem + R_RING + s * UNIT + (wave + NW * q) * 1024), 16,
+                                             lrow * ldb * 2 + lpiece, 2 * (wave + NW * q) * ldb * 2, 0, 0);
+  };
+
+  // addresses this lane supplies to the transposing reads of k-step 0 (see tn_body); tile i's differ in two bits that no row changes
+  const int s16 = lane & 15, r0 = (lane >> 5) * 8 + (s16 >> 2), mh = (lane >> 4) & 1;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
+  const uint32_t col = (uint32_t)(r0 * 512 + ((2 * mh + ((s16 & 3) >> 1)) << 4) + (s16 & 1) * 8);
+  uint32_t l_off[TM], r_off[TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) l_off[i] = lds0 + col + ((((wm * TM + i) ^ (r0 & 3)) & 7) << 6);
+#pragma unroll
+  for (int j = 0; j < TN; ++j) r_off[j] = lds0 + R_RING + col + ((((wn * TN + j) ^ (r0 & 3)) & 7) << 6);
+
+  f32x16 acc[TM][TN];
+  auto clear = [&] {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+  };
+  clear();
+  typedef std::integral_constant<int, 0> I0;
+  typedef std::integral_constant<int, 1> I1;
+  typedef std::integral_constant<int, 2> I2;
+  typedef std::integral_constant<int, 3> I3;
+#pragma unroll
+  for (int q = 0; q < CH; ++q) request_l(q, 0);
+#pragma unroll
+  for (int q = 0; q < CH; ++q) request_r(q, 0);
+  if (begin + 1 < end) {
+    advance(begin);
+#pragma unroll
+    for (int q = 0; q < CH; ++q) request_l(q, 1);
+#pragma unroll
+    for (int q = 0; q < CH; ++q) request_r(q, 1);
+    advance(begin + 1);
+    wait_vmcnt<2 * CH>();
   } else {
-    tn_body<256, 256, 2, 8>(g, bid % tiles, bid / tiles, nsplit);
+    wait_vmcnt<0>();
   }
-}
-__global__ __launch_bounds__(512, 1) void gemm_tn2_kernel(GemmArgs g, int nsplit) { tn2_block(g, (int)blockIdx.x, nsplit, false); }
-// The same for several matrices in one launch (Tn2Group). Where every product's block count is a multiple of 8 (all the
-// shapes of the benchmark configurations), a block's position within its product goes to the same XCD as in a launch of
-// its own; otherwise only the L2 reuse of the later products suffers.
-__global__ __launch_bounds__(512, 1) void gemm_tn2_group_kernel(Tn2Group tg) {
-  int p = 0;
-  while (p + 1 < tg.count && (int)blockIdx.x >= tg.first_block[p + 1]) ++p;
-  tn2_block(tg.g[p], (int)blockIdx.x - tg.first_block[p], tg.splits[p], tg.near != 0);
+  bare_barrier();
+
+  i32x2 llo[2][TM], lhi[2][TM], rlo[2][TN], rhi[2][TN];
+  auto read_l = [&](auto buf_c, auto ks_c, auto i_c, uint32_t base) {
+    constexpr int buf = decltype(buf_c)::value, ks = decltype(ks_c)::value, i = decltype(i_c)::value;
+    llo[buf][i] = tr_read8<ks * 16 * 512>(base + l_off[i]);
+    lhi[buf][i] = tr_read8<ks * 16 * 512 + 4 * 512>(base + l_off[i]);
+  };
+  auto read_r = [&](auto buf_c, auto ks_c, auto j_c, uint32_t base) {
+    constexpr int buf = decltype(buf_c)::value, ks = decltype(ks_c)::value, j = decltype(j_c)::value;
+    rlo[buf][j] = tr_read8<ks * 16 * 512>(base + r_off[j]);
+    rhi[buf][j] = tr_read8<ks * 16 * 512 + 4 * 512>(base + r_off[j]);
+  };
+  bf16x8 lf[TM], rf[TN];
+  auto landed = [&](auto buf_c) {
+    constexpr int buf = decltype(buf_c)::value;
+    lds_wait<0>();
+#pragma unroll
+    for (int i = 0; i < TM; ++i) { tr_landed(llo[buf][i]); tr_landed(lhi[buf][i]); lf[i] = tr_pair(llo[buf][i], lhi[buf][i]); }
+#pragma unroll
+    for (int j = 0; j < TN; ++j) { tr_landed(rlo[buf][j]); tr_landed(rhi[buf][j]); rf[j] = tr_pair(rlo[buf][j], rhi[buf][j]); }
+  };
+  // one k-step as in pipe2_body: the reads of the next one and the requests in front of the pairs of matrix instructions
+  auto kstep = [&](auto buf_c, auto nks_c, uint32_t lbase, uint32_t rbase, auto reads_c, auto req) {
+    typedef std::integral_constant<int, 1 - decltype(buf_c)::value> NB;
+    constexpr bool reads = decltype(reads_c)::value;
+    auto pair = [&](auto i_c) {
+      constexpr int i = decltype(i_c)::value;
+      if constexpr (reads) {
+        if constexpr (i < TN) { read_r(NB{}, nks_c, i_c, rbase); read_l(NB{}, nks_c, i_c, lbase); }
+        else read_l(NB{}, nks_c, i_c, lbase);
+      }
+      req(i);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lf[i], rf[j], acc[i][j], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    pair(I0{}); pair(I1{}); pair(I2{}); pair(I3{});
+  };
+  // the sums of the tile the arithmetic has finished, or of the part of it that is this workgroup's
+  auto store = [&] {
+    const uint32_t e = (uint32_t)__builtin_amdgcn_readfirstlane((int)tg.order[fade_tile_seq(pl, xcd, grp, c.j)]);
+    const GemmArgs &g = tg.g[e >> 24];
+    const int slice = member - fade_tile_first(pl, c.j);
+    const int m = (int)((e >> 12) & 0xfff) * 256 + wm * 128 + (lane >> 5) * 4, n = (int)(e & 0xfff) * 256 + wn * 64;
+    // a pair of matrices, columns interleaved per 64: the wavefront's 64 columns belong to one of them
+    float *dst = static_cast<float *>(g.C3 && (n & 64) ? g.C3 : g.C);
+    const int width = g.C3 ? g.N / 2 : g.N, n1 = g.C3 ? (n >> 7) * 64 : n;
+    dst += (size_t)slice * g.M * width + (size_t)m * width + n1 + (lane & 31);
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int e16 = 0; e16 < 16; ++e16)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) dst[(size_t)(i * 32 + (e16 >> 2) * 8 + (e16 & 3)) * width + j * 32] = acc[i][j][e16];
+    clear();
+  };
+#pragma unroll
+  for (int j = 0; j < 1; ++j) {
+    read_r(I0{}, I0{}, I0{}, 0); read_r(I0{}, I0{}, I1{}, 0);
+    read_l(I0{}, I0{}, I0{}, 0); read_l(I0{}, I0{}, I1{}, 0); read_l(I0{}, I0{}, I2{}, 0); read_l(I0{}, I0{}, I3{}, 0);
+  }
+  int aslot = 0, afill = 2;
+  auto none = [](int) {};
+  // mode 2: unit u + 2 is requested; 1: nothing is left to request; 0: the last unit
+  auto unit = [&](int u, auto mode_c) {
+    constexpr int mode = decltype(mode_c)::value;
+    const uint32_t lb = aslot * UNIT, rb = ((u - begin) & 1) * UNIT;
+    auto req_l0 = [&](int i) { if constexpr (mode == 2) { if (i < CH / 2) request_l(i, afill); } };
+    auto req_l1 = [&](int i) { if constexpr (mode == 2) { if (i < CH / 2) request_l(CH / 2 + i, afill); } };
+    auto req_r = [&](int i) { if constexpr (mode == 2) request_r(i, (u - begin) & 1); };
+    landed(I0{});
+    kstep(I0{}, I1{}, lb, rb, std::true_type{}, req_l0);
+    landed(I1{});
+    kstep(I1{}, I2{}, lb, rb, std::true_type{}, req_l1);
+    landed(I0{});
+    kstep(I0{}, I3{}, lb, rb, std::true_type{}, none);
+    landed(I1{});
+    if constexpr (mode != 0) {
+      if constexpr (mode == 2) wait_vmcnt<CH>();  // unit u + 1 has landed, L of unit u + 2 may be in flight
+      else wait_vmcnt<0>();
+      __builtin_amdgcn_sched_barrier(0);
+      bare_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      aslot = aslot == AUNITS - 1 ? 0 : aslot + 1;
+      afill = afill == AUNITS - 1 ? 0 : afill + 1;
+      kstep(I1{}, I0{}, aslot * UNIT, rb ^ UNIT, std::true_type{}, req_r);
+      if constexpr (mode == 2) advance(u + 2);
+    } else {
+      kstep(I1{}, I0{}, lb, rb, std::false_type{}, none);
+    }
+    if (++c.k == pl.units || mode == 0) {
+      store();
+      c.k = 0; ++c.j;
+    }
+  };
+  int u = begin;
+  for (; u + 2 < end; ++u) unit(u, I2{});
+  if (u + 1 < end) {
+    unit(u, I1{});
+    ++u;
+  }
+  unit(u, I0{});
 }
 
 // Several independent products in ONE launch (a block-uniform switch picks the problem and its kernel body): the products
@@ -1457,63 +1610,25 @@ hipError_t launch_tn(const GemmArgs &g, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_tn2(const GemmArgs &g, hipStream_t s) {
-  constexpr size_t lds = (size_t)2 * 64 * (256 + 256) * 2;
-  static_assert(lds >= (size_t)64 * 260 * sizeof(float) && lds <= 160 * 1024, "LDS per compute unit");
-  static bool attr_done = false;
-  if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_tn2_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    attr_done = true;
-  }
-  const int splits = g.splits > 1 ? g.splits : 1;
-  if (g.M % 256 || g.N % 256 || g.K <= 0 || g.K % (splits * 64) || g.a_rows <= 0 || g.a_rows > g.K || g.lda % 8 || g.ldb % 8) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(gemm_tn2_kernel, dim3((g.M / 256) * (g.N / 256) * splits), dim3(512), lds, s, g, splits);
-  return hipGetLastError();
-}
-
 }  // namespace
-hipError_t fade_gemm_tn2_group_add(Tn2Group &tg, const GemmArgs &g) {
-  const int splits = g.splits > 1 ? g.splits : 1;
-  if (tg.count >= 8 || !fade_gemm_tn2_ok(g.M, g.N, g.K) || g.K % (splits * 64) || g.a_rows <= 0 || g.a_rows > g.K || g.lda % 8 || g.ldb % 8)
-    return hipErrorInvalidValue;
-  const int p = tg.count, blocks = (g.M / 256) * (g.N / 256) * splits;
-  if (p == 0) tg.first_block[0] = 0;
-  tg.g[p] = g; tg.splits[p] = splits; tg.first_block[p + 1] = tg.first_block[p] + blocks;
-  tg.count = p + 1;
-  return hipSuccess;
-}
-hipError_t fade_gemm_tn2_group_launch(const Tn2Group &tg, hipStream_t s) {
-  if (tg.count <= 0) return hipSuccess;
-  constexpr size_t lds = (size_t)2 * 64 * (256 + 256) * 2;
+// tg.plan, tg.order and tg.tiles belong to the context; product p of the group is matrix p of the plan's order.
+hipError_t fade_gemm_tn2_launch(const Tn2Group &tg, hipStream_t s) {
   static bool attr_done = false;
   if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_tn2_group_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_tn2_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, TN2_LDS);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
-  // the products with the most workgroups first: their blocks then start on a multiple of 256, and the units an XCD runs
-  // side by side belong to one product
-  Tn2Group o{};
-  o.count = tg.count;
-  int idx[8];
-  for (int p = 0; p < tg.count; ++p) idx[p] = p;
-  for (int i = 1; i < tg.count; ++i)
-    for (int j = i; j > 0; --j) {
-      const int a = idx[j - 1], b = idx[j];
-      if (tg.first_block[b + 1] - tg.first_block[b] <= tg.first_block[a + 1] - tg.first_block[a]) break;
-      idx[j - 1] = b; idx[j] = a;
-    }
-  o.first_block[0] = 0;
+  int tiles = 0;
   for (int p = 0; p < tg.count; ++p) {
-    const int q = idx[p];
-    o.g[p] = tg.g[q]; o.splits[p] = tg.splits[q];
-    o.first_block[p + 1] = o.first_block[p] + (tg.first_block[q + 1] - tg.first_block[q]);
+    const GemmArgs &g = tg.g[p];
+    if (!g.A || !g.W || !g.C || !fade_gemm_tn2_ok(g.M, g.N, g.K) || g.K != tg.plan.units * 64 || g.a_rows <= 0 || g.a_rows > g.K || g.K - g.a_rows >= 64 ||
+        g.lda % 8 || g.ldb % 8 || g.lda < g.M || g.ldb < g.N || g.lda > (1 << 20) || g.ldb > (1 << 20))
+      return hipErrorInvalidValue;
+    tiles += (g.M / 256) * (g.N / 256);
   }
-  static int near = -1;
-  if (near < 0) { const char *e = getenv("FADE_TN2_NEAR"); near = (e && e[0] == '0') ? 0 : 1; }
-  o.near = near;
-  hipLaunchKernelGGL(gemm_tn2_group_kernel, dim3(o.first_block[o.count]), dim3(512), lds, s, o);
+  if (tg.count <= 0 || tg.count > 8 || tiles != tg.tiles || !tg.order) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(gemm_tn2_kernel, dim3(256), dim3(512), TN2_LDS, s, tg);
   return hipGetLastError();
 }
 namespace {
@@ -1610,13 +1725,12 @@ static bool tn_shape(int M, int N, int &kind, int &bm, int &bn) {
   if (N % 64 == 0) { kind = GK_TN_64x64; bm = 64; bn = 64; return true; }
   return false;
 }
-// A weight gradient that gets the 256 x 256 tiles of gemm_tn2_kernel, as a launch of its own: large batches, 16 tiles or
-// more (fewer would need ranges of the batch shorter than the pipeline is worth). At B = 4096 the grouped 128 x 128 tiles
-// are faster (gate and router phases 104 / 106 us against 138 / 138, and 31 us less in the Adam pass).
+// A weight gradient that gets the 256 x 256 tiles of gemm_tn2_kernel: large batches, 16 tiles or more. At B = 4096 the grouped
+// 128 x 128 tiles are faster (gate and router phases 104 / 106 us against 138 / 138, and 31 us less in the Adam pass).
 bool fade_gemm_tn2_ok(int M, int N, int K) {
   static int mink = -1;  // rows of the batch from which the 256 x 256 weight-gradient tiles are used (sweeps: FADE_TN2_MINK)
   if (mink < 0) { const char *e = getenv("FADE_TN2_MINK"); mink = e ? atoi(e) : 8192; }
-  return M > 0 && M % 256 == 0 && N % 256 == 0 && K >= mink && (M / 256) * (N / 256) >= 16 && fade_gemm_tune() != 26;
+  return M > 0 && M % 256 == 0 && N % 256 == 0 && K % 64 == 0 && K >= mink && (M / 256) * (N / 256) >= 16;
 }
 int fade_gemm_tn_tiles(int M, int N) {
   int kind, bm, bn;
@@ -1718,7 +1832,6 @@ hipError_t fade_gemm(int op, bool bf16, const GemmArgs &g, hipStream_t s) {
         if (g.N % 128 == 0) return launch_pipe<64, 128, 4, EPI_GRAD, true>(g, s);
         return launch_pipe<64, 64, 4, EPI_GRAD, true>(g, s);
       case GEMM_W_TN:     // the same from row-major operands (no copies): A = L [a_rows][lda], W = R [K][ldb]
-        if (fade_gemm_tn2_ok(g.M, g.N, g.K)) return launch_tn2(g, s);
         if (g.N % 128 == 0) {
           if (fade_gemm_tune() == 7 && g.M % 128 == 0) return launch_tn<128, 128, 4>(g, s);
           return launch_tn<64, 128, 4>(g, s);

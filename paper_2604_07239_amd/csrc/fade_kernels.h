@@ -15,12 +15,11 @@ enum {
 // Launch one of the model step's products (see fade_gemm.hip). bf16 selects the MFMA path (activations
 // bf16, W in fragment order) or the fp32 path (activations fp32, W plain [K][N]).
 hipError_t fade_gemm(int op, bool bf16, const GemmArgs &g, hipStream_t s);
-bool fade_gemm_tn2_ok(int M, int N, int K);  // dW[M][N] over a batch of K rows runs on 256 x 256 tiles as a launch of its own
+bool fade_gemm_tn2_ok(int M, int N, int K);  // dW[M][N] over a batch of K rows runs on 256 x 256 tiles, in one launch with the others of a backward pass
 int fade_gemm_tn_tiles(int M, int N);  // workgroups per batch range of a grouped weight-gradient product dW[M][N]; 0: shape not supported
 hipError_t fade_gemm_group_add(GemmGroup &gg, int op, const GemmArgs &g);
 hipError_t fade_gemm_group_launch(const GemmGroup &gg, hipStream_t s);
-hipError_t fade_gemm_tn2_group_add(Tn2Group &tg, const GemmArgs &g);  // g as for GEMM_W_TN with fade_gemm_tn2_ok(g.M, g.N, g.K)
-hipError_t fade_gemm_tn2_group_launch(const Tn2Group &tg, hipStream_t s);
+hipError_t fade_gemm_tn2_launch(const Tn2Group &tg, hipStream_t s);  // products as for GEMM_W_TN, each with fade_gemm_tn2_ok(g.M, g.N, g.K)
 
 enum { CODE_NONE = 0, CODE_ENCODE = 1, CODE_DECODE = 2, CODE_RANGES = 3 };  // CODE_RANGES: leave each row's coding interval for a later pass
 
@@ -325,9 +324,11 @@ struct AdamMat {
   float *fold_part;        // [K / 64][2][VN] when gamma is set
   int first_block;
   // gradient left as gsplits partial sums [gsplits][K][N] over ranges of the batch (NULL: complete in the gradient array);
-  // the Adam pass adds them in range order and stores the sum in the gradient array
+  // the Adam pass adds them in range order and stores the sum in the gradient array. gparts: the 256 x 256 tiles of the virtual
+  // matrix [K / 256][VN / 256] have gparts[tile] <= gsplits partial sums (NULL: gsplits each)
   const float *gpart;
   int gsplits;
+  const uint8_t *gparts;
 };
 struct AdamRefreshBatch {
   int count, total_blocks;

@@ -32,3 +32,34 @@ constexpr bool fade_streamed(bool bf16, bool online, size_t params, size_t B, si
   const size_t MB = (size_t)1 << 20;
   return bf16 && (online ? 16 * params + 20 * 2 * B * Dh >= 184 * MB : 2 * params >= 128 * MB);
 }
+
+// How `tiles` equal contractions of `units` steps each are shared out over 256 workgroups, 32 on each of 8 XCDs. On an XCD, `groups`
+// groups of `wgs` workgroups take `tpg` tiles each: the group's tiles lie end to end and its members take per_wg steps each, so a
+// tile is cut where a member's share ends and arrives as one partial sum per member that worked on it. Small groups (at most
+// eight members) keep the members' starting points few, so that the same members of an XCD's groups read the same operand rows
+// at the same time; among them the one that takes the least steps. Tile j of group g of XCD x is tile (x tpg + j) groups + g of the
+// order: the g-th neighbours of one another.
+struct FadeTilePlan {
+  int tpg, wgs, groups, units, per_wg;
+};
+constexpr FadeTilePlan fade_tile_plan(int tiles, int units) {
+  FadeTilePlan best{0, 1, 32, units, 0};
+  for (int wgs = 1; wgs <= 8; ++wgs) {
+    const int groups = 32 / wgs, tpg = (tiles + 8 * groups - 1) / (8 * groups), per = (tpg * units + wgs - 1) / wgs;
+    if (best.tpg == 0 || per < best.per_wg) best = FadeTilePlan{tpg, wgs, groups, units, per};
+  }
+  return best;
+}
+constexpr int fade_tile_seq(const FadeTilePlan &p, int xcd, int group, int j) { return (xcd * p.tpg + j) * p.groups + group; }
+constexpr int fade_tile_of_seq(const FadeTilePlan &p, int seq) { return seq / p.groups % p.tpg; }  // its place j in its group
+constexpr int fade_tile_first(const FadeTilePlan &p, int j) { return j * p.units / p.per_wg; }  // first member on tile j of a group
+constexpr int fade_tile_parts(const FadeTilePlan &p, int j) {  // members on it = partial sums of it
+  return ((j + 1) * p.units - 1) / p.per_wg - fade_tile_first(p, j) + 1;
+}
+// end of a member's steps (its first is member * per_wg); the last groups may have fewer tiles than tpg
+constexpr int fade_tile_end(const FadeTilePlan &p, int tiles, int xcd, int group, int member) {
+  int have = 0;
+  while (have < p.tpg && fade_tile_seq(p, xcd, group, have) < tiles) ++have;
+  const int end = (member + 1) * p.per_wg;
+  return end < have * p.units ? end : have * p.units;
+}

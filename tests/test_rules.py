@@ -81,3 +81,43 @@ int main() {
 
 def test_which_sizes_go_past_the_caches(tmp_path):
     _run(STREAMED, tmp_path)
+
+
+TILE_PLAN = """
+#include <stdio.h>
+#include <vector>
+#include "fade_rules.h"
+int main() {
+  for (int tiles = 1; tiles <= 1100; tiles = tiles < 300 ? tiles + 1 : tiles + 37)
+    for (int units : {1, 2, 7, 64, 129, 256}) {
+      const FadeTilePlan p = fade_tile_plan(tiles, units);
+      if (p.wgs < 1 || p.wgs > 8 || p.wgs * p.groups > 32) { printf("tiles=%d units=%d: %d x %d workgroups on an XCD\\n", tiles, units, p.groups, p.wgs); return 1; }
+      std::vector<int> steps((size_t)tiles * units, 0), slices((size_t)tiles * 64, 0);
+      for (int x = 0; x < 8; ++x)
+        for (int s = 0; s < 32; ++s) {  // as a workgroup goes through its share
+          const int g = s / p.wgs, member = s % p.wgs;
+          if (g >= p.groups) continue;
+          for (int u = member * p.per_wg; u < fade_tile_end(p, tiles, x, g, member); ++u) {
+            const int j = u / units, seq = fade_tile_seq(p, x, g, j), slice = member - fade_tile_first(p, j);
+            if (seq >= tiles || fade_tile_of_seq(p, seq) != j || slice < 0 || slice >= fade_tile_parts(p, j)) {
+              printf("tiles=%d units=%d: tile %d slice %d of %d\\n", tiles, units, seq, slice, fade_tile_parts(p, j)); return 1;
+            }
+            ++steps[(size_t)seq * units + u % units];
+            slices[(size_t)seq * 64 + slice] = 1;
+          }
+        }
+      for (size_t i = 0; i < steps.size(); ++i)
+        if (steps[i] != 1) { printf("tiles=%d units=%d: step %zu of tile %zu taken %d times\\n", tiles, units, i % units, i / units, steps[i]); return 1; }
+      for (int t = 0; t < tiles; ++t)
+        for (int k = 0; k < fade_tile_parts(p, fade_tile_of_seq(p, t)); ++k)
+          if (!slices[(size_t)t * 64 + k]) { printf("tiles=%d units=%d: tile %d has no slice %d\\n", tiles, units, t, k); return 1; }
+    }
+  return 0;
+}
+"""
+
+
+def test_tile_plan_takes_every_step_once(tmp_path):
+    """Weight gradients at large batches: the workgroups' shares cover every step of every tile exactly once, and a tile's partial
+    sums are the slices that the optimiser adds."""
+    _run(TILE_PLAN, tmp_path)

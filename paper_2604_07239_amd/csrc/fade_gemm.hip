@@ -551,16 +551,20 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g) {
 }
 
 // ---------------------------------------------------------------------------------------------------
-// bf16 MFMA core, pipelined: both operands stream global -> LDS with the asynchronous LDS-DMA loads
-// (global_load_lds_dwordx4: 16 bytes per lane land at M0-base + lane * 16, no registers involved), STAGES
-// K blocks deep. Each 1 KiB DMA is one MFMA fragment (32 rows x 16 k): the lanes gather 16-byte row pieces
-// of the row-major A (two lanes per 32-byte run) or read a ready-made fragment of W, so that the later
-// ds_read_b128 of a fragment is one contiguous, conflict-free 1 KiB read. Synchronisation is by hand:
-// s_waitcnt vmcnt(n) for this wavefront's own DMAs, then a bare s_barrier (a __syncthreads() would drain
-// every outstanding load and with it the pipeline).
-//   A: plain row-major bf16 [M][lda] (rows past M are clamped to row M-1 and never stored)
-//   W: bf16 fragments as written by the weight preparation
-//   grid.y > 1: split K, each block leaves an fp32 partial tile (EPI_PARTIAL)
+// bf16 MFMA core, pipelined: both operands stream global -> LDS with the asynchronous LDS-DMA loads (16 bytes per lane land at
+// M0-base + lane * 16, no registers involved) through a ring of STAGES units of 64 along K. A: plain row-major bf16 [M][lda] (rows
+// past M are clamped to row M - 1 and never stored), W: bf16 fragments as written by the weight preparation.
+// Synchronisation is by hand: s_waitcnt vmcnt(n) for this wavefront's own DMAs, then a bare s_barrier (a __syncthreads() would
+// drain every outstanding load and with it the pipeline).
+// Four wavefronts, one or two per SIMD, so nothing hides a wavefront's own waits and the loop has to (unit_loop): the fragments of
+// the next half unit are read from LDS under the matrix instructions of this one, into a second set of registers. A unit's hand-over
+// (DMA wait, barrier) sits between its halves: its reads are complete by then, so behind the barrier its slot is free for
+// the unit STAGES further on, whose requests go between the matrix instructions. Their addresses are a buffer resource, lane
+// offsets and a scalar offset: no vector instructions.
+// M = 1024, N = K = 2048, 64 x 128 tiles with the mix / gate epilogue: 18.7 / 18.4 us with the first fragments of a unit waited
+// for behind its barrier and the requests in one burst in front of them, 16.2 / 15.7 now, where what a compute unit is
+// fed with from the L2 (24 KiB per unit) bounds it.
+// grid.y > 1: split K, each block leaves an fp32 partial tile (EPI_PARTIAL)
 // ---------------------------------------------------------------------------------------------------
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
@@ -570,9 +574,12 @@ __device__ __forceinline__ void bare_barrier() {
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 }
-__device__ __forceinline__ void dma16(const bf16_t *src, unsigned char *lds_chunk) {
-  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
-                                   (__attribute__((address_space(3))) void *)lds_chunk, 16, 0, 0);
+// The LDS-DMA of one KiB: lane offset + scalar offset from the resource's base, to lds + lane * 16.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t dma_rsrc(const void *base) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, 0x7fffffff, 0x00020000);
+}
+__device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t off, unsigned char *lds) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)lds, 16, lane_off, off, 0, 0);
 }
 
 // LDS fragment reads whose completion is waited for by hand: the compiler would wait for every outstanding read before the
@@ -604,160 +611,174 @@ __device__ __forceinline__ bf16x8 tr_pair(i32x2 lo, i32x2 hi) {
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3));
 }
 
-template <int BM, int BN, int STAGES, int EPI, bool BROW, int NW = 4>
+template <int I> using Int = std::integral_constant<int, I>;
+template <int N, typename F> __device__ __forceinline__ void static_for(F &&f) {  // f(Int<0>) ... f(Int<N - 1>)
+  if constexpr (N > 0) {
+    static_for<N - 1>(f);
+    f(Int<N - 1>{});
+  }
+}
+// NM matrix instructions mm(i); in front of them, evenly spread and in this order, NR reads rd(i) and ND requests dma(i)
+template <int NM, int NR, int ND, typename MM, typename RD, typename DMA>
+__device__ __forceinline__ void woven(MM &&mm, RD &&rd, DMA &&dma) {
+  static_for<NM>([&](auto i_c) {
+    constexpr int i = decltype(i_c)::value, r0 = (i * NR + NM - 1) / NM, r1 = ((i + 1) * NR + NM - 1) / NM, d0 = i * ND / NM, d1 = (i + 1) * ND / NM;
+    static_for<r1 - r0>([&](auto k) { rd(Int<r0 + decltype(k)::value>{}); });
+    static_for<d1 - d0>([&](auto k) { dma(Int<d0 + decltype(k)::value>{}); });
+    __builtin_amdgcn_sched_barrier(0);
+    mm(i_c);
+    __builtin_amdgcn_sched_barrier(0);
+  });
+}
+// wait until at most min(units, MAX) units of ND requests each are in flight
+template <int MAX, int ND> __device__ __forceinline__ void wait_units(int units) {
+  if constexpr (MAX == 0) wait_vmcnt<0>();
+  else if (units >= MAX) wait_vmcnt<MAX * ND>();
+  else wait_units<MAX - 1, ND>(units);
+}
+// The loop of pipe_body and tn_body over U units of four k-steps in two groups. read(buf, h, i, slot): read i < NR of group h of the unit in
+// `slot` into register set buf; landed(buf): they have; mm(buf, i): matrix instruction i < NM of the group in that set;
+// request(i, u, slot): request i < ND of unit u; unit_done().
+template <int STAGES, int NM, int NR, int ND, typename READ, typename LANDED, typename MM, typename REQ, typename DONE>
+__device__ __forceinline__ void unit_loop(int U, READ &&read, LANDED &&landed, MM &&mm, REQ &&request, DONE &&unit_done) {
+  static_assert(STAGES >= 2 && (STAGES - 1) * ND <= 63, "vmcnt range");
+  for (int s = 0; s < STAGES && s < U; ++s) static_for<ND>([&](auto i) { request(i, s, s); });
+  wait_units<STAGES - 1, ND>(U - 1);
+  bare_barrier();  // unit 0 is in LDS for everyone
+  static_for<NR>([&](auto i) { read(Int<0>{}, Int<0>{}, i, 0); });
+  int slot = 0;
+  // In the tail (the last STAGES units) nothing is left to request and the wait asks how many units are in flight; reads behind the last unit fetch old bytes of the
+  // ring and are dropped. One copy of the matrix instructions per loop: with several, the compiler moves the sums between
+  // register sets where the paths meet.
+  auto unit = [&](int u, auto tail_c) {
+    constexpr bool tail = decltype(tail_c)::value;
+    landed(Int<0>{});
+    woven<NM, NR, 0>([&](auto i) { mm(Int<0>{}, i); }, [&](auto i) { read(Int<1>{}, Int<1>{}, i, slot); }, [](auto) {});
+    landed(Int<1>{});  // every read of unit u
+    if constexpr (tail) wait_units<STAGES - 2, ND>(U - 2 - u);
+    else wait_vmcnt<(STAGES - 2) * ND>();  // unit u + 1 has landed, younger ones may be in flight
+    __builtin_amdgcn_sched_barrier(0);
+    bare_barrier();  // unit u + 1 is in LDS for everyone, and everyone is done reading unit u
+    __builtin_amdgcn_sched_barrier(0);
+    const int free_slot = slot;
+    slot = slot + 1 == STAGES ? 0 : slot + 1;
+    woven<NM, NR, tail ? 0 : ND>([&](auto i) { mm(Int<1>{}, i); }, [&](auto i) { read(Int<0>{}, Int<0>{}, i, slot); },
+                                 [&](auto i) { request(i, u + STAGES, free_slot); });
+    unit_done();
+  };
+  int u = 0;
+  for (; u + STAGES < U; ++u) unit(u, std::false_type{});
+  for (; u < U; ++u) unit(u, std::true_type{});
+  landed(Int<0>{});  // the reads behind the last unit too: their registers are free from here on
+}
+
+// SUMS: several ranges of K may be walked in turn (sum_splits; EPI_PARTIAL outside grouped launches)
+template <int BM, int BN, int STAGES, int EPI, bool SUMS = EPI == EPI_PARTIAL>
 __device__ __forceinline__ void pipe_body(const GemmArgs &g, int bid, int split, int nsplit) {
   typedef bf16_t AT;
-  constexpr int BK = 64, KS = 4;
-  constexpr int WN = NW / 2;                         // wavefronts 2 (rows) x WN (columns)
-  constexpr int TM = BM / 64, TN = BN / (32 * WN);   // 32x32 tiles per wavefront
+  constexpr int BK = 64, KS = 4, NW = 4;
+  constexpr int TM = BM / 64, TN = BN / 64;          // 32x32 tiles per wavefront, 2 x 2 wavefronts
+  constexpr int GK = 2;                              // k-steps per group of reads
   constexpr int BFR = BN / 32;
   constexpr int A_BYTES = BM * 128;                  // A stage: BM rows of 64 k (128 bytes), 16-byte pieces XOR-swizzled
   constexpr int ACH = BM / 8 / NW;                   // A DMAs per wavefront and stage (one DMA = 8 rows x 128 bytes)
-  constexpr int BCH = BROW ? BN / 8 / NW : BFR * KS / NW;  // W DMAs per wavefront and stage (one fragment, or 8 rows x 128 bytes)
-  constexpr int LPW = ACH + BCH;
+  constexpr int BCH = BFR * KS / NW;                 // W DMAs per wavefront and stage (one fragment)
   constexpr int STAGE_BYTES = A_BYTES + BFR * KS * 1024, LDC = BN + 4;
-  static_assert((BM / 8) % NW == 0 && (BFR * KS) % NW == 0 && (BN / 8) % NW == 0, "chunk split");
-  static_assert((STAGES - 2) * LPW <= 63, "vmcnt range");
+  static_assert((BM / 8) % NW == 0 && (BFR * KS) % NW == 0, "chunk split");
   extern __shared__ __align__(16) unsigned char smem[];
   float *Cs = reinterpret_cast<float *>(smem);
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / 2, wn = wave % 2;
   const int ntn = g.N / BN, ntm = (g.M + BM - 1) / BM;
   int mt, nt;
   if (!tile_of_block(bid, ntm, ntn, g.col_groups, mt, nt)) return;
   const int m0 = mt * BM, n0 = nt * BN;
-  const int ksplit = g.K / nsplit, nkb = ksplit / BK;
-  const int ksteps = g.K / 16;
+  // sum_splits: this workgroup walks all K ranges itself and adds their sums in range order, which is
+  // bit for bit what the reducing kernels make of separate partials; otherwise it owns the one range `split`.
+  const bool fuse = SUMS && g.sum_splits != 0;
+  const int range = g.K / nsplit / BK, kb0 = fuse ? 0 : split * range, units = fuse ? g.K / BK : range;
 
   // DMA sources of this wavefront for one stage.
   // A: DMA c covers rows 8c .. 8c+7; lane i fetches row r = 8c + i/8, 16-byte piece (i % 8) ^ ((r / 2) % 8): eight lanes
   //    read one 128-byte run of a row, and the XOR spreads the pieces that a later fragment read touches (16 rows
   //    x one piece per quarter-wavefront) over all 64 LDS banks.
   // W: DMA c is fragment c / 4 (32 columns), k-step c % 4, already contiguous.
-  const bf16_t *src[LPW];
+  const auto rsrc_a = dma_rsrc(static_cast<const bf16_t *>(g.A) + (size_t)m0 * g.lda + kb0 * BK);
+  const auto rsrc_w = dma_rsrc(static_cast<const bf16_t *>(g.W) + (size_t)n0 * g.K + (size_t)kb0 * KS * 512);
+  uint32_t a_vo[ACH], w_so[BCH];
 #pragma unroll
   for (int q = 0; q < ACH; ++q) {
-    const int c = wave + NW * q;
-    int row = m0 + c * 8 + (lane >> 3);
-    row = row < g.M ? row : g.M - 1;
-    const int sw = ((c * 8 + (lane >> 3)) >> 1) & 7;
-    src[q] = static_cast<const bf16_t *>(g.A) + (size_t)row * g.lda + (((lane & 7) ^ sw) << 3);
+    const int r = (wave + NW * q) * 8 + (lane >> 3), rc = m0 + r < g.M ? r : g.M - 1 - m0;
+    a_vo[q] = (uint32_t)(rc * g.lda * 2 + (((lane & 7) ^ ((r >> 1) & 7)) << 4));
   }
 #pragma unroll
   for (int q = 0; q < BCH; ++q) {
     const int c = wave + NW * q;
-    if (BROW) {  // row-major [N][ldb]: same 8-rows-per-DMA, XOR-swizzled scheme as A
-      const int row = n0 + c * 8 + (lane >> 3);
-      const int sw = ((c * 8 + (lane >> 3)) >> 1) & 7;
-      src[ACH + q] = static_cast<const bf16_t *>(g.W) + (size_t)row * g.ldb + (((lane & 7) ^ sw) << 3);
-    } else {
-      const int fr = c / KS, ks = c % KS;
-      src[ACH + q] = static_cast<const bf16_t *>(g.W) + (((size_t)(n0 / 32 + fr) * ksteps + ks) * 64 + lane) * 8;
-    }
+    w_so[q] = (uint32_t)(((c / KS) * (g.K / 16) + c % KS) * 1024);
   }
-  auto issue = [&](int slot, int kb) {  // kb: 64-wide k block counted from the start of K
+  auto request = [&](auto i_c, int u, int slot) {  // request i of unit u
+    constexpr int i = decltype(i_c)::value;
     unsigned char *base = smem + slot * STAGE_BYTES;
-#pragma unroll
-    for (int q = 0; q < ACH; ++q) dma16(src[q] + (size_t)kb * BK, base + (wave + NW * q) * 1024);
-#pragma unroll
-    for (int q = 0; q < BCH; ++q) dma16(src[ACH + q] + (BROW ? (size_t)kb * BK : (size_t)kb * KS * 512), base + A_BYTES + (wave + NW * q) * 1024);
+    if constexpr (i < ACH) dma16(rsrc_a, a_vo[i], u * (BK * 2), base + (wave + NW * i) * 1024);
+    else dma16(rsrc_w, (uint32_t)lane * 16, w_so[i - ACH] + u * (KS * 1024), base + A_BYTES + (wave + NW * (i - ACH)) * 1024);
   };
 
-
-  // fragment read offsets inside a stage: row r, k-step ks, half h -> r * 128 + (((2 ks + h) ^ ((r / 2) & 7)) * 16)
-  // as LDS addresses of this lane per k-step (A tile i of the wavefront 4096 bytes = 32 rows further on; W fragment j
-  // KS KiB further on, or 32 rows for a row-major W)
+  // fragment read offsets inside a stage: row r, k-step ks, half h -> r * 128 + (((2 ks + h) ^ ((r / 2) & 7)) * 16), i.e. k-step 0's
+  // with 32 ks XORed in (A tile i of the wavefront 4096 bytes = 32 rows further on; W fragment j KS KiB further on)
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
-  const int a_sw = (lane >> 1) & 7, a_half = lane >> 5;  // tile rows start at multiples of 32, so (r / 2) & 7 == (lane / 2) & 7
-  uint32_t a_ks[KS], b_ks[KS];
+  const uint32_t a_first = lds0 + (wm * TM * 32 + (lane & 31)) * 128 + (((lane >> 5) ^ ((lane >> 1) & 7)) << 4);
+  const uint32_t w_first = lds0 + A_BYTES + wn * TN * KS * 1024 + lane * 16;
+  bf16x8 af[2][GK][TM], bf[2][GK][TN];
+  auto read = [&](auto buf_c, auto h_c, auto i_c, int slot) {  // read i of group h of the unit in `slot`
+    constexpr int buf = decltype(buf_c)::value, i = decltype(i_c)::value, k = i / (TM + TN), x = i % (TM + TN), ks = decltype(h_c)::value * GK + k;
+    if constexpr (x < TN) bf[buf][k][x] = lds_read16<ks * 1024 + x * KS * 1024>(w_first + slot * STAGE_BYTES);
+    else af[buf][k][x - TN] = lds_read16<(x - TN) * 4096>((a_first + slot * STAGE_BYTES) ^ (ks * 32));
+  };
+  auto landed = [&](auto buf_c) {
+    constexpr int buf = decltype(buf_c)::value;
+    lds_wait<0>();
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    a_ks[ks] = lds0 + (wm * TM * 32 + (lane & 31)) * 128 + (((2 * ks + a_half) ^ a_sw) << 4);
-    b_ks[ks] = BROW ? lds0 + A_BYTES + (wn * TN * 32 + (lane & 31)) * 128 + (((2 * ks + a_half) ^ a_sw) << 4)
-                    : lds0 + A_BYTES + (((wn * TN * KS) * 64 + lane) << 4);
-  }
-
-  // EPI_PARTIAL with sum_splits: this workgroup walks all K ranges itself and adds their sums in range order, which is
-  // bit for bit what the reducing kernels make of separate partials; otherwise it owns the one range `split`.
-  const bool fuse = EPI == EPI_PARTIAL && g.sum_splits != 0;
-  const int sp_first = fuse ? 0 : split, sp_end = fuse ? nsplit : split + 1;
-  f32x16 acc[TM][TN], tot[EPI == EPI_PARTIAL ? TM : 1][EPI == EPI_PARTIAL ? TN : 1];
-  for (int sp = sp_first; sp < sp_end; ++sp) {
-  const int kb0 = sp * nkb;
+    for (int k = 0; k < GK; ++k) {
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+      for (int i = 0; i < TM; ++i) lds_landed(af[buf][k][i]);
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-  if (sp != sp_first) bare_barrier();  // every wavefront has read the last stages of the previous range
-#pragma unroll
-  for (int s = 0; s < STAGES - 1; ++s)
-    if (s < nkb) issue(s, kb0 + s);
-
-  for (int kb = 0; kb < nkb; ++kb) {
-    // stage kb must have landed; up to STAGES-2 younger stages may stay in flight
-    if (kb + STAGES - 2 < nkb) wait_vmcnt<(STAGES - 2) * LPW>();
-    else wait_vmcnt<0>();
-    bare_barrier();  // everyone's part of stage kb is in LDS, and everyone is done reading stage kb-1
-    if (kb + STAGES - 1 < nkb) issue((kb + STAGES - 1) % STAGES, kb0 + kb + STAGES - 1);
-    // fragments of k-step ks+1 are fetched from LDS while the matrix cores work on k-step ks: reads through lds_read16 with
-    // hand-placed waits (the compiler's own wait in front of a group of matrix instructions also covers the reads just issued
-    // for the next group)
-    const uint32_t st = (kb % STAGES) * STAGE_BYTES;
-    bf16x8 af[2][TM], bf[2][TN];
-    auto fetch = [&](auto buf_c, auto ks_c) {
-      constexpr int buf = decltype(buf_c)::value, ks = decltype(ks_c)::value;
-      static_assert(TM <= 4 && TN <= 4, "tiles per wavefront");
-      const uint32_t sa = a_ks[ks] + st, sb = BROW ? b_ks[ks] + st : b_ks[0] + st;
-      constexpr int BO = BROW ? 0 : ks * 1024, BS = BROW ? 4096 : KS * 1024;
-      af[buf][0] = lds_read16<0>(sa);
-      if constexpr (TM > 1) af[buf][1] = lds_read16<4096>(sa);
-      if constexpr (TM > 2) af[buf][2] = lds_read16<8192>(sa);
-      if constexpr (TM > 3) af[buf][3] = lds_read16<12288>(sa);
-      bf[buf][0] = lds_read16<BO>(sb);
-      if constexpr (TN > 1) bf[buf][1] = lds_read16<BO + BS>(sb);
-      if constexpr (TN > 2) bf[buf][2] = lds_read16<BO + 2 * BS>(sb);
-      if constexpr (TN > 3) bf[buf][3] = lds_read16<BO + 3 * BS>(sb);
-    };
-    auto mfma = [&](auto buf_c, auto newer_c) {  // newer: reads issued after this buffer's, allowed to stay in flight
-      constexpr int buf = decltype(buf_c)::value;
-      lds_wait<decltype(newer_c)::value>();
-#pragma unroll
-      for (int i = 0; i < TM; ++i) lds_landed(af[buf][i]);
-#pragma unroll
-      for (int j = 0; j < TN; ++j) lds_landed(bf[buf][j]);
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[buf][i], bf[buf][j], acc[i][j], 0, 0, 0);
-    };
-    typedef std::integral_constant<int, 0> I0;
-    typedef std::integral_constant<int, 1> I1;
-    typedef std::integral_constant<int, 2> I2;
-    typedef std::integral_constant<int, 3> I3;
-    typedef std::integral_constant<int, TM + TN> INext;
-    static_assert(KS == 4, "k-steps per stage");
-    fetch(I0{}, I0{});
-    fetch(I1{}, I1{});
-    mfma(I0{}, INext{});
-    fetch(I0{}, I2{});
-    mfma(I1{}, INext{});
-    fetch(I1{}, I3{});
-    mfma(I0{}, INext{});
-    mfma(I1{}, I0{});
-  }
-  if constexpr (EPI == EPI_PARTIAL) {
+      for (int j = 0; j < TN; ++j) lds_landed(bf[buf][k][j]);
+    }
+  };
+  f32x16 acc[TM][TN], tot[SUMS ? TM : 1][SUMS ? TN : 1];
+  auto clear = [&] {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        if (sp == sp_first) tot[i][j] = acc[i][j];
-        else tot[i][j] += acc[i][j];
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+  };
+  clear();
+  auto mm = [&](auto buf_c, auto x_c) {
+    constexpr int buf = decltype(buf_c)::value, x = decltype(x_c)::value, k = x / (TM * TN), i = x % (TM * TN) / TN, j = x % TN;
+    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[buf][k][i], bf[buf][k][j], acc[i][j], 0, 0, 0);
+  };
+  int in_range = 0;
+  bool first = true;
+  auto unit_done = [&] {
+    if constexpr (SUMS) {
+      if (++in_range == range) {
+        in_range = 0;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            if (first) tot[i][j] = acc[i][j];
+            else tot[i][j] += acc[i][j];
+          }
+        first = false;
+        clear();
       }
-  }
-  }
+    }
+  };
+  unit_loop<STAGES, TM * TN * GK, (TM + TN) * GK, ACH + BCH>(units, read, landed, mm, request, unit_done);
 
   wait_vmcnt<0>();
   __syncthreads();
@@ -769,15 +790,15 @@ __device__ __forceinline__ void pipe_body(const GemmArgs &g, int bid, int split,
       for (int e = 0; e < 16; ++e) {
         const int row = (wm * TM + i) * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
         const int col = (wn * TN + j) * 32 + (lane & 31);
-        if constexpr (EPI == EPI_PARTIAL) Cs[row * LDC + col] = tot[i][j][e];
+        if constexpr (SUMS) Cs[row * LDC + col] = tot[i][j][e];
         else Cs[row * LDC + col] = acc[i][j][e];
       }
   __syncthreads();
   epilogue<EPI, AT, BM, BN>(g, Cs, m0, n0, nt, tid, fuse ? 0 : split);
 }
-template <int BM, int BN, int STAGES, int EPI, bool BROW>
-__global__ __launch_bounds__(256, (STAGES == 2 && BM * BN <= 128 * 128) ? 2 : 1) void gemm_pipe_kernel(GemmArgs g) {
-  pipe_body<BM, BN, STAGES, EPI, BROW>(g, (int)blockIdx.x, (int)blockIdx.y, g.sum_splits ? g.splits : (int)gridDim.y);
+template <int BM, int BN, int STAGES, int EPI>
+__global__ __launch_bounds__(256, STAGES == 2 ? 2 : 1) void gemm_pipe_kernel(GemmArgs g) {
+  pipe_body<BM, BN, STAGES, EPI>(g, (int)blockIdx.x, (int)blockIdx.y, g.sum_splits ? g.splits : (int)gridDim.y);
 }
 
 
@@ -828,8 +849,7 @@ __device__ __forceinline__ void pipe2_body(const GemmArgs &g, int bid) {
   const int nku = g.K / 64;
 
   // DMA sources: a resource at the tile's first row / fragment, one lane offset each, and scalar offsets per request
-  const auto rsrc_a = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(static_cast<const bf16_t *>(g.A) + (size_t)m0 * g.lda), 0, 0x7fffffff, 0x00020000);
-  const auto rsrc_w = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(static_cast<const bf16_t *>(g.W) + (size_t)n0 * g.K), 0, 0x7fffffff, 0x00020000);
+  const auto rsrc_a = dma_rsrc(static_cast<const bf16_t *>(g.A) + (size_t)m0 * g.lda), rsrc_w = dma_rsrc(static_cast<const bf16_t *>(g.W) + (size_t)n0 * g.K);
   // A: DMA c = wave + NW q covers rows 8c .. 8c + 7, lane i piece (i % 8) ^ ((r / 2) % 8) of row r = 8c + i / 8; as NW is even,
   // (r / 2) % 8 is 4 (wave % 2) + i / 16 for every q
   const uint32_t a_vo = (uint32_t)((lane >> 3) * g.lda * 2 + (((lane & 7) ^ (((wave & 1) << 2) + (lane >> 4))) << 4)), w_vo = (uint32_t)lane * 16;
@@ -841,12 +861,10 @@ __device__ __forceinline__ void pipe2_body(const GemmArgs &g, int bid) {
     w_so[q] = (uint32_t)(((c / KS) * (g.K / 16) + c % KS) * 1024);
   }
   auto dma_a = [&](int q, int u, int slot) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_a, (__attribute__((address_space(3))) void *)(smem + slot * UNIT + (wave + NW * q) * 1024), 16, a_vo,
-                                             a_so + q * a_q + u * 128, 0, 0);
+    dma16(rsrc_a, a_vo, a_so + q * a_q + u * 128, smem + slot * UNIT + (wave + NW * q) * 1024);
   };
   auto dma_w = [&](int q, int u, int slot) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_w, (__attribute__((address_space(3))) void *)(smem + A_RING + slot * UNIT + (wave + NW * q) * 1024), 16, w_vo,
-                                             w_so[q] + u * (KS * 1024), 0, 0);
+    dma16(rsrc_w, w_vo, w_so[q] + u * (KS * 1024), smem + A_RING + slot * UNIT + (wave + NW * q) * 1024);
   };
   // fragment reads: row r, piece p of a unit at r * 128 + ((p ^ ((r / 2) % 8)) * 16); k-step ks, half h reads piece 2 ks + h, i.e.
   // the address of k-step 0 with 32 ks XORed in (slots start at multiples of 128)
@@ -1083,56 +1101,100 @@ template <int PITCH> __device__ __forceinline__ int tn_swizzle(int r) {
 template <int BM, int BN, int STAGES>
 __device__ __forceinline__ void tn_body(const GemmArgs &g, int bid, int split = 0, int nsplit = 1) {
   typedef bf16_t AT;
-  constexpr int BK = 64, KS = 4, NW = 4;
-  constexpr int WN = NW / 2;
-  constexpr int TM = BM / 64, TN = BN / (32 * WN);
+  constexpr int BK = 64, NW = 4;
+  constexpr int TM = BM / 64, TN = BN / 64;
+  constexpr int GK = 2;                            // k-steps per group of reads
   constexpr int PA = BM / 8, PB = BN / 8;          // 16-byte pieces per row
   constexpr int RA = 64 / PA, RB = 64 / PB;        // rows per DMA
   constexpr int A_BYTES = BK * BM * 2, B_BYTES = BK * BN * 2;
   constexpr int ACH = BK / RA / NW, BCH = BK / RB / NW;  // DMAs per wavefront and stage
-  constexpr int LPW = ACH + BCH, STAGE_BYTES = A_BYTES + B_BYTES, LDC = BN + 4;
-  static_assert(PA >= 8 && PB >= 8 && (BK / RA) % NW == 0 && (BK / RB) % NW == 0 && BN % (32 * WN) == 0, "tile shape");
-  static_assert((STAGES - 2) * LPW <= 63, "vmcnt range");
+  constexpr int STAGE_BYTES = A_BYTES + B_BYTES, LDC = BN + 4;
+  static_assert(PA >= 8 && PB >= 8 && (BK / RA) % NW == 0 && (BK / RB) % NW == 0, "tile shape");
   extern __shared__ __align__(16) unsigned char smem[];
   float *Cs = reinterpret_cast<float *>(smem);
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / 2, wn = wave % 2;
   const int ntn = g.N / BN, ntm = g.M / BM;
   int mt, nt;
   if (!tile_of_block(bid, ntm, ntn, 8, mt, nt)) return;
   const int m0 = mt * BM, n0 = nt * BN;
-  const int nkb = g.K / BK / nsplit, kb0 = split * nkb;  // this workgroup's range of the contraction (the batch)
+  const int units = g.K / BK / nsplit, kb0 = split * units;  // this workgroup's range of the contraction (the batch)
 
   // DMA c of an operand covers rows c * R .. c * R + R - 1 of the stage; lane i lands at byte 16 i of that KiB, i.e. at
   // (row, piece) = (c * R + i / P, i % P), and fetches the piece whose index is XORed as described above.
-  int a_row[ACH], b_row[BCH];
-  const bf16_t *a_col[ACH], *b_src[BCH];
+  int a_row[ACH], a_piece[ACH];
+  uint32_t b_vo[BCH];
 #pragma unroll
   for (int q = 0; q < ACH; ++q) {
-    const int row = (wave + NW * q) * RA + lane / PA, piece = (lane % PA) ^ tn_swizzle<BM * 2>(row);
-    a_row[q] = row;
-    a_col[q] = static_cast<const bf16_t *>(g.A) + m0 + piece * 8;
+    a_row[q] = (wave + NW * q) * RA + lane / PA;
+    a_piece[q] = ((lane % PA) ^ tn_swizzle<BM * 2>(a_row[q])) * 16;
   }
 #pragma unroll
   for (int q = 0; q < BCH; ++q) {
-    const int row = (wave + NW * q) * RB + lane / PB, piece = (lane % PB) ^ tn_swizzle<BN * 2>(row);
-    b_row[q] = row;
-    b_src[q] = static_cast<const bf16_t *>(g.W) + (size_t)row * g.ldb + n0 + piece * 8;
+    const int row = (wave + NW * q) * RB + lane / PB;
+    b_vo[q] = (uint32_t)(row * g.ldb * 2 + ((lane % PB) ^ tn_swizzle<BN * 2>(row)) * 16);
   }
-  const int last_a = g.a_rows - 1;
-  auto issue = [&](int slot, int kb) {
+  uint32_t a_vo[ACH];
+#pragma unroll
+  for (int q = 0; q < ACH; ++q) a_vo[q] = (uint32_t)(a_row[q] * g.lda * 2 + a_piece[q]);
+  const bf16_t *a_src = static_cast<const bf16_t *>(g.A) + (size_t)kb0 * BK * g.lda + m0, *b_src = static_cast<const bf16_t *>(g.W) + (size_t)kb0 * BK * g.ldb + n0;
+  auto request = [&](auto i_c, int u, int slot) {  // request i of unit u
+    constexpr int i = decltype(i_c)::value;
     unsigned char *base = smem + slot * STAGE_BYTES;
-#pragma unroll
-    for (int q = 0; q < ACH; ++q) {
-      int r = kb * BK + a_row[q];
-      r = r < last_a ? r : last_a;  // past the batch: any finite row, its partner row of W is zero
-      dma16(a_col[q] + (size_t)r * g.lda, base + (wave + NW * q) * 1024);
+    if constexpr (i < ACH) {
+      const int rows = g.a_rows - (kb0 + u) * BK;  // that exist from the unit's first row on
+      const auto rs = dma_rsrc(a_src + (size_t)u * BK * g.lda);
+      if (rows >= BK) {
+        dma16(rs, a_vo[i], 0, base + (wave + NW * i) * 1024);
+      } else {  // past the batch: any finite row, its partner row of W is zero
+        const int r = a_row[i] < rows ? a_row[i] : rows - 1;
+        dma16(rs, r * g.lda * 2 + a_piece[i], 0, base + (wave + NW * i) * 1024);
+      }
+    } else {
+      dma16(dma_rsrc(b_src + (size_t)u * BK * g.ldb), b_vo[i - ACH], 0, base + A_BYTES + (wave + NW * (i - ACH)) * 1024);
     }
-#pragma unroll
-    for (int q = 0; q < BCH; ++q) dma16(b_src[q] + (size_t)kb * BK * g.ldb, base + A_BYTES + (wave + NW * q) * 1024);
   };
 
+  // address this lane supplies to the transposing loads of k-step 0 (first of the two loads; the second is 4 rows on):
+  // row 8 * (lane / 32) + (lane % 16) / 4, columns tile * 32 + 16 * ((lane / 16) % 2) + 4 * (lane % 4) .. + 3
+  const int s16 = lane & 15, r0 = (lane >> 5) * 8 + (s16 >> 2), mh = (lane >> 4) & 1;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
+  uint32_t a_off[TM], b_off[TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+    a_off[i] = lds0 + r0 * (BM * 2) + ((((wm * TM + i) * 4 + 2 * mh + ((s16 & 3) >> 1)) ^ tn_swizzle<BM * 2>(r0)) << 4) + (s16 & 1) * 8;
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+    b_off[j] = lds0 + A_BYTES + r0 * (BN * 2) + ((((wn * TN + j) * 4 + 2 * mh + ((s16 & 3) >> 1)) ^ tn_swizzle<BN * 2>(r0)) << 4) + (s16 & 1) * 8;
+  // rows 4 and 16 further on have the same (r & 3) and the same ((r >> 1) & 1): the permutation term does not change
+
+  // The transposing reads go through inline assembly with hand-placed waits (tr_read8 / lds_wait / tr_landed): issued through
+  // the builtin, the compiler orders every one of them behind the LDS-DMA just requested for a later stage
+  // (s_waitcnt vmcnt(0) in front of the first read), which exposes a full memory latency per stage.
+  i32x2 alo[2][GK][TM], ahi[2][GK][TM], blo[2][GK][TN], bhi[2][GK][TN];
+  auto read = [&](auto buf_c, auto h_c, auto i_c, int slot) {  // pair i of group h of the unit in `slot`
+    constexpr int buf = decltype(buf_c)::value, i = decltype(i_c)::value, k = i / (TM + TN), x = i % (TM + TN), ks = decltype(h_c)::value * GK + k;
+    if constexpr (x < TN) {
+      blo[buf][k][x] = tr_read8<ks * 16 * (BN * 2)>(b_off[x] + slot * STAGE_BYTES);
+      bhi[buf][k][x] = tr_read8<ks * 16 * (BN * 2) + 4 * (BN * 2)>(b_off[x] + slot * STAGE_BYTES);
+    } else {
+      alo[buf][k][x - TN] = tr_read8<ks * 16 * (BM * 2)>(a_off[x - TN] + slot * STAGE_BYTES);
+      ahi[buf][k][x - TN] = tr_read8<ks * 16 * (BM * 2) + 4 * (BM * 2)>(a_off[x - TN] + slot * STAGE_BYTES);
+    }
+  };
+  bf16x8 af[GK][TM], bf[GK][TN];
+  auto landed = [&](auto buf_c) {
+    constexpr int buf = decltype(buf_c)::value;
+    lds_wait<0>();
+#pragma unroll
+    for (int k = 0; k < GK; ++k) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) { tr_landed(alo[buf][k][i]); tr_landed(ahi[buf][k][i]); af[k][i] = tr_pair(alo[buf][k][i], ahi[buf][k][i]); }
+#pragma unroll
+      for (int j = 0; j < TN; ++j) { tr_landed(blo[buf][k][j]); tr_landed(bhi[buf][k][j]); bf[k][j] = tr_pair(blo[buf][k][j], bhi[buf][k][j]); }
+    }
+  };
   f32x16 acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -1140,75 +1202,11 @@ __device__ __forceinline__ void tn_body(const GemmArgs &g, int bid, int split = 
     for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-
-#pragma unroll
-  for (int s = 0; s < STAGES - 1; ++s)
-    if (s < nkb) issue(s, kb0 + s);
-
-  // address this lane supplies to the transposing loads of k-step 0 (first of the two loads; the second is 4 rows on):
-  // row 8 * (lane / 32) + (lane % 16) / 4, columns tile * 32 + 16 * ((lane / 16) % 2) + 4 * (lane % 4) .. + 3
-  const int s16 = lane & 15, r0 = (lane >> 5) * 8 + (s16 >> 2), mh = (lane >> 4) & 1;
-  int a_off[TM], b_off[TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-    a_off[i] = r0 * (BM * 2) + ((((wm * TM + i) * 4 + 2 * mh + ((s16 & 3) >> 1)) ^ tn_swizzle<BM * 2>(r0)) << 4) + (s16 & 1) * 8;
-#pragma unroll
-  for (int j = 0; j < TN; ++j)
-    b_off[j] = A_BYTES + r0 * (BN * 2) + ((((wn * TN + j) * 4 + 2 * mh + ((s16 & 3) >> 1)) ^ tn_swizzle<BN * 2>(r0)) << 4) + (s16 & 1) * 8;
-  // rows 4 and 16 further on have the same (r & 3) and the same ((r >> 1) & 1): the permutation term does not change
-
-  // The transposing reads go through inline assembly with hand-placed waits (tr_read8 / lds_wait / tr_landed): issued through
-  // the builtin, the compiler orders every one of them behind the LDS-DMA just requested for the next stage
-  // (s_waitcnt vmcnt(0) in front of the first read), which exposes a full memory latency per stage.
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
-  for (int kb = 0; kb < nkb; ++kb) {
-    if (kb + STAGES - 2 < nkb) wait_vmcnt<(STAGES - 2) * LPW>();
-    else wait_vmcnt<0>();
-    bare_barrier();
-    if (kb + STAGES - 1 < nkb) issue((kb + STAGES - 1) % STAGES, kb0 + kb + STAGES - 1);
-    const uint32_t st = lds0 + (kb % STAGES) * STAGE_BYTES;
-    i32x2 alo[2][TM], ahi[2][TM], blo[2][TN], bhi[2][TN];
-    auto fetch = [&](auto buf_c, auto ks_c) {
-      constexpr int buf = decltype(buf_c)::value, ks = decltype(ks_c)::value;
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        alo[buf][i] = tr_read8<ks * 16 * (BM * 2)>(st + a_off[i]);
-        ahi[buf][i] = tr_read8<ks * 16 * (BM * 2) + 4 * (BM * 2)>(st + a_off[i]);
-      }
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        blo[buf][j] = tr_read8<ks * 16 * (BN * 2)>(st + b_off[j]);
-        bhi[buf][j] = tr_read8<ks * 16 * (BN * 2) + 4 * (BN * 2)>(st + b_off[j]);
-      }
-    };
-    auto mfma = [&](auto buf_c, auto newer_c) {  // newer: reads issued after this buffer's, allowed to stay in flight
-      constexpr int buf = decltype(buf_c)::value;
-      lds_wait<decltype(newer_c)::value>();
-      bf16x8 af[TM], bf[TN];
-#pragma unroll
-      for (int i = 0; i < TM; ++i) { tr_landed(alo[buf][i]); tr_landed(ahi[buf][i]); af[i] = tr_pair(alo[buf][i], ahi[buf][i]); }
-#pragma unroll
-      for (int j = 0; j < TN; ++j) { tr_landed(blo[buf][j]); tr_landed(bhi[buf][j]); bf[j] = tr_pair(blo[buf][j], bhi[buf][j]); }
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bf[j], acc[i][j], 0, 0, 0);
-    };
-    typedef std::integral_constant<int, 0> I0;
-    typedef std::integral_constant<int, 1> I1;
-    typedef std::integral_constant<int, 2> I2;
-    typedef std::integral_constant<int, 3> I3;
-    typedef std::integral_constant<int, 2 * (TM + TN)> INext;
-    static_assert(KS == 4 && 2 * (TM + TN) <= 15, "k-steps per stage; lgkmcnt range");
-    fetch(I0{}, I0{});
-    fetch(I1{}, I1{});
-    mfma(I0{}, INext{});
-    fetch(I0{}, I2{});
-    mfma(I1{}, INext{});
-    fetch(I1{}, I3{});
-    mfma(I0{}, INext{});
-    mfma(I1{}, I0{});
-  }
+  auto mm = [&](auto, auto x_c) {
+    constexpr int x = decltype(x_c)::value, k = x / (TM * TN), i = x % (TM * TN) / TN, j = x % TN;
+    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[k][i], bf[k][j], acc[i][j], 0, 0, 0);
+  };
+  unit_loop<STAGES, TM * TN * GK, (TM + TN) * GK, ACH + BCH>(units, read, landed, mm, request, [] {});
 
   wait_vmcnt<0>();
   __syncthreads();
@@ -1225,10 +1223,6 @@ __device__ __forceinline__ void tn_body(const GemmArgs &g, int bid, int split = 
   __syncthreads();
   epilogue<EPI_GRAD, AT, BM, BN>(g, Cs, m0, n0, nt, tid, split);
 }
-template <int BM, int BN, int STAGES>
-__global__ __launch_bounds__(256) void gemm_tn_kernel(GemmArgs g) {
-  tn_body<BM, BN, STAGES>(g, (int)blockIdx.x);
-}
 // ---------------------------------------------------------------------------------------------------
 // The same on 256 x 256 tiles, eight wavefronts (2 x 4, 128 x 64 each), for large batches: all such matrices of a backward pass in
 // one launch, one workgroup per compute unit (Tn2Group). The tiles' contractions are laid end to end and cut into 256 pieces of
@@ -1241,7 +1235,7 @@ __global__ __launch_bounds__(256) void gemm_tn_kernel(GemmArgs g) {
 // ring of three, R through a ring of two, one hand-over per unit, requests with scalar offsets spread between the matrix
 // instructions. It does not stop at the end of a tile: the requests run two units ahead into the next tile while the sums
 // leave as they lie in the registers (a lane holds a column: 128-byte runs).
-// B = 16384 (411 Gflop): the launch 412 -> TN2_US us, the Adam pass behind it ADAM_OLD -> ADAM_NEW (half the slices to add).
+// B = 16384 (411 Gflop): the launch 412 -> 331 us (1.24 PFLOP/s), the Adam pass behind it 103.5 -> 88 (half the slices to add).
 // ---------------------------------------------------------------------------------------------------
 constexpr int TN2_LDS = 160 * 1024;
 __global__ __launch_bounds__(512, 1) void gemm_tn2_kernel(Tn2Group tg) {
@@ -1277,20 +1271,17 @@ __global__ __launch_bounds__(512, 1) void gemm_tn2_kernel(Tn2Group tg) {
   // and fetches the piece whose index is XORed with 4 (row % 4); as NW is even, row % 4 is 2 (wave % 2) + i / 32 for every q
   const int lrow = lane >> 5, lpiece = ((lane & 31) ^ ((((wave & 1) << 1) + lrow) << 2)) << 4;
   auto request_l = [&](int q, int s) {
-    const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(pa), 0, 0x7fffffff, 0x00020000);
     const int r = 2 * (wave + NW * q);
-    auto *dst = (__attribute__((address_space(3))) void *)(smem + s * UNIT + (wave + NW * q) * 1024);
+    unsigned char *dst = smem + s * UNIT + (wave + NW * q) * 1024;
     if (rows >= 64) {
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst, 16, lrow * lda * 2 + lpiece, r * lda * 2, 0, 0);
+      dma16(dma_rsrc(pa), lrow * lda * 2 + lpiece, r * lda * 2, dst);
     } else {  // past the batch: any finite row, its partner row of R is zero
       const int rr = r + lrow < rows ? r + lrow : rows - 1;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst, 16, rr * lda * 2 + lpiece, 0, 0, 0);
+      dma16(dma_rsrc(pa), rr * lda * 2 + lpiece, 0, dst);
     }
   };
   auto request_r = [&](int q, int s) {
-    const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(pb), 0, 0x7fffffff, 0x00020000);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)(smem + R_RING + s * UNIT + (wave + NW * q) * 1024), 16,
-                                             lrow * ldb * 2 + lpiece, 2 * (wave + NW * q) * ldb * 2, 0, 0);
+    dma16(dma_rsrc(pb), lrow * ldb * 2 + lpiece, 2 * (wave + NW * q) * ldb * 2, smem + R_RING + s * UNIT + (wave + NW * q) * 1024);
   };
 
   // addresses this lane supplies to the transposing reads of k-step 0 (see tn_body); tile i's differ in two bits that no row changes
@@ -1448,9 +1439,9 @@ __device__ __forceinline__ void group_body(const GemmGroup &gg) {
   const int local = (int)blockIdx.x - gg.first_block[p], tiles = gg.tiles[p];
   const GemmArgs &g = gg.g[p];
   switch (gg.kind[p]) {
-    case GK_STORE_64x128:   pipe_body<64, 128, STAGES, EPI_STORE, false>(g, local, 0, 1); break;
-    case GK_STORE_128x128:  pipe_body<128, 128, STAGES, EPI_STORE, false>(g, local, 0, 1); break;
-    case GK_STORE_64x64:    pipe_body<64, 64, STAGES, EPI_STORE, false>(g, local, 0, 1); break;
+    case GK_STORE_64x128:   pipe_body<64, 128, STAGES, EPI_STORE>(g, local, 0, 1); break;
+    case GK_STORE_128x128:  pipe_body<128, 128, STAGES, EPI_STORE>(g, local, 0, 1); break;
+    case GK_STORE_64x64:    pipe_body<64, 64, STAGES, EPI_STORE>(g, local, 0, 1); break;
     case GK_PARTIAL_64x64:  pipe_body<64, 64, STAGES, EPI_PARTIAL, false>(g, local % tiles, local / tiles, gg.splits[p]); break;
     case GK_PARTIAL_128x128: pipe_body<128, 128, STAGES, EPI_PARTIAL, false>(g, local % tiles, local / tiles, gg.splits[p]); break;
     case GK_TN_64x128:      tn_body<64, 128, STAGES>(g, local % tiles, local / tiles, gg.splits[p]); break;
@@ -1569,20 +1560,20 @@ int fade_gemm_col_groups(int M, int K, int N, size_t w_slice = (size_t)2 << 20) 
   return cg;
 }
 
-template <int BM, int BN, int STAGES, int EPI, bool BROW = false>
+template <int BM, int BN, int STAGES, int EPI>
 hipError_t launch_pipe(const GemmArgs &g, hipStream_t s) {
   constexpr int BK = 64;
   constexpr size_t lds_ring = (size_t)STAGES * (BM * 128 + (BN / 32) * 4 * 1024), lds_c = (size_t)BM * (BN + 4) * sizeof(float);
   constexpr size_t lds = lds_ring > lds_c ? lds_ring : lds_c;
   static bool attr_done = false;
-  auto kern = gemm_pipe_kernel<BM, BN, STAGES, EPI, BROW>;
+  auto kern = gemm_pipe_kernel<BM, BN, STAGES, EPI>;
   if (!attr_done) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
   const int splits = g.splits > 1 ? g.splits : 1;
-  if (g.N % BN || g.M <= 0 || g.K % (splits * BK) || (EPI != EPI_PARTIAL && splits != 1) || g.lda % 8 || (BROW && g.ldb % 8)) return hipErrorInvalidValue;
+  if (g.N % BN || g.M <= 0 || g.K % (splits * BK) || (EPI != EPI_PARTIAL && splits != 1) || g.lda % 8) return hipErrorInvalidValue;
   GemmArgs ga = g;
   const int ntm = (g.M + BM - 1) / BM, ntn = g.N / BN;
   if (ga.col_groups == 0) ga.col_groups = fade_gemm_col_groups(g.M, g.K, g.N);
@@ -1591,22 +1582,6 @@ hipError_t launch_pipe(const GemmArgs &g, hipStream_t s) {
   if (ga.sum_splits && EPI != EPI_PARTIAL) return hipErrorInvalidValue;
   const dim3 grid((ntn % ga.col_groups == 0 ? (ntm + rg - 1) / rg * rg : ntm) * ntn, ga.sum_splits ? 1 : splits);
   hipLaunchKernelGGL(kern, grid, dim3(256), lds, s, ga);
-  return hipGetLastError();
-}
-
-template <int BM, int BN, int STAGES>
-hipError_t launch_tn(const GemmArgs &g, hipStream_t s) {
-  constexpr size_t lds_ring = (size_t)STAGES * 64 * (BM + BN) * 2, lds_c = (size_t)BM * (BN + 4) * sizeof(float);
-  constexpr size_t lds = lds_ring > lds_c ? lds_ring : lds_c;
-  static bool attr_done = false;
-  auto kern = gemm_tn_kernel<BM, BN, STAGES>;
-  if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    attr_done = true;
-  }
-  if (g.M % BM || g.N % BN || g.K % 64 || g.K <= 0 || g.a_rows <= 0 || g.a_rows > g.K || g.lda % 8 || g.ldb % 8) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(kern, dim3((g.M / BM) * (g.N / BN)), dim3(256), lds, s, g);
   return hipGetLastError();
 }
 
@@ -1670,7 +1645,6 @@ hipError_t launch_pipe_auto(const GemmArgs &g, hipStream_t s) {
     if (g.N % 256 == 0 && g.M % 256 == 0 && (tune == 20 || (tune == 0 && tiles256 >= 256 && g.K >= 256))) return launch_pipe2<EPI>(g, s);
   }
   if (tune == 11 || (tune == 0 && tiles128 >= 512)) return launch_pipe<128, 128, 2, EPI>(g, s);
-  if (tune == 10) return launch_pipe<256, 128, 3, EPI>(g, s);
   if (tune == 1 || (tune == 0 && tiles128 >= 256)) return launch_pipe<128, 128, 4, EPI>(g, s);
   return launch_pipe<64, 128, 4, EPI>(g, s);
 }
@@ -1800,8 +1774,7 @@ hipError_t fade_gemm_group_launch(const GemmGroup &gg, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Tuning override for experiments (FADE_GEMM_TUNE: 0 automatic, 1 force 128x128x4 stages, 2 force 64x128, 10 force 256x128x3,
-// 11 force 128x128x2 with two workgroups per compute unit; 20 force 256x256 on eight wavefronts; grouped launches: 13 force
+// Tuning override for experiments (FADE_GEMM_TUNE: 0 automatic, 1 force 128x128x4 stages, 2 force 64x128, 11 force 128x128x2 with two workgroups per compute unit; 20 force 256x256 on eight wavefronts; grouped launches: 13 force
 // the four-stage kernel, 14 force the two-stage one).
 int fade_gemm_tune() {
   static int v = -1;
@@ -1828,15 +1801,6 @@ hipError_t fade_gemm(int op, bool bf16, const GemmArgs &g, hipStream_t s) {
       case GEMM_X_STORE:  // backward dX = dY W^T: W^T is kept as a second set of fragments
         if (g.N % 128) return launch_pipe<64, 64, 4, EPI_STORE>(g, s);
         return launch_pipe_auto<EPI_STORE>(g, s);
-      case GEMM_W:        // backward dW = L^T R over the batch: both operands are feature-major copies [*][Bp]
-        if (g.N % 128 == 0) return launch_pipe<64, 128, 4, EPI_GRAD, true>(g, s);
-        return launch_pipe<64, 64, 4, EPI_GRAD, true>(g, s);
-      case GEMM_W_TN:     // the same from row-major operands (no copies): A = L [a_rows][lda], W = R [K][ldb]
-        if (g.N % 128 == 0) {
-          if (fade_gemm_tune() == 7 && g.M % 128 == 0) return launch_tn<128, 128, 4>(g, s);
-          return launch_tn<64, 128, 4>(g, s);
-        }
-        return launch_tn<64, 64, 4>(g, s);
       case GEMM_CONVT:    return launch_bf16<4, 1, 1, 1, PRO_CONVT, EPI_STORE>(g, s);
       case GEMM_HEAD:     // head on H = psi(LN(V)) + lam * H_coarse formed in the operand load (Eq. 10's tail never goes to memory):
         // 32 rows x all 256 columns per workgroup (two workgroups per unit), so every row is transformed once; split-K partials as GEMM_PARTIAL leaves them

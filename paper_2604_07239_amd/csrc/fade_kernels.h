@@ -153,6 +153,14 @@ hipError_t fade_code_tables(const uint16_t *freq, uint8_t *sym, int n_steps, int
                             hipStream_t s);
 hipError_t fade_code_uniform(const WinSrc &ws, uint8_t *sym_base, int B, const CoderBufs &cb, long long last, int mode, hipStream_t s);  // steps ws.i .. last - 1
 hipError_t fade_coder_init(const CoderBufs &cb, int B, int decode, hipStream_t s);
+// The canonical blob as runs of the device layout: elements from to[t] on (up to to[t + 1]) lie at from[t].
+struct BlobRuns {
+  static constexpr int MAX = 32;
+  int n;
+  size_t to[MAX], from[MAX];
+};
+// host: pinned memory, 16-byte aligned
+hipError_t fade_read_out(const BlobRuns &runs, const float *dev, float *host, size_t first, size_t count, hipStream_t s);
 hipError_t fade_fill_u32(uint32_t *dst, uint32_t value, size_t n, hipStream_t s);  // a fill as a kernel (safe to capture in a graph, unlike a memset node)
 hipError_t fade_coder_finish(const CoderBufs &cb, int B, long long stride, long long n, hipStream_t s);
 hipError_t fade_payload_move(uint8_t *strided, size_t cap, uint8_t *flat, const unsigned long long *offsets, const uint32_t *lens, int B,

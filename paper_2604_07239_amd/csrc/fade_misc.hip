@@ -1398,9 +1398,38 @@ hipError_t fade_embed_steps(const EmbedArgs &a, hipStream_t s) {
   hipLaunchKernelGGL(embed_steps_kernel, dim3((a.B * a.S + rpb - 1) / rpb), dim3(256), 0, s, a, rpb);
   return hipGetLastError();
 }
+// Elements [first, first + count) of the canonical blob from the device layout, to pinned host memory. A thread writes 16 bytes; its
+// four elements may lie in two runs of the layout (or more, around the scalars).
+__global__ __launch_bounds__(256) void read_out_kernel(BlobRuns runs, const float *dev, float *host, size_t first, size_t count) {
+  const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (i >= count) return;
+  int t = 0;
+  while (t + 1 < runs.n && first + i >= runs.to[t + 1]) ++t;
+  float v[4];
+  const size_t left = count - i;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const size_t e = first + i + ((size_t)j < left ? (size_t)j : 0);
+    int u = (size_t)j < left ? t : 0;
+    while (u + 1 < runs.n && e >= runs.to[u + 1]) ++u;
+    if ((size_t)j < left) t = u;
+    v[j] = dev[runs.from[u] + (e - runs.to[u])];
+  }
+  if (left >= 4) {
+    *reinterpret_cast<f32x4 *>(host + i) = f32x4{v[0], v[1], v[2], v[3]};
+  } else {
+    for (size_t j = 0; j < left; ++j) host[i + j] = v[j];
+  }
+}
 __global__ void fill_u32_kernel(uint32_t *dst, uint32_t value, size_t n) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) dst[i] = value;
+}
+hipError_t fade_read_out(const BlobRuns &runs, const float *dev, float *host, size_t first, size_t count, hipStream_t s) {
+  if (count == 0) return hipSuccess;
+  if (runs.n <= 0 || runs.n > BlobRuns::MAX) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(read_out_kernel, dim3((unsigned)((count + 1023) / 1024)), dim3(256), 0, s, runs, dev, host, first, count);
+  return hipGetLastError();
 }
 hipError_t fade_fill_u32(uint32_t *dst, uint32_t value, size_t n, hipStream_t s) {
   if (!n) return hipSuccess;

@@ -924,7 +924,7 @@ int plan_weight_gradients(fade_ctx *c, const WeightGrad *gw, int n_gw) try {
             order.push_back(p << 24 | (uint32_t)mm << 12 | (uint32_t)nn);
           }
   }
-  if (order.empty()) return FADE_OK;
+  if (!fade_tile_launch((int)c->Bp, (int)order.size())) return FADE_OK;
   Tn2Group &tg = c->tn2q;
   tg.count = (int)at.size();
   tg.tiles = (int)order.size();

@@ -1699,13 +1699,8 @@ static bool tn_shape(int M, int N, int &kind, int &bm, int &bn) {
   if (N % 64 == 0) { kind = GK_TN_64x64; bm = 64; bn = 64; return true; }
   return false;
 }
-// A weight gradient that gets the 256 x 256 tiles of gemm_tn2_kernel: large batches, 16 tiles or more. At B = 4096 the grouped
-// 128 x 128 tiles are faster (gate and router phases 104 / 106 us against 138 / 138, and 31 us less in the Adam pass).
-bool fade_gemm_tn2_ok(int M, int N, int K) {
-  static int mink = -1;  // rows of the batch from which the 256 x 256 weight-gradient tiles are used (sweeps: FADE_TN2_MINK)
-  if (mink < 0) { const char *e = getenv("FADE_TN2_MINK"); mink = e ? atoi(e) : 8192; }
-  return M > 0 && M % 256 == 0 && N % 256 == 0 && K % 64 == 0 && K >= mink && (M / 256) * (N / 256) >= 16;
-}
+// Shape of a weight gradient that can be tiles of gemm_tn2_kernel (whether a context uses it: plan_weight_gradients).
+bool fade_gemm_tn2_ok(int M, int N, int K) { return M > 0 && N > 0 && M % 256 == 0 && N % 256 == 0 && K > 0 && K % 64 == 0 && (M / 256) * (N / 256) >= 16; }
 int fade_gemm_tn_tiles(int M, int N) {
   int kind, bm, bn;
   if (M <= 0 || M % 64 || !tn_shape(M, N, kind, bm, bn)) return 0;

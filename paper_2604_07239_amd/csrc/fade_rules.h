@@ -33,6 +33,14 @@ constexpr bool fade_streamed(bool bf16, bool online, size_t params, size_t B, si
   return bf16 && (online ? 16 * params + 20 * 2 * B * Dh >= 184 * MB : 2 * params >= 128 * MB);
 }
 
+// Whether the weight gradients that can be 256 x 256 tiles (`tiles` of them together) leave the grouped launches of their phases, 64 / 128-wide
+// tiles beside an activation gradient, and become one launch of equal shares: with 8192 rows of the batch and more, and from 2048 on when
+// the tiles are three quarters of the compute units or more. Adapting step in us, grouped and in one launch, D_h = 2048:
+// H = 512 (192 tiles) 2048 rows 644 -> 628, 4096 932 -> 918, and D_h = 512, D_cache = 4096, D_e = 8192 (224) 4096 1113 -> 1082;
+// H = 512, 1536 rows 561 -> 562; H = 384 (152) 2048 627 -> 632; H = 256 (144) 3072 781 -> 770, 4096 867 -> 918, 6144 1244 -> 1252;
+// H = 128 (128) 4096 843 -> 906; D_h = 1024, H = 512 (48) 4096 615 -> 622, 6144 902 -> 889-904.
+constexpr bool fade_tile_launch(int rows, int tiles) { return tiles > 0 && (rows >= 8192 || (rows >= 2048 && tiles >= 192)); }
+
 // How `tiles` equal contractions of `units` steps each are shared out over 256 workgroups, 32 on each of 8 XCDs. On an XCD, `groups`
 // groups of `wgs` workgroups take `tpg` tiles each: the group's tiles lie end to end and its members take per_wg steps each, so a
 // tile is cut where a member's share ends and arrives as one partial sum per member that worked on it. Small groups (at most

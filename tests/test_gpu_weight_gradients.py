@@ -1,0 +1,41 @@
+"""The launch that shares all 256 x 256 weight-gradient tiles out in equal pieces, at batches that end inside a block of 64 rows:
+gradients of one step against the oracle on a few active streams (the others have a gradient of zero), the last ones among them."""
+import numpy as np
+import pytest
+
+import fade_inputs as fi
+import oracle as orc
+from gpu_helpers import need_gpu
+from test_gpu_online import _compare_gradients, _sub_view
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,T,H,widths", [(2050, 64, 512, {}),   # 192 tiles of 33 blocks: the smallest batch that takes the launch
+                                          (8200, 32, 320, {}),    # 32 tiles (gradients of W_c, W_r): eight workgroups to a tile
+                                          (2111, 16, 64, dict(d_cache=4096, d_e=8192))])  # 224 tiles of a wide refiner, one row short of a block
+def test_weight_gradients_of_ragged_batches(B, T, H, widths, monkeypatch):
+    torch = need_gpu()
+    import paper_2604_07239_amd as fa
+    D = 32
+    idx = np.unique(np.r_[0, 63, 64, np.linspace(0, B - 1, 12).astype(np.int64), B - 2, B - 1])
+    act = np.zeros(B, np.uint8)
+    act[idx] = 1
+    blob = fi.init_blob(B, T, D, H, 7, std=0.05, **widths)
+    monkeypatch.setenv("FADE_DEBUG_WU_GRAD", "1")  # the sums of the slices go to the gradient array
+    g = fa.Fade(fa.make_config(B, T, D, H, dtype=fa.BF16, update_mode=fa.ONLINE_ADAM, **widths))
+    g.load_weights(blob.data)
+    sub = fi.Blob(len(idx), T, D, H, **widths)
+    for name, _, _ in sub.specs:
+        sub[name] = blob[name][idx] if name == "W_U" else blob[name]
+    o = orc.Oracle(orc.make_config(len(idx), T, D, H, dtype=orc.BF16, update_mode=orc.ONLINE_ADAM, **widths))
+    o.load_weights(sub.data)
+    data = np.random.default_rng(B).integers(0, 256, (B, T + 1), dtype=np.uint8)
+    win, tgt = np.ascontiguousarray(data[:, :T]), np.ascontiguousarray(data[:, T])
+    ad = torch.from_numpy(act).cuda()
+    g.step_probs(torch.from_numpy(win).cuda(), ad, None, None)
+    o.step_probs(np.ascontiguousarray(win[idx]), None)
+    go = o.backward(np.ascontiguousarray(tgt[idx]), None)
+    g.step_update(torch.from_numpy(tgt).cuda(), ad)
+    _compare_gradients(sub, _sub_view(blob, sub, g.debug_grad(), idx), go, 3e-2, f"B={B}")
+    g.close()

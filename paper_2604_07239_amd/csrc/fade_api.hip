@@ -184,6 +184,7 @@ struct fade_ctx {
   // weight gradients with few output tiles are left as partial sums over ranges of the batch (bf16 path): per parameter
   // tensor the number of ranges (1: none) and the slices [ranges][K][N]; the Adam pass adds them up
   int gsp[P_COUNT] = {};
+  bool du_tall = false;  // du's partials on 256 x 256 tiles
   // weight gradients on 256 x 256 tiles wait here until the end of the backward pass and run as one launch: tn2q.g[tn2_slot[id]]
   Tn2Group tn2q{};
   int tn2_slot[P_COUNT] = {};  // -1: not there
@@ -889,7 +890,7 @@ int run_phase(fade_ctx *c, const char *name, const PhaseGemms &ph) {
     GemmGroup gg{};
     for (int i = 0; i < ph.n; ++i) {
       const GemmArgs &g = ph.g[i];
-      const bool alone = ph.op[i] == GEMM_X_STORE && g.N % 256 == 0 && g.K >= 1024 && ((g.M + 255) / 256) * (g.N / 256) >= 256;
+      const bool alone = ph.op[i] == GEMM_PARTIAL_TALL || (ph.op[i] == GEMM_X_STORE && g.N % 256 == 0 && g.K >= 512 && ((g.M + 255) / 256) * (g.N / 256) >= 256);
       if (ph.op[i] == GEMM_W_TN && c->tn2_slot[g.weight - 1] >= 0) c->tn2q.g[c->tn2_slot[g.weight - 1]] = g;  // launched at the end of the pass
       else if (alone) HIP_TRY(c, fade_gemm(ph.op[i], true, g, c->stream));
       else HIP_TRY(c, fade_gemm_group_add(gg, ph.op[i], g));
@@ -1043,7 +1044,7 @@ int backward(fade_ctx *c, const WinSrc &ws, const uint8_t *targets, long long ts
     GemmArgs gx = args_x(c, c->dE, 2 * De, Dh, c->WT_fgv, static_cast<const float *>(c->Wfgv_c), 2 * De, c->du);
     if (c->sp_du > 1) {  // a long contraction (K = 2 D_e) over few output tiles: ranges of K as fp32 partials, summed by the next kernel
       gx.splits = c->sp_du; gx.C = c->du_part;
-      ph.add(GEMM_PARTIAL, gx);
+      ph.add(c->du_tall ? GEMM_PARTIAL_TALL : GEMM_PARTIAL, gx);
       ph.add(GEMM_W_TN, args_w(c, c->LT[2], Dh, c->LT[2], Dh, c->dE, 2 * De, P_WFG, P_WFV));
     } else {
       ph.add(GEMM_W_TN, args_w(c, c->LT[2], Dh, c->LT[2], Dh, c->dE, 2 * De, P_WFG, P_WFV));
@@ -1658,7 +1659,12 @@ int fade_create(const fade_config *cfg, fade_ctx **out) {
       }
     }
     if (c->bf16 && 2 * d.De >= 4096 && d.Dh % 128 == 0) {
-      c->sp_du = pick_splits((int)((d.B + 127) / 128 * (d.Dh / 128)) / 2, (int)(2 * d.De / 64 / 4), 16);  // ~384+ workgroups, ranges of 8+ blocks
+      // on 256 x 256 tiles where ranges of 1024 and more give every compute unit one (D_h = 512, D_e = 8192, B = 4096: 32 tiles x 8
+      // ranges; the product 117 -> 87 us, the sum of the ranges behind it 23 -> 30), else on 128 x 128: 384 workgroups or more, ranges of 8 blocks or more
+      const size_t t256 = d.B % 256 == 0 && d.Dh % 256 == 0 ? d.B / 256 * (d.Dh / 256) : 0;
+      for (int sp = 2; t256 > 0 && t256 < 256 && sp <= 16; sp *= 2)
+        if (t256 * sp >= 256 && 2 * d.De % (64 * sp) == 0 && 2 * d.De / sp >= 1024) { c->du_tall = true; c->sp_du = sp; break; }
+      if (!c->du_tall) c->sp_du = pick_splits((int)((d.B + 127) / 128 * (d.Dh / 128)) / 2, (int)(2 * d.De / 64 / 4), 16);
       if (c->sp_du > 1) TRY_ALLOC(dev_alloc(c, &c->du_part, (size_t)c->sp_du * d.B * d.Dh));
     }
     c->sp_dz = c->bf16 ? pick_splits((int)((d.B + 63) / 64), (int)(d.Dh / 64), 16) : 1;

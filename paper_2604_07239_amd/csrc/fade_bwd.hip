@@ -442,6 +442,7 @@ __global__ __launch_bounds__(256) void bwd_gate_kernel(BwdGateArgs a) {
         for (int i = 0; i < 8; ++i) du[i] = 0.0f;
       }
       if (a.du_part) {
+#pragma unroll 4
         for (int sp = 0; sp < a.du_splits; ++sp) {
           float pv[8];
           ld8<float>(a.du_part + (size_t)sp * a.B * a.Dh + base, pv);

@@ -829,7 +829,7 @@ constexpr int PIPE2_LDS = 160 * 1024;
 template <int EPI>
 __device__ __forceinline__ void pipe2_body(const GemmArgs &g, int bid) {
   typedef bf16_t AT;
-  static_assert(EPI == EPI_STORE || EPI == EPI_GLOBAL || EPI == EPI_MIX || EPI == EPI_GATE || EPI == EPI_GEGLU_FOLD, "epilogue");
+  static_assert(EPI == EPI_STORE || EPI == EPI_GLOBAL || EPI == EPI_MIX || EPI == EPI_GATE || EPI == EPI_GEGLU_FOLD || EPI == EPI_PARTIAL, "epilogue");
   constexpr bool kPair = EPI == EPI_GEGLU_FOLD;
   constexpr int BM = 256, BN = 256, NW = 8, KS = 4, AUNITS = 3, WUNITS = 2;
   constexpr int WN = NW / 2;                         // wavefronts 2 (rows) x WN (columns)
@@ -843,13 +843,18 @@ __device__ __forceinline__ void pipe2_body(const GemmArgs &g, int bid) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
   const int ntn = g.N / BN, ntm = g.M / BM;
+  // EPI_PARTIAL: ranges of K innermost, so that with eight of them an XCD streams one range of both operands
+  constexpr bool kPart = EPI == EPI_PARTIAL;
+  const int splits = kPart ? g.splits : 1, split = kPart ? bid % splits : 0;
   int mt, nt;
-  if (!tile_of_block(bid, ntm, ntn, g.col_groups, mt, nt)) return;
+  if (kPart) { mt = bid / splits / ntn; nt = bid / splits % ntn; }
+  else if (!tile_of_block(bid, ntm, ntn, g.col_groups, mt, nt)) return;
   const int m0 = mt * BM, n0 = nt * BN;
-  const int nku = g.K / 64;
+  const int nku = g.K / 64 / splits;
 
   // DMA sources: a resource at the tile's first row / fragment, one lane offset each, and scalar offsets per request
-  const auto rsrc_a = dma_rsrc(static_cast<const bf16_t *>(g.A) + (size_t)m0 * g.lda), rsrc_w = dma_rsrc(static_cast<const bf16_t *>(g.W) + (size_t)n0 * g.K);
+  const auto rsrc_a = dma_rsrc(static_cast<const bf16_t *>(g.A) + (size_t)m0 * g.lda + (size_t)split * nku * 64);
+  const auto rsrc_w = dma_rsrc(static_cast<const bf16_t *>(g.W) + (size_t)n0 * g.K + (size_t)split * nku * (KS * 512));
   // A: DMA c = wave + NW q covers rows 8c .. 8c + 7, lane i piece (i % 8) ^ ((r / 2) % 8) of row r = 8c + i / 8; as NW is even,
   // (r / 2) % 8 is 4 (wave % 2) + i / 16 for every q
   const uint32_t a_vo = (uint32_t)((lane >> 3) * g.lda * 2 + (((lane & 7) ^ (((wave & 1) << 2) + (lane >> 4))) << 4)), w_vo = (uint32_t)lane * 16;
@@ -1032,7 +1037,9 @@ __device__ __forceinline__ void pipe2_body(const GemmArgs &g, int bid) {
       const size_t o = (size_t)(m0 + row) * g.ldc + nout;
       float x[8];
       load8(slab + r * LDC + c8, x);
-      if constexpr (kPair) {
+      if constexpr (kPart) {
+        store8(static_cast<float *>(g.C) + (size_t)split * g.M * g.ldc + o, x);
+      } else if constexpr (kPair) {
         float xv[8];
         load8(slab + r * LDC + 32 + c8, xv);
         const float2 mr = sums[row];
@@ -1055,7 +1062,7 @@ __device__ __forceinline__ void pipe2_body(const GemmArgs &g, int bid) {
     __builtin_amdgcn_wave_barrier();
   }
   };
-  if (EPI != EPI_STORE && g.C2) slabs(std::integral_constant<int, KEEP_YES>{});
+  if (EPI != EPI_STORE && !kPart && g.C2) slabs(std::integral_constant<int, KEEP_YES>{});
   else slabs(std::integral_constant<int, KEEP_NO>{});
   if constexpr (EPI == EPI_STORE || EPI == EPI_MIX || EPI == EPI_GATE) {
     if (g.stats_out) {  // a row's 16 chunk sums per 128 columns, added as the 16-lane butterfly of the smaller tiles adds them
@@ -1617,14 +1624,17 @@ hipError_t launch_pipe2(const GemmArgs &g, hipStream_t s) {
     if (e != hipSuccess) return e;
     attr_done = true;
   }
-  if (g.M <= 0 || g.N <= 0 || g.K <= 0 || g.M % 256 || g.N % 256 || g.K % 64 || g.splits > 1 || g.sum_splits || g.lda % 8) return hipErrorInvalidValue;
+  if (g.M <= 0 || g.N <= 0 || g.K <= 0 || g.M % 256 || g.N % 256 || g.sum_splits || g.lda % 8) return hipErrorInvalidValue;
+  const int splits = EPI == EPI_PARTIAL && g.splits > 1 ? g.splits : 1;
+  if (g.K % (64 * splits) || (EPI != EPI_PARTIAL && g.splits > 1)) return hipErrorInvalidValue;
   if ((size_t)256 * g.lda * 2 + (size_t)g.K * 2 > 0x7fffffff || (EPI == EPI_GEGLU_FOLD && (g.C2 == nullptr) != (g.C3 == nullptr))) return hipErrorInvalidValue;
   GemmArgs ga = g;
   const int ntm = g.M / 256, ntn = g.N / 256;
   if (ga.col_groups == 0) ga.col_groups = fade_gemm_col_groups(g.M, g.K, g.N, (size_t)4 << 20);
   if ((ga.col_groups != 1 && ga.col_groups != 2 && ga.col_groups != 4) || ntn % ga.col_groups) ga.col_groups = 8;
-  const int rg = 8 / ga.col_groups;
-  hipLaunchKernelGGL(kern, dim3((ntn % ga.col_groups == 0 ? (ntm + rg - 1) / rg * rg : ntm) * ntn), dim3(512), PIPE2_LDS, s, ga);
+  ga.splits = splits;
+  const int rg = 8 / ga.col_groups, tiles = EPI == EPI_PARTIAL ? ntm * ntn * splits : (ntn % ga.col_groups == 0 ? (ntm + rg - 1) / rg * rg : ntm) * ntn;
+  hipLaunchKernelGGL(kern, dim3(tiles), dim3(512), PIPE2_LDS, s, ga);
   return hipGetLastError();
 }
 
@@ -1790,6 +1800,7 @@ hipError_t fade_gemm(int op, bool bf16, const GemmArgs &g, hipStream_t s) {
       case GEMM_FNR_IN:   // Eq. 9 in one piece (no split-K): folded LayerNorm and GeGLU in the epilogue
         if (!g.stats || !g.fold_s || !g.fold_t) return hipErrorInvalidValue;
         return launch_pipe_auto<EPI_GEGLU_FOLD>(g, s);
+      case GEMM_PARTIAL_TALL: return launch_pipe2<EPI_PARTIAL>(g, s);
       case GEMM_PARTIAL:  // split-K products whose LayerNorm / bias / non-linearity follow in the reducing kernel
         if (g.N % 128 == 0) return launch_pipe<128, 128, 4, EPI_PARTIAL>(g, s);
         return launch_pipe<64, 64, 4, EPI_PARTIAL>(g, s);

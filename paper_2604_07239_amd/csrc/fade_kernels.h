@@ -5,6 +5,7 @@
 enum {
   GEMM_CONV = 0, GEMM_GLOBAL, GEMM_ROUTER, GEMM_DOWN, GEMM_UP, GEMM_GATE, GEMM_FNR_IN, GEMM_FNR_OUT, GEMM_HEAD,
   GEMM_PARTIAL,  // product leaving fp32 partials [splits][M][N] (fp32 path: one split)
+  GEMM_PARTIAL_TALL,  // bf16: the same on 256 x 256 tiles, M and N multiples of 256
   GEMM_X_STORE,  // backward: dX = dY W^T, stored as activations
   GEMM_W,        // backward: dW = L^T R, reduction over the batch, fp32 gradient out
   GEMM_W_TN,     // the same from row-major operands (bf16 path): A = L [a_rows][lda], W = R [K][ldb], K = padded batch

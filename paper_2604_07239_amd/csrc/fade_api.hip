@@ -670,10 +670,14 @@ int forward_bf16(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uin
     g.lam = c->P(P_LAMBDA_C); g.stats_out = c->stats_f;
     HIP_TRY(c, fade_gemm(GEMM_GATE, true, g, s));
   }
+  // Eq. 9 in one launch, folded LN and GeGLU in the product's epilogue: with tiles enough without splitting K, and, single steps, where
+  // its 64 x 128 tiles are a round of the chip or less (then two groups of wavefronts share K, see gemm_fnr_kernel)
+  const bool fnr_few = c->sp_fnr > 1 && !fuse && ((B + 63) / 64) * (2 * De / 128) <= 256 && De % 64 == 0;
   if (level < 5) {
-  } else if (c->sp_fnr == 1) {  // Eq. 9, enough tiles without splitting K: folded LN and GeGLU in the product's epilogue
+  } else if (c->sp_fnr == 1 || fnr_few) {
     Prof p(c, "gemm_fnr_in");
     GemmArgs g{};
+    g.splits = fnr_few ? c->sp_fnr : 1;
     g.M = B; g.N = 2 * De; g.K = Dh;
     g.A = c->Hc; g.lda = Dh; g.W = c->Wfgv_c; g.C = c->Hexp; g.ldc = De; if (c->online) { g.C2 = c->eg; g.C3 = c->ev; }
     g.stats = c->stats_f; g.stats_n = SN; g.fold_s = c->s_fnr; g.fold_t = c->t_fnr;

@@ -803,6 +803,142 @@ __global__ __launch_bounds__(256, STAGES == 2 ? 2 : 1) void gemm_pipe_kernel(Gem
 
 
 // ---------------------------------------------------------------------------------------------------
+// Eq. 9's gate | value product where its tiles are too few to fill the chip (M = 1024, N = 512: 64 of 64 x 128): folded LayerNorm and GeGLU
+// in the epilogue all the same, K = 2048 walked by two groups of four wavefronts, each with its own ring, side by side. The sum is
+// that of g.splits ranges of K added in range order, as a pass over many steps adds them (GEMM_PARTIAL with sum_splits, then
+// geglu_kernel) and to the same bits: group 0 adds the first half of the ranges as it goes, group 1 keeps its ranges' sums apart,
+// and they are added to group 0's one by one at the end.
+// In place of fp32 partials of 128 x 128 tiles (64 KiB written by every workgroup and read back by the GeGLU kernel), us for the two
+// launches and for the one: M = 1024, N = 512, K = 2048, 8 ranges 12.9 + 6.3 -> 12.9; M = 1500, N = 384, K = 1024
+// 14.5 + 6.2 -> 9.8; M = 128, N = 1024, K = 512 7.2 + 4.1 -> 8.0. Tiles of 32 rows (with 64, on half the compute units, 16.5 / 12.7 / 11.8) up to 256 of them.
+// ---------------------------------------------------------------------------------------------------
+template <int BM> struct FnrRing {
+  static constexpr int stages = BM == 32 ? 4 : 3, unit = BM * 128 + 128 * 128, bytes = 2 * stages * unit;
+};
+template <int BM>  // 32 or 64 rows x 128 columns
+__global__ __launch_bounds__(512, 1) void gemm_fnr_kernel(GemmArgs g) {
+  typedef bf16_t AT;
+  constexpr int BN = 128, KS = 4, NW = 4, WN = BM == 32 ? 4 : 2, TN = 4 / WN, GK = 2, UNIT = FnrRing<BM>::unit, A_BYTES = BM * 128, ACH = BM / 8 / NW, BCH = BN / 32 * KS / NW, LDC = BN + 4;
+  constexpr int OWN = 4;  // ranges a group can keep
+  static_assert(FnrRing<BM>::bytes <= 160 * 1024 && OWN * BM * BN * 4 <= FnrRing<BM>::bytes && BM * LDC * 4 <= FnrRing<BM>::bytes, "LDS");
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, wave8 = __builtin_amdgcn_readfirstlane(tid >> 6), grp = wave8 >> 2, wave = wave8 & 3;
+  const int wm = wave / WN, wn = wave % WN;
+  const int ntn = g.N / BN, ntm = (g.M + BM - 1) / BM;
+  int mt, nt;
+  if (!tile_of_block((int)blockIdx.x, ntm, ntn, g.col_groups, mt, nt)) return;
+  const int m0 = mt * BM, n0 = nt * BN;
+  const int range = g.K / 64 / g.splits, own = g.splits / 2, units = own * range, kb0 = grp * units;
+  unsigned char *ring = smem + grp * (FnrRing<BM>::bytes / 2);
+
+  // requests and reads as in pipe_body
+  const auto rsrc_a = dma_rsrc(static_cast<const bf16_t *>(g.A) + (size_t)m0 * g.lda + kb0 * 64);
+  const auto rsrc_w = dma_rsrc(static_cast<const bf16_t *>(g.W) + (size_t)n0 * g.K + (size_t)kb0 * KS * 512);
+  uint32_t a_vo[ACH], w_so[BCH];
+#pragma unroll
+  for (int q = 0; q < ACH; ++q) {
+    const int r = (wave + NW * q) * 8 + (lane >> 3), rc = m0 + r < g.M ? r : g.M - 1 - m0;
+    a_vo[q] = (uint32_t)(rc * g.lda * 2 + (((lane & 7) ^ ((r >> 1) & 7)) << 4));
+  }
+#pragma unroll
+  for (int q = 0; q < BCH; ++q) {
+    const int c = wave + NW * q;
+    w_so[q] = (uint32_t)(((c / KS) * (g.K / 16) + c % KS) * 1024);
+  }
+  auto request = [&](auto i_c, int u, int slot) {
+    constexpr int i = decltype(i_c)::value;
+    unsigned char *base = ring + slot * UNIT;
+    if constexpr (i < ACH) dma16(rsrc_a, a_vo[i], u * 128, base + (wave + NW * i) * 1024);
+    else dma16(rsrc_w, (uint32_t)lane * 16, w_so[i - ACH] + u * (KS * 1024), base + A_BYTES + (wave + NW * (i - ACH)) * 1024);
+  };
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)ring;
+  const uint32_t a_first = lds0 + (wm * 32 + (lane & 31)) * 128 + (((lane >> 5) ^ ((lane >> 1) & 7)) << 4);
+  const uint32_t w_first = lds0 + A_BYTES + wn * TN * KS * 1024 + lane * 16;
+  bf16x8 af[2][GK], bf[2][GK][TN];
+  auto read = [&](auto buf_c, auto h_c, auto i_c, int slot) {
+    constexpr int buf = decltype(buf_c)::value, i = decltype(i_c)::value, k = i / (1 + TN), x = i % (1 + TN), ks = decltype(h_c)::value * GK + k;
+    if constexpr (x < TN) bf[buf][k][x] = lds_read16<ks * 1024 + x * KS * 1024>(w_first + slot * UNIT);
+    else af[buf][k] = lds_read16<0>((a_first + slot * UNIT) ^ (ks * 32));
+  };
+  auto landed = [&](auto buf_c) {
+    constexpr int buf = decltype(buf_c)::value;
+    lds_wait<0>();
+#pragma unroll
+    for (int k = 0; k < GK; ++k) {
+      lds_landed(af[buf][k]);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) lds_landed(bf[buf][k][j]);
+    }
+  };
+  f32x16 acc[TN], keep[OWN][TN];  // group 0: keep[0] is the sum of its ranges
+  auto clear = [&] {
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[j][e] = 0.0f;
+  };
+  clear();
+#pragma unroll
+  for (int r = 0; r < OWN; ++r)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) keep[r][j] = acc[j];
+  auto mm = [&](auto buf_c, auto x_c) {
+    constexpr int buf = decltype(buf_c)::value, x = decltype(x_c)::value, k = x / TN, j = x % TN;
+    acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[buf][k], bf[buf][k][j], acc[j], 0, 0, 0);
+  };
+  int in_range = 0, slot_of_range = 0;  // group 0 adds into the one place, group 1 takes the next
+  auto unit_done = [&] {
+    if (++in_range < range) return;
+    in_range = 0;
+    static_for<OWN>([&](auto q_c) {
+      constexpr int q = decltype(q_c)::value;
+      if (slot_of_range == q) {
+        asm volatile("");  // a branch: as selects every set of sums would be rewritten
+#pragma unroll
+        for (int j = 0; j < TN; ++j) keep[q][j] += acc[j];
+      }
+    });
+    slot_of_range += grp;
+    clear();
+  };
+  unit_loop<FnrRing<BM>::stages, TN * GK, (1 + TN) * GK, ACH + BCH>(units, read, landed, mm, request, unit_done);
+
+  wait_vmcnt<0>();
+  __syncthreads();  // the rings are no longer being read
+  float *part = reinterpret_cast<float *>(smem), *Cs = part;
+  const int at = wave * 64 * 16 * TN + lane;  // [range][wavefront][element][lane]: as the registers lie
+  if (grp) {
+    static_for<OWN>([&](auto q_c) {
+      constexpr int q = decltype(q_c)::value;
+      if (q < own) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) part[q * (BM * BN) + at + (j * 16 + e) * 64] = keep[q][j][e];
+      }
+    });
+  }
+  __syncthreads();
+  if (!grp) {
+    for (int q = 0; q < own; ++q)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) keep[0][j][e] += part[q * (BM * BN) + at + (j * 16 + e) * 64];
+  }
+  __syncthreads();
+  if (!grp) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        Cs[(wm * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)) * LDC + (wn * TN + j) * 32 + (lane & 31)] = keep[0][j][e];
+  }
+  __syncthreads();
+  epilogue<EPI_GEGLU_FOLD, AT, BM, BN, LDC, 512>(g, Cs, m0, n0, nt, tid);
+}
+
+// ---------------------------------------------------------------------------------------------------
 // The same product on 256 x 256 tiles, eight wavefronts (2 x 4, 128 x 64 each), one workgroup per compute unit, for batches that
 // give every unit a tile. Both operands come in units of 64 along K (32 KiB each: A as rows of 128 bytes, whole cache lines,
 // swizzled as in pipe_body; W as ready-made fragments), A through a ring of three, W through a ring of two: 160 KiB of LDS.
@@ -1638,6 +1774,24 @@ hipError_t launch_pipe2(const GemmArgs &g, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int BM>
+hipError_t launch_fnr(const GemmArgs &g, hipStream_t s) {
+  static bool attr_done = false;
+  if (!attr_done) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_fnr_kernel<BM>), hipFuncAttributeMaxDynamicSharedMemorySize, FnrRing<BM>::bytes);
+    if (e != hipSuccess) return e;
+    attr_done = true;
+  }
+  if (g.M <= 0 || g.N % 128 || (g.splits != 2 && g.splits != 4 && g.splits != 8) || g.K % (64 * g.splits) || g.lda % 8 || !g.stats || !g.fold_s || !g.fold_t) return hipErrorInvalidValue;
+  GemmArgs ga = g;
+  const int ntm = (g.M + BM - 1) / BM, ntn = g.N / 128;
+  ga.col_groups = fade_gemm_col_groups(g.M, g.K, g.N);
+  if ((ga.col_groups != 1 && ga.col_groups != 2 && ga.col_groups != 4) || ntn % ga.col_groups) ga.col_groups = 8;
+  const int rg = 8 / ga.col_groups;
+  hipLaunchKernelGGL(gemm_fnr_kernel<BM>, dim3((ntn % ga.col_groups == 0 ? (ntm + rg - 1) / rg * rg : ntm) * ntn), dim3(512), FnrRing<BM>::bytes, s, ga);
+  return hipGetLastError();
+}
+
 // Tile shape by problem size. Small batches: 64 x 128 tiles, four stages, so that every compute unit gets a tile. From
 // 512 tiles of 128 x 128 on: that tile with a two-stage ring (64 KiB of LDS), two workgroups per compute unit: one's
 // epilogue (side inputs from HBM, stores) and pipeline fill run under the other's products, which measured faster than
@@ -1799,6 +1953,8 @@ hipError_t fade_gemm(int op, bool bf16, const GemmArgs &g, hipStream_t s) {
       case GEMM_FNR_OUT:  return launch_pipe_auto<EPI_STORE>(g, s);
       case GEMM_FNR_IN:   // Eq. 9 in one piece (no split-K): folded LayerNorm and GeGLU in the epilogue
         if (!g.stats || !g.fold_s || !g.fold_t) return hipErrorInvalidValue;
+        if (g.splits > 1)  // as the sum of ranges of K, few tiles
+          return ((g.M + 31) / 32) * (g.N / 128) <= 256 ? launch_fnr<32>(g, s) : launch_fnr<64>(g, s);
         return launch_pipe_auto<EPI_GEGLU_FOLD>(g, s);
       case GEMM_PARTIAL_TALL: return launch_pipe2<EPI_PARTIAL>(g, s);
       case GEMM_PARTIAL:  // split-K products whose LayerNorm / bias / non-linearity follow in the reducing kernel

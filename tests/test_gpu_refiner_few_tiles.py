@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("B,T,H,d_e", [
     (33, 8, 128, 64),      # 2 ranges of two units of 64; a tile of one row, one column tile
     (65, 16, 256, 192),    # 4 ranges of two units
-    (40, 40, 192, 64),     # 4 ranges of five units
+    (40, 40, 320, 64),     # 4 ranges of five units
     (130, 32, 256, 128),   # 8 ranges of two units
     (513, 16, 256, 1024),  # 64-row tiles, one row in the last; 4 ranges
     (1024, 32, 256, 1024), # 256 tiles of 64 rows: the most that take the launch; 2 ranges of eight units

@@ -1,19 +1,20 @@
 // fade_gemm.hip — the dense products of the model step with fused prologues and epilogues (gfx950).
 //
 // bf16 path: C[M][N] = A[M][K] * W[K][N] on the matrix cores (v_mfma_f32_32x32x16_bf16, fp32 accumulate).
-//   * Both operands stream global -> LDS by LDS-DMA (global_load_lds_dwordx4) through a ring of stages synchronised by
-//     hand (s_waitcnt vmcnt + a bare s_barrier); A is row-major with its 16-byte pieces XOR-permuted in LDS, W was
-//     rearranged at load time into MFMA fragment order (1 KiB per 32 columns x 16 k, contiguous along K).
-//     pipe_body: 4 wavefronts, tiles of 64 / 128 rows x 64 / 128 columns, stages of 64 along K (small and medium batches,
-//     grouped launches, split-K partials). pipe2_body: 8 wavefronts on a 256 x 256 tile, ring of four 32-wide stages with
-//     the stage hand-over between the two k-steps of a stage (large batches). Fragment reads go through inline assembly
-//     with hand-placed lgkmcnt waits, so that the next k-step's reads stay in flight under the matrix instructions.
+//   * Both operands stream global -> LDS by LDS-DMA through rings of units of 64 along K, synchronised by hand (s_waitcnt vmcnt +
+//     a bare s_barrier); A is row-major with its 16-byte pieces XOR-permuted in LDS, W was rearranged at load time into MFMA
+//     fragment order (1 KiB per 32 columns x 16 k, contiguous along K). Fragment reads go through inline assembly with
+//     hand-placed lgkmcnt waits, a k-step or more ahead of the matrix instructions they feed.
+//     pipe_body: 4 wavefronts, tiles of 64 / 128 rows x 64 / 128 columns (small and medium batches, grouped launches, split-K
+//     partials). gemm_fnr_kernel: 32 / 64 x 128 on two groups of 4 wavefronts that share the ranges of K (the refiner's input
+//     with few tiles). pipe2_body: 8 wavefronts on a 256 x 256 tile (large batches, tall split-K partials).
 //   * gemm_bf16_kernel forms A on the fly instead (the causal-conv row gather; Eq. 10's tail for the head product) and
 //     stages it through LDS from registers; its W fragments go straight from L2 into registers.
 //   * Weight gradients dW = L^T R contract over the batch: tn_body stages both row-major operands as they lie in memory
 //     and turns them on the way out of LDS with the transposing read (ds_read_b64_tr_b16); 4 wavefronts on up to
-//     128 x 128 inside grouped launches, 8 wavefronts on 256 x 256 as a launch of its own at large batches.
-//   * The accumulators are parked in LDS (fp32; 64-row slabs for the 256-row tiles) and re-read row-wise, so that every
+//     128 x 128 inside grouped launches. gemm_tn2_kernel: 256 x 256 tiles on 8 wavefronts, all matrices in one launch that shares the
+//     k-steps out to the compute units in equal pieces (large batches).
+//   * The accumulators are parked in LDS (fp32; the 256-row tiles a wavefront's rows at a time) and re-read row-wise, so that every
 //     side input and every output moves in 16-byte pieces and per-row statistics for the next LayerNorm fall out of a
 //     16-lane butterfly. Partial statistics are stored per 128-column tile and summed by the consumer in index order: no
 //     atomics, so the result is reproducible bit for bit, and the same for every tile shape.
@@ -1796,10 +1797,9 @@ hipError_t launch_fnr(const GemmArgs &g, hipStream_t s) {
 // 512 tiles of 128 x 128 on: that tile with a two-stage ring (64 KiB of LDS), two workgroups per compute unit: one's
 // epilogue (side inputs from HBM, stores) and pipeline fill run under the other's products, which measured faster than
 // either a deeper ring or a 256 x 128 tile with one workgroup per unit (router product, M = 4096: 43 us against 54).
-// Once every compute unit gets a 256 x 256 tile (M >= 8192 at N = 2048): that tile on eight wavefronts with the finer
-// rings of pipe2_body: half the operand bytes per flop of 128 x 128 and two wavefronts per SIMD. On random operands at
-// M = 16384, N = 2048 (then with A in 32-wide stages): K = 2048 188 us against 207 for the same tile on a two-stage ring of
-// 64-wide stages, 230 for 128 x 128; K = 512 88 against 104; mix epilogue in both. With a contraction of 64 the two shapes tie.
+// Once every compute unit gets a 256 x 256 tile (M >= 8192 at N = 2048): that tile on eight wavefronts (pipe2_body): half the operand
+// bytes per flop of 128 x 128 and two wavefronts per SIMD. On random operands at M = 16384, N = K = 2048 with the mix epilogue: 146 us
+// against 230 for 128 x 128. With a contraction of 64 the two shapes tie.
 template <int EPI>
 hipError_t launch_pipe_auto(const GemmArgs &g, hipStream_t s) {
   const int tiles128 = ((g.M + 127) / 128) * (g.N / 128);

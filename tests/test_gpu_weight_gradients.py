@@ -13,7 +13,9 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("B,T,H,widths", [(2050, 64, 512, {}),   # 192 tiles of 33 blocks: the smallest batch that takes the launch
                                           (8200, 32, 320, {}),    # 32 tiles (gradients of W_c, W_r): eight workgroups to a tile
-                                          (2111, 16, 64, dict(d_cache=4096, d_e=8192))])  # 224 tiles of a wide refiner, one row short of a block
+                                          (2111, 16, 64, dict(d_cache=4096, d_e=8192)),   # 224 tiles of a wide refiner, one row short of a block
+                                          (4096, 16, 64, dict(d_cache=512, d_e=8192)),    # gradient at H_coarse: 32 tiles x 8 ranges of its own on 256 x 256
+                                          (4096, 8, 64, dict(d_cache=512, d_e=8192))])    # the same with 16 tiles x 16 ranges of 1024, the most ranges
 def test_weight_gradients_of_ragged_batches(B, T, H, widths, monkeypatch):
     torch = need_gpu()
     import paper_2604_07239_amd as fa

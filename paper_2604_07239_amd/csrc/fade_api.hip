@@ -911,46 +911,57 @@ int run_phase(fade_ctx *c, const char *name, const PhaseGemms &ph) {
 struct WeightGrad { int id, pair, M, N, level; };
 
 // Weight gradients on 256 x 256 tiles feed nothing but the optimiser: they wait for the end of the backward pass and run as ONE
-// launch, whose workgroups share the tiles' contractions out in equal pieces (fade_tile_plan). The order of the tiles:
-// neighbours behind one another, in blocks of 2 x 4.
+// launch, whose workgroups share the tiles' ranges of the batch out in equal pieces (fade_tile_ranges, fade_tile_plan). Their
+// order: per matrix one range behind the other, in a range neighbouring tiles behind one another, in blocks of 2 x 4.
 int plan_weight_gradients(fade_ctx *c, const WeightGrad *gw, int n_gw) try {
   for (int &v : c->tn2_slot) v = -1;
-  std::vector<uint32_t> order;
-  std::vector<std::pair<int, std::vector<size_t>>> at;  // per matrix: its row of gw, its tiles' places in the order
+  struct Matrix { int row, tm, tn; };  // row of gw, tiles
+  std::vector<Matrix> mats;
+  int tiles = 0, least = 0;
+  const int units = (int)(c->Bp / 64);
   for (int i = 0; i < n_gw; ++i) {
-    if (!fade_gemm_tn2_ok(gw[i].M, gw[i].N, (int)c->Bp) || c->level() < gw[i].level || at.size() == 8) continue;
-    const uint32_t p = (uint32_t)at.size();
-    const int tm = gw[i].M / 256, tn = gw[i].N / 256;
-    at.emplace_back(i, std::vector<size_t>((size_t)tm * tn));
-    for (int m = 0; m < tm; m += 2)
-      for (int n = 0; n < tn; n += 4)
-        for (int mm = m; mm < m + 2 && mm < tm; ++mm)
-          for (int nn = n; nn < n + 4 && nn < tn; ++nn) {
-            at.back().second[(size_t)mm * tn + nn] = order.size();
-            order.push_back(p << 24 | (uint32_t)mm << 12 | (uint32_t)nn);
-          }
+    if (!fade_gemm_tn2_ok(gw[i].M, gw[i].N, (int)c->Bp) || c->level() < gw[i].level || mats.size() == 8) continue;
+    mats.push_back({i, gw[i].M / 256, gw[i].N / 256});
+    const int n = mats.back().tm * mats.back().tn;
+    tiles += n;
+    least = least == 0 || n < least ? n : least;
   }
-  if (!fade_tile_launch((int)c->Bp, (int)order.size())) return FADE_OK;
+  if (!fade_tile_launch((int)c->Bp, tiles)) return FADE_OK;
   Tn2Group &tg = c->tn2q;
-  tg.count = (int)at.size();
-  tg.tiles = (int)order.size();
-  tg.plan = fade_tile_plan(tg.tiles, (int)(c->Bp / 64));
-  uint32_t *dev = nullptr;
+  tg.count = (int)mats.size();
+  tg.ranges = fade_tile_ranges(tiles, least, tg.count, units);
+  tg.pieces = tiles * tg.ranges;
+  tg.plan = fade_tile_plan(tg.pieces, units / tg.ranges);
+  std::vector<Tn2Piece> order;
+  std::vector<std::vector<uint8_t>> parts;  // per matrix: partial sums of each tile
+  for (size_t p = 0; p < mats.size(); ++p) {
+    const Matrix &w = mats[p];
+    parts.emplace_back((size_t)w.tm * w.tn, (uint8_t)0);
+    for (int r = 0; r < tg.ranges; ++r)
+      for (int m = 0; m < w.tm; m += 2)
+        for (int n = 0; n < w.tn; n += 4)
+          for (int mm = m; mm < m + 2 && mm < w.tm; ++mm)
+            for (int nn = n; nn < n + 4 && nn < w.tn; ++nn) {
+              uint8_t &have = parts[p][(size_t)mm * w.tn + nn];
+              const int seq = (int)order.size();
+              order.push_back({(uint32_t)p << 28 | (uint32_t)r << 24 | (uint32_t)mm << 12 | (uint32_t)nn, have});
+              have = (uint8_t)(have + fade_tile_parts(tg.plan, fade_tile_of_seq(tg.plan, seq)));
+            }
+  }
+  Tn2Piece *dev = nullptr;
   int rc = dev_alloc(c, &dev, order.size());
   if (rc) return rc;
   tg.order = dev;
-  HIP_TRY(c, hipMemcpyAsync(dev, order.data(), order.size() * sizeof(uint32_t), hipMemcpyHostToDevice, c->stream));
+  HIP_TRY(c, hipMemcpyAsync(dev, order.data(), order.size() * sizeof(Tn2Piece), hipMemcpyHostToDevice, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
-  for (size_t p = 0; p < at.size(); ++p) {
-    const WeightGrad &w = gw[at[p].first];
-    std::vector<uint8_t> parts;
-    for (size_t seq : at[p].second) parts.push_back((uint8_t)fade_tile_parts(tg.plan, fade_tile_of_seq(tg.plan, (int)seq)));
-    const int most = *std::max_element(parts.begin(), parts.end());
+  for (size_t p = 0; p < mats.size(); ++p) {
+    const WeightGrad &w = gw[mats[p].row];
+    const int most = *std::max_element(parts[p].begin(), parts[p].end());
     c->tn2_slot[w.id] = (int)p;
     if (most == 1) continue;  // every tile whole: straight to the gradient array
     uint8_t *dp = nullptr;
-    if ((rc = dev_alloc(c, &dp, parts.size()))) return rc;
-    HIP_TRY(c, hipMemcpyAsync(dp, parts.data(), parts.size(), hipMemcpyHostToDevice, c->stream));
+    if ((rc = dev_alloc(c, &dp, parts[p].size()))) return rc;
+    HIP_TRY(c, hipMemcpyAsync(dp, parts[p].data(), parts[p].size(), hipMemcpyHostToDevice, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     for (int id : {w.id, w.pair}) {
       if (id < 0) continue;

@@ -151,12 +151,16 @@ struct GemmGroup {
 };
 
 // Weight gradients on 256 x 256 tiles of several matrices in ONE launch (gemm_tn2_kernel). A weight gradient feeds nothing but the
-// optimiser, so the products of a whole backward pass can wait for its end. order[i]: the i-th tile as product << 24 |
-// row tile << 12 | column tile; the plan says which workgroup works on which rows of the batch of which tiles.
+// optimiser, so the products of a whole backward pass can wait for its end. order[i]: the i-th piece, one of `ranges` equal
+// ranges of the batch for one tile; the plan (whose tiles are these pieces) says which workgroup works on which rows of which.
+struct Tn2Piece {
+  uint32_t at;     // product << 28 | range << 24 | row tile << 12 | column tile
+  uint32_t slice;  // of the product's partial sums: the piece's first one
+};
 struct Tn2Group {
-  int count, tiles;
+  int count, pieces, ranges;
   FadeTilePlan plan;
-  const uint32_t *order;
+  const Tn2Piece *order;
   GemmArgs g[8];
 };
 

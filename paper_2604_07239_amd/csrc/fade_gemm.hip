@@ -1369,17 +1369,17 @@ __device__ __forceinline__ void tn_body(const GemmArgs &g, int bid, int split = 
 }
 // ---------------------------------------------------------------------------------------------------
 // The same on 256 x 256 tiles, eight wavefronts (2 x 4, 128 x 64 each), for large batches: all such matrices of a backward pass in
-// one launch, one workgroup per compute unit (Tn2Group). The tiles' contractions are laid end to end and cut into 256 pieces of
-// equal length (fade_tile_plan: D_h = 2048, D_cache = D_e = 512: 192 tiles, three quarters of one per workgroup), so no round of
-// the chip is left half full whatever the number of tiles, and a tile arrives as two slices of the batch instead of the four that
-// equal ranges took; the Adam pass adds a tile's slices in order (tile_parts). Members of a group start at different rows of
-// the batch, but the same members of an XCD's groups work on neighbouring tiles (2 x 4) and the same rows, so six operand
-// panels in its L2 serve eight workgroups.
+// one launch, one workgroup per compute unit (Tn2Group). Every tile's contraction is summed in a few equal ranges of the batch
+// (fade_tile_ranges), as slices that the Adam pass adds in order; these pieces are laid end to end and cut into 256 equal shares
+// (fade_tile_plan), so no round of the chip is left half full whatever their number. D_h = 2048, D_cache = D_e = 512, 16384 rows: 192
+// tiles in 4 ranges, three whole pieces per workgroup; 4096 rows: 2 ranges, a share is one and a half pieces.
+// An XCD's workgroups are on neighbouring tiles (blocks of 2 x 4) of one range at a time, so six operand panels in its L2 serve eight.
 // The K loop is pipe2_body's: units of 64 rows of the batch (32 KiB per operand, rows of 512 bytes as they lie in memory), L through a
 // ring of three, R through a ring of two, one hand-over per unit, requests with scalar offsets spread between the matrix
-// instructions. It does not stop at the end of a tile: the requests run two units ahead into the next tile while the sums
+// instructions. It does not stop at the end of a piece: the requests run two units ahead into the next one while the sums
 // leave as they lie in the registers (a lane holds a column: 128-byte runs).
-// B = 16384 (411 Gflop): the launch 412 -> 331 us (1.24 PFLOP/s), the Adam pass behind it 103.5 -> 88 (half the slices to add).
+// B = 16384 (411 Gflop): 336 us (1.22 PFLOP/s) against 375 for a launch of 768 workgroups; with shares that cut whole tiles, half the
+// slices and chains of up to 12288 rows 325, and 87 us in the Adam pass against 104.
 // ---------------------------------------------------------------------------------------------------
 constexpr int TN2_LDS = 160 * 1024;
 __global__ __launch_bounds__(512, 1) void gemm_tn2_kernel(Tn2Group tg) {
@@ -1390,20 +1390,21 @@ __global__ __launch_bounds__(512, 1) void gemm_tn2_kernel(Tn2Group tg) {
   const FadeTilePlan pl = tg.plan;
   const int xcd = (int)blockIdx.x & 7, slot = (int)blockIdx.x >> 3, grp = slot / pl.wgs, member = slot - grp * pl.wgs;
   if (grp >= pl.groups) return;
-  const int begin = member * pl.per_wg, end = fade_tile_end(pl, tg.tiles, xcd, grp, member);
+  const int begin = member * pl.per_wg, end = fade_tile_end(pl, tg.pieces, xcd, grp, member);
   if (begin >= end) return;
 
-  // requests: one cursor two units ahead of the arithmetic. f_*: tile (position in the group), rows left of it, operand addresses
+  // requests: one cursor two units ahead of the arithmetic. j: piece (position in the group), k: unit of it
   struct Cursor { int j, k; } f{begin / pl.units, begin % pl.units}, c = f;
   const bf16_t *pa = nullptr, *pb = nullptr;  // first row of the unit the cursor stands at, first column of the tile
   int lda = 0, ldb = 0, rows = 0;             // rows of L that exist from that row on
   auto open = [&](const Cursor &t) {
-    const uint32_t e = (uint32_t)__builtin_amdgcn_readfirstlane((int)tg.order[fade_tile_seq(pl, xcd, grp, t.j)]);
-    const GemmArgs &g = tg.g[e >> 24];
+    const uint32_t e = (uint32_t)__builtin_amdgcn_readfirstlane((int)tg.order[fade_tile_seq(pl, xcd, grp, t.j)].at);
+    const GemmArgs &g = tg.g[e >> 28];
+    const int first = ((int)((e >> 24) & 15) * pl.units + t.k) * 64;
     lda = g.lda; ldb = g.ldb;
-    pa = static_cast<const bf16_t *>(g.A) + (size_t)t.k * 64 * lda + (size_t)((e >> 12) & 0xfff) * 256;
-    pb = static_cast<const bf16_t *>(g.W) + (size_t)t.k * 64 * ldb + (size_t)(e & 0xfff) * 256;
-    rows = g.a_rows - t.k * 64;
+    pa = static_cast<const bf16_t *>(g.A) + (size_t)first * lda + (size_t)((e >> 12) & 0xfff) * 256;
+    pb = static_cast<const bf16_t *>(g.W) + (size_t)first * ldb + (size_t)(e & 0xfff) * 256;
+    rows = g.a_rows - first;
   };
   open(f);
   auto advance = [&](int u) {  // to the unit behind u (counted like begin); nothing past the end
@@ -1507,11 +1508,12 @@ __global__ __launch_bounds__(512, 1) void gemm_tn2_kernel(Tn2Group tg) {
     };
     pair(I0{}); pair(I1{}); pair(I2{}); pair(I3{});
   };
-  // the sums of the tile the arithmetic has finished, or of the part of it that is this workgroup's
+  // the sums of the piece the arithmetic has finished, or of the part of it that is this workgroup's
   auto store = [&] {
-    const uint32_t e = (uint32_t)__builtin_amdgcn_readfirstlane((int)tg.order[fade_tile_seq(pl, xcd, grp, c.j)]);
-    const GemmArgs &g = tg.g[e >> 24];
-    const int slice = member - fade_tile_first(pl, c.j);
+    const Tn2Piece *piece = tg.order + fade_tile_seq(pl, xcd, grp, c.j);
+    const uint32_t e = (uint32_t)__builtin_amdgcn_readfirstlane((int)piece->at);
+    const GemmArgs &g = tg.g[e >> 28];
+    const int slice = __builtin_amdgcn_readfirstlane((int)piece->slice) + member - fade_tile_first(pl, c.j);
     const int m = (int)((e >> 12) & 0xfff) * 256 + wm * 128 + (lane >> 5) * 4, n = (int)(e & 0xfff) * 256 + wn * 64;
     // a pair of matrices, columns interleaved per 64: the wavefront's 64 columns belong to one of them
     float *dst = static_cast<float *>(g.C3 && (n & 64) ? g.C3 : g.C);
@@ -1730,7 +1732,7 @@ hipError_t launch_pipe(const GemmArgs &g, hipStream_t s) {
 }
 
 }  // namespace
-// tg.plan, tg.order and tg.tiles belong to the context; product p of the group is matrix p of the plan's order.
+// tg.plan, tg.order, tg.pieces and tg.ranges belong to the context; product p of the group is matrix p of the plan's order.
 hipError_t fade_gemm_tn2_launch(const Tn2Group &tg, hipStream_t s) {
   static bool attr_done = false;
   if (!attr_done) {
@@ -1741,12 +1743,12 @@ hipError_t fade_gemm_tn2_launch(const Tn2Group &tg, hipStream_t s) {
   int tiles = 0;
   for (int p = 0; p < tg.count; ++p) {
     const GemmArgs &g = tg.g[p];
-    if (!g.A || !g.W || !g.C || !fade_gemm_tn2_ok(g.M, g.N, g.K) || g.K != tg.plan.units * 64 || g.a_rows <= 0 || g.a_rows > g.K || g.K - g.a_rows >= 64 ||
+    if (!g.A || !g.W || !g.C || !fade_gemm_tn2_ok(g.M, g.N, g.K) || g.K != tg.ranges * tg.plan.units * 64 || g.a_rows <= 0 || g.a_rows > g.K || g.K - g.a_rows >= 64 ||
         g.lda % 8 || g.ldb % 8 || g.lda < g.M || g.ldb < g.N || g.lda > (1 << 20) || g.ldb > (1 << 20))
       return hipErrorInvalidValue;
     tiles += (g.M / 256) * (g.N / 256);
   }
-  if (tg.count <= 0 || tg.count > 8 || tiles != tg.tiles || !tg.order) return hipErrorInvalidValue;
+  if (tg.count <= 0 || tg.count > 8 || tg.ranges < 1 || tg.ranges > 16 || tiles * tg.ranges != tg.pieces || !tg.order) return hipErrorInvalidValue;
   hipLaunchKernelGGL(gemm_tn2_kernel, dim3(256), dim3(512), TN2_LDS, s, tg);
   return hipGetLastError();
 }

@@ -41,7 +41,30 @@ constexpr bool fade_streamed(bool bf16, bool online, size_t params, size_t B, si
 // H = 128 (128) 4096 843 -> 906; D_h = 1024, H = 512 (48) 4096 615 -> 622, 6144 902 -> 889-904.
 constexpr bool fade_tile_launch(int rows, int tiles) { return tiles > 0 && (rows >= 8192 || (rows >= 2048 && tiles >= 192)); }
 
-// How `tiles` equal contractions of `units` steps each are shared out over 256 workgroups, 32 on each of 8 XCDs. On an XCD, `groups`
+// Equal ranges of the batch that every tile's contraction over `units` blocks of 64 rows is summed in, each from zero, and added up by
+// the Adam pass in their order: a sum over thousands of rows in one fp32 accumulator drifts with its length (16384 rows of bf16 operands
+// against 64 bits: one chain 8.2e-7 of the result's norm, 12288 + 4096 rows 6.5e-7, four of 4096 4.1e-7). `count` matrices with `tiles`
+// tiles together, `least` in the smallest. Below 8192 rows two: what the grouped launches cut W_f and W_fg | W_fv into there.
+// From there on the smallest count, of eight blocks or more each, with two pieces or more per compute unit that leaves least of the last round
+// of the chip empty; where none divides the batch so, as many as give the smallest matrix a piece per unit. What the shorter chains
+// cost, adapting step in us with shares that cut whole tiles | shares of these ranges: D_h = 2048, H = 512, 16384 rows (4 ranges)
+// 2578 | 2601, 8192 (4) 1457 | 1485, 4096 (2) 927 | 935; H = 256, 16384 rows (16) 2478 | 2625; D_h = 1024, H = 512, 16384 rows (16)
+// 1595 | 1642; D_h = 512, D_cache = 4096, D_e = 8192, 4096 rows (2) 1069 | 1073.
+constexpr int fade_tile_ranges(int tiles, int least, int count, int units) {
+  if (units < 128) return units % 2 == 0 ? 2 : 1;
+  int best = 0, best_rounds = 1;
+  for (int r = 1; count >= 2 && r <= 16; r *= 2) {
+    const int rounds = (tiles * r + 255) / 256;
+    if (units % r != 0 || units / r < 8 || tiles * r < 512) continue;
+    if (best == 0 || r * best_rounds > best * rounds) { best = r; best_rounds = rounds; }  // ranges per round: the fill
+  }
+  if (best > 0) return best;
+  int r = 1;
+  while (r < 16 && least * r * 2 <= 256 && units % (r * 2) == 0 && units / (r * 2) >= 8) r *= 2;
+  return r;
+}
+
+// How `tiles` equal contractions of `units` steps each (a weight-gradient tile's ranges count as one each) are shared out over 256 workgroups, 32 on each of 8 XCDs. On an XCD, `groups`
 // groups of `wgs` workgroups take `tpg` tiles each: the group's tiles lie end to end and its members take per_wg steps each, so a
 // tile is cut where a member's share ends and arrives as one partial sum per member that worked on it. Small groups (at most
 // eight members) keep the members' starting points few, so that the same members of an XCD's groups read the same operand rows

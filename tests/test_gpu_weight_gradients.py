@@ -41,3 +41,38 @@ def test_weight_gradients_of_ragged_batches(B, T, H, widths, monkeypatch):
     g.step_update(torch.from_numpy(tgt).cuda(), ad)
     _compare_gradients(sub, _sub_view(blob, sub, g.debug_grad(), idx), go, 3e-2, f"B={B}")
     g.close()
+
+
+@pytest.mark.parametrize("B,T,H,matrices,bar", [
+    # sums over at most 2048 rows are exact: a product of two bf16 has 16 significant bits, 128 k-steps of 16 equal rows add 7
+    (4096, 64, 512, ("W_m", "W_r", "W_c", "W_fg", "W_fv", "W_f"), 1e-12),
+    (16384, 32, 512, ("W_r", "W_c", "W_fg", "W_fv"), 1e-12),
+    # 4096 rows in one chain, 256 k-steps of equal terms: below 2 ** k half the steps err by at most half a unit of 2 ** (k - 24), the
+    # binades below by a quarter of that each time: 256 / 3 units of 2 ** -24 of the sum
+    (16384, 64, 512, ("W_m", "W_r", "W_c", "W_fg", "W_fv", "W_f"), 256 / 3 * 2.0 ** -24)])
+def test_sums_over_many_rows_do_not_drift(B, T, H, matrices, bar, monkeypatch):
+    """Every stream the same: a weight gradient is then B times the outer product of two bf16 vectors, and what its best approximation
+    by one outer product (in 64 bits) leaves of it is the rounding of the sums, which grows with the rows added in one chain."""
+    torch = need_gpu()
+    import paper_2604_07239_amd as fa
+    D = 32
+    monkeypatch.setenv("FADE_DEBUG_WU_GRAD", "1")  # the sums of the slices go to the gradient array
+    one, blob = fi.init_blob(1, T, D, H, 7, std=0.05), fi.Blob(B, T, D, H)
+    for name, _, _ in one.specs:
+        blob[name] = np.broadcast_to(one[name], blob[name].shape) if name == "W_U" else one[name]
+    g = fa.Fade(fa.make_config(B, T, D, H, dtype=fa.BF16, update_mode=fa.ONLINE_ADAM))
+    g.load_weights(blob.data)
+    g.step_probs(torch.from_numpy(np.tile(fi.text(3, T), (B, 1))).cuda(), None, None, None)
+    g.step_update(torch.full((B,), 101, dtype=torch.uint8, device="cuda"))
+    blob.data[:] = np.asarray(g.debug_grad()).reshape(-1)
+    g.close()
+    for name in matrices:
+        G = torch.from_numpy(blob[name].astype(np.float64)).cuda()
+        right = G[G.norm(dim=1).argmax()].clone()
+        for _ in range(3):  # power iteration on what is one outer product but for rounding
+            right /= right.norm()
+            left = G @ right
+            right = G.t() @ left
+        right /= right.norm()
+        rest = G - (G @ right)[:, None] * right[None, :]
+        assert float(rest.norm() / G.norm()) <= bar, name

@@ -121,3 +121,43 @@ def test_tile_plan_takes_every_step_once(tmp_path):
     """Weight gradients at large batches: the workgroups' shares cover every step of every tile exactly once, and a tile's partial
     sums are the slices that the optimiser adds."""
     _run(TILE_PLAN, tmp_path)
+
+
+TILE_RANGES = """
+#include <stdio.h>
+#include "fade_rules.h"
+// ranges of a launch per matrix or of equal ranges over all of them (what the sums were formed in by launches of equal workgroups)
+static int by_launch(int tiles, int least, int count, int units) {
+  double best = 0.0;
+  int ranges = 0;
+  for (int sp = 1; count >= 2 && sp <= 16; sp *= 2) {
+    if (units % sp || units / sp < 8 || tiles * sp < 512) continue;
+    const int blocks = tiles * sp;
+    const double fill = (double)blocks / (((blocks + 255) / 256) * 256);
+    if (fill > best + 1e-9) { best = fill; ranges = sp; }
+  }
+  if (ranges) return ranges;
+  int sp = 1;
+  while (sp < 16 && least * sp * 2 <= 256 && units % (sp * 2) == 0 && units / (sp * 2) >= 8) sp *= 2;
+  return sp;
+}
+int main() {
+  const int sets[][3] = {{192, 16, 5}, {144, 16, 3}, {152, 24, 3}, {128, 64, 2}, {48, 16, 3}, {32, 16, 2}, {16, 16, 1}, {20, 20, 1}, {24, 24, 1}, {224, 32, 3}, {512, 64, 5}};
+  for (const auto &q : sets)
+    for (int units = 32; units <= 16384; units = units < 300 ? units + 1 : units + 97) {
+      const int r = fade_tile_ranges(q[0], q[1], q[2], units);
+      const int least = units < 128 ? (units % 2 == 0 ? 2 : 1) : by_launch(q[0], q[1], q[2], units);
+      if (r < least || r > 16 || units % r) { printf("%d tiles, %d blocks of rows: %d ranges, %d before\\n", q[0], units, r, least); return 1; }
+      const FadeTilePlan p = fade_tile_plan(q[0] * r, units / r);  // partial sums of a tile: counted in 8 bits
+      int most = 0;
+      for (int j = 0; j < p.tpg; ++j) most = fade_tile_parts(p, j) > most ? fade_tile_parts(p, j) : most;
+      if (most * r > 255) { printf("%d tiles, %d blocks of rows: %d x %d partial sums\\n", q[0], units, r, most); return 1; }
+    }
+  return 0;
+}
+"""
+
+
+def test_tile_ranges_keep_the_sums_short(tmp_path):
+    """Weight gradients at large batches: no fp32 chain is longer than with a launch of equal ranges for every workgroup."""
+    _run(TILE_RANGES, tmp_path)

@@ -10,12 +10,11 @@
 #include <memory>
 #include <new>
 #include <string>
-#include <system_error>
-#include <thread>
 #include <vector>
 
 #include "../../include/fade.h"
 #include "fade_kernels.h"
+#include "fade_lanes.h"
 #include "fade_rules.h"
 
 namespace {
@@ -2058,14 +2057,7 @@ static int read_blob(fade_ctx *c, const float *dev, void *blob_host) {
     }
     err[l] = e;
   };
-  std::thread helpers[READ_LANES];
-  try {
-    for (int l = 1; l < READ_LANES && (size_t)l < chunks; ++l) helpers[l] = std::thread(lane, l);
-  } catch (const std::system_error &) {  // the threads there are take all the chunks
-  }
-  lane(0);
-  for (std::thread &t : helpers)
-    if (t.joinable()) t.join();
+  fade_on_lanes<READ_LANES>((int)std::min<size_t>(READ_LANES, chunks), lane);
   for (const hipError_t e : err)
     if (e != hipSuccess) {
       (void)hipStreamSynchronize(c->stream);  // nothing writes to the buffers after the call

@@ -2057,7 +2057,8 @@ static int read_blob(fade_ctx *c, const float *dev, void *blob_host) {
     }
     err[l] = e;
   };
-  fade_on_lanes<READ_LANES>((int)std::min<size_t>(READ_LANES, chunks), lane);
+  // hipStreamPerThread names another stream on every thread: only the caller's has the work in front of the read-out
+  fade_on_lanes<READ_LANES>(c->stream == hipStreamPerThread ? 1 : (int)std::min<size_t>(READ_LANES, chunks), lane);
   for (const hipError_t e : err)
     if (e != hipSuccess) {
       (void)hipStreamSynchronize(c->stream);  // nothing writes to the buffers after the call

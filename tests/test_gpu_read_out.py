@@ -21,3 +21,27 @@ def test_weights_come_back_as_loaded(dtype, B, T, D, H, level):
     ctx.load_weights(data)
     for _ in range(3):  # the buffers are used again and again
         assert np.array_equal(ctx.get_weights(), data)
+
+
+def test_weights_behind_work_on_the_callers_per_thread_stream():
+    """hipStreamPerThread as the context's stream: every thread has its own, and the read-out waits for the caller's."""
+    torch = need_gpu()
+    import paper_2604_07239_amd as fa
+    B, T, D, H = 128, 16, 32, 128  # several chunks
+    blob = fi.init_blob(B, T, D, H, 3)
+    text = np.random.default_rng(5).integers(0, 256, (B, T + 1), dtype=np.uint8)
+    win, tgt = torch.from_numpy(np.ascontiguousarray(text[:, :T])).cuda(), torch.from_numpy(np.ascontiguousarray(text[:, T])).cuda()
+    torch.cuda.synchronize()
+    got = []
+    for handle in (0, 2):  # a stream of the library's own; hipStreamPerThread
+        g = fa.Fade(fa.make_config(B, T, D, H, dtype=fa.BF16, update_mode=fa.ONLINE_ADAM, hip_stream=handle))
+        g.load_weights(blob.data)
+        if handle:
+            with torch.cuda.stream(torch.cuda.ExternalStream(handle)):
+                torch.cuda._sleep(200_000_000)  # some 100 ms in front of the step
+        g.step_probs(win)
+        g.step_update(tgt)
+        got.append(g.get_weights())
+        g.close()
+    assert not np.array_equal(got[0], blob.data)
+    assert np.array_equal(got[0], got[1])

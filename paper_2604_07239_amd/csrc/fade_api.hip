@@ -122,8 +122,9 @@ struct fade_ctx {
   // fade_destroy, so a context that codes job after job allocates once
   void *stage[3] = {nullptr, nullptr, nullptr};
   size_t stage_cap[3] = {0, 0, 0};
-  // weights on their way to the host (read_blob): pinned chunks of an adapting context
+  // weights on their way to the host (read_blob): pinned chunks of an adapting context, from its first read-out on
   float *read_buf = nullptr;
+  bool read_tried = false;
   hipEvent_t read_ev[READ_LANES] = {};
 
   // progressive ablation: the last stage that is switched on feeds the head (5: the full model)
@@ -1716,17 +1717,6 @@ int fade_create(const fade_config *cfg, fade_ctx **out) {
   *c->dev_err = 0;
   c->cb.err = c->dev_err;
 #undef TRY_ALLOC
-  if (c->online) {  // without them the weights are read out more slowly
-    bool have = hipHostMalloc(reinterpret_cast<void **>(&c->read_buf), READ_LANES * READ_CHUNK * sizeof(float), hipHostMallocDefault) == hipSuccess;
-    if (!have) c->read_buf = nullptr;
-    else memset(c->read_buf, 0, READ_LANES * READ_CHUNK * sizeof(float));  // mapped here, not on the way of the first read-out
-    for (hipEvent_t &ev : c->read_ev) have = have && hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess;
-    if (!have) {
-      (void)hipGetLastError();
-      if (c->read_buf) (void)hipHostFree(c->read_buf);
-      c->read_buf = nullptr;
-    }
-  }
   if (c->online && hipMalloc(reinterpret_cast<void **>(&c->loaded), np * sizeof(float)) != hipSuccess) {  // last: nothing gives way to it
     (void)hipGetLastError();
     c->loaded = nullptr;
@@ -2020,12 +2010,29 @@ size_t fade_tap(fade_ctx *c, int which, float *out_host, size_t cap_floats) {
   return width;
 }
 
+// The pinned chunks of the read-out and their events: made at the first one, since a context that codes jobs never reads its weights
+// (in fade_create they took 1.5 ms, mapping 4 MiB page by page). True: they are new, and no page of them is mapped yet.
+// Without them the weights leave more slowly.
+static bool read_buffers(fade_ctx *c) {
+  if (c->read_tried || !c->online) return false;
+  c->read_tried = true;
+  bool have = hipHostMalloc(reinterpret_cast<void **>(&c->read_buf), READ_LANES * READ_CHUNK * sizeof(float), hipHostMallocDefault) == hipSuccess;
+  if (!have) c->read_buf = nullptr;
+  for (hipEvent_t &ev : c->read_ev) have = have && hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess;
+  if (have) return true;
+  (void)hipGetLastError();
+  if (c->read_buf) (void)hipHostFree(c->read_buf);
+  c->read_buf = nullptr;
+  return false;
+}
 // device array (device layout) -> canonical blob on the host
-// The blob leaves in chunks of 1 MiB through pinned buffers: a kernel brings a chunk into the blob's order on its way over the bus, then a
+// The blob leaves in chunks through pinned buffers: a kernel brings a chunk into the blob's order on its way over the bus, then a
 // host thread copies it to where the caller wants it; READ_LANES threads, the caller's among them, each with its own buffer, since one
 // of them copies (and has the pages of a fresh destination zeroed) at half the bus's rate. Copies straight to pageable memory go
 // one run of the layout at a time, each with its own round trip and at a third of that rate: 4.2 MB (T = 32, D = 16, H = 128, 16
-// streams) 326 us, 9.2 MB (T = 16, D = 32, H = 512, 128 streams) 715; through one thread 261 and 512, now 240 and 412.
+// streams) 329-338 us, 9.2 MB (T = 16, D = 32, H = 512, 128 streams) 695-726, 62 MB (T = 64, D = 32, H = 256, 1024 streams) 6080-6120;
+// this way 247-262, 459-484 and 2380-2430, the first time 1 ms more. With chunks of half the size an adaptation of 16 streams and its
+// read-out took 1192 us instead of 1123; with a quarter 62 MB took 3740, two such chunks per thread in turn 3180.
 static int read_blob(fade_ctx *c, const float *dev, void *blob_host) {
   constexpr size_t CHUNK = READ_CHUNK;
   const size_t total = c->blob.off[P_COUNT], chunks = (total + CHUNK - 1) / CHUNK;
@@ -2036,6 +2043,7 @@ static int read_blob(fade_ctx *c, const float *dev, void *blob_host) {
     return (int)FADE_OK;
   });
   if (rc) return rc;
+  const bool fresh = read_buffers(c);
   if (!c->read_buf) {  // frozen weights, or no pinned memory left: run by run to where the caller wants it
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     return for_each_run(c->blob, c->lay, [&](size_t to, size_t from, size_t n) {
@@ -2052,6 +2060,8 @@ static int read_blob(fade_ctx *c, const float *dev, void *blob_host) {
       const size_t n = std::min(CHUNK, total - k * CHUNK);
       e = fade_read_out(runs, dev, buf, k * CHUNK, n, c->stream);
       if (e == hipSuccess) e = hipEventRecord(c->read_ev[l], c->stream);
+      if (fresh)  // the pages of a new buffer are mapped while the device still works
+        for (size_t i = 0; i < n; i += 1024) (void)*static_cast<volatile float *>(buf + i);
       if (e == hipSuccess) e = hipEventSynchronize(c->read_ev[l]);
       if (e == hipSuccess) memcpy(static_cast<float *>(blob_host) + k * CHUNK, buf, n * sizeof(float));
     }

@@ -8,9 +8,9 @@ from gpu_helpers import need_gpu
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("dtype,B,T,D,H,level", [("f32", 1, 16, 16, 64, 0),     # less than one chunk
+@pytest.mark.parametrize("dtype,B,T,D,H,level", [("f32", 1, 16, 16, 64, 0),     # two chunks, the second one short
                                                   ("f32", 5, 32, 16, 128, 0),    # the scalars leave no run aligned alike in blob and layout
-                                                  ("bf16", 67, 64, 32, 128, 0),  # ten chunks and more than threads, the last one ragged
+                                                  ("bf16", 67, 64, 32, 128, 0),  # 41 chunks, the last one ragged
                                                   ("bf16", 3, 16, 32, 128, 2)])
 def test_weights_come_back_as_loaded(dtype, B, T, D, H, level):
     need_gpu()
@@ -27,7 +27,7 @@ def test_weights_behind_work_on_the_callers_per_thread_stream():
     """hipStreamPerThread as the context's stream: every thread has its own, and the read-out waits for the caller's."""
     torch = need_gpu()
     import paper_2604_07239_amd as fa
-    B, T, D, H = 128, 16, 32, 128  # several chunks
+    B, T, D, H = 128, 16, 32, 128  # six chunks
     blob = fi.init_blob(B, T, D, H, 3)
     text = np.random.default_rng(5).integers(0, 256, (B, T + 1), dtype=np.uint8)
     win, tgt = torch.from_numpy(np.ascontiguousarray(text[:, :T])).cuda(), torch.from_numpy(np.ascontiguousarray(text[:, T])).cuda()

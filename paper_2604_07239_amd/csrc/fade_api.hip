@@ -1675,11 +1675,9 @@ int fade_create(const fade_config *cfg, fade_ctx **out) {
       }
     }
     if (c->bf16 && 2 * d.De >= 4096 && d.Dh % 128 == 0) {
-      // on 256 x 256 tiles where ranges of 1024 and more give every compute unit one (D_h = 512, D_e = 8192, B = 4096: 32 tiles x 8
-      // ranges; the product 117 -> 87 us, the sum of the ranges behind it 23 -> 30), else on 128 x 128: 384 workgroups or more, ranges of 8 blocks or more
-      const size_t t256 = d.B % 256 == 0 && d.Dh % 256 == 0 ? d.B / 256 * (d.Dh / 256) : 0;
-      for (int sp = 2; t256 > 0 && t256 < 256 && sp <= 16; sp *= 2)
-        if (t256 * sp >= 256 && 2 * d.De % (64 * sp) == 0 && 2 * d.De / sp >= 1024) { c->du_tall = true; c->sp_du = sp; break; }
+      // on 256 x 256 tiles (fade_tall_ranges), else on 128 x 128: 384 workgroups or more, ranges of 8 blocks or more
+      c->sp_du = fade_tall_ranges(d.B, d.Dh, 2 * d.De);
+      c->du_tall = c->sp_du > 0;
       if (!c->du_tall) c->sp_du = pick_splits((int)((d.B + 127) / 128 * (d.Dh / 128)) / 2, (int)(2 * d.De / 64 / 4), 16);
       if (c->sp_du > 1) TRY_ALLOC(dev_alloc(c, &c->du_part, (size_t)c->sp_du * d.B * d.Dh));
     }

@@ -94,3 +94,23 @@ constexpr int fade_tile_end(const FadeTilePlan &p, int tiles, int xcd, int group
   const int end = (member + 1) * p.per_wg;
   return end < have * p.units ? end : have * p.units;
 }
+
+// Ranges of the contraction over K = 2 D_e that the gradient at H_coarse (B x D_h of them) is cut into on 256 x 256 tiles, as fp32
+// partials that the kernel behind adds; 0: no such tiles (then 128 x 128, cut or not). As many as one round of the chip has workgroups
+// for, of 1024 or more each: a few workgroups past a round cost another round, and every range is written and read again. Over half
+// the chip, or 128-wide tiles are as fast. From 128 tiles on two, where a range is 4096 or the rows are narrow (D_h <= 512: the
+// narrower tiles read the long operand once per 128 columns). The product and the kernel behind in us, 128 x 128 tiles | this rule,
+// and (with so many ranges) the first power of two that gives 256 workgroups where that is another:
+// D_h = 512, D_e = 8192: 18 tiles 107 | 89, (16) 95; 32 146 | 123; 34 162 | 151, (8) 155; 48 218 | 182, (8) 196; 66 331 | 261, (4) 294;
+// 96 404 | 274, (4) 355; 120 397 | 307, (4) 368; 128 398 | 300. D_e = 2048: 32 90 | as that, (4) 94; 66 134 | 118, (4) 137; 96 147 | 130, (4) 155;
+// 128 169 | 150. D_h = 1024, D_e = 4096: 64 138 | 107; 136 291 | 260; 200 346 | 291. D_h = 2048, D_e = 4096: 136 235 | 226; 200 272 | 263.
+// D_e = 2048, 128 tiles: D_h = 1024 145 | as that, (2) 145; D_h = 2048 106 | as that, (2) 110.
+constexpr int fade_tall_ranges(size_t B, size_t Dh, size_t K) {
+  if (B % 256 != 0 || Dh % 256 != 0) return 0;
+  const size_t tiles = B / 256 * (Dh / 256);
+  if (tiles == 0 || tiles >= 256) return 0;
+  size_t r = 2;
+  while (r < 16 && tiles * r * 2 <= 256 && K % (64 * r * 2) == 0 && K / (r * 2) >= 1024) r *= 2;
+  if (K % (64 * r) != 0 || K / r < 1024 || tiles * r <= 128) return 0;
+  return tiles < 128 || K / r >= 4096 || Dh <= 512 ? (int)r : 0;
+}

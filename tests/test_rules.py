@@ -161,3 +161,28 @@ int main() {
 def test_tile_ranges_keep_the_sums_short(tmp_path):
     """Weight gradients at large batches: no fp32 chain is longer than with a launch of equal ranges for every workgroup."""
     _run(TILE_RANGES, tmp_path)
+
+
+TALL_RANGES = """
+#include <stdio.h>
+#include "fade_rules.h"
+int main() {
+  for (size_t De = 2048; De <= 8192; De += 64)
+    for (size_t Dh = 128; Dh <= 2048; Dh += 128)
+      for (size_t B = 1; B <= 20000; B += B % 256 == 1 ? 255 : 1) {
+        const int r = fade_tall_ranges(B, Dh, 2 * De);
+        if (r == 0) continue;
+        const size_t tiles = B / 256 * (Dh / 256), wgs = tiles * r;
+        const bool whole = B % 256 == 0 && Dh % 256 == 0 && 2 * De % (64 * r) == 0 && 2 * De / r >= 1024 && r <= 16;
+        // one round of the chip, more than half full; two from 128 tiles on
+        if (!whole || wgs <= 128 || (wgs > 256 && !(tiles > 128 && r == 2)) || tiles >= 256) {
+          printf("B=%zu D_h=%zu D_e=%zu: %zu tiles x %d ranges\\n", B, Dh, De, tiles, r); return 1;
+        }
+      }
+  return fade_tall_ranges(4096, 512, 16384) != 8 || fade_tall_ranges(4096, 256, 16384) != 16 || fade_tall_ranges(8448, 512, 16384) != 2;
+}
+"""
+
+
+def test_ranges_of_the_wide_refiners_gradient_fit_a_round(tmp_path):
+    _run(TALL_RANGES, tmp_path)

@@ -184,6 +184,7 @@ struct fade_ctx {
   // weight gradients with few output tiles are left as partial sums over ranges of the batch (bf16 path): per parameter
   // tensor the number of ranges (1: none) and the slices [ranges][K][N]; the Adam pass adds them up
   int gsp[P_COUNT] = {};
+  bool fnr_few = false;  // single steps take Eq. 9 in one launch though K is split
   bool du_tall = false;  // du's partials on 256 x 256 tiles
   // weight gradients on 256 x 256 tiles wait here until the end of the backward pass and run as one launch: tn2q.g[tn2_slot[id]]
   Tn2Group tn2q{};
@@ -670,9 +671,7 @@ int forward_bf16(fade_ctx *c, const WinSrc &ws, int mode, uint8_t *sym_base, uin
     g.lam = c->P(P_LAMBDA_C); g.stats_out = c->stats_f;
     HIP_TRY(c, fade_gemm(GEMM_GATE, true, g, s));
   }
-  // Eq. 9 in one launch, folded LN and GeGLU in the product's epilogue: with tiles enough without splitting K, and, single steps, where
-  // its 64 x 128 tiles are a round of the chip or less (then two groups of wavefronts share K, see gemm_fnr_kernel)
-  const bool fnr_few = c->sp_fnr > 1 && !fuse && ((B + 63) / 64) * (2 * De / 128) <= 256 && De % 64 == 0;
+  const bool fnr_few = c->fnr_few && !fuse;
   if (level < 5) {
   } else if (c->sp_fnr == 1 || fnr_few) {
     Prof p(c, "gemm_fnr_in");
@@ -1537,7 +1536,11 @@ int fade_create(const fade_config *cfg, fade_ctx **out) {
     // single steps leave one slice per K range, multi-step passes one slice of all their rows
     const auto part_rows = [&](int splits) { return std::max((size_t)splits * d.B, R); };
     TRY_ALLOC(dev_alloc(c, &c->part_down, part_rows(c->sp_down) * d.dl));
-    if (c->sp_fnr > 1) TRY_ALLOC(dev_alloc(c, &c->part_fnr, part_rows(c->sp_fnr) * 2 * d.De));  // one K range: no partials (folded epilogue)
+    // Eq. 9 in one launch, folded LN and GeGLU in the product's epilogue: with tiles enough without splitting K, and, single steps, where
+    // its 64 x 128 tiles are a round of the chip or less (then two groups of wavefronts share K, see gemm_fnr_kernel)
+    c->fnr_few = c->sp_fnr > 1 && (d.B + 63) / 64 * (2 * d.De / 128) <= 256;
+    const size_t fnr_rows = c->sp_fnr == 1 ? 0 : !c->fnr_few ? part_rows(c->sp_fnr) : c->steps_max > 1 ? R : 0;
+    if (fnr_rows > 0) TRY_ALLOC(dev_alloc(c, &c->part_fnr, fnr_rows * 2 * d.De));
     TRY_ALLOC(dev_alloc(c, &c->part_head, part_rows(c->sp_head) * 256));
     if (c->steps_max > 1) TRY_ALLOC(dev_alloc(c, &c->ranges, R));
     if (!c->online) {

@@ -888,9 +888,10 @@ int run_phase(fade_ctx *c, const char *name, const PhaseGemms &ph) {
   if (c->bf16) {
     // An activation gradient that fills the chip with 256 x 256 tiles by itself (large batches) runs as a launch of its
     // own on the eight-wavefront kernel: half the operand bytes per flop of the 128 x 128 tiles a group is made of
-    // (B = 16384, when the group also held the weight gradient: gate phase 357 -> 337 us, router phase 454 -> 434; B = 4096 with
-    // K = 512, D_e = 8192: 138.9 -> 136.4 ms per job together with du's partial sums on such tiles). With a shorter contraction (the head's
-    // K = 256) the overlap inside a group is worth more (87 us grouped against 105).
+    // (B = 16384, when the group also held the weight gradient: gate phase 357 -> 337 us, router phase 454 -> 434; K = 512, N = 2048:
+    // 8192 rows 30 -> 24, and where the rows are no multiple of 256, on 128 x 128 tiles of its own: 10001 rows 36 -> 32, K = 768
+    // 8700 rows 47 -> 43, K = 512, N = 8192 4001 rows 49.5 -> 46.5). With a shorter contraction (the head's K = 256) the overlap
+    // inside a group is worth more (87 us grouped against 105).
     GemmGroup gg{};
     for (int i = 0; i < ph.n; ++i) {
       const GemmArgs &g = ph.g[i];

@@ -1,5 +1,6 @@
 """The launch that shares all 256 x 256 weight-gradient tiles out in equal pieces, at batches that end inside a block of 64 rows:
-gradients of one step against the oracle on a few active streams (the others have a gradient of zero), the last ones among them."""
+gradients of one step against the oracle, an active stream in every block (the others have a gradient of zero), so that a block that is
+left out, taken twice or read from another place shows wherever a workgroup's share or a range of the batch ends."""
 import numpy as np
 import pytest
 
@@ -11,16 +12,22 @@ from test_gpu_online import _compare_gradients, _sub_view
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B,T,H,widths", [(2050, 64, 512, {}),   # 192 tiles of 33 blocks: the smallest batch that takes the launch
-                                          (8200, 32, 320, {}),    # 32 tiles (gradients of W_c, W_r): eight workgroups to a tile
-                                          (2111, 16, 64, dict(d_cache=4096, d_e=8192)),   # 224 tiles of a wide refiner, one row short of a block
-                                          (4096, 16, 64, dict(d_cache=512, d_e=8192)),    # gradient at H_coarse: 32 tiles x 8 ranges of its own on 256 x 256
-                                          (4096, 8, 64, dict(d_cache=512, d_e=8192))])    # the same with 16 tiles x 16 ranges of 1024, the most ranges
-def test_weight_gradients_of_ragged_batches(B, T, H, widths, monkeypatch):
+@pytest.mark.parametrize("B,T,H,widths,launch", [
+    (2050, 64, 512, {}, True),    # 192 tiles of 33 blocks, one range: the smallest batch that takes the launch
+    (2170, 64, 512, {}, True),    # 34 blocks: two ranges of 17, shares that end inside them
+    (8200, 32, 320, {}, True),    # 32 tiles of 129 blocks (gradients of W_c, W_r): eight workgroups to a tile
+    (8300, 32, 320, {}, True),    # 130 blocks: two ranges, four workgroups to each
+    (8192, 32, 320, {}, True),    # 128 blocks: 16 ranges, a workgroup's share is two of them
+    (8192, 16, 64, dict(d_cache=64, d_e=1024), True),    # one matrix of 16 tiles (W_fg | W_fv): 16 ranges give every compute unit one
+    (2111, 16, 64, dict(d_cache=4096, d_e=8192), True),  # 224 tiles of a wide refiner, one row short of a block
+    (4096, 16, 64, dict(d_cache=512, d_e=8192), True),   # gradient at H_coarse: 32 tiles x 8 ranges of its own on 256 x 256
+    (4096, 8, 64, dict(d_cache=512, d_e=8192), False)])  # the same with 16 tiles x 16 ranges of 1024, the most ranges
+def test_weight_gradients_of_ragged_batches(B, T, H, widths, launch, monkeypatch):
     torch = need_gpu()
     import paper_2604_07239_amd as fa
     D = 32
-    idx = np.unique(np.r_[0, 63, 64, np.linspace(0, B - 1, 12).astype(np.int64), B - 2, B - 1])
+    blocks = np.arange((B + 63) // 64)
+    idx = np.unique(np.r_[0, np.minimum(64 * blocks + 37 * blocks % 64, B - 1), B - 2, B - 1])  # 37: the rows wander through the blocks
     act = np.zeros(B, np.uint8)
     act[idx] = 1
     blob = fi.init_blob(B, T, D, H, 7, std=0.05, **widths)
@@ -35,10 +42,12 @@ def test_weight_gradients_of_ragged_batches(B, T, H, widths, monkeypatch):
     data = np.random.default_rng(B).integers(0, 256, (B, T + 1), dtype=np.uint8)
     win, tgt = np.ascontiguousarray(data[:, :T]), np.ascontiguousarray(data[:, T])
     ad = torch.from_numpy(act).cuda()
+    g.profile(True)
     g.step_probs(torch.from_numpy(win).cuda(), ad, None, None)
     o.step_probs(np.ascontiguousarray(win[idx]), None)
     go = o.backward(np.ascontiguousarray(tgt[idx]), None)
     g.step_update(torch.from_numpy(tgt).cuda(), ad)
+    assert ("gemms_weights" in g.profile_read()) == launch
     _compare_gradients(sub, _sub_view(blob, sub, g.debug_grad(), idx), go, 3e-2, f"B={B}")
     g.close()
 

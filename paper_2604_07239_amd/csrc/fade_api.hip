@@ -2039,12 +2039,16 @@ static int read_blob(fade_ctx *c, const float *dev, void *blob_host) {
   constexpr size_t CHUNK = READ_CHUNK;
   const size_t total = c->blob.off[P_COUNT], chunks = (total + CHUNK - 1) / CHUNK;
   BlobRuns runs{};
+  static_assert(P_COUNT <= BlobRuns::MAX, "runs");
   int rc = for_each_run(c->blob, c->lay, [&](size_t to, size_t from, size_t) {
     runs.to[runs.n] = to;
     runs.from[runs.n++] = from;
     return (int)FADE_OK;
   });
   if (rc) return rc;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;  // a result for the host cannot wait in a graph
+  HIP_TRY(c, hipStreamIsCapturing(c->stream, &capture));
+  if (capture != hipStreamCaptureStatusNone) return hip_fail(c, hipErrorStreamCaptureUnsupported, "reading the weights");
   const bool fresh = read_buffers(c);
   if (!c->read_buf) {  // frozen weights, or no pinned memory left: run by run to where the caller wants it
     HIP_TRY(c, hipStreamSynchronize(c->stream));

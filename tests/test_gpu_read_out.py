@@ -45,3 +45,29 @@ def test_weights_behind_work_on_the_callers_per_thread_stream():
         g.close()
     assert not np.array_equal(got[0], blob.data)
     assert np.array_equal(got[0], got[1])
+
+
+def test_weights_do_not_join_a_graph():
+    """A read-out while the context's stream is captured is refused and leaves nothing in the graph."""
+    torch = need_gpu()
+    import paper_2604_07239_amd as fa
+    B, T, D, H = 1, 16, 16, 64
+    blob = fi.init_blob(B, T, D, H, 3)
+    s = torch.cuda.Stream()
+    g = fa.Fade(fa.make_config(B, T, D, H, dtype=fa.F32, update_mode=fa.ONLINE_ADAM, hip_stream=s.cuda_stream))
+    g.load_weights(blob.data)
+    x = torch.zeros(64, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(s):
+        graph.capture_begin()
+        x.add_(1.0)
+        with pytest.raises(fa.FadeError):
+            g.get_weights()
+        graph.capture_end()
+        for k in (1, 2):
+            graph.replay()
+            s.synchronize()
+            assert float(x.sum()) == 64.0 * k
+    assert np.array_equal(g.get_weights(), blob.data)
+    g.close()

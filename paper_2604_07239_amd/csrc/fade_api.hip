@@ -1683,6 +1683,7 @@ int fade_create(const fade_config *cfg, fade_ctx **out) {
       c->sp_du = fade_tall_ranges(d.B, d.Dh, 2 * d.De);
       c->du_tall = c->sp_du > 0;
       if (!c->du_tall) c->sp_du = pick_splits((int)((d.B + 127) / 128 * (d.Dh / 128)) / 2, (int)(2 * d.De / 64 / 4), 16);
+      while (2 * d.De / 64 % c->sp_du != 0) c->sp_du /= 2;  // equal ranges (D_e = 2112: 66 blocks)
       if (c->sp_du > 1) TRY_ALLOC(dev_alloc(c, &c->du_part, (size_t)c->sp_du * d.B * d.Dh));
     }
     c->sp_dz = c->bf16 ? pick_splits((int)((d.B + 63) / 64), (int)(d.Dh / 64), 16) : 1;

@@ -26,3 +26,19 @@ def test_large_tile_contraction_lengths(d_cache, d_e, monkeypatch):
         np.testing.assert_array_equal(g.decode(outs[-1], n), src)
         g.close()
     assert outs[0].tobytes() == outs[1].tobytes()
+
+
+@pytest.mark.parametrize("B,d_e", [(37, 2112), (130, 4160)])  # 66 and 130 blocks of 64 along K = 2 D_e: two ranges, where four or eight do not divide
+def test_wide_refiner_whose_contraction_divides_into_few_ranges(B, d_e):
+    torch = need_gpu()
+    from test_gpu_online import _compare_gradients, _make_pair_with_wu_grad
+    T, D, H = 8, 32, 64
+    g, o, blob = _make_pair_with_wu_grad(B, T, D, H, "bf16", seed=B, update_mode=1, std=0.05, d_e=d_e)
+    data = np.random.default_rng(B).integers(0, 256, (B, T + 1), dtype=np.uint8)
+    win, tgt = np.ascontiguousarray(data[:, :T]), np.ascontiguousarray(data[:, T])
+    g.step_probs(torch.from_numpy(win).cuda())
+    o.step_probs(win, None)
+    go = o.backward(tgt, None)
+    g.step_update(torch.from_numpy(tgt).cuda())
+    _compare_gradients(blob, g.debug_grad(), go, 3e-2, f"D_e={d_e}")
+    g.close()

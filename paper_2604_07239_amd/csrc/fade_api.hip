@@ -1645,12 +1645,10 @@ int fade_create(const fade_config *cfg, fade_ctx **out) {
       // W_down (128 K elements) is cut down to ranges of 2 blocks. B = 1024: Down phase 16 -> 13 us, the others unchanged
       // (cutting them too cost 11 us more in the Adam pass than it saved); B = 4096: head / FNR-out / FNR-in / Down
       // phases 52 / 55 / 55 / 62 -> 24 / 37 / 39 / 16 us for 12 us more in the Adam pass.
-      // The two D_h x D_h gradients (256 tiles: a full product by the rule above) share their phase with an activation
-      // gradient whose workgroups walk D_h / 64 blocks while theirs walk the batch; after the first round of the 512
-      // workgroup slots they run on half the chip, and two ranges make that second round a full one. The Adam pass pays
-      // 15 us for the two extra 16 MiB slices, which B = 4096 only just gets back (phases 114 / 123 -> 106 / 115 us) and
-      // B = 16384 does (445 / 460 -> 375 / 470, step 3.74 -> 3.64 ms): from 8192 rows on, with W_up and W_m of the same phases.
-      // level: the ablation level from which the matrix takes part
+      // Gradients of 192 to 511 tiles share their phase with an activation gradient that leaves half the chip's 512 workgroup slots idle
+      // in its second round: two ranges of them from 2048 rows on (W_fg | W_fv of D_h = 2048, D_e = 384, 2048 / 4096 / 6144 rows: phase
+      // 36 / 64 / 92 -> 31 / 49 / 67 us; W_f of D_h = 1024, D_e = 2048, 4096 rows 67 -> 53), for which the Adam pass pays 1 to 7 us.
+      // W_up, W_m and the D_h x D_h ones that are not tiles of the one launch below are cut from 8192 rows on.
       const WeightGrad gw[] = {{P_WC, -1, (int)d.Dh, (int)d.Dh, 4}, {P_WR, -1, (int)d.Dh, (int)d.Dh, 2},
                                                            {P_WFG, P_WFV, (int)d.Dh, (int)(2 * d.De), 5}, {P_WF, -1, (int)d.De, (int)d.Dh, 5},
                                                            {P_WM, -1, (int)d.Dc, (int)d.Dh, 1}, {P_WO, -1, (int)d.Dh, 256, 1},

@@ -563,7 +563,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g) {
 // the unit STAGES further on, whose requests go between the matrix instructions. Their addresses are a buffer resource, lane
 // offsets and a scalar offset: no vector instructions.
 // M = 1024, N = K = 2048, 64 x 128 tiles with the mix / gate epilogue: 18.7 / 18.4 us with the first fragments of a unit waited
-// for behind its barrier and the requests in one burst in front of them, 16.2 / 15.7 now, where what a compute unit is
+// for behind its barrier and the requests in one burst in front of them, 17.0 / 16.4 now (kernel traces of whole steps), where what a compute unit is
 // fed with from the L2 (24 KiB per unit) bounds it.
 // grid.y > 1: split K, each block leaves an fp32 partial tile (EPI_PARTIAL)
 // ---------------------------------------------------------------------------------------------------
@@ -1238,8 +1238,8 @@ typedef __attribute__((ext_vector_type(4))) short i16x4;
 typedef __attribute__((ext_vector_type(8))) short i16x8;
 // piece permutation of row r in a stage whose rows are PITCH bytes long
 template <int PITCH> __device__ __forceinline__ int tn_swizzle(int r) {
-  static_assert(PITCH == 128 || PITCH == 256 || PITCH == 512, "row pitch");
-  return PITCH >= 256 ? ((r & 3) << 2) : (((r >> 1) & 1) << 2);  // 512: the permutation stays inside a row's 256-byte half
+  static_assert(PITCH == 128 || PITCH == 256, "row pitch");
+  return PITCH == 256 ? ((r & 3) << 2) : (((r >> 1) & 1) << 2);
 }
 
 template <int BM, int BN, int STAGES>
@@ -1883,8 +1883,9 @@ hipError_t fade_gemm_group_add(GemmGroup &gg, int op, const GemmArgs &g) {
     const int t128 = g.N % 128 == 0 ? ((g.M + 127) / 128) * (g.N / 128) : 0;
     // 128 x 128 tiles from 256 of them on, or from 128 when the contraction is long (then the bytes per flop matter more than
     // the number of workgroups: B = 1024, K = D_h = 2048: 43 us against 48 with 64 x 128; K = 64: 12.6 against 9.0)
-    // a very long contraction with few output tiles (du = dE [W_fg W_fv]^T at D_e = 8192: K = 16384, 4096 x 512 outputs) is a
-    // chain of hundreds of K blocks per workgroup: small tiles, many workgroups (D_e = 8192, B = 4096: that phase 327 -> 2xx us)
+    // a very long contraction with few output tiles whose blocks no split divides (du = dE [W_fg W_fv]^T at D_e = 8128) is a chain of
+    // hundreds of K blocks per workgroup: small tiles, many workgroups (that phase in us with 64 x 64 | without, D_h = 512: 1500 rows
+    // 213-224 | 228, 4096 313 | 310, but 2100 257 | 220 and 3000 281 | 233; D_h = 2048: 700 rows 258 | 275)
     if (g.K >= 4096 && g.N % 64 == 0 && t128 < 256) { kind = GK_STORE_64x64; bn = 64; }
     else if ((t128 >= 256 || (t128 >= 128 && g.K >= 1024)) && fade_gemm_tune() != 9) { kind = GK_STORE_128x128; bm = 128; bn = 128; }
     else if (g.N % 128 == 0 && ((g.M + 63) / 64) * (g.N / 128) >= 128) { kind = GK_STORE_64x128; bn = 128; }
@@ -1935,8 +1936,9 @@ hipError_t fade_gemm_group_launch(const GemmGroup &gg, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Tuning override for experiments (FADE_GEMM_TUNE: 0 automatic, 1 force 128x128x4 stages, 2 force 64x128, 11 force 128x128x2 with two workgroups per compute unit; 20 force 256x256 on eight wavefronts; grouped launches: 13 force
-// the four-stage kernel, 14 force the two-stage one).
+// Tuning override for experiments (FADE_GEMM_TUNE: 0 automatic, 1 force 128x128x4 stages, 2 force 64x128, 11 force 128x128x2 with two
+// workgroups per compute unit, 20 force 256x256 on eight wavefronts; grouped launches: 8 weight gradients without 128x128 tiles,
+// 9 activation gradients without them, 13 force the four-stage kernel, 14 force the two-stage one).
 int fade_gemm_tune() {
   static int v = -1;
   if (v < 0) { const char *e = getenv("FADE_GEMM_TUNE"); v = e ? atoi(e) : 0; }

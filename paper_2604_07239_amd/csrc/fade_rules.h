@@ -34,11 +34,14 @@ constexpr bool fade_streamed(bool bf16, bool online, size_t params, size_t B, si
 }
 
 // Whether the weight gradients that can be 256 x 256 tiles (`tiles` of them together) leave the grouped launches of their phases, 64 / 128-wide
-// tiles beside an activation gradient, and become one launch of equal shares: with 8192 rows of the batch and more, and from 2048 on when
-// the tiles are three quarters of the compute units or more. Adapting step in us, grouped and in one launch, D_h = 2048:
-// H = 512 (192 tiles) 2048 rows 644 -> 628, 4096 932 -> 918, and D_h = 512, D_cache = 4096, D_e = 8192 (224) 4096 1113 -> 1082;
-// H = 512, 1536 rows 561 -> 562; H = 384 (152) 2048 627 -> 632; H = 256 (144) 3072 781 -> 770, 4096 867 -> 918, 6144 1244 -> 1252;
-// H = 128 (128) 4096 843 -> 906; D_h = 1024, H = 512 (48) 4096 615 -> 622, 6144 902 -> 889-904.
+// tiles beside an activation gradient, and become one launch of equal shares: with 8192 rows of the batch and more, whatever the tiles, and
+// from 2048 on when they are three quarters of the compute units or more. Adapting step in us, grouped | in one launch (ranges below):
+// D_h = 2048, H = 512 (192 tiles): 2048 rows 648 | 624, 4096 937 | 935, 7000 1550 | 1482, 8192 1537 | 1442, 10001 2212 | 2035, 16384 2780 | 2518;
+// D_h = 512, D_cache = 4096, D_e = 8192 (224), 4096 rows 1118 | 1073. Fewer tiles from 8192 rows on: D_h = 2048, H = 384 (152) 8192 1592 | 1590,
+// 16384 2908 | 2790; D_h = 1024, H = 512 (48) 8192 990 | 1004, 16384 1678 | 1602; H = 256 (32) 16384 1531 | 1479, 8200 1288 | 1343;
+// D_h = 512, D_e = 1024 (16) 8192 780 | 784, 16384 1281 | 1260. D_h = 2048, H = 256 (144) 10001 2056 | 1981, but 8192 1441 | 1553 and 16384
+// 2584 | 2636: there the launch sums in 16 ranges, the groups in 2 and 4. Fewer tiles below 8192 rows, with no ranges yet (the better case):
+// H = 384 2048 rows 627 | 632; H = 256 4096 867 | 918, 6144 1244 | 1252; H = 128 (128) 4096 843 | 906; D_h = 1024, H = 512 4096 615 | 622.
 constexpr bool fade_tile_launch(int rows, int tiles) { return tiles > 0 && (rows >= 8192 || (rows >= 2048 && tiles >= 192)); }
 
 // Equal ranges of the batch that every tile's contraction over `units` blocks of 64 rows is summed in, each from zero, and added up by
@@ -64,12 +67,12 @@ constexpr int fade_tile_ranges(int tiles, int least, int count, int units) {
   return r;
 }
 
-// How `tiles` equal contractions of `units` steps each (a weight-gradient tile's ranges count as one each) are shared out over 256 workgroups, 32 on each of 8 XCDs. On an XCD, `groups`
-// groups of `wgs` workgroups take `tpg` tiles each: the group's tiles lie end to end and its members take per_wg steps each, so a
-// tile is cut where a member's share ends and arrives as one partial sum per member that worked on it. Small groups (at most
-// eight members) keep the members' starting points few, so that the same members of an XCD's groups read the same operand rows
-// at the same time; among them the one that takes the least steps. Tile j of group g of XCD x is tile (x tpg + j) groups + g of the
-// order: the g-th neighbours of one another.
+// How `tiles` equal contractions of `units` steps each (every range of a weight gradient's tile is one) are shared out over 256
+// workgroups, 32 on each of 8 XCDs. On an XCD, `groups` groups of `wgs` workgroups take `tpg` tiles each: the group's tiles lie end to end
+// and its members take per_wg steps each, so a tile is cut where a member's share ends and arrives as one partial sum per member that
+// worked on it. Small groups (at most eight members) keep the members' starting points few, so that the same members of an XCD's
+// groups read the same operand rows at the same time; among them the one that takes the least steps. Tile j of group g of XCD x is
+// tile (x tpg + j) groups + g of the order: the g-th neighbours of one another.
 struct FadeTilePlan {
   int tpg, wgs, groups, units, per_wg;
 };

@@ -38,12 +38,12 @@ MiB = 1 << 20
 # was not profiled reports null.
 ROUTER_GATE_TRAFFIC_BYTES = {
     (16384, 2048, "frozen"): int(0.5 * (320.3 + 66.2 + 315.9 + 66.1) * MiB),   # profiles/cfg5_frozen_kernel_trace_and_hbm.md (cfg 2's 16-step passes have the same shape)
-    (16384, 2048, "online"): int(0.5 * (322.2 + 130.3 + 315.9 + 130.1) * MiB), # profiles/cfg5_online_kernel_trace_and_hbm.md
+    (16384, 2048, "online"): int(0.5 * (323.4 + 130.3 + 316.0 + 130.1) * MiB), # profiles/cfg5_online_kernel_trace_and_hbm.md
     (1024, 2048, "online"): int(0.5 * (48.1 + 8.3 + 45.2 + 8.2) * MiB),                    # profiles/cfg2_online_kernel_trace_and_hbm.md
 }
 # adam_refresh_kernel by (parameters of the nine big matrices, mode), same counter runs
 ADAM_TRAFFIC_BYTES = {(11272192, "online"): int((173.4 + 168.8) * MiB),      # profiles/cfg2_online_kernel_trace_and_hbm.md
-                      (13369344, "online"): int((258.3 + 194.5) * MiB)}        # profiles/cfg5_online_kernel_trace_and_hbm.md
+                      (13369344, "online"): int((349.5 + 194.5) * MiB)}        # profiles/cfg5_online_kernel_trace_and_hbm.md
 
 
 def parse():
